@@ -141,25 +141,45 @@ def _buf(dtype, *shape):
     return torch.empty(shape, device="cuda", dtype=dtype)
 
 
-def prepare(case, seed):
+def _inputs(case, seed):
+    """The random tensors of a case, in the order they are drawn."""
     gen = torch.Generator(device="cuda")
     gen.manual_seed(seed)
+    kind, n = case["kind"], case["n"]
+    layers = _layers(case)
+    c, h, w, k, r, s = layers[0]
+    t = {"x": _normal(gen, n, c, h, w),
+         "weights": [_normal(gen, lk, lc, lr, lr) * case["w_std"] for lc, _, _, lk, lr, _ in layers]}
+    if kind in ("block", "linear"):
+        t["bn"] = _batchnorm(gen, c) if case.get("bn") else (None, None)
+    elif kind == "pool":
+        t["bn_next"] = _batchnorm(gen, k)
+    elif kind == "chain":
+        t["bn"] = [_batchnorm(gen, lc) for lc, *_ in layers]
+    elif kind == "kbit":
+        t["x"] = torch.tanh(t["x"])                             # k-bit levels cover [-1, 1]
+        t["weights"] = [torch.tanh(v / case["w_std"]) for v in t["weights"]]
+    elif kind == "train":
+        t["bn"] = _batchnorm(gen, c)
+        t["g_out"] = _normal(gen, n, k, _out(h, case), _out(w, case)) * 1e-3    # arrives from the next layer
+    return t
+
+
+def prepare(case, seed):
     kind, n = case["kind"], case["n"]
     layers = _layers(case)
     descs = [xnor.make_desc(n, c, h, w, k, r, r, s, r // 2) for c, h, w, k, r, s in layers]
     c, h, w, k, r, _ = layers[0]
     ho, wo = xnor.output_hw(descs[0])
-    st = {"case": case, "kind": kind, "descs": descs, "desc": descs[0], "x": _normal(gen, n, c, h, w)}
-    weights = [_normal(gen, lk, lc, lr, lr) * case["w_std"] for lc, _, _, lk, lr, _ in layers]
+    st = {"case": case, "kind": kind, "descs": descs, "desc": descs[0], **_inputs(case, seed)}
+    weights = st.pop("weights")
     i32, f32, u8 = torch.int32, torch.float32, torch.uint8
     if kind in ("block", "linear", "pool", "chain"):
         st["weights"] = [xnor.PackedWeights(v) for v in weights]
     if kind in ("block", "linear"):
-        st["bn"] = _batchnorm(gen, c) if case.get("bn") else (None, None)
         st["bufs"] = xnor.ConvBuffers(descs[0])
     elif kind == "pool":
         st["bufs"] = xnor.ConvBuffers(descs[0])
-        st["bn_next"] = _batchnorm(gen, k)
         win, ps = (case["window"],) * 2, (case["pstride"],) * 2
         hp, wp = (ho - win[0]) // ps[0] + 1, (wo - win[1]) // ps[1] + 1
         st["window"], st["pstride"] = win, ps
@@ -169,7 +189,6 @@ def prepare(case, seed):
         st["xbits_next"] = _buf(i32, n, hp, wp, xnor.words_per_pixel(k))
         st["A_next"] = _buf(f32, n, hp, wp)
     elif kind == "chain":
-        st["bn"] = [_batchnorm(gen, lc) for lc, *_ in layers]
         st["xbits"] = [_buf(i32, n, h, w, xnor.words_per_pixel(lc)) for lc, *_ in layers]
         st["A"] = [_buf(f32, n, h, w) for _ in layers]
         st["ws"] = _buf(u8, max([16] + [xnor.conv2d_binactiv_workspace_bytes(d) for d in descs[:-1]]))
@@ -179,15 +198,11 @@ def prepare(case, seed):
         xnor.xnor_bwn_pack_weights(weights[0], st["alpha"], st["wimg"], k, c, r, r)
         st["parts"], st["out"] = _buf(u8, xnor.bwn_parts_bytes(n, c, h, w)), _buf(f32, n, k, ho, wo)
     elif kind == "kbit":
-        st["x"] = torch.tanh(st["x"])                           # k-bit levels cover [-1, 1]
         st["wq"], st["scale"] = _buf(u8, xnor.kbit_wimg_bytes(k, c, r, r)), _buf(f32, k)
-        xnor.xnor_kbit_pack_weights(torch.tanh(weights[0] / case["w_std"]), st["scale"], st["wq"], case["ka"],
-                                    case["kb"], k, c, r, r)
+        xnor.xnor_kbit_pack_weights(weights[0], st["scale"], st["wq"], case["ka"], case["kb"], k, c, r, r)
         st["xq"], st["out"] = _buf(u8, xnor.kbit_input_bytes(n, c, h, w)), _buf(f32, n, k, ho, wo)
     elif kind == "train":
         st["w"], st["bufs"] = weights[0], xnor.ConvBuffers(descs[0])
-        st["bn"] = _batchnorm(gen, c)
-        st["g_out"] = _normal(gen, n, k, ho, wo) * 1e-3         # the gradient that arrives from the next layer
         st["wbits"], st["alpha"] = _buf(i32, k, r, r, xnor.words_per_pixel(c)), _buf(f32, k)
         st["wmfma"] = _buf(u8, xnor.wmfma_bytes(k, c, r, r))
         st["wtbits"], st["ones"] = _buf(i32, c, r * r, xnor.words_per_pixel(k)), _buf(f32, c)
@@ -308,3 +323,80 @@ def tolerance(case):
     if case["kind"] == "pool":
         return {"rel": 2.5e-7, "max": 1.3e-6, "differ": 1e-5}       # seen: 6.1e-8, 3.3e-7, no word
     return {"rel": 4.2e-7, "max": 3e-6}             # seen: 1.05e-7, 7.2e-7
+
+
+# ---- the same numbers in 64 bits, from torch alone -------------------------------------------------------------------
+def _sign(t):
+    return (t >= 0).double() * 2 - 1
+
+
+def _patch(x, dy, dx, ho, wo, stride):
+    """Pixels that tap (dy, dx) meets, channels first: x [c][n][padded h][padded w] -> [c][n * ho * wo]."""
+    return x[:, :, dy:dy + (ho - 1) * stride + 1:stride, dx:dx + (wo - 1) * stride + 1:stride].reshape(x.shape[0], -1)
+
+
+def _conv64(x, w, stride):
+    n, r, pad = x.shape[0], w.shape[2], w.shape[2] // 2
+    ho, wo = ((v + 2 * pad - r) // stride + 1 for v in x.shape[2:])
+    x = torch.nn.functional.pad(x.transpose(0, 1), (pad,) * 4)
+    out = sum(w[:, :, dy, dx] @ _patch(x, dy, dx, ho, wo, stride) for dy in range(r) for dx in range(r))
+    return out.reshape(w.shape[0], n, ho, wo).transpose(0, 1)
+
+
+def _data_grad64(g, w, stride, h_in, w_in):
+    """Transpose of _conv64: every tap scatters its products to the input positions it met in the forward pass."""
+    n, k, ho, wo = g.shape
+    c, r, pad = w.shape[1], w.shape[2], w.shape[2] // 2
+    out = torch.zeros((c, n, h_in + 2 * pad, w_in + 2 * pad), device=g.device, dtype=torch.float64)
+    flat = g.transpose(0, 1).reshape(k, -1)
+    for dy in range(r):
+        for dx in range(r):
+            out[:, :, dy:dy + (ho - 1) * stride + 1:stride, dx:dx + (wo - 1) * stride + 1:stride] += (
+                w[:, :, dy, dx].t() @ flat).reshape(c, n, ho, wo)
+    return out[:, :, pad:pad + h_in, pad:pad + w_in].transpose(0, 1)
+
+
+def _bn64(x, scale, shift):
+    return x if scale is None else x * scale.double().view(1, -1, 1, 1) + shift.double().view(1, -1, 1, 1)
+
+
+def _k64(y, w, stride):
+    box = torch.full((1, 1) + tuple(w.shape[2:]), 1.0 / (w.shape[2] * w.shape[3]), device=y.device, dtype=torch.float64)
+    return _conv64(y.abs().mean(1, keepdim=True), box, stride)
+
+
+def _block64(y, w, stride):
+    return _conv64(_sign(y), _sign(w), stride) * _k64(y, w, stride) * w.abs().mean((1, 2, 3)).view(1, -1, 1, 1)
+
+
+def _levels(x, bits):
+    """Numerators of q_k: the level is defined by float32 steps, one bit by the comparison with zero."""
+    if bits == 1:
+        return _sign(x)
+    levels = 2 ** bits - 1
+    return torch.floor((x + 1.0) * 0.5 * levels + 0.5).clamp(0, levels).double() * 2 - levels
+
+
+def exact(case, seed):
+    t, kind, layers = _inputs(case, seed), case["kind"], _layers(case)
+    x, ws = t["x"].double(), [v.double() for v in t["weights"]]
+    w, stride = ws[0], layers[0][5]
+    if kind in ("block", "linear"):
+        return _block64(_bn64(x, *t["bn"]), w, stride)
+    if kind == "chain":
+        for v, bn in zip(ws, t["bn"]):
+            x = _block64(_bn64(x, *bn), v, 1)
+        return x
+    if kind == "pool":
+        y = torch.nn.functional.max_pool2d(_block64(x, w, stride), case["window"], case["pstride"])
+        return [None, _bn64(y, *t["bn_next"]).abs().mean(1)]    # the packed words are not numbers
+    if kind == "bwn":
+        return _conv64(x, _sign(w), stride) * w.abs().mean((1, 2, 3)).view(1, -1, 1, 1)
+    if kind == "kbit":
+        num = _conv64(_levels(t["x"], case["ka"]), _levels(t["weights"][0], case["kb"]), stride)
+        return num / ((2 ** case["ka"] - 1) * (2 ** case["kb"] - 1))
+    y = _bn64(x, *t["bn"])
+    gd = t["g_out"].double() * w.abs().mean((1, 2, 3)).view(1, -1, 1, 1) * _k64(y, w, stride)
+    gmax = gd.abs().amax((1, 2, 3))
+    g_in = _data_grad64(_sign(gd), _sign(w), stride, *x.shape[2:]) * gmax.view(-1, 1, 1, 1)
+    return {"out": _block64(y, w, stride), "g_in": g_in, "gmax": gmax}
