@@ -3,7 +3,8 @@
 // matrix-core operand order, so the convolution can fetch a whole 32-filter operand as one
 // contiguous KiB: once as int8 (+1/-1, 0 for channel or filter padding) for the 32x32x32 int8
 // instruction and once as 4-bit floats (E2M1 0x2/0xA/0x0) for the 32x32x64 f8f6f4 instruction.
-#include "xnor_internal.h"
+#include "mfma_common.h"
+#include <type_traits>
 
 namespace xnor {
 
@@ -33,131 +34,201 @@ __device__ __forceinline__ int qk_level_index(float x, int L)
     return min(max((int)__builtin_floorf(v), 0), L);
 }
 
+// Shape of the work of one launch.  An image workgroup packs 8 filters x 32 * words channels x tap_run taps;
+// workgroups of their own form alpha, one filter each (mode 0).
+struct PackPlan {
+    int tap_run, tap_chunks;        // taps per workgroup (at most 16), ceil(taps / tap_run)
+    int words_log2, word_groups;    // channel words per workgroup (a power of two), ceil(cw / words)
+    uint32_t image_groups, groups;  // image workgroups, all workgroups
+    FastDiv div_tap, div_gt, div_chunks, div_wgroups, div_units;
+};
+constexpr int PACK_ROWS = 8;                        // filters per image workgroup: 128-byte runs of the images
+constexpr int PACK_PAIRS = 16;                      // (word, tap) pairs of a workgroup at most
+constexpr int PACK_BYTES = PACK_ROWS * (32 * PACK_PAIRS + 4) + 32 * 16 * 4;     // either layout below, rows padded
+
+// What bounds it: the bytes are few (4 per weight read, 1.9 written), so the time is round trips and instructions.
+// Each workgroup reads 8 filters x 32 channels x the taps once, as runs of memory copied without index arithmetic to
+// one byte per weight in LDS; a wave-wide comparison of 64 such bytes gives two packed words, and all images are
+// written from the words in runs of whole cache lines.  Measured against one workgroup per filter that walked it four
+// times: 15.2 -> 6.9 us at 128 filters of 128 x 3 x 3 (15.3 -> 7.1 us transposed), 334 -> 101 us at 4096 x 9216 (0.25 GB
+// read and written, 2.3 TB/s).
 template <int MODE>
 __global__ __launch_bounds__(256) void pack_weights_kernel(
     const float *__restrict__ w, uint32_t *__restrict__ wbits, float *__restrict__ alpha,
-    int8_t *__restrict__ wmfma, int k_out, int c, int taps, int cw, int aux, int stage, float alpha_fill)
+    int8_t *__restrict__ wmfma, int k_out, int c, int taps, int cw, int levels, float alpha_fill, PackPlan pl)
 {
-    constexpr bool TRANSPOSED = MODE == 1;
+    __shared__ __attribute__((aligned(16))) uint8_t bytes[PACK_BYTES];
+    __shared__ uint32_t words[PACK_PAIRS * PACK_ROWS];                           // [word * tap_run + tap][filter]
     __shared__ float red[256];
-    const int k = blockIdx.x;              // grid covers the filters padded to a multiple of 32
-    const int tid = threadIdx.x;
-    const bool real = k < k_out;
-    const size_t n = (size_t)c * taps;
-    const int kk = real ? k : 0;
-    const int kf = kk;
-    // element (channel ch, tap t) of this filter, read from the tensor in the mode's order
-    struct Source {
-        const float *base;
-        size_t ch_stride;
-        int taps, L;
-        __device__ float operator()(int ch, int t) const
-        {
-            if (MODE == 3) return (float)(2 * qk_level_index(base[(size_t)ch * ch_stride + t], L) - L);
-            return TRANSPOSED ? base[(size_t)ch * ch_stride + (taps - 1 - t)] : base[(size_t)ch * ch_stride + t];
-        }
-    };
-    const Source src{TRANSPOSED ? w + (size_t)kf * taps : w + (size_t)kf * n,
-                     TRANSPOSED ? (size_t)k_out * taps : (size_t)taps, taps, (1 << aux) - 1};
-    // The four images below each walk the whole filter with a 32-channel stride per thread.  When the
-    // filter fits the staging buffer it is first copied to LDS in [channel][tap] order (one coalesced pass
-    // in mode 0) and every later access reads LDS; larger filters are read from memory each time.
-    extern __shared__ float staged[];
-    if (stage) {
-        for (int i = tid; i < (int)n; i += 256) {
-            const int ch = i / taps;
-            staged[i] = src(ch, i - ch * taps);
-        }
-        __syncthreads();
-    }
-    struct Filter {
-        const Source &src;
-        const float *lds;
-        int taps;
-        __device__ float operator()(int ch, int t) const { return lds ? lds[ch * taps + t] : src(ch, t); }
-    };
-    const Filter wk{src, stage ? staged : nullptr, taps};
-
-    if (real && wbits) {
-        for (int item = tid; item < taps * cw; item += 256) {
-            const int t = item / cw, wd = item - t * cw;
-            const int nch = min(32, c - wd * 32);
-            uint32_t word = 0;
-            for (int j = 0; j < nch; ++j)
-                word |= (wk(wd * 32 + j, t) >= 0.0f ? 1u : 0u) << j;
-            wbits[((size_t)k * taps + t) * cw + wd] = word;
-        }
-    }
-    if (real) {
-        if (MODE != 0) {
-            if (tid == 0) alpha[k] = MODE == 3 ? alpha_fill : 1.0f;
-        } else {
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    for (uint32_t blk = blockIdx.x; blk < pl.groups; blk += gridDim.x) {
+        if (blk != blockIdx.x) __syncthreads();     // the previous turn's LDS contents are consumed
+        if (MODE == 0 && blk >= pl.image_groups) {
+            // alpha of one filter: strided partial sums, then a tree of fixed order
+            const uint32_t k = blk - pl.image_groups;
+            const size_t n = (size_t)c * taps;
+            const float *wf = w + (size_t)k * n;
             float s = 0.0f;
-            for (size_t i = tid; i < n; i += 256) s += __builtin_fabsf(stage ? staged[i] : src.base[i]);
+            for (size_t i0 = tid; i0 < n; i0 += 256 * 8) {
+                float v[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) v[u] = i0 + u * 256 < n ? wf[i0 + u * 256] : 0.0f;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) s += __builtin_fabsf(v[u]);          // (+0 past the end changes nothing)
+            }
             red[tid] = s;
             __syncthreads();
-            for (int step = 128; step > 0; step >>= 1) {
-                if (tid < step) red[tid] += red[tid + step];
-                __syncthreads();
-            }
-            if (tid == 0) alpha[k] = red[0] / (float)n;
-        }
-    }
-    if (wmfma) {
-        const int fb = k >> 5, row = k & 31;
-        for (int item = tid; item < taps * cw * 2; item += 256) {
-            const int half = item & 1;
-            const int tw = item >> 1;               // t*cw + wd
-            const int t = tw / cw, wd = tw - t * cw;
-            const int ch0 = wd * 32 + half * 16;
-            union { int8_t b[16]; uint4 v; } u;
+            if (tid < 64) {
+                float t = (red[tid] + red[tid + 128]) + (red[tid + 64] + red[tid + 192]);
 #pragma unroll
-            for (int j = 0; j < 16; ++j) {
-                int8_t s = 0;
-                if (real && ch0 + j < c) s = MODE == 3 ? (int8_t)wk(ch0 + j, t) : (wk(ch0 + j, t) >= 0.0f) ? 1 : -1;
-                u.b[j] = s;
+                for (int step = 32; step > 0; step >>= 1) t += __shfl_down(t, step, 64);
+                if (tid == 0) alpha[k] = t / (float)n;
             }
-            const size_t rec = ((size_t)fb * taps + t) * cw + wd;
-            *reinterpret_cast<uint4 *>(wmfma + rec * 1024 + (size_t)(row + 32 * half) * 16) = u.v;
+            continue;
         }
-        if (MODE == 3) {        // the int8 image alone: its trailing all-zero record, then done
-            if (k == 0 && tid < 64)
-                *reinterpret_cast<uint4 *>(wmfma + wimg_i8_bytes(k_out, c, taps) - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
-            return;
-        }
-        int8_t *w4 = wmfma + wimg_i8_bytes(k_out, c, taps);
-        const int nblk = taps * cw, nrec = (nblk + 1) / 2;
-        for (int item = tid; item < nrec * 2; item += 256) {
-            const int half = item & 1, r = item >> 1;
-            const int b = 2 * r + half;
-            union { uint8_t b[16]; uint4 v; } u;
-            u.v = make_uint4(0, 0, 0, 0);
-            if (real && b < nblk) {
-                const int t = b / cw, wd = b - t * cw;
+        const uint32_t fq = pl.div_chunks.div(blk), tchunk = blk - fq * (uint32_t)pl.tap_chunks;
+        const uint32_t fg = pl.div_wgroups.div(fq), wg = fq - fg * (uint32_t)pl.word_groups;
+        const int run = pl.tap_run;
+        const int t0 = (int)tchunk * run, wd0 = (int)wg << pl.words_log2;
+        const int f0 = (int)fg * PACK_ROWS, ch0 = wd0 * 32;
+        const int nch = 32 << pl.words_log2, gt = run << pl.words_log2;          // channels; (word, tap) pairs
+        // ---- weights -> one byte each (modes 0, 1: 1 = positive; mode 3: the level's numerator; 0 outside) ----
+        // A row is a filter with its channels (mode 1: a channel with its filters), `sub` runs of `run` taps in memory
+        // order; its bytes lie in LDS the same way, tap run by tap run.
+        const int rows = MODE == 1 ? nch : PACK_ROWS, sub = MODE == 1 ? PACK_ROWS : nch;
+        const int pitch = sub * run + 4;
+        const int r_real = MODE == 1 ? c - ch0 : k_out - f0, s_real = MODE == 1 ? k_out - f0 : c - ch0;
+        const size_t row_stride = (size_t)(MODE == 1 ? k_out : c) * taps;
+        const float *base = w + (MODE == 1 ? (size_t)ch0 * row_stride + (size_t)f0 * taps
+                                           : (size_t)f0 * row_stride + (size_t)ch0 * taps);
+        const int m0 = MODE == 1 ? taps - t0 - run : t0;        // first tap in memory order (may be negative: masked)
+        const int len = sub * run;
+        // units of 64 consecutive elements of a row, eight in flight per wave
+        const int upr = (len + 63) >> 6, units = rows * upr;
+        auto stage_bytes = [&](auto whole) {
+            for (int u0 = wave; u0 < units; u0 += 4 * 8) {
+                float v[8];
+                int dst[8];
+                bool ok[8];
 #pragma unroll
-                for (int j = 0; j < 32; ++j) {
-                    const int ch = wd * 32 + j;
-                    uint32_t code = 0;
-                    if (ch < c) code = (wk(ch, t) >= 0.0f) ? 0x2u : 0xAu;
-                    u.b[j >> 1] |= (uint8_t)(code << (4 * (j & 1)));
+                for (int u = 0; u < 8; ++u) {
+                    const int unit = min(u0 + 4 * u, units - 1);
+                    const int r = (int)pl.div_units.div_small((uint32_t)unit), i = ((unit - r * upr) << 6) + lane;
+                    // (a padded filter group lies past the tensor altogether: masked elements read its first float)
+                    const bool real = r < r_real && s_real > 0;
+                    const char *src = reinterpret_cast<const char *>(real ? base + (size_t)r * row_stride : w);
+                    const int limit = real ? min(s_real, sub) * taps : 0;        // floats of the row that exist here
+                    int at = i;
+                    if constexpr (whole.value) {                                 // every tap: one run of memory
+                        ok[u] = i < limit;
+                    } else {
+                        const int q = (int)pl.div_tap.div_small((uint32_t)i), m = m0 + i - q * run;
+                        at = q * taps + m;
+                        ok[u] = i < len && m >= 0 && m < taps && at < limit;
+                    }
+                    dst[u] = i < len ? r * pitch + i : -1;
+                    v[u] = *reinterpret_cast<const float *>(src + (ok[u] ? (uint32_t)at * 4u : 0u));
+                }
+#pragma unroll
+                for (int u = 0; u < 8; ++u)
+                    if (dst[u] >= 0)
+                        bytes[dst[u]] = !ok[u] ? 0
+                                        : MODE == 3 ? (uint8_t)(int8_t)(2 * qk_level_index(v[u], levels) - levels)
+                                                    : (uint8_t)(v[u] >= 0.0f);
+            }
+        };
+        if (pl.tap_chunks == 1) stage_bytes(std::true_type{});
+        else stage_bytes(std::false_type{});
+        // byte of (filter f, channel ch, tap tl of the run)
+        auto at = [&](int f, int ch, int tl) -> uint32_t {
+            return MODE == 1 ? bytes[ch * pitch + f * run + (run - 1 - tl)] : bytes[f * pitch + ch * run + tl];
+        };
+        if (MODE != 0 && wg == 0 && tchunk == 0 && tid < PACK_ROWS && f0 + tid < k_out)
+            alpha[f0 + tid] = MODE == 3 ? alpha_fill : 1.0f;
+        __syncthreads();
+        if constexpr (MODE != 3) {
+            // lanes are the 32 channels of a word of filters f and f + 1
+            for (int q0 = wave; q0 < gt * (PACK_ROWS / 2); q0 += 4 * 4) {
+                uint32_t byte[4];
+                int slot[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int q = min(q0 + 4 * u, gt * (PACK_ROWS / 2) - 1);
+                    const int pair = q / (PACK_ROWS / 2), f = 2 * (q % (PACK_ROWS / 2)) + (lane >> 5);
+                    const int g = (int)pl.div_tap.div_small((uint32_t)pair), tl = pair - g * run;
+                    byte[u] = at(f, g * 32 + (lane & 31), tl);
+                    slot[u] = pair * PACK_ROWS + f;
+                }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const unsigned long long mask = __ballot(byte[u] != 0);
+                    if ((lane & 31) == 0) words[slot[u]] = (uint32_t)(lane ? mask >> 32 : mask);
                 }
             }
-            const size_t rec = (size_t)fb * nrec + r;
-            *reinterpret_cast<uint4 *>(w4 + rec * 1024 + (size_t)(row + 32 * half) * 16) = u.v;
-        }
-        // scalar-path image: this filter's words, 32 filters interleaved per (tap, channel word)
-        uint32_t *wp = reinterpret_cast<uint32_t *>(w4 + wimg_f4_bytes(k_out, c, taps));
-        for (int item = tid; item < taps * cw; item += 256) {
-            const int t = item / cw, wd = item - t * cw;
-            uint32_t word = 0;
-            if (real) {
-                const int nch = min(32, c - wd * 32);
-                for (int j = 0; j < nch; ++j)
-                    word |= (wk(wd * 32 + j, t) >= 0.0f ? 1u : 0u) << j;
+            __syncthreads();
+            if (wbits) {
+                for (int i = tid; i < gt * PACK_ROWS; i += 256) {     // [filter][tap][word] with the words innermost
+                    const int f = (int)pl.div_gt.div_small((uint32_t)i), rem = i - f * gt;
+                    const int tl = rem >> pl.words_log2, g = rem & ((1 << pl.words_log2) - 1);
+                    if (f0 + f < k_out && t0 + tl < taps && wd0 + g < cw)
+                        wbits[((size_t)(f0 + f) * taps + t0 + tl) * cw + wd0 + g] =
+                            words[(g * run + tl) * PACK_ROWS + f];
+                }
             }
-            wp[(((size_t)fb * taps + t) * cw + wd) * 32 + row] = word;
         }
-        if (k == 0 && tid < 128) {      // the trailing all-zero record of each image
+        if (!wmfma) continue;
+        // ---- images: every (word, tap) pair is a contiguous run of each --------------------------------------
+        const int fb = f0 >> 5, row0 = f0 & 31;
+        for (int i = tid; i < gt * PACK_ROWS * 2; i += 256) {
+            const int pair = i / (PACK_ROWS * 2), f = i % PACK_ROWS, half = (i / PACK_ROWS) & 1;
+            const int g = (int)pl.div_tap.div_small((uint32_t)pair), tl = pair - g * run;
+            const int t = t0 + tl, wd = wd0 + g;
+            if (t >= taps || wd >= cw) continue;
+            uint32_t v[4];
+            if constexpr (MODE == 3) {
+                const int ch = g * 32 + half * 16;
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    v[j] = at(f, ch + 4 * j, tl) | at(f, ch + 4 * j + 1, tl) << 8 | at(f, ch + 4 * j + 2, tl) << 16 |
+                           at(f, ch + 4 * j + 3, tl) << 24;
+            } else {
+                const uint32_t bits = words[pair * PACK_ROWS + f] >> (16 * half);
+                const int left = f0 + f < k_out ? c - wd * 32 - half * 16 : 0;         // channels from here on
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int r = left - 4 * j;
+                    v[j] = Enc<0>::widen4((bits >> (4 * j)) & 15u) &
+                           (r >= 4 ? 0xFFFFFFFFu : r <= 0 ? 0u : (1u << (8 * r)) - 1u);
+                }
+            }
+            const size_t rec = ((size_t)fb * taps + t) * cw + wd;
+            *reinterpret_cast<uint4 *>(wmfma + rec * 1024 + (size_t)(row0 + f + 32 * half) * 16) =
+                make_uint4(v[0], v[1], v[2], v[3]);
+        }
+        int8_t *w4 = wmfma + wimg_i8_bytes(k_out, c, taps);
+        if (MODE == 3) {
+            if (blk == 0 && tid < 64)           // the trailing all-zero record
+                *reinterpret_cast<uint4 *>(w4 - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
+            continue;
+        }
+        const int nblk = taps * cw, nrec = (nblk + 1) / 2;
+        uint32_t *wp = reinterpret_cast<uint32_t *>(w4 + wimg_f4_bytes(k_out, c, taps));
+        for (int i = tid; i < gt * PACK_ROWS; i += 256) {
+            const int pair = i / PACK_ROWS, f = i % PACK_ROWS;
+            const int g = (int)pl.div_tap.div_small((uint32_t)pair), tl = pair - g * run;
+            const int t = t0 + tl, wd = wd0 + g;
+            if (t >= taps || wd >= cw) continue;
+            const uint32_t bits = words[i];
+            const int b = t * cw + wd;
+            int8_t *rec = w4 + ((size_t)fb * nrec + (b >> 1)) * 1024;
+            *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32 * (b & 1)) * 16) =
+                Enc<1>::widen_word_regs(bits, f0 + f < k_out, c - wd * 32);
+            if (b == nblk - 1 && !(b & 1))      // an odd number of blocks: the last record's other half is zero
+                *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32) * 16) = make_uint4(0, 0, 0, 0);
+            wp[((size_t)fb * nblk + b) * 32 + row0 + f] = bits;      // scalar-path image
+        }
+        if (blk == 0 && tid < 128) {            // the trailing all-zero record of each image
             int8_t *z = tid < 64 ? w4 - 1024 : w4 + wimg_f4_bytes(k_out, c, taps) - 1024;
             *reinterpret_cast<uint4 *>(z + (size_t)(tid & 63) * 16) = make_uint4(0, 0, 0, 0);
         }
@@ -168,15 +239,32 @@ xnor_status launch_pack_weights(const float *w, uint32_t *wbits, float *alpha, v
                                 int k_out, int c, int taps, hipStream_t stream, int mode, int aux, float alpha_fill)
 {
     const int cw = (c + 31) / 32;
-    const int kpad = (k_out + 31) / 32 * 32;
-    dim3 grid((unsigned)(wmfma ? kpad : k_out)), block(256);
-    const size_t fbytes = (size_t)c * taps * sizeof(float);
-    const int stage = fbytes <= 60 * 1024 ? 1 : 0;
-    const size_t lds = stage ? fbytes : 0;
-#define XNOR_PACK(M, AUX) pack_weights_kernel<M><<<grid, block, lds, stream>>>(w, wbits, alpha, (int8_t *)wmfma, k_out, c, taps, cw, AUX, stage, alpha_fill)
-    if (mode == 1) XNOR_PACK(1, 1);
-    else if (mode == 3) XNOR_PACK(3, aux);
-    else XNOR_PACK(0, 1);
+    PackPlan pl;
+    pl.tap_chunks = (taps + PACK_PAIRS - 1) / PACK_PAIRS;
+    pl.tap_run = (taps + pl.tap_chunks - 1) / pl.tap_chunks;
+    pl.tap_chunks = (taps + pl.tap_run - 1) / pl.tap_run;
+    // few taps: several words per workgroup, so that its runs of memory stay long (1x1 filters: 2 KiB per filter)
+    pl.words_log2 = 0;
+    while ((2 << pl.words_log2) * pl.tap_run <= PACK_PAIRS && (1 << pl.words_log2) < cw) ++pl.words_log2;
+    pl.word_groups = (cw + (1 << pl.words_log2) - 1) >> pl.words_log2;
+    // the images hold whole blocks of 32 filters, the words only the filters that exist
+    const long long fgroups = wmfma ? ((long long)k_out + 31) / 32 * (32 / PACK_ROWS)
+                                    : ((long long)k_out + PACK_ROWS - 1) / PACK_ROWS;
+    const long long image = fgroups * pl.word_groups * pl.tap_chunks;
+    const long long groups = image + (mode == 0 ? k_out : 0);
+    if (groups > 0xffffffffLL) return XNOR_ERR_UNSUPPORTED;
+    pl.image_groups = (uint32_t)image;
+    pl.groups = (uint32_t)groups;
+    pl.div_tap = FastDiv::make((uint32_t)pl.tap_run);
+    pl.div_gt = FastDiv::make((uint32_t)(pl.tap_run << pl.words_log2));
+    pl.div_units = FastDiv::make((uint32_t)(((mode == 1 ? PACK_ROWS : 32 << pl.words_log2) * pl.tap_run + 63) / 64));
+    pl.div_chunks = FastDiv::make((uint32_t)pl.tap_chunks);
+    pl.div_wgroups = FastDiv::make((uint32_t)pl.word_groups);
+    const dim3 grid((unsigned)(groups < (1 << 22) ? groups : (1 << 22))), block(256);      // (larger ones in turns)
+#define XNOR_PACK(M) pack_weights_kernel<M><<<grid, block, 0, stream>>>(w, wbits, alpha, (int8_t *)wmfma, k_out, c, taps, cw, (1 << aux) - 1, alpha_fill, pl)
+    if (mode == 1) XNOR_PACK(1);
+    else if (mode == 3) XNOR_PACK(3);
+    else XNOR_PACK(0);
 #undef XNOR_PACK
     return hip_status(hipGetLastError());
 }
