@@ -194,6 +194,8 @@ xnor_status conv_dispatch(const ConvGeom &g, const uint32_t *xbits, const uint32
         if (!wmfma) return XNOR_ERR_NULL;
         return launch_conv_mfma(algo == XNOR_ALGO_MFMA_F4 ? 1 : 0, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
     case XNOR_ALGO_AUTO: {
+        if (linear_popcount_applies(g))
+            return launch_linear_popcount(xbits, wbits, K ? K : A, alpha, out, dot_out, g, st);
         if (wmfma) {        // 4-bit operands, then int8 (sums of 2^24 and more terms), then the vector ALU
             xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
             if (s != XNOR_ERR_UNSUPPORTED) return s;

@@ -166,4 +166,99 @@ xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, c
     return launch_f<32>(xbits, wbits, K, A, alpha, out, dot_out, g, stream);
 }
 
+// Fully connected layers whose batch is small: the weights are read once and each meets few rows, so the time is that of
+// bringing them in.  The matrix-core form reads them as 4-bit operands (four times the packed bits) and walks the whole K
+// in one workgroup; here 16 lanes share a filter's row of packed words, V words per lane and load with U loads in flight,
+// each word meeting the same word of NB rows of the batch.  The 16 partial counts meet by lane exchanges.  Bound by the
+// latency of one trip to memory and the launch.  9216 -> 4096 back to back: one row 9.7 -> 2.5 us, eight rows
+// 15.9 -> 4.1 us.  (Two rows per workgroup: with four or eight the rows' counts are a serial chain in one wave,
+// 4.7 and 7.2 us for eight rows.)
+constexpr int FC_LANES = 16;
+template <int V, int NB>
+__global__ __launch_bounds__(256) void linear_popcount_kernel(
+    const uint32_t *__restrict__ xbits, const uint32_t *__restrict__ wbits, const float *__restrict__ Krow,
+    const float *__restrict__ alpha, float *__restrict__ out, int32_t *__restrict__ dot_out, int n, int c, int cw,
+    int k_out)
+{
+    constexpr int U = V == 4 ? 5 : 8;                  // loads in flight per lane (V = 4: 320 words of a row at once)
+    typedef uint32_t vec __attribute__((ext_vector_type(V)));
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & (FC_LANES - 1);
+    const int f = (blockIdx.x * 4 + wave) * (64 / FC_LANES) + lane / FC_LANES;
+    const int n0 = blockIdx.y * NB;
+    const uint32_t *wr = wbits + (size_t)min(f, k_out - 1) * cw;
+    uint32_t acc[NB];
+#pragma unroll
+    for (int b = 0; b < NB; ++b) acc[b] = 0;
+    for (int base = 0; base < cw; base += FC_LANES * V * U) {
+        vec w[U];
+        int idx[U];
+        bool ok[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int i = base + (u * FC_LANES + sub) * V;      // V divides cw: a lane's V words lie in the row or none does
+            ok[u] = i < cw;
+            idx[u] = ok[u] ? i : 0;
+            w[u] = *reinterpret_cast<const vec *>(wr + idx[u]);
+        }
+#pragma unroll
+        for (int b = 0; b < NB; ++b) {
+            const uint32_t *xr = xbits + (size_t)min(n0 + b, n - 1) * cw;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const vec x = *reinterpret_cast<const vec *>(xr + idx[u]);
+                uint32_t cnt = 0;
+#pragma unroll
+                for (int q = 0; q < V; ++q) cnt += __builtin_popcount(x[q] ^ w[u][q]);
+                acc[b] += ok[u] ? cnt : 0u;
+            }
+        }
+    }
+    uint32_t mine = 0;                                 // lane b of the 16 keeps the count of row n0 + b
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        uint32_t s = acc[b];
+#pragma unroll
+        for (int off = FC_LANES / 2; off > 0; off >>= 1) s += (uint32_t)__shfl_xor((int)s, off, 64);
+        mine = sub == b ? s : mine;
+    }
+    const int m = n0 + sub;
+    if (sub < NB && m < n && f < k_out) {
+        const int dot = c - 2 * (int)mine;
+        const size_t o = (size_t)m * k_out + f;
+        out[o] = (float)dot * Krow[m] * alpha[f];
+        if (dot_out) dot_out[o] = dot;
+    }
+}
+
+// Where it is ahead of the matrix-core form (back to back, us; rows x filters, c channels):
+//     32768 pairs: 4.1 to 5.0 against 4.9 to 16;  65536: 6.0 against 7.6 (c = 2048), 8.0 against 5.2 (c = 64);
+//     131072: 10.0 against 17 (c = 9216), 9.8 against 6.7 (c = 2048).
+// The time here grows with the pairs and hardly with c, there with c and hardly with the pairs.
+bool linear_popcount_applies(const ConvGeom &g)
+{
+    if (g.h != 1 || g.w != 1 || g.taps != 1 || g.ph != 0 || g.pw != 0 || g.dil_h != 1 || g.dil_w != 1) return false;
+    if (g.n > 65535 || g.fblocks > 65535) return false;        // (grid limits)
+    const long long pairs = (long long)g.n * g.k_out;
+    return pairs <= (g.c >= 4096 ? 131072 : g.c >= 2048 ? 65536 : 32768);
+}
+
+// (a 1x1 image and filter: K of a row is its A)
+xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits, const float *Krow, const float *alpha,
+                                   float *out, int32_t *dot_out, const ConvGeom &g, hipStream_t stream)
+{
+    constexpr int FPB = 4 * 64 / FC_LANES;             // filters per workgroup
+    const unsigned gx = (unsigned)((g.k_out + FPB - 1) / FPB);
+#define XNOR_GO(V, NB)                                                                                                 \
+    linear_popcount_kernel<V, NB><<<dim3(gx, (unsigned)((g.n + NB - 1) / NB)), dim3(256), 0, stream>>>(                \
+        xbits, wbits, Krow, alpha, out, dot_out, g.n, g.c, g.cw, g.k_out)
+#define XNOR_GO_N(V)                                                                                                   \
+    do { if (g.n == 1) XNOR_GO(V, 1); else XNOR_GO(V, 2); } while (0)
+    if (g.cw % 4 == 0) XNOR_GO_N(4);
+    else if (g.cw % 2 == 0) XNOR_GO_N(2);
+    else XNOR_GO_N(1);
+#undef XNOR_GO_N
+#undef XNOR_GO
+    return hip_status(hipGetLastError());
+}
+
 }  // namespace xnor

@@ -88,6 +88,9 @@ xnor_status launch_bingrad_scale_plane(const float *gmax, float *plane, int n, i
 xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, const void *wmfma, const float *K, const float *A,
                                  const float *alpha, float *out, int32_t *dot_out,
                                  const ConvGeom &g, hipStream_t stream);
+bool linear_popcount_applies(const ConvGeom &g);
+xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits, const float *Krow, const float *alpha,
+                                   float *out, int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
 // Third image of the wmfma buffer (after the int8 and 4-bit images): the packed weight words in
 // scalar-path order, [filter block of 32][tap][channel word][32 filters], so that the 32 words a
 // wave needs for one (tap, channel word) are one aligned 128-byte scalar load.
