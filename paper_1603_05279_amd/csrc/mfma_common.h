@@ -63,17 +63,19 @@ inline void set_fast_staging(MfmaPlan *pl, const ConvGeom &g, int fmt)
 inline int worst_region_rows(const ConvGeom &g, int run, int step)
 {
     const long long howo = (long long)g.ho * g.wo;
-    long long a = step, b = howo;
-    while (b) { const long long t = a % b; a = b; b = t; }      // gcd(step, howo)
-    const long long period = howo / a;
-    const long long starts = (g.m_total + step - 1) / step;
-    const long long n = starts < period ? starts : period;
+    // (the validated geometry keeps m_total within 31 bits: 32-bit divisions, a third of the 64-bit ones' time)
+    uint32_t a = (uint32_t)step, b = (uint32_t)howo;
+    while (b) { const uint32_t t = a % b; a = b; b = t; }       // gcd(step, howo)
+    const uint32_t period = (uint32_t)howo / a;
+    const uint32_t starts = ((uint32_t)g.m_total + (uint32_t)step - 1) / (uint32_t)step;
+    const uint32_t n = starts < period ? starts : period;
     int worst = 0;
-    for (long long i = 0; i < n; ++i) {
-        const long long m0 = i * step;
-        const long long m1 = (m0 + run < g.m_total ? m0 + run : g.m_total) - 1;
-        const int ia = (int)(m0 / howo), ib = (int)(m1 / howo);
-        const int oa = (int)((m0 % howo) / g.wo), ob = (int)((m1 % howo) / g.wo);
+    for (uint32_t i = 0; i < n; ++i) {
+        const uint32_t m0 = i * (uint32_t)step;
+        const uint32_t m1 = (m0 + (uint32_t)run < (uint32_t)g.m_total ? m0 + (uint32_t)run : (uint32_t)g.m_total) - 1;
+        const int ia = (int)(m0 / (uint32_t)howo), ib = (int)(m1 / (uint32_t)howo);
+        const int oa = (int)((m0 - (uint32_t)ia * (uint32_t)howo) / (uint32_t)g.wo);
+        const int ob = (int)((m1 - (uint32_t)ib * (uint32_t)howo) / (uint32_t)g.wo);
         const int rows = (ib * g.hp + ob * g.sh + g.kh - 1) - (ia * g.hp + oa * g.sh) + 1;
         if (rows > worst) worst = rows;
     }

@@ -172,6 +172,7 @@ def output_hw(desc):
 
 
 def _ptr(t, dtype=None):
+    """Device address of a dense device tensor, as a plain integer (the declared argument types convert it)."""
     if t is None:
         return None
     if not t.is_cuda:
@@ -180,12 +181,20 @@ def _ptr(t, dtype=None):
         raise ValueError("libxnor takes densely packed tensors")
     if dtype is not None and t.dtype != dtype:
         raise ValueError(f"expected {dtype}, got {t.dtype}")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 
 
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the handle alone: building torch's Stream object on every call costs more than a kernel launch
+    # (a call's Python share about 6 -> 3 us; one small block, two calls: 16.9 -> 12.0 us)
+    if stream is not None:
+        return stream.cuda_stream
+    if _current_raw_stream is not None:
+        return _current_raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _check(fn, st):
