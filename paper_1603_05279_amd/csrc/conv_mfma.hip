@@ -438,7 +438,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
         const uint32_t mc = plive[j] ? m : m_end - 1u;
         pimg[j] = g.div_howo.div(mc);
         ppix[j] = mc - pimg[j] * howo;
-        Km[j] = RAW ? 1.0f : (K ? K[mc] : ktile[pl_idx]);      // real and k-bit activations carry no K
+        Km[j] = RAW ? 1.0f : (K ? K[g.k_per_image ? pimg[j] : mc] : ktile[pl_idx]);      // real and k-bit activations carry no K
     }
     // Float (and optional integer) results leave through buffer stores: the resource starts at the
     // tile's first image, a lane's vector offset names its pixel (plus its half-wave's four rows),

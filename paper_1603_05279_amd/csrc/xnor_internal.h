@@ -23,6 +23,7 @@ struct ConvGeom {
     // divisions are exact and in range, and zero otherwise.  1 / h / w for ordinary convolutions.
     int dil_h, dil_w, real_h, real_w;
     FastDiv div_dil_h, div_dil_w;
+    int k_per_image;   // 1: the K given to the matrix-core kernels is one value per image [n] instead of a plane [n][ho][wo]
 };
 
 // K of output pixel m (flattened image, row, column): the in-bounds taps of A summed in row-major
