@@ -292,7 +292,8 @@ XNOR_API int xnor_bwn_conv2d(const void *parts, const void *wimg, const float *a
  *   xnor_bingrad_conv2d        gbits, wtbits, wtmfma, gmax, ones  ->  g_in float32 [n][c][h_in][w_in] =
  *       gmax[n] * sum over filters and taps of sign(gd) * sign(W) (positions that were padding in the forward
  *       pass receive and contribute nothing); dot_out int32 [n][c][h_in][w_in] (may be NULL) = the integer sum.
- *       scale_plane float32 [n][h_in][w_in] is scratch the caller provides (overwritten).  algo as xnor_conv2d;
+ *       scale_plane float32 [n][h_in][w_in] is scratch the caller provides (written where the scale is needed
+ *       per pixel, left alone by the matrix-core paths).  algo as xnor_conv2d;
  *       for a forward stride above 1 the gradient is staged with zeros between its pixels, which the matrix-core
  *       paths do (wtmfma required; XNOR_ALGO_POPCOUNT gives XNOR_ERR_UNSUPPORTED).
  * The straight-through factor of sign() on the forward input and the gradient through K are not part of
