@@ -160,3 +160,15 @@ def test_full_size_alexnet_conv3():
     K, alpha = fwd["K"].astype(np.float32), fwd["alpha"].astype(np.float32)
     r = run(g, W, K, alpha, (layer.h, layer.w), pad, "mfma_f4")
     check(r, g, W, K, alpha, (layer.h, layer.w), pad)
+
+
+@pytest.mark.parametrize("algo", ["auto", "mfma_i8", "mfma_f4"])
+@pytest.mark.parametrize("n,c,h,w,k", [(40, 33, 1, 1, 70), (70, 40, 2, 3, 64), (7, 64, 6, 7, 130)])
+def test_scale_of_each_image_where_a_tile_spans_many(n, c, h, w, k, algo):
+    # the epilogue picks gmax by the pixel's image: maxima that differ by powers of two, several images per tile
+    rng = np.random.default_rng(n)
+    W = rng.standard_normal((k, c, 1, 1)).astype(np.float32)
+    g = (rng.standard_normal((n, k, h, w)) * 2.0 ** (np.arange(n) % 9)[:, None, None, None]).astype(np.float32)
+    r = run(g, W, None, None, (h, w), (0, 0), algo)
+    check(r, g, W, None, None, (h, w), (0, 0))
+    assert np.array_equal(r["gin"], r["dot"].astype(np.float32) * r["gmax"][:, None, None, None])
