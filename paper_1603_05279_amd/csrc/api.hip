@@ -195,7 +195,7 @@ xnor_status conv_dispatch(const ConvGeom &g, const uint32_t *xbits, const uint32
         if (!wmfma) return XNOR_ERR_NULL;
         return launch_conv_mfma(algo == XNOR_ALGO_MFMA_F4 ? 1 : 0, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
     case XNOR_ALGO_AUTO: {
-        if (linear_popcount_applies(g))
+        if (linear_popcount_applies(g, wmfma != nullptr))
             return launch_linear_popcount(xbits, wbits, K ? K : A, alpha, out, dot_out, g, st);
         if (wmfma) {        // 4-bit operands, then int8 (sums of 2^24 and more terms), then the vector ALU
             xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
@@ -454,7 +454,7 @@ int xnor_bingrad_conv2d(const uint32_t *gbits, const uint32_t *wtbits, const voi
     // The matrix-core kernels read the scale of an image from gmax itself.  The plane is written only for the vector-ALU
     // forms, which index K by pixel: writing it was a launch of its own
     // ahead of the convolution (training step of a 128-channel 28 x 28 layer, 256 images: 119.8 -> 114.5 us).
-    if (wtmfma && algo != XNOR_ALGO_POPCOUNT && !(algo == XNOR_ALGO_AUTO && linear_popcount_applies(g))) {
+    if (wtmfma && algo != XNOR_ALGO_POPCOUNT && !(algo == XNOR_ALGO_AUTO && linear_popcount_applies(g, true))) {
         ConvGeom gi = g;
         gi.k_per_image = 1;
         xnor_status s = XNOR_ERR_UNSUPPORTED;

@@ -6,6 +6,7 @@
 // while each lane holds the words of its own pixel for the current tap.  Out-of-bounds taps are
 // skipped per lane, which is exactly "padding contributes 0".
 #include "xnor_internal.h"
+#include "linear_route.h"
 
 namespace xnor {
 
@@ -166,13 +167,14 @@ xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, c
     return launch_f<32>(xbits, wbits, K, A, alpha, out, dot_out, g, stream);
 }
 
-// Fully connected layers whose batch is small: the weights are read once and each meets few rows, so the time is that of
-// bringing them in.  The matrix-core form reads them as 4-bit operands (four times the packed bits) and walks the whole K
-// in one workgroup; here 16 lanes share a filter's row of packed words, V words per lane and load with U loads in flight,
-// each word meeting the same word of NB rows of the batch.  The 16 partial counts meet by lane exchanges.  Bound by the
-// latency of one trip to memory and the launch.  9216 -> 4096 back to back: one row 9.7 -> 2.5 us, eight rows
-// 15.9 -> 4.1 us.  (Two rows per workgroup: with four or eight the rows' counts are a serial chain in one wave,
-// 4.7 and 7.2 us for eight rows.)
+// Fully connected layers whose batch is small: every pair of rows reads the weights once (from memory the first, from L2
+// the others), so the time is that of bringing them in.  The matrix-core form reads them as 4-bit operands (four times the
+// packed bits) and walks the whole K in one workgroup; here 16 lanes share a filter's row of packed words, V words per
+// lane and load with U loads in flight, each word meeting the same word of NB rows of the batch.  The 16 partial counts
+// meet by lane exchanges.  Bound by the latency of one trip to memory and the launch.  9216 -> 4096 back to back: one row
+// 9.7 -> 2.5 us, eight rows 15.9 -> 4.1 us.  (Two rows per workgroup: with four or eight the rows' counts are a serial chain in one wave,
+// 4.7 and 7.2 us for eight rows.)  A lane's loads past the end of a row fetch its first words again and count nothing:
+// 2048 rows x 16 filters take 4.2 us at any length from 512 to 9216 features, 7.8 us at 25088 (three passes).
 constexpr int FC_LANES = 16;
 template <int V, int NB>
 __global__ __launch_bounds__(256) void linear_popcount_kernel(
@@ -180,7 +182,8 @@ __global__ __launch_bounds__(256) void linear_popcount_kernel(
     const float *__restrict__ alpha, float *__restrict__ out, int32_t *__restrict__ dot_out, int n, int c, int cw,
     int k_out)
 {
-    constexpr int U = V == 4 ? 5 : 8;                  // loads in flight per lane (V = 4: 320 words of a row at once)
+    constexpr int U = V == 4 ? 5 : 8;                  // loads in flight per lane (linear_words_per_pass in all)
+    static_assert(FC_LANES * V * U == linear_words_per_pass(V), "the rule counts passes of this size");
     typedef uint32_t vec __attribute__((ext_vector_type(V)));
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, sub = lane & (FC_LANES - 1);
     const int f = (blockIdx.x * 4 + wave) * (64 / FC_LANES) + lane / FC_LANES;
@@ -230,16 +233,10 @@ __global__ __launch_bounds__(256) void linear_popcount_kernel(
     }
 }
 
-// Where it is ahead of the matrix-core form (back to back, us; rows x filters, c channels):
-//     32768 pairs: 4.1 to 5.0 against 4.9 to 16;  65536: 6.0 against 7.6 (c = 2048), 8.0 against 5.2 (c = 64);
-//     131072: 10.0 against 17 (c = 9216), 9.8 against 6.7 (c = 2048).
-// The time here grows with the pairs and hardly with c, there with c and hardly with the pairs.
-bool linear_popcount_applies(const ConvGeom &g)
+bool linear_popcount_applies(const ConvGeom &g, bool matrix_image)
 {
     if (g.h != 1 || g.w != 1 || g.taps != 1 || g.ph != 0 || g.pw != 0 || g.dil_h != 1 || g.dil_w != 1) return false;
-    if (g.n > 65535 || g.fblocks > 65535) return false;        // (grid limits)
-    const long long pairs = (long long)g.n * g.k_out;
-    return pairs <= (g.c >= 4096 ? 131072 : g.c >= 2048 ? 65536 : 32768);
+    return linear_popcount_route(g.n, g.k_out, g.c, g.cw, matrix_image);
 }
 
 // (a 1x1 image and filter: K of a row is its A)
@@ -253,9 +250,11 @@ xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits,
         xbits, wbits, Krow, alpha, out, dot_out, g.n, g.c, g.cw, g.k_out)
 #define XNOR_GO_N(V)                                                                                                   \
     do { if (g.n == 1) XNOR_GO(V, 1); else XNOR_GO(V, 2); } while (0)
-    if (g.cw % 4 == 0) XNOR_GO_N(4);
-    else if (g.cw % 2 == 0) XNOR_GO_N(2);
-    else XNOR_GO_N(1);
+    switch (linear_words_per_load(g.cw)) {
+    case 4: XNOR_GO_N(4); break;
+    case 2: XNOR_GO_N(2); break;
+    default: XNOR_GO_N(1);
+    }
 #undef XNOR_GO_N
 #undef XNOR_GO
     return hip_status(hipGetLastError());

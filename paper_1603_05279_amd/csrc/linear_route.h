@@ -1,0 +1,46 @@
+// Which fully connected layers XNOR_ALGO_AUTO gives to linear_popcount_kernel.  Plain integers, no HIP headers: a host
+// compiler can check the rule against measurements.
+#pragma once
+#include <stdint.h>
+
+namespace xnor {
+
+// Packed words per load, and words of a row that one pass of the 16 lanes covers (linear_popcount_kernel).
+constexpr int linear_words_per_load(int cw) { return cw % 4 == 0 ? 4 : cw % 2 == 0 ? 2 : 1; }
+constexpr int linear_words_per_pass(int v) { return v == 4 ? 320 : v == 2 ? 256 : 128; }
+
+// n rows of c features (cw words), k filters; matrix_image: the caller gave the images of the matrix-core forms.
+//
+// A workgroup holds two rows (one if there is only one) and 16 filters whether they exist or not, so the time follows the
+// padded product: 2.5 us + rows * filters * passes over the row * 0.052 ns with 4 words per load (0.083 ns with 2, 0.032 ns
+// with 1; measured from 8192 to 2^20 padded products, 32 to 131072 features).  The matrix-core form takes 5 us for the
+// shortest rows and grows with c, hardly with rows and filters.  Both, back to back, us (rows x filters, c):
+//       2048 x 16, 512: 4.2 / 5.2      8192 x 4, 64: 13.3 / 5.0       32768 x 1, 512: 29.6 / 6.0
+//       8 x 8192, 2560: 6.0 / 6.2      8 x 8192, 2368 (2 words per load): 8.0 / 6.6
+//       96 x 1024, 4096: 8.3 / 8.4     128 x 1000, 4096: 10.4 / 8.5   8192 x 16, 9216: 9.4 / 12.9
+// The lines below keep the slower of the two at most 7 % behind over the 3590 measured shapes of more than two rows and at
+// most 10240 features.  Apart from them:
+//   - one or two rows, where nothing is padded, and more than 320 words, which the matrix-core form walks in many chunks:
+//     ahead wherever measured (1 x 32768, 64: 6.1 / 6.1; 128 x 1000, 25088: 25 / 44; above 32768 rows at most 25 % behind);
+//   - 16384 filters and more: the matrix-core form needs more workgroups than there are CUs for a few rows
+//     (4 x 32768, 4096: 9.4 / 15.2), except with 2 words per load (3 x 16384, 2112: 7.9 / 7.1);
+//   - from 16384 rows and 5120 features the matrix-core form's larger tiles no longer hold a row (16384 x 4, 9216:
+//     16.3 / 36.1; 32768 x 4, 5120: 30.1 / 32.3).
+inline bool linear_popcount_route(int n, int k, int c, int cw, bool matrix_image)
+{
+    // rows times filters: beyond these no shape was measured ahead
+    const int64_t pairs = (int64_t)n * k;
+    if (n > 65535 || pairs > (c >= 4096 ? 131072 : c >= 2048 ? 65536 : 32768)) return false;       // (n: grid limit)
+    if (n <= 2) return true;
+    const int v = linear_words_per_load(cw), pass = linear_words_per_pass(v);
+    const int64_t padded = ((int64_t)n + 1) / 2 * 2 * (((int64_t)k + 15) / 16 * 16);
+    const int64_t cost = padded * ((cw + pass - 1) / pass) * (v == 4 ? 8 : v == 2 ? 13 : 5) / 8;
+    // against the vector-ALU convolution (5.3 us + 6.5 ns per feature: 32768 x 1, 512: 30.8 / 7.4, 2048: 31.0 / 18.7,
+    // 4096: 30.6 / 32.1)
+    if (!matrix_image) return cost <= 53500 + 124 * (int64_t)c;
+    if (cw > 320 || (k >= 16384 && v != 2)) return true;
+    if (n >= 16384 && c >= 5120) return padded <= 524288 && (v != 2 || cw <= 256);
+    return cost <= (c < 4096 ? 40960 + 15 * (int64_t)c : c < 6144 ? 122880 : 28 * (int64_t)c);
+}
+
+}  // namespace xnor

@@ -89,7 +89,7 @@ xnor_status launch_bingrad_scale_plane(const float *gmax, float *plane, int n, i
 xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, const void *wmfma, const float *K, const float *A,
                                  const float *alpha, float *out, int32_t *dot_out,
                                  const ConvGeom &g, hipStream_t stream);
-bool linear_popcount_applies(const ConvGeom &g);
+bool linear_popcount_applies(const ConvGeom &g, bool matrix_image);
 xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits, const float *Krow, const float *alpha,
                                    float *out, int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
 // Third image of the wmfma buffer (after the int8 and 4-bit images): the packed weight words in

@@ -14,7 +14,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("shape", [
     (1, 1, 1), (1, 32, 17), (2, 33, 16), (3, 95, 15), (1, 64 * 32, 33), (5, 129 * 32, 31),     # words: 1, 2, 3, 64, 129
     (1, 256 * 32, 64), (2, 320 * 32, 9), (3, 324 * 32 - 7, 40),        # one whole turn of 4-word lanes, one word more
-    (257, 70, 127), (258, 70, 128), (8, 2100, 8192), (9, 2100, 8192),  # both sides of the rule
+    # both sides of the rule: pairs, padded rows and filters, words per load, few filters
+    (257, 70, 127), (258, 70, 128), (8, 2170, 8192), (9, 2170, 8192), (8, 2100, 8192), (128, 4096, 960), (128, 4096, 961),
+    (1025, 40, 3), (4099, 500, 2), (37, 1000, 1030),
 ])
 def test_few_rows_match_oracle_and_matrix_cores(shape):
     b, f, o = shape
