@@ -170,10 +170,11 @@ def test_linear_with_waves_along_K_matches_oracle(shape, algo):
     np.testing.assert_allclose(out.cpu().numpy(), r["out"], rtol=RTOL, atol=ATOL)
 
 
-@pytest.mark.parametrize("algo", ["auto", "mfma_f4"])
+@pytest.mark.parametrize("algo", ["auto", "mfma_i8", "mfma_f4"])
 def test_linear_with_few_rows_falls_back_to_the_four_wave_tiling(algo):
     """Five rows leave the activation region too small for the partial sums of the eight-wave tiling: asked for
-    explicitly it is refused, the library's own choice takes the four-wave form and matches the oracle."""
+    explicitly it is refused, the matrix-core forms' own choice of tiling takes the four-wave form and matches the
+    oracle ("auto" gives so few rows to the vector ALU and never asks for a tiling)."""
     rng = np.random.default_rng(151)
     b, f, o = 5, 4096 + 64, 33
     x = rng.standard_normal((b, f)).astype(np.float32)
