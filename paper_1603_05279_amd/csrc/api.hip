@@ -450,10 +450,9 @@ int xnor_bingrad_conv2d(const uint32_t *gbits, const uint32_t *wtbits, const voi
     if ((algo == XNOR_ALGO_MFMA_I8 || algo == XNOR_ALGO_MFMA_F4) && !wtmfma) return XNOR_ERR_NULL;
     if (algo == XNOR_ALGO_AUTO && dilated && !wtmfma) return XNOR_ERR_UNSUPPORTED;
     hipStream_t st = (hipStream_t)hip_stream;
-    if (fwd.n > 65535) return XNOR_ERR_UNSUPPORTED;
+    if (fwd.n > 65535) return XNOR_ERR_UNSUPPORTED;     // grid limit of the plane's launch, one answer for every algo
     // The matrix-core kernels read the scale of an image from gmax itself.  The plane is written only for the vector-ALU
-    // forms, which index K by pixel: writing it was a launch of its own
-    // ahead of the convolution (training step of a 128-channel 28 x 28 layer, 256 images: 119.8 -> 114.5 us).
+    // forms, which index K by pixel: writing it is a launch of its own ahead of the convolution (training step of a 128-channel 28 x 28 layer, 256 images: 119.8 -> 114.5 us).
     if (wtmfma && algo != XNOR_ALGO_POPCOUNT && !(algo == XNOR_ALGO_AUTO && linear_popcount_applies(g, true))) {
         ConvGeom gi = g;
         gi.k_per_image = 1;
@@ -462,7 +461,8 @@ int xnor_bingrad_conv2d(const uint32_t *gbits, const uint32_t *wtbits, const voi
             s = launch_conv_mfma(1, gbits, wtmfma, gmax, nullptr, ones, g_in, dot_out, gi, st);
         if (s == XNOR_ERR_UNSUPPORTED && algo != XNOR_ALGO_MFMA_F4)
             s = launch_conv_mfma(0, gbits, wtmfma, gmax, nullptr, ones, g_in, dot_out, gi, st);
-        if (s != XNOR_ERR_UNSUPPORTED || algo != XNOR_ALGO_AUTO) return s;
+        if (s != XNOR_ERR_UNSUPPORTED || algo != XNOR_ALGO_AUTO || dilated) return s;
+        algo = XNOR_ALGO_POPCOUNT;      // both matrix-core forms have refused the geometry
     }
     if (xnor_status s = launch_bingrad_scale_plane(gmax, scale_plane, fwd.n, fwd.h * fwd.w, st)) return s;
     return conv_dispatch(g, gbits, wtbits, wtmfma, scale_plane, nullptr, ones, g_in, dot_out, algo, st);

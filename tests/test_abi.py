@@ -100,6 +100,10 @@ def test_invalid_arguments_return_error_codes_without_launching():
     huge = xnor.make_desc(1, 32, 256, 256, 32768, 1, 1, 1, 0)
     assert L.xnor_conv2d(fake, fake, fake, fake, None, fake, fake, None, ctypes.byref(huge), 3, None) == ERR_UNSUP
     assert L.xnor_conv2d(fake, fake, fake, fake, None, fake, fake, None, ctypes.byref(huge), 2, None) == ERR_UNSUP
+    # strided backward convolution whose result both matrix-core forms refuse: no other form takes it, so nothing is launched
+    strided = xnor.make_desc(1, 32768, 256, 256, 32, 1, 1, 2, 0)
+    for algo in (0, 2, 3):
+        assert L.xnor_bingrad_conv2d(fake, fake, fake, fake, fake, fake, fake, None, ctypes.byref(strided), algo, None) == ERR_UNSUP
     # fused epilogue: matrix-core loops only, workspace required above 64 filters
     assert L.xnor_conv2d_binactiv(fake, fake, fake, fake, None, fake, None, None, fake, fake, None, fake,
                                   ctypes.byref(good), 1, None) == ERR_UNSUP
