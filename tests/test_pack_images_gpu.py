@@ -68,3 +68,17 @@ def test_weight_images(case, transposed):
     expect = np.ones(fk) if transposed else np.abs(F.astype(np.float64)).mean((1, 2, 3))
     # a float sum of n terms of one sign: at most n / 256 + 9 roundings on any path of the tree
     assert np.allclose(factor.cpu().numpy(), expect, rtol=(F[0].size / 256 + 10) * 2.0 ** -24, atol=0)
+
+
+def test_more_groups_than_workgroups():
+    # one filter value each: k_out / 8 image groups and k_out alpha groups, past the 2^22 workgroups of a launch by less
+    # than a turn (the first ones take a second turn)
+    k = (1 << 22) - (1 << 18)
+    rng = np.random.default_rng(22)
+    W = rng.standard_normal((k, 1, 1, 1)).astype(np.float32)
+    bits = torch.full((k, 1, 1), -1, dtype=torch.int32, device="cuda")
+    factor = torch.full((k,), -1.0, device="cuda")
+    xnor.xnor_pack_weights(to_dev(W), bits, factor, None, k, 1, 1, 1)
+    assert k + k // 8 > 1 << 22
+    assert np.array_equal(bits.cpu().numpy().reshape(-1), (W.reshape(-1) >= 0).astype(np.int32))
+    assert np.array_equal(factor.cpu().numpy(), np.abs(W.reshape(-1)))
