@@ -442,7 +442,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
     }
     // Float (and optional integer) results leave through buffer stores: the resource starts at the
     // tile's first image, a lane's vector offset names its pixel (plus its half-wave's four rows),
-    // the filter row is a scalar offset, so a store needs no per-lane address arithmetic.  Dead
+    // the filter row is a scalar offset (16-byte stores: see there), so a store needs no per-lane address arithmetic.  Dead
     // pixel columns and rows past the last filter get an offset beyond the resource, which the
     // buffer bounds check discards.  (The host refuses shapes whose tile span exceeds 2 GiB.)
     const size_t img_elems = (size_t)g.k_out * howo;
@@ -458,12 +458,17 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
         const int row0 = f0 + (wf_s * FW + i) * 32;                 // wave-uniform
         if (row0 + 32 <= g.k_out && howo == 1u && (g.k_out & 3) == 0) {
             // planes of one pixel (fully connected layers): a lane's four consecutive filter rows are 16
-            // contiguous, aligned bytes
+            // contiguous, aligned bytes.  A store of more than 64 bits still reads its data two wait states after it
+            // issued; the compiler keeps the next write of those registers that far away unless the scalar offset is a
+            // register, so the row goes into the vector offset (with it in the scalar one, 16 to 64 of the 280576 results
+            // of 8768 rows, 5 features and 32 filters were now and then those of other filters).  The distance costs
+            // 0.25 us of a launch (256 rows, 9216 -> 4096: 12.4 -> 12.65 us), as does one kept by explicit waits.
+            const uint32_t v0 = voff[j] + 4u * (uint32_t)row0;
 #pragma unroll
             for (int q = 0; q < 4; ++q)
                 __builtin_amdgcn_raw_buffer_store_b128(v4u{value_of(4 * q), value_of(4 * q + 1), value_of(4 * q + 2),
                                                            value_of(4 * q + 3)},
-                                                       rs, (int)voff[j], (row0 + 8 * q) * 4, 0);
+                                                       rs, (int)(v0 + 32u * q), 0, 0);
             return;
         }
         // Results larger than a quarter of the 256 MB last-level cache leave with the non-temporal hint (measured: a

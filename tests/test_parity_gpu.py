@@ -170,6 +170,25 @@ def test_linear_with_waves_along_K_matches_oracle(shape, algo):
     np.testing.assert_allclose(out.cpu().numpy(), r["out"], rtol=RTOL, atol=ATOL)
 
 
+@pytest.mark.parametrize("shape", [(8768, 5, 32), (300, 70, 256), (257, 4128, 64)])
+def test_linear_forms_agree_on_every_call(shape):
+    """Results of whole 32-filter blocks leave four at a time; every call gives the float expression of the same integers."""
+    rng = np.random.default_rng(157)
+    b, f, o = shape
+    xd = to_dev(rng.standard_normal((b, f, 1, 1)).astype(np.float32))
+    pw = xnor.PackedWeights(to_dev(rng.standard_normal((o, f, 1, 1)).astype(np.float32)))
+    desc = xnor.make_desc(b, f, 1, 1, o, 1, 1)
+    bufs = xnor.ConvBuffers(desc)
+    xnor.xnor_binactiv(xd, None, None, bufs.xbits, bufs.A, None, desc)
+    want = torch.empty((b, o), device="cuda")
+    xnor.xnor_linear(bufs.xbits, pw.wbits, pw.wmfma, bufs.A, pw.alpha, want, None, b, f, o, xnor.XNOR_ALGO_POPCOUNT)
+    for algo in ("mfma_i8", "mfma_f4"):
+        outs = [torch.empty((b, o), device="cuda") for _ in range(20)]
+        for out in outs:
+            xnor.xnor_linear(bufs.xbits, pw.wbits, pw.wmfma, bufs.A, pw.alpha, out, None, b, f, o, xnor.ALGOS[algo])
+        assert all(torch.equal(out, want) for out in outs)
+
+
 @pytest.mark.parametrize("algo", ["auto", "mfma_i8", "mfma_f4"])
 def test_linear_with_few_rows_falls_back_to_the_four_wave_tiling(algo):
     """Five rows leave the activation region too small for the partial sums of the eight-wave tiling: asked for
