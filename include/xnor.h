@@ -17,9 +17,9 @@
  *    asynchronously; no entry point synchronises.
  *  - Return value: XNOR_OK (0) or a negative xnor_status.  Arguments are validated before anything is
  *    launched.  The entry points that enqueue two kernels (xnor_compute_K, xnor_binactiv and xnor_binactiv_streamed with K,
- *    xnor_bingrad_binarize, xnor_bingrad_conv2d, xnor_conv2d_binactiv) may have enqueued the first one
- *    when the second reports XNOR_ERR_UNSUPPORTED (no kernel fits the shape) or XNOR_ERR_HIP; the first
- *    kernel writes only that call's own outputs or scratch.
+ *    xnor_bingrad_binarize, xnor_bingrad_conv2d where a vector-ALU form runs it, xnor_conv2d_binactiv) may have
+ *    enqueued the first one when the second reports XNOR_ERR_UNSUPPORTED (no kernel fits the shape) or
+ *    XNOR_ERR_HIP; the first kernel writes only that call's own outputs or scratch.
  *  - Real tensors are float32, NCHW, densely packed, row-major:
  *        x   [n][c][h_in][w_in]      w [k_out][c][kh][kw]      out [n][k_out][h_out][w_out]
  *    h_out = (h_in + 2*pad_h - kh)/stride_h + 1 (floor), same for w_out.

@@ -171,10 +171,10 @@ xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, c
 // the others), so the time is that of bringing them in.  The matrix-core form reads them as 4-bit operands (four times the
 // packed bits) and walks the whole K in one workgroup; here 16 lanes share a filter's row of packed words, V words per
 // lane and load with U loads in flight, each word meeting the same word of NB rows of the batch.  The 16 partial counts
-// meet by lane exchanges.  Bound by the latency of one trip to memory and the launch.  9216 -> 4096 back to back: one row
-// 9.7 -> 2.5 us, eight rows 15.9 -> 4.1 us.  (Two rows per workgroup: with four or eight the rows' counts are a serial chain in one wave,
-// 4.7 and 7.2 us for eight rows.)  A lane's loads past the end of a row fetch its first words again and count nothing:
-// 2048 rows x 16 filters take 4.2 us at any length from 512 to 9216 features, 7.8 us at 25088 (three passes).
+// meet by lane exchanges.  Bound by the latency of one trip to memory and the launch.  9216 -> 4096, launches of one graph:
+// one row 9.4 -> 2.1 us, eight rows 11.0 -> 3.6 us.  (Two rows per workgroup: with four or eight the rows' counts are a
+// serial chain in one wave, 0.6 and 3.1 us more for eight rows.)  A lane's loads past the end of a row fetch its first words again and
+// count nothing: 2048 rows x 16 filters take 4.2 us at any length from 512 to 9216 features, 7.8 us at 25088 (three passes).
 constexpr int FC_LANES = 16;
 template <int V, int NB>
 __global__ __launch_bounds__(256) void linear_popcount_kernel(

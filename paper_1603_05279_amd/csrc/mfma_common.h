@@ -63,7 +63,8 @@ inline void set_fast_staging(MfmaPlan *pl, const ConvGeom &g, int fmt)
 inline int worst_region_rows(const ConvGeom &g, int run, int step)
 {
     const long long howo = (long long)g.ho * g.wo;
-    // (the validated geometry keeps m_total within 31 bits: 32-bit divisions, a third of the 64-bit ones' time)
+    // (the validated geometry keeps m_total within 31 bits: 32-bit divisions; a 27 x 27 layer's 243 starts 3.5 -> 2.2 us of
+    // host time against 64-bit ones)
     uint32_t a = (uint32_t)step, b = (uint32_t)howo;
     while (b) { const uint32_t t = a % b; a = b; b = t; }       // gcd(step, howo)
     const uint32_t period = (uint32_t)howo / a;

@@ -46,12 +46,14 @@ constexpr int PACK_ROWS = 8;                        // filters per image workgro
 constexpr int PACK_PAIRS = 16;                      // (word, tap) pairs of a workgroup at most
 constexpr int PACK_BYTES = PACK_ROWS * (32 * PACK_PAIRS + 4) + 32 * 16 * 4;     // either layout below, rows padded
 
-// What bounds it: the bytes are few (4 per weight read, 1.9 written), so the time is round trips and instructions.
-// Each workgroup reads 8 filters x 32 channels x the taps once, as runs of memory copied without index arithmetic to
-// one byte per weight in LDS; a wave-wide comparison of 64 such bytes gives two packed words, and all images are
-// written from the words in runs of whole cache lines.  Measured against one workgroup per filter that walked it four
-// times: 15.2 -> 6.9 us at 128 filters of 128 x 3 x 3 (15.3 -> 7.1 us transposed), 334 -> 101 us at 4096 x 9216 (0.25 GB
-// read and written, 2.3 TB/s).
+// What bounds it: the bytes are few (4 per weight read by the image workgroups and, in mode 0, again for alpha; 1.75
+// written), so the time of a layer is round trips and instructions.  Each workgroup reads 8 filters x 32 channels x the
+// taps once, as runs of memory copied without index arithmetic to one byte per weight in LDS; a wave-wide comparison of 64
+// such bytes gives two packed words, and all images are written from the words: the int8 and 4-bit images in whole cache
+// lines, the scalar-path image in 32-byte runs, wbits in runs of the words a workgroup holds (one word from 9 taps on).
+// Measured back to back against one workgroup per filter that walked it four times: 14.2 -> 6.2 us at 128 filters of
+// 128 x 3 x 3 (13.6 -> 6.4 us transposed), 292 -> 95 us at 4096 x 9216 (0.30 GB read, 0.07 GB written: 3.9 TB/s; 358 -> 264 us
+// transposed, where a row of memory is a channel).
 template <int MODE>
 __global__ __launch_bounds__(256) void pack_weights_kernel(
     const float *__restrict__ w, uint32_t *__restrict__ wbits, float *__restrict__ alpha,
