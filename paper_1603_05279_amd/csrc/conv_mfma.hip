@@ -12,8 +12,10 @@
 // (pixels flattened over image, row, column so small images still fill the tile).  Per channel
 // chunk it widens the packed activation bits of the input rows its pixels touch (halo included,
 // halo = 0) into LDS once; every tap then reads the same LDS image at a shifted offset.
-// Weights come from the pre-widened image written by the weight packer, one contiguous KiB per
-// 32-filter operand, prefetched several K-steps ahead in registers.  Filters are the M operand
+// Weights: 4-bit operands are widened in the K loop from the packed words (WStreamBits: 256 bytes per K-step and 32
+// filters, seven vector instructions that hide behind the matrix instructions of the step before); the other formats read
+// the pre-widened image written by the weight packer, one contiguous KiB per 32-filter operand.  Both are
+// prefetched several K-steps ahead in registers.  Filters are the M operand
 // and pixels the N operand, so each lane of the result holds one pixel column: stores along a
 // filter plane are contiguous across lanes.
 #include "mfma_common.h"
@@ -38,19 +40,62 @@ template <int KH, int KW> __device__ __forceinline__ float box_sum_lds(const flo
     return s;
 }
 
+// Everything a convolution kernel is given.  One struct, so that its place in the kernel argument segment is known: a phase of
+// the kernel reads the fields it needs again from there (reload) instead of holding all phases' fields in scalar registers,
+// which the compiler would otherwise park in vector register lanes (two vector instructions per field and wave).
+struct ConvArgs {
+    const uint32_t *xbits;
+    const v4i *wimg;
+    const float *K, *A, *alpha;
+    float *out;
+    int32_t *dot_out;
+    uint32_t wimg_bytes;
+    ConvGeom g;
+    MfmaPlan pl;
+    FuseArgs fz;
+};
+
+// A fresh copy of the kernel's arguments: only the fields that are used afterwards are loaded, by scalar loads.
+__device__ __forceinline__ ConvArgs reload_args()
+{
+    typedef const __attribute__((address_space(4))) uint64_t *seg_t;
+    seg_t p = (seg_t)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(p));           // the compiler must not find the earlier loads' values behind it
+    static_assert(sizeof(ConvArgs) % 8 == 0, "copied by 64-bit words");
+    struct Words { uint64_t w[sizeof(ConvArgs) / 8]; } words;
+#pragma unroll
+    for (int i = 0; i < (int)(sizeof(ConvArgs) / 8); ++i) words.w[i] = p[i];
+    return __builtin_bit_cast(ConvArgs, words);
+}
+
+// What bounds it: with a few waves per SIMD every phase costs its instructions (5.2 cycles each for a wave, 4 for the SIMD);
+// the K loop then runs at the matrix pipes' 19 ns per instruction and SIMD (34 cycles; the clock is 1.6 to 1.8 GHz while all
+// pipes are busy), which up to four vector instructions per matrix instruction do not slow down.
+// Against 4-bit records in memory, a staging loop of one word per item and one set of arguments held throughout (launches
+// back to back): 256 rows x 9216 -> 4096 12.7 -> 8.6 us, 128 x 28 x 28 batch 256 30.5 -> 26.7 us (983 -> 653 vector
+// instructions per wave), 96 x 27 x 27 5 x 5 batch 64 22.6 -> 19.9, 384 x 13 x 13 batch 128 21.5 -> 19.9, 512 x 7 x 7 batch
+// 256 22.7 -> 21.0, 256 x 14 x 14 batch 256 24.0 -> 22.1 us.
+//
 // Accumulator tiles of up to 8 result blocks leave room for two waves per SIMD (256 registers each).
 // KS > 1: KS groups of WF x WP waves share the K loop of the same tile (group k takes the k-th run of steps) and add
 // their accumulators through LDS at the end: more weight loads in flight and more waves for the staging where a
 // problem offers few output tiles and a long K (fully connected layers).  Consecutive-record streams only.
 template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, bool LINEAR, bool POOL = false, int KS = 1>
-__global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ? 2 : 1)) void conv_mfma_kernel(
-    const uint32_t *__restrict__ xbits, const v4i *__restrict__ wimg, uint32_t wimg_bytes,
-    const float *__restrict__ K, const float *__restrict__ A, const float *__restrict__ alpha,
-    float *__restrict__ out, int32_t *__restrict__ dot_out, ConvGeom g, MfmaPlan pl, FuseArgs fz)
+__global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) && WF * WP * KS <= 8 ? 2 : 1)) void conv_mfma_kernel(
+    ConvArgs args)
 {
+    const uint32_t *xbits = args.xbits;
+    const v4i *wimg = args.wimg;
+    const float *K = args.K, *A = args.A, *alpha = args.alpha;
+    const uint32_t wimg_bytes = args.wimg_bytes;
+    const ConvGeom &g = args.g;
+    const MfmaPlan &pl = args.pl;
+    const FuseArgs &fz = args.fz;
     typedef Enc<FMT> E;
     // operands staged as they are (no sign bits to widen, no K): bfloat16 parts and int8 levels
     constexpr bool RAW = FMT == 2 || FMT == 3;
+    // packed bits staged through set_direct_staging's plan
+    constexpr bool DIRECT = LINEAR && !RAW;
     typedef typename E::acc_t acc_t;
     static_assert(KS == 1 || (LINEAR && !FUSE && !POOL), "waves along K: plain epilogue, consecutive records");
     constexpr int NT = 64 * WF * WP * KS;
@@ -59,13 +104,10 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
     // Weight prefetch depth.  Five steps pay off on long K loops; the 64-filter tiles serve layers
     // with short K loops and many workgroups, and the fused epilogue needs registers of its own:
     // there three steps keep more waves resident.
+    // (Packed words cost one register per step: five steps throughout.)
     // A wave tile of a single result block (fully connected layers: few output tiles, long K) issues one matrix
-    // instruction per KiB of weights: only a deep ring keeps enough bytes in flight to cover the L2 latency.
-    // The division-free staging loop costs four more registers at the kernel's peak (the end of the K loop).  The
-    // 64 x 256 and 128 x 64 tilings sit exactly at a count where one more wave per SIMD fits (127 and 96): they keep
-    // the general loop (measured: ResNet 64x56 41 -> 44 us with the fast loop).
-    constexpr bool FAST_STAGING = !(FW == 2 && PW == 2 && WF == 1 && WP == 4) && !(FW == 1 && PW == 2 && WF == 4 && WP == 1);
-    constexpr int DW = (FW * PW == 1 && FMT < 2 && !FUSE) ? 7 : (FUSE || FT <= 64 || FMT == 2) ? 3 : 5;      // (bfloat16 parts: a step is three times as long)
+    // instruction per record: only a deep ring keeps enough bytes in flight to cover the L2 latency.
+    constexpr int DW = (FW * PW == 1 && FMT < 2 && !FUSE) ? 7 : (FMT == 1) ? 5 : (FUSE || FT <= 64 || FMT == 2) ? 3 : 5;      // (bfloat16 parts: a step is three times as long)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     int *rowinfo = reinterpret_cast<int *>(lds + pl.region_bytes);
     int *xoff_tab = rowinfo + pl.max_rows;     // [(nsteps + KLOOP_TABLE_PAD) * BPS]
@@ -132,18 +174,22 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
     const int r_hi = (int)(img_b * g.hp + oy_b * g.sh) + g.kh - 1;
     const int nrows = r_hi - r_lo + 1;
 
-    E::build_lut(lds + pl.lut_offset, tid, NT);
-    // alpha (fused epilogue: also scale and shift) of this workgroup's filters, staged once behind the
-    // widening table ([FT] each); filters past the last one repeat it and are masked later
-    float *par_lds = reinterpret_cast<float *>(lds + pl.lut_offset + E::LUT_BYTES);
-    for (int t = tid; t < FT; t += NT) {
-        const int kc = min(f0 + t, g.k_out - 1);
-        par_lds[t] = alpha[kc];
+    // alpha (fused epilogue: also scale and shift) of this workgroup's filters: requested first, written behind the widening
+    // table ([FT] each) once the staging loads are on their way; filters past the last one repeat it and are masked later
+    constexpr int NP = (FT + NT - 1) / NT;
+    float par[NP][FUSE ? 3 : 1];
+#pragma unroll
+    for (int u = 0; u < NP; ++u) {
+        const int kc = min(f0 + tid + u * NT, g.k_out - 1);
+        par[u][0] = alpha[kc];
         if constexpr (FUSE) {
-            par_lds[FT + t] = fz.bn_scale ? fz.bn_scale[kc] : 1.0f;
-            par_lds[2 * FT + t] = fz.bn_scale ? fz.bn_shift[kc] : 0.0f;
+            par[u][1] = fz.bn_scale ? fz.bn_scale[kc] : 1.0f;
+            par[u][2] = fz.bn_scale ? fz.bn_shift[kc] : 0.0f;
         }
     }
+    float *par_lds = reinterpret_cast<float *>(lds + pl.lut_offset + E::LUT_BYTES);
+    E::build_lut(lds + pl.lut_offset, tid, NT);
+    if constexpr (!DIRECT)
     for (int rr = tid; rr < nrows; rr += NT) {
         const uint32_t R = (uint32_t)(r_lo + rr);
         const uint32_t img = pl.div_hp.div(R);
@@ -166,16 +212,35 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
             xoff_tab[b] = (int)(dy * pl.row_pitch + dx * pl.ps + wl * E::BPB);
         }
     }
+    // pixel t of the tile: image (counted from img_a), padded row (from r_lo) and column of its window's origin
+    const uint32_t rel0 = m0 - img_a * howo;
+    auto locate = [=](const ConvGeom &g, const MfmaPlan &pl, uint32_t t, uint32_t &img, uint32_t &pix, int &row, int &col) {
+        const uint32_t rel = rel0 + min(t, m_end - 1u - m0);
+        uint32_t oy, ox;
+        if constexpr (DIRECT) {
+            const uint32_t rows = pl.sd_wo.div(rel);
+            img = pl.sd_ho.div(rows);
+            oy = rows - mul24(img, (uint32_t)g.ho);
+            ox = rel - mul24(rows, (uint32_t)g.wo);
+            pix = rel - mul24(img, (uint32_t)(g.ho * g.wo));
+        } else {
+            const uint32_t howo = (uint32_t)(g.ho * g.wo);
+            img = g.div_howo.div(rel);
+            pix = rel - img * howo;
+            oy = g.div_wo.div(pix);
+            ox = pix - oy * g.wo;
+        }
+        row = (int)(img * g.hp + (oy - oy_a) * g.sh);
+        col = (int)ox * g.sw;
+    };
     // LDS byte offset of each of this lane's pixel columns (window origin in the padded frame)
     int pbase[PW];
 #pragma unroll
     for (int j = 0; j < PW; ++j) {
-        const uint32_t m = min(m0 + (uint32_t)((wp * PW + j) * 32 + l32), m_end - 1u);
-        const uint32_t img = g.div_howo.div(m);
-        const uint32_t pix = m - img * howo;
-        const uint32_t oy = g.div_wo.div(pix), ox = pix - oy * g.wo;
-        pbase[j] = ((int)(img * g.hp + oy * g.sh) - r_lo) * pl.row_pitch + (int)ox * g.sw * pl.ps +
-                   (E::HALF_SPLIT ? 16 * half : 0);
+        uint32_t img, pix;
+        int row, col;
+        locate(g, pl, (uint32_t)((wp * PW + j) * 32 + l32), img, pix, row, col);
+        pbase[j] = row * pl.row_pitch + col * pl.ps + (E::HALF_SPLIT ? 16 * half : 0);
     }
     // weight records of this wave's filter blocks: record index = fblk * recs_per_fblock + step record
     const int recs_per_fb = (g.taps * g.cw + E::BPS - 1) / E::BPS;
@@ -201,100 +266,88 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
     const int steps_per_tap = pl.tap_jump ? ccw / E::BPS : 0x7fffffff;
-    for (int wbase = 0; wbase < g.cw; wbase += ccw) {
-        __syncthreads();   // tables visible / previous chunk fully consumed
-        // the first words of the matrix A are requested before the activation words, so that the two round trips
-        // to memory overlap
-        constexpr int FA = FW * PW > 4 ? 2 : 0;       // (small tiles: the registers are worth more as a fourth wave per SIMD)
-        float a_reg[FA + 1];
+    // (direct staging: one chunk holds every channel word)
+    for (int wbase = 0; DIRECT ? wbase < 1 : wbase < args.g.cw; wbase += DIRECT ? 1 : ccw) {
+        // (read per chunk: otherwise everything a chunk derives from them is hoisted in front of the first one and held)
+        const ConvArgs now = reload_args();
+        const ConvGeom &g = now.g;
+        const MfmaPlan &pl = now.pl;
+        const uint32_t *xbits = now.xbits;
+        const v4i *wimg = now.wimg;
+        const float *K = now.K, *A = now.A, *alpha = now.alpha;
+        if (wbase > 0 || !DIRECT || E::LUT_BYTES > 0) __syncthreads();   // tables visible / previous chunk fully consumed
         const bool stageA = !RAW && wbase == 0 && !K;
-        auto a_load = [&](int it) -> float {
-            const uint32_t rr = pl.div_wp.div_small((uint32_t)it);
-            const int xcol = it - (int)rr * g.wp - g.pw;
-            const int rowbase = rowinfo[rr];
-            const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w;
-            return ok ? A[(size_t)rowbase + xcol] : 0.0f;
-        };
+        if constexpr (DIRECT) {
+            const int px_a = g.h * g.w;
+            const uint32_t left = (uint32_t)(g.n - (int)img_a) * (uint32_t)px_a;       // (validated: n * h * w fits 31 bits)
+            // (the images a tile can touch stay below 2 GiB; the resource may end early, never late)
+            const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<uint32_t *>(xbits) + (size_t)img_a * px_a * g.cw, 0,
+                (int)min((size_t)left * (uint32_t)g.cw * 4u, (size_t)0x7ffffff0), 0x00020000);
+            const __amdgpu_buffer_rsrc_t arsrc = __builtin_amdgcn_make_buffer_rsrc(
+                const_cast<float *>(A) + (size_t)img_a * px_a, 0, stageA ? (int)(min(left, 0x1fffffffu) * 4u) : 0, 0x00020000);
+            const int items = nrows * g.wp * pl.quads;
+            const int y0 = (int)oy_a * g.sh;
+            auto stage = [&](auto vecc) {
+                constexpr int V = decltype(vecc)::value;
+                constexpr int FB = 4;           // items in flight per thread: a tile rarely has more
+                for (int base = 0; base < items; base += NT * FB) {
+                    uint32_t bits[FB][V];
+                    float av[FB];
+                    int dst[FB], adst[FB], wl[FB];
+                    bool ok[FB];
 #pragma unroll
-        for (int u = 0; u < FA; ++u) a_reg[u] = (stageA && tid + u * NT < nrows * g.wp) ? a_load(tid + u * NT) : 0.0f;
-        if (!RAW && pl.dense == 1) {
-          if constexpr (!RAW) {
-            // 1x1 filter without padding: the tile's pixels are consecutive pixels of the input and their packed
-            // words one contiguous, 16-byte aligned run of memory: four words per load, up to twelve loads in flight
-            // (a fully connected layer's 36 words per thread in one round trip)
-            constexpr int FD = FW * PW == 1 ? 12 : 4;     // (the one-block wave tiles of fully connected layers have the registers)
-            const int nwords = (int)(m_end - m0) * ccw;
-            const uint4 *src = reinterpret_cast<const uint4 *>(xbits + (size_t)m0 * g.cw);
-            for (int i0 = tid * 4; i0 < nwords; i0 += NT * 4 * FD) {
-                uint4 v[FD];
+                    for (int u = 0; u < FB; ++u) {
+                        if (base + u * NT >= items) break;                              // (uniform)
+                        const uint32_t it = (uint32_t)(base + u * NT + tid);
+                        const uint32_t px = pl.sd_quads.div(it), q = it - mul24(px, (uint32_t)pl.quads);
+                        const uint32_t rr = pl.sd_wp.div(px);
+                        const uint32_t xc = px - mul24(rr, (uint32_t)g.wp);
+                        const uint32_t yy = (uint32_t)y0 + rr, img = pl.sd_hp.div(yy);
+                        const uint32_t y = yy - mul24(img, (uint32_t)g.hp) - (uint32_t)g.ph, x = xc - (uint32_t)g.pw;
+                        ok[u] = (int)it < items && y < (uint32_t)g.h && x < (uint32_t)g.w;
+                        const uint32_t pix = mul24(mul24(img, (uint32_t)g.h) + y, (uint32_t)g.w) + x;
+                        const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + q * (V * 4u) : 0x80000000u;
+                        if constexpr (V == 4) {
+                            const v4u r = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
+                            bits[u][0] = r[0]; bits[u][1] = r[1]; bits[u][2] = r[2]; bits[u][3] = r[3];
+                        } else if constexpr (V == 3) {
+                            const auto r = __builtin_amdgcn_raw_buffer_load_b96(xrsrc, (int)off, 0, 0);
+                            bits[u][0] = r[0]; bits[u][1] = r[1]; bits[u][2] = r[2];
+                        } else if constexpr (V == 2) {
+                            const auto r = __builtin_amdgcn_raw_buffer_load_b64(xrsrc, (int)off, 0, 0);
+                            bits[u][0] = r[0]; bits[u][1] = r[1];
+                        } else {
+                            bits[u][0] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)off, 0, 0);
+                        }
+                        wl[u] = (int)q * V;
+                        const bool first = stageA && q == 0 && (int)it < items;
+                        adst[u] = first ? (int)px : -1;
+                        if (stageA)
+                            av[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                                                                  arsrc, (int)(ok[u] && q == 0 ? pix * 4u : 0x80000000u), 0, 0));
+                        dst[u] = (int)it < items ? (int)(mul24(rr, (uint32_t)pl.row_pitch) + mul24(xc, (uint32_t)pl.ps) +
+                                                         q * (uint32_t)(V * E::BPB))
+                                                 : -1;
+                    }
 #pragma unroll
-                for (int u = 0; u < FD; ++u) {
-                    const int i = i0 + u * NT * 4;
-                    v[u] = src[min(i, nwords - 4) >> 2];
-                }
+                    for (int u = 0; u < FB; ++u) {
+                        if (base + u * NT >= items) break;
+                        if (dst[u] >= 0) {
 #pragma unroll
-                for (int u = 0; u < FD; ++u) {
-                    const int i = i0 + u * NT * 4;
-                    if (i < nwords) {
-                        const uint32_t px = pl.div_ccw.div_small((uint32_t)i);
-                        const int wl = i - (int)px * ccw;
-                        const uint32_t m = m0 + px;
-                        const uint32_t R = g.div_wo.div(m);                 // image row of the pixel (h_out = h, w_out = w)
-                        uint8_t *dst = lds + ((int)R - r_lo) * pl.row_pitch + (int)(m - R * g.wo) * pl.ps + wl * E::BPB;
-                        const uint32_t wv[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
-#pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            E::widen_word_lut(dst + q * E::BPB, lut, wv[q], true, g.c - (wl + q) * 32);
+                            for (int v = 0; v < V; ++v) {
+                                const int nch = g.c % 32 == 0 ? 32 : g.c - (wl[u] + v) * 32;
+                                E::widen_word_lut(lds + dst[u] + v * E::BPB, lut, bits[u][v], ok[u], nch);
+                            }
+                            if (stageA && adst[u] >= 0) a_lds[adst[u]] = av[u];
+                        }
                     }
                 }
-            }
-          }
-        } else if (!RAW && FAST_STAGING && pl.dense == 2) {
-          if constexpr (!RAW && FAST_STAGING) {
-            // (row, column, word) of the thread's current item, advanced by the stride's increments with carries
-            const int items = nrows * g.wp * ccw;
-            const uint32_t q0 = pl.div_ccw.div_small((uint32_t)tid);
-            int wl = tid - (int)q0 * ccw;
-            int rr = (int)pl.div_wp.div_small(q0);
-            int xc = (int)q0 - rr * g.wp;
-            int it = tid;
-            // what one workgroup-wide stride of NT items adds to (word, column, row): wave-uniform
-            const uint32_t dq = pl.div_ccw.div_small((uint32_t)NT);
-            const int st_dwl = NT - (int)dq * ccw;
-            const int st_drr = (int)pl.div_wp.div_small(dq);
-            const int st_dx = (int)dq - st_drr * g.wp;
-            const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
-                const_cast<uint32_t *>(xbits), 0, (int)((uint32_t)(g.n * g.h * g.w) * (uint32_t)g.cw * 4u), 0x00020000);
-            constexpr int FB = 8;
-            for (; it < items;) {
-                uint32_t bits[FB];
-                int dst[FB];
-                bool ok[FB];
-#pragma unroll
-                for (int u = 0; u < FB; ++u) {
-                    const int rowbase = rowinfo[min(rr, nrows - 1)];
-                    const int xv = xc - g.pw;
-                    ok[u] = rowbase >= 0 && (uint32_t)xv < (uint32_t)g.w && it < items;
-                    // word index (rowbase + xv) * cw + wbase + wl, in bytes; outside the image: beyond the buffer
-                    const int woff = (int)__umul24((uint32_t)(rowbase + xv), (uint32_t)g.cw) + wbase + wl;
-                    bits[u] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, ok[u] ? woff * 4 : (int)0x80000000u, 0, 0);
-                    dst[u] = it < items ? (int)(__umul24((uint32_t)rr, (uint32_t)pl.row_pitch) +
-                                                __umul24((uint32_t)xc, (uint32_t)pl.ps)) + wl * E::BPB
-                                        : -1;
-                    it += NT;
-                    wl += st_dwl;
-                    const int c1 = wl >= ccw ? 1 : 0;
-                    wl -= c1 ? ccw : 0;
-                    xc += st_dx + c1;
-                    const int c2 = xc >= g.wp ? 1 : 0;
-                    xc -= c2 ? g.wp : 0;
-                    rr += st_drr + c2;
-                }
-#pragma unroll
-                for (int u = 0; u < FB; ++u)
-                    if (dst[u] >= 0) E::widen_word_lut(lds + dst[u], lut, bits[u], ok[u], 32);
-            }
-          }
+            };
+            if (pl.vec == 4) stage(std::integral_constant<int, 4>{});
+            else if (pl.vec == 3) stage(std::integral_constant<int, 3>{});
+            else if (pl.vec == 2) stage(std::integral_constant<int, 2>{});
+            else stage(std::integral_constant<int, 1>{});
         } else {
         const int items = nrows * g.wp * ccw;
         constexpr int FB = RAW ? 4 : 8;        // items in flight per thread: loads first, then widening (every batch costs one round trip to L2 or HBM)
@@ -341,23 +394,35 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
                 }
         }
         }
-        if (stageA) {
+        if (!DIRECT && stageA) {
             // the matrix A of the same input rows (0 in the halo), for the K of this tile
+            for (int it = tid; it < nrows * g.wp; it += NT) {
+                const uint32_t rr = pl.div_wp.div_small((uint32_t)it);
+                const int xcol = it - (int)rr * g.wp - g.pw;
+                const int rowbase = rowinfo[rr];
+                a_lds[it] = rowbase >= 0 && xcol >= 0 && xcol < g.w ? A[(size_t)rowbase + xcol] : 0.0f;
+            }
+        }
+        if (wbase == 0) {
 #pragma unroll
-            for (int u = 0; u < FA; ++u)
-                if (tid + u * NT < nrows * g.wp) a_lds[tid + u * NT] = a_reg[u];
-            for (int it = tid + FA * NT; it < nrows * g.wp; it += NT) a_lds[it] = a_load(it);
+            for (int u = 0; u < NP; ++u)
+                if (NP * NT == FT || tid + u * NT < FT) {
+                    par_lds[tid + u * NT] = par[u][0];
+                    if constexpr (FUSE) {
+                        par_lds[FT + tid + u * NT] = par[u][1];
+                        par_lds[2 * FT + tid + u * NT] = par[u][2];
+                    }
+                }
         }
         __syncthreads();
         // K of the tile's output pixels, an equal share per wave: the kh x kw taps of A in row-major order over the
         // staged rows (halo entries add +0.0f, the same bits as skipping them), divided by kh*kw
         constexpr int KPW = (PT + WF * WP * KS - 1) / (WF * WP * KS);
         if (!RAW && wbase == 0 && !K) for (int kt = wave * KPW + lane; kt < min((wave + 1) * KPW, PT); kt += 64) {
-            const uint32_t m = min(m0 + (uint32_t)kt, m_end - 1u);
-            const uint32_t img = g.div_howo.div(m);
-            const uint32_t pix = m - img * howo;
-            const uint32_t oy = g.div_wo.div(pix), ox = pix - oy * g.wo;
-            const float *ap = a_lds + ((int)(img * g.hp + oy * g.sh) - r_lo) * g.wp + (int)ox * g.sw;
+            uint32_t img, pix;
+            int row, col;
+            locate(g, pl, (uint32_t)kt, img, pix, row, col);
+            const float *ap = a_lds + row * g.wp + col;
             // the common filters with every tap's read in flight at once (one LDS latency instead of one per group
             // of four taps); the additions keep the row-major order either way
             float s;
@@ -380,7 +445,21 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
 
         // ---- software-pipelined K loop over this chunk's steps --------------------------------
         // record of step s: rec0 + s + (s / steps_per_tap) * tap_jump
-        if constexpr (LINEAR && KS > 1) {
+        if constexpr (FMT == 1) {
+            // packed words, widened in the K loop
+            int fblk[FW];
+#pragma unroll
+            for (int i = 0; i < FW; ++i)
+                fblk[i] = __builtin_amdgcn_readfirstlane(min(f0 / 32 + wf * FW + i, g.fblocks - 1));
+            const int nblk = g.taps * g.cw;
+            const int per = (nsteps + KS - 1) / KS;
+            const int s0 = KS > 1 ? __builtin_amdgcn_readfirstlane(wk * per) : 0;
+            const int ns = KS > 1 ? max(0, min(per, nsteps - s0)) : nsteps;
+            const bool odd = (g.taps * ccw) % 2 != 0 && s0 + ns == nsteps;
+            WStreamBits<FW, LINEAR, KS != 1 ? 2 : 0> ws(reinterpret_cast<const uint32_t *>(wimg), fblk, nblk,
+                                                        wbase / E::BPS + s0, ns, odd, lane, steps_per_tap, pl.tap_jump);
+            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab + s0 * E::BPS, tab_lane, ws, ns);
+        } else if constexpr (LINEAR && KS > 1) {
             const int per = (nsteps + KS - 1) / KS;
             const int s0 = __builtin_amdgcn_readfirstlane(wk * per);
             const int ns = max(0, min(per, nsteps - s0));
@@ -396,6 +475,15 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
             mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab, tab_lane, ws, nsteps);
         }
     }
+    {
+    const ConvArgs late = reload_args();
+    const ConvGeom &g = late.g;
+    const MfmaPlan &pl = late.pl;
+    const FuseArgs &fz = late.fz;
+    const float *K = late.K;
+    float *out = late.out;
+    int32_t *dot_out = late.dot_out;
+    const uint32_t howo = (uint32_t)(g.ho * g.wo);
     // epilogue: out = float(dot) * K * alpha; result register v of a lane is filter row
     // 8*(v/4) + 4*half + v%4 of the 32-filter block, pixel column l32.  alpha of the lane's
     // filter rows is fetched once (clamped index, no branch), stores are predicated.
@@ -435,10 +523,13 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
         const int pl_idx = (wp * PW + j) * 32 + l32;
         const uint32_t m = m0 + (uint32_t)pl_idx;
         plive[j] = m < m_end;
-        const uint32_t mc = plive[j] ? m : m_end - 1u;
-        pimg[j] = g.div_howo.div(mc);
-        ppix[j] = mc - pimg[j] * howo;
-        Km[j] = RAW ? 1.0f : (K ? K[g.k_per_image ? pimg[j] : mc] : ktile[pl_idx]);      // real and k-bit activations carry no K
+        int row, col;
+        locate(g, pl, (uint32_t)pl_idx, pimg[j], ppix[j], row, col);
+        Km[j] = 1.0f;                                 // (real and k-bit activations carry no K)
+        if constexpr (!RAW) {
+            if (K) Km[j] = K[g.k_per_image ? img_a + pimg[j] : min(m, m_end - 1u)];
+            else Km[j] = ktile[pl_idx];
+        }
     }
     // Float (and optional integer) results leave through buffer stores: the resource starts at the
     // tile's first image, a lane's vector offset names its pixel (plus its half-wave's four rows),
@@ -451,7 +542,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
     uint32_t voff[PW];
 #pragma unroll
     for (int j = 0; j < PW; ++j)
-        voff[j] = plive[j] ? (uint32_t)(((pimg[j] - img_a) * (uint32_t)img_elems + ppix[j] + 4u * half * howo) * 4u) : OOB;
+        voff[j] = plive[j] ? (uint32_t)((pimg[j] * (uint32_t)img_elems + ppix[j] + 4u * half * howo) * 4u) : OOB;
     const int wf_s = __builtin_amdgcn_readfirstlane(wf);
     auto store_rows = [&](auto *dst, int i, int j, auto value_of) {
         const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(dst + (size_t)img_a * img_elems, 0, (int)span, 0x00020000);
@@ -694,6 +785,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 ? 6 : 8) ?
         else fz.workspace[(size_t)ftile * g.m_total + m] = sum;
     }
     }
+    }
 }
 
 static const int LDS_LIMIT = 160 * 1024;
@@ -811,7 +903,8 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not
     // (a chunk of a 1x1 filter is a run of consecutive records too)
-    const bool linear = pl.tap_jump == 0 || g.taps == 1;
+    set_direct_staging(&pl, g, FMT, PT);
+    const bool linear = FMT > 1 ? pl.tap_jump == 0 || g.taps == 1 : pl.vec > 0;
     // waves along K: consecutive weight records only, and the partial sums need the activation region's room
     if (KS > 1 && (!linear || (size_t)pl.region_bytes < (size_t)(KS - 1) * WF * WP * FW * PW * 16 * 64 * 4))
         return XNOR_ERR_UNSUPPORTED;
@@ -821,9 +914,6 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     if (xnor_status s = allow_full_lds(kern, attr_done[linear])) return s;
     pl.ptiles = (g.m_total + PT - 1) / PT;
     pl.ftiles = (g.k_out + FT - 1) / FT;
-    pl.dense = FMT < 2 && g.taps == 1 && g.ph == 0 && g.pw == 0 && g.sh == 1 && g.sw == 1 && g.dil_h == 1 &&
-               g.dil_w == 1 && pl.cc_words == g.cw && g.cw % 4 == 0;
-    set_fast_staging(&pl, g, FMT);
     // (measured on whole benchmark steps: 64 MiB 382 us, 40 MiB 403 us, 120 MiB 408 us, never 428 us)
     pl.stream_out = (long long)g.m_total * g.k_out * 4 > (64ll << 20);
     // weight-heavy: the weight image outweighs the packed activations and there are filter tiles to spread
@@ -835,12 +925,12 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
         grid = dim3((unsigned)wg, 1u);
     }
     if (grid.y > 65535u) return XNOR_ERR_UNSUPPORTED;
-    const size_t img_bytes = FMT == 1 ? wimg_f4_bytes(g.k_out, g.c, g.taps)
+    const size_t img_bytes = FMT == 1 ? wimg_pop_bytes(g.k_out, g.c, g.taps)
                              : FMT == 2 ? wimg_bf16_bytes(g.k_out, g.cw / 3, g.taps)
                                         : wimg_i8_bytes(g.k_out, g.c, g.taps);
     if (img_bytes > 0x7fffffffull) return XNOR_ERR_UNSUPPORTED;
-    kern<<<grid, block, lds, stream>>>(xbits, reinterpret_cast<const v4i *>(wimg), (uint32_t)img_bytes, K, A, alpha,
-                                       out, dot_out, g, pl, FUSE ? *fz : FuseArgs{});
+    kern<<<grid, block, lds, stream>>>(ConvArgs{xbits, reinterpret_cast<const v4i *>(wimg), K, A, alpha, out, dot_out,
+                                                (uint32_t)img_bytes, g, pl, FUSE ? *fz : FuseArgs{}});
     if (xnor_status s = hip_status(hipGetLastError())) return s;
     if (FUSE && pl.ftiles > 1) {
         sum_planes_kernel<<<dim3((unsigned)((g.m_total + 255) / 256)), dim3(256), 0, stream>>>(
@@ -865,7 +955,8 @@ static xnor_status launch_cfg_pool(const uint32_t *xbits, const void *wimg, cons
     pl.lut_offset = plan_lut_offset(pl, 1, g.wp, PT, 0, FT * 4);
     lds = std::max(lds, (size_t)WAVES * 16 * (PT + 1) * sizeof(float));       // the epilogue's per-wave y tiles
     if (lds > (size_t)LDS_LIMIT) return XNOR_ERR_UNSUPPORTED;
-    const bool linear = pl.tap_jump == 0 || g.taps == 1;
+    set_direct_staging(&pl, g, 1, PT);
+    const bool linear = pl.vec > 0;
     auto kern = linear ? conv_mfma_kernel<1, FW, PW, WF, WP, false, true, true>
                        : conv_mfma_kernel<1, FW, PW, WF, WP, false, false, true>;
     static std::atomic<bool> attr_done[2];
@@ -875,16 +966,15 @@ static xnor_status launch_cfg_pool(const uint32_t *xbits, const void *wimg, cons
     pl.ptiles = (int)ptiles;
     pl.ftiles = (g.k_out + FT - 1) / FT;
     pl.wmajor = 0;
-    pl.dense = 0;
-    set_fast_staging(&pl, g, 1);
     pl.stream_out = 0;
     pl.pool = pool;
     if (pl.ftiles > 65535) return XNOR_ERR_UNSUPPORTED;
-    const size_t img_bytes = wimg_f4_bytes(g.k_out, g.c, g.taps);
+    const size_t img_bytes = wimg_pop_bytes(g.k_out, g.c, g.taps);
     if (img_bytes > 0x7fffffffull) return XNOR_ERR_UNSUPPORTED;
     // the XCD-aware tile order works on whole windows of 64 pixel tiles; the grid is not padded beyond ptiles
     kern<<<dim3((unsigned)pl.ptiles, (unsigned)pl.ftiles), dim3(64 * WAVES), lds, stream>>>(
-        xbits, reinterpret_cast<const v4i *>(wimg), (uint32_t)img_bytes, K, A, alpha, out_pool, nullptr, g, pl, FuseArgs{});
+        ConvArgs{xbits, reinterpret_cast<const v4i *>(wimg), K, A, alpha, out_pool, nullptr, (uint32_t)img_bytes, g, pl,
+                 FuseArgs{}});
     return hip_status(hipGetLastError());
 }
 
@@ -919,7 +1009,8 @@ xnor_status launch_conv_mfma_pool(const uint32_t *xbits, const void *wmfma, cons
     pool.pr = best_pr;
     pool.groups = (pool.hpo + best_pr - 1) / best_pr;
     pool.div_groups = FastDiv::make((uint32_t)pool.groups);
-    const uint8_t *img = static_cast<const uint8_t *>(wmfma) + wimg_i8_bytes(g.k_out, g.c, g.taps);
+    const uint8_t *img = static_cast<const uint8_t *>(wmfma) + wimg_i8_bytes(g.k_out, g.c, g.taps) +
+                         wimg_f4_bytes(g.k_out, g.c, g.taps);
     switch (best) {
     case 0: return launch_cfg_pool<2, 3, 4, 1>(xbits, img, K, A, alpha, out_pool, g, pool, stream);
     case 1: return launch_cfg_pool<2, 5, 4, 1>(xbits, img, K, A, alpha, out_pool, g, pool, stream);
@@ -939,7 +1030,11 @@ static xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const flo
         // 64 x 256 or 128 x 128, so that one workgroup holds every filter).  129..256 filters: a tile that
         // holds every filter (weights stream through L1 once per pixel tile, the fused epilogue needs no
         // partial sums), 256 x 96 or 256 x 128, whichever leaves fewer CUs idle in its last round of
-        // workgroups.  More filters: 256 x 128 when the filter count is a multiple of 256, else 128 x 128.
+        // workgroups; 4-bit operands 256 x 64 in place of 256 x 96 where that idles no more of them (three workgroups per
+        // CU instead of two: 96 x 27 x 27 batch 64 20.4 -> 19.9 us).  More filters: 256 x 128 when the filter count is a
+        // multiple of 256, else 128 x 128; fused epilogue with 4-bit operands up to 512 filters: 384 x 96 or 512 x 64, so
+        // that one workgroup holds every filter and no second launch adds partial sums (128 images of 13 x 13, 384 filters:
+        // 256 channels 17.1 -> 16.1 us, 384 channels 20.4 -> 19.8; 512 filters on 7 x 7, batch 256: 22.1 -> 18.3).
         // Problems with few output tiles (fully connected layers: few "pixels", long K) take the largest
         // smaller tile that still gives every CU a workgroup.
         auto wgs = [&](int ft, int pt) {
@@ -962,10 +1057,14 @@ static xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const flo
             }
         } else if (g.k_out <= 64) tile = (fz || wgs(64, 256) >= 2 * cus) ? 2 : 11;
         else if (g.k_out <= 128) tile = fz ? 1 : wgs(128, 64) >= 2 * cus ? 13 : 11;
-        else if (g.k_out <= 256) tile = waste(wgs(256, 96)) <= waste(wgs(256, 128)) ? 4 : 5;
+        else if (g.k_out <= 256) {
+            tile = waste(wgs(256, 96)) <= waste(wgs(256, 128)) ? 4 : 5;
+            if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) tile = 6;
+        } else if (FMT == 1 && fz && g.k_out <= 512) tile = g.k_out <= 384 ? 9 : 8;
         else tile = g.k_out % 256 == 0 ? 5 : fz ? 13 : 1;      // (fused epilogue: 128 x 64 ahead of 128 x 128)
         const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
-                             : tile == 5 ? wgs(256, 128) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
+                             : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
+                             : tile == 9 ? wgs(384, 96) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
         if (w0 < (FMT == 2 ? 128 : 160)) {
             if (wgs(64, 128) >= cus) tile = 11;
             else if (wgs(128, 64) >= cus) tile = 13;
@@ -979,14 +1078,28 @@ static xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const flo
             if (fz) return launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz); \
         }                                                                                                 \
         return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr);
+#define XNOR_TILE_F4(ID, FW, PW, WF, WP)                                                                  \
+    case ID:                                                                                              \
+        if constexpr (FMT == 1)                                                                           \
+            return fz ? launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz)        \
+                      : launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr); \
+        return XNOR_ERR_UNSUPPORTED;
     switch (tile) {
         XNOR_TILE_F(1, 2, 2, 2, 2);   // 128 filters x 128 pixels
         XNOR_TILE_F(2, 2, 2, 1, 4);   //  64 x 256
         XNOR_TILE_F(4, 2, 3, 4, 1);   // 256 x  96
         XNOR_TILE_F(5, 2, 4, 4, 1);   // 256 x 128
+        XNOR_TILE_F4(6, 2, 2, 4, 1);  // 256 x  64
         XNOR_TILE_F(11, 1, 2, 2, 2);  //  64 x 128
         XNOR_TILE_F(13, 1, 2, 4, 1);  // 128 x  64
         XNOR_TILE_F(14, 1, 1, 4, 1);  // 128 x  32
+    case 8:                           // 512 x  64, eight waves, and 384 x 96, six: one workgroup holds every filter of the
+    case 9:                           // fused epilogue (4-bit operands)
+        if constexpr (FMT == 1) {
+            if (fz && tile == 8) return launch_cfg<FMT, 2, 2, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
+            if (fz) return launch_cfg<FMT, 2, 3, 6, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
+        }
+        return XNOR_ERR_UNSUPPORTED;
     case 15:                          // 128 x  32, two groups of four waves along K (no fused epilogue, packed-bit operands)
         if constexpr (FMT < 2) {
             if (!fz) {
@@ -1000,6 +1113,7 @@ static xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const flo
     default: return XNOR_ERR_UNSUPPORTED;
     }
 #undef XNOR_TILE_F
+#undef XNOR_TILE_F4
 }
 
 xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, const float *K, const float *A,
@@ -1015,7 +1129,7 @@ xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, 
     // float accumulation of the 4-bit path is exact while every sum stays below 2^24
     if (fmt != 0 && (long long)g.c * g.taps >= (1ll << 24)) return XNOR_ERR_UNSUPPORTED;
     if (fmt == 0) return launch_fmt<0>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);
-    img += wimg_i8_bytes(g.k_out, g.c, g.taps);
+    img += wimg_i8_bytes(g.k_out, g.c, g.taps) + wimg_f4_bytes(g.k_out, g.c, g.taps);
     return launch_fmt<1>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);
 }
 

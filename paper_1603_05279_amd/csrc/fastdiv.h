@@ -49,4 +49,34 @@ struct FastDiv {
     XNOR_HD inline uint32_t div_small(uint32_t x) const { return mulhi(x, magic) + (x & pass); }
 };
 
+// Division of small numbers, x <= max: q = (x * mul) >> shift with both factors within 24 bits and the product within 32, so
+// that it costs one full-rate 24-bit multiply and a shift (a 32-bit multiply-high runs at a quarter of the rate).
+// mul = ceil(2^shift / d) = (2^shift + e) / d with 0 <= e < d, so x * mul / 2^shift = x / d + x * e / (d * 2^shift): exact
+// while x * e < 2^shift.  make() takes the largest shift that fits; false when none is exact.
+XNOR_HD static inline uint32_t mul24(uint32_t a, uint32_t b)      // both below 2^24; the product's low 32 bits
+{
+#if defined(__HIP_DEVICE_COMPILE__)
+    return (uint32_t)__umul24(a, b);         // (declared signed)
+#else
+    return a * b;
+#endif
+}
+struct SmallDiv {
+    uint32_t mul, shift;
+    static bool make(uint32_t d, uint64_t max, SmallDiv *out)
+    {
+        if (d == 0 || max >= (1u << 24)) return false;
+        for (int s = 31; s >= 0; --s) {
+            const uint64_t mul = ((1ull << s) + d - 1) / d, e = mul * d - (1ull << s);
+            if (mul >= (1u << 24) || max * mul >= (1ull << 32)) continue;
+            if (max * e >= (1ull << s)) return false;       // smaller shifts are coarser still
+            out->mul = (uint32_t)mul;
+            out->shift = (uint32_t)s;
+            return true;
+        }
+        return false;
+    }
+    XNOR_HD inline uint32_t div(uint32_t x) const { return mul24(x, mul) >> shift; }
+};
+
 }  // namespace xnor

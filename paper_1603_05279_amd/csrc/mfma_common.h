@@ -1,6 +1,7 @@
 // Operand encodings and the LDS plan shared by the matrix-core convolution kernels.
 #pragma once
 #include "xnor_internal.h"
+#include <type_traits>
 
 namespace xnor {
 
@@ -35,26 +36,39 @@ struct MfmaPlan {
     int lut_offset;   // LDS byte offset of the sign-byte widening table
     int ftiles;       // filter tiles of the launch
     int wmajor;       // 1: 1-D grid that keeps the pixel tiles of a filter tile on one XCD
-    int dense;        // 1: 1x1 filter, no padding, stride 1, one chunk, words per pixel a multiple of 4: the tile's
-                      //    packed words are one contiguous run of memory, staged 16 bytes per load
-                      // 2: staging without per-item divisions or 64-bit addresses (see set_fast_staging)
+    int vec;          // > 0: channel words per load of the direct staging loop (1 to 4, divides cc_words); 0: the general loop
+    int quads;        // cc_words / vec
+    SmallDiv sd_quads, sd_wp, sd_hp, sd_wo, sd_ho;   // direct staging: item, padded and output coordinates of a tile
     int stream_out;   // 1: float results are stored with the non-temporal hint (they exceed a quarter of the last-level cache)
     FastDiv div_wp, div_hp, div_ccw, div_cw;
     PoolPlan pool;    // used by the pooled-epilogue instantiations only
 };
 
-// The staging loop walks the items (padded row, padded column, channel word), word fastest, a workgroup-wide stride
-// of `threads` items at a time.  When the input is not dilated, every channel word is full (c a multiple of 32) and
-// pixel and byte counts fit 24 and 31 bits, a thread keeps its (row, column, word) in registers and advances them by
-// the stride's constant increments with carries, addresses LDS and memory with 24-bit multiply-adds, and reads the
-// packed words through a bounds-checked buffer (positions outside the image get an offset beyond it): no division,
-// no 64-bit arithmetic and no branch per item.
-inline void set_fast_staging(MfmaPlan *pl, const ConvGeom &g, int fmt)
+// Direct staging: an item of the staging loop is `vec` channel words of one pixel, read by one load and widened together.
+// Coordinates are divided down from the tile's first image with 24-bit multiplies, memory is read through a bounds-checked
+// buffer that starts at that image (positions outside an image get an offset beyond it and come back as zero): no 64-bit
+// arithmetic, no branch per item.  Needs an input that is not dilated, one chunk that holds every channel word, and a tile whose images' pixels, packed words and
+// padded pixels fit the ranges of those divisions and offsets; anything else takes the general loop.
+inline void set_direct_staging(MfmaPlan *pl, const ConvGeom &g, int fmt, int run)
 {
-    const long long px = (long long)g.n * g.h * g.w;
-    if (fmt < 2 && !pl->dense && g.dil_h == 1 && g.dil_w == 1 && g.c % 32 == 0 && px < (1 << 24) &&
-        g.cw < (1 << 16) && px * g.cw * 4 < 0x7fffffffLL && pl->row_pitch < (1 << 23))
-        pl->dense = 2;
+    pl->vec = pl->quads = 0;
+    if (fmt > 1 || pl->cc_words != g.cw || g.dil_h != 1 || g.dil_w != 1) return;
+    const int vec = pl->cc_words % 4 == 0 ? 4 : pl->cc_words == 3 ? 3 : pl->cc_words % 2 == 0 ? 2 : 1;
+    const int quads = pl->cc_words / vec;
+    const long long howo = (long long)g.ho * g.wo, hw = (long long)g.h * g.w;
+    const long long images = run / howo + 2;                        // that a tile can touch
+    const long long px = (long long)pl->max_rows * g.wp;
+    if (images * hw >= (1 << 24) || images * hw * g.cw * 4 >= 0x7fffffffLL || g.cw >= (1 << 22) ||
+        px * quads >= (1 << 24) || pl->row_pitch >= (1 << 23) || howo + run >= (1 << 24))
+        return;
+    if (!SmallDiv::make((uint32_t)quads, (uint64_t)(px * quads), &pl->sd_quads) ||
+        !SmallDiv::make((uint32_t)g.wp, (uint64_t)px, &pl->sd_wp) ||
+        !SmallDiv::make((uint32_t)g.hp, (uint64_t)g.hp + pl->max_rows, &pl->sd_hp) ||
+        !SmallDiv::make((uint32_t)g.wo, (uint64_t)(howo + run), &pl->sd_wo) ||
+        !SmallDiv::make((uint32_t)g.ho, (uint64_t)(howo + run) / g.wo, &pl->sd_ho))
+        return;
+    pl->vec = vec;
+    pl->quads = quads;
 }
 
 // Most padded input rows touched by any run of `run` consecutive (flattened) output pixels that
@@ -223,9 +237,24 @@ template <> struct Enc<1> {                    // 4-bit float E2M1
         }
         return v;
     }
+    // Operand order of the convolution: dword q of a word's 16 bytes holds in nibble j channel 4j + 3 - q, so that a dword
+    // is one shift and one and-or of the packed word (7 vector instructions per word; canonical nibble order takes 17).  A
+    // sign bit of 1 becomes 0xA (-1), of 0 becomes 0x2 (+1): inverted in both operands alike, which leaves their products
+    // what they are.  `code` has the sign positions that exist (0x88888888, per lane 0 for a block that must not count).
+    static __device__ __forceinline__ v4i widen_bits(uint32_t bits, uint32_t code, uint32_t one) {    // one = code >> 2
+        return v4i{(int)((bits & code) | one), (int)(((bits << 1) & code) | one), (int)(((bits << 2) & code) | one),
+                   (int)(((bits << 3) & code) | one)};
+    }
     static __device__ __forceinline__ void widen_word_lut(uint8_t *dst, const uint8_t *, uint32_t bits, bool ok,
                                                           int nch) {
-        *reinterpret_cast<uint4 *>(dst) = widen_word_regs(bits, ok, nch);
+        // positions outside the image: code 0x0 = 0.0
+        v4i v = widen_bits(bits, ok ? 0x88888888u : 0u, ok ? 0x22222222u : 0u);
+        if (nch < 32) {                                       // channels past the last one: 0.0 too
+            const uint32_t real = (1u << nch) - 1u;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[q] &= (int)((((real << q) & 0x88888888u) >> 3) * 15u);
+        }
+        *reinterpret_cast<v4i *>(dst) = v;
     }
 };
 
@@ -281,6 +310,8 @@ constexpr int KLOOP_TABLE_PAD = 20;
 // offset.  No other bookkeeping in the loop.
 // AUX: cache policy of the loads (2 = non-temporal hint).
 template <int FW, int AUX = 0> struct WStreamLinear {
+    typedef v4i word_t;
+    static constexpr bool WIDEN = false;
     __amdgpu_buffer_rsrc_t rsrc[FW];
     int voff;
     __device__ __forceinline__ WStreamLinear(const v4i *wimg, const int (&wrec0)[FW], int rec_start, int nsteps,
@@ -307,6 +338,8 @@ template <int FW, int AUX = 0> struct WStreamLinear {
 // +tap_jump more when the chunk moves to the next tap; steps past the end read the all-zero record.
 // Branch-free scalar bookkeeping, so the loop body stays one basic block.
 template <int FW> struct WStreamChunked {
+    typedef v4i word_t;
+    static constexpr bool WIDEN = false;
     __amdgpu_buffer_rsrc_t rsrc;
     int wrec0[FW];
     int wlane, zero_rec, w_rec, w_cnt, w_left, steps_per_tap, tap_jump;
@@ -336,12 +369,56 @@ template <int FW> struct WStreamChunked {
     }
 };
 
+// Weight stream of the 4-bit operands: the packed words themselves, [filter block][(tap, channel word)][32 filters], two
+// (tap, word) blocks = 256 bytes per K-step and filter block, one word per lane, widened in registers while the matrix
+// pipes work on the step before (a matrix instruction leaves its wave seven issue slots).  Each filter block has a
+// resource of its own that ends with its words: prefetches beyond are answered with zeros.  When the block count is odd the
+// second half-wave of the last step holds no block: its code is 0 (operand 0.0).
+// Steps are consecutive (LINEAR) or, where a chunk holds part of the channel words, run on within a tap and skip
+// tap_jump steps to the next one (uniform bookkeeping in the scalar offset; steps past the end read the chunk's
+// first words, which nothing multiplies).
+template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
+    typedef uint32_t word_t;
+    static constexpr bool WIDEN = true;
+    __amdgpu_buffer_rsrc_t rsrc[FW];
+    int voff, w_rec, w_cnt, w_left, steps_per_tap, tap_jump;
+    uint32_t last_code;          // code of the last step
+    __device__ __forceinline__ WStreamBits(const uint32_t *words, const int (&fblk)[FW], int nblk, int rec_start,
+                                           int nsteps, bool odd_last, int lane, int steps_per_tap_, int tap_jump_)
+        : voff(lane * 4 + (LINEAR ? rec_start * 256 : 0)), w_rec(rec_start), w_cnt(0), w_left(nsteps),
+          steps_per_tap(steps_per_tap_), tap_jump(tap_jump_), last_code(odd_last && lane >= 32 ? 0u : 0x88888888u)
+    {
+#pragma unroll
+        for (int i = 0; i < FW; ++i)
+            rsrc[i] = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t *>(words) + (size_t)fblk[i] * nblk * 32, 0,
+                                                        nblk * 128, 0x00020000);
+    }
+    __device__ __forceinline__ void load(word_t (&dst)[FW])
+    {
+#pragma unroll
+        for (int i = 0; i < FW; ++i)
+            dst[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc[i], voff, LINEAR ? 0 : w_rec * 256, AUX);
+        if constexpr (LINEAR) {
+            voff += 256;
+        } else {
+            const int live = w_left > 0 ? 1 : 0;
+            w_left -= live;
+            w_cnt += live;
+            const int wrap = w_cnt == steps_per_tap ? 1 : 0;
+            w_cnt = wrap ? 0 : w_cnt;
+            w_rec += live + (wrap ? tap_jump : 0);
+            w_rec = w_left > 0 ? w_rec : 0;
+        }
+    }
+};
+
 // One chunk's K loop of a wave: acc[i][j] += W(filter block i, step s) x X(pixel block j, step s)
-// for s = 0 .. nsteps-1, weights from the stream `ws` (one of the two above), activations from LDS
+// for s = 0 .. nsteps-1, weights from the stream `ws` (one of those above), activations from LDS
 // through the per-step offset table (padded by KLOOP_TABLE_PAD steps).  Operands are requested DW
 // steps (weights: buffer loads with a scalar offset, L2 latency) and DX steps (activations) ahead
 // of their use and live in register rings of DW+1 and DX+1 slots; the body is unrolled until both
-// rings are back at slot 0.  A wave issues one instruction every four cycles, so everything that is
+// rings are back at slot 0.  Packed weight words are widened one step ahead of their use.  A wave issues one
+// instruction every four cycles, so everything that is
 // not a matrix instruction competes with them for issue slots: the loop carries no address or
 // bounds arithmetic beyond PW + 1 vector adds per step.
 // The scheduling barriers pin the order written here (next operands requested, then the current
@@ -356,7 +433,7 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
     constexpr int TURN = ring_lcm(RW, RX);     // sub-steps after which both rings are back at slot 0
     static_assert(RX <= RW && TURN <= 16 && TURN % 2 == 0, "unrolled turn: even, at most 16 sub-steps");
     static_assert(TURN + DX + 2 <= KLOOP_TABLE_PAD, "offset table padding");
-    auto load_w = [&](v4i (&dst)[FW]) { ws.load(dst); };
+    typedef typename WS::word_t word_t;
     const int *tab = xoff_tab + tab_lane;
     auto load_t = [&](int s) -> int { return tab[s * E::BPS]; };
     constexpr int NX = E::NX;                  // words of a step that share its weight record
@@ -376,43 +453,60 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
                 for (int i = 0; i < FW; ++i) acc[i][j] = E::mfma(w[i], x[j][q], acc[i][j]);
     };
 
-    v4i w[RW][FW], x[RX][PW][NX];
+    word_t w[RW][FW];
+    v4i x[RX][PW][NX], wide[2][FW];
     int tq[2];
+    // (in registers: an and-or takes no two literals)
+    uint32_t full = 0x88888888u, full_one = 0x22222222u;
+    if constexpr (WS::WIDEN) asm("" : "+v"(full), "+v"(full_one));
+    auto widen = [&](v4i (&dst)[FW], const word_t (&src)[FW], int s, bool tail) {
+        if constexpr (WS::WIDEN) {
+            // every step but the last counts both half-waves
+            const uint32_t code = tail && s == nsteps - 1 ? ws.last_code : full;
+            const uint32_t one = tail && s == nsteps - 1 ? ws.last_code >> 2 : full_one;
 #pragma unroll
-    for (int u = 0; u < DW; ++u) load_w(w[u]);
+            for (int i = 0; i < FW; ++i) dst[i] = E::widen_bits(src[i], code, one);
+        }
+    };
+#pragma unroll
+    for (int u = 0; u < DW; ++u) ws.load(w[u]);
 #pragma unroll
     for (int u = 0; u < DX; ++u) load_x(x[u], load_t(u));
     tq[0] = load_t(DX);
-    auto substep = [&](int s, int u) {
-        load_w(w[(u + DW) % RW]);                       // step s+u+DW
+    widen(wide[0], w[0], 0, true);
+    auto substep = [&](int s, int u, bool tail) {
+        ws.load(w[(u + DW) % RW]);                      // step s+u+DW
         tq[(u + 1) & 1] = load_t(s + u + DX + 1);
         load_x(x[(u + DX) % RX], tq[u & 1]);            // step s+u+DX, offset read one sub-step ago
-        fma_all(w[u % RW], x[u % RX]);
-        // one LDS read behind each of the first PW*NX+1 MFMAs, then the FW weight loads
-#pragma unroll
-        for (int q = 0; q < PW * NX + 1; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+        if constexpr (WS::WIDEN) {
+            fma_all(wide[u & 1], x[u % RX]);
+            widen(wide[(u + 1) & 1], w[(u + 1) % RW], s + u + 1, tail);
+        } else {
+            fma_all(w[u % RW], x[u % RX]);
         }
+        // one LDS read behind each of the first PW*NX+1 MFMAs, then the FW weight loads; widening instructions fill the
+        // slots behind all of them
+        constexpr int MM = FW * PW * NX, VALU = WS::WIDEN ? 7 * FW : 0;
 #pragma unroll
-        for (int q = 0; q < FW; ++q) {
+        for (int q = 0; q < MM; ++q) {
             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (q < PW * NX + 1) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+            else if (q < PW * NX + 1 + FW) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+            if (VALU) __builtin_amdgcn_sched_group_barrier(0x002, (VALU + MM - 1) / MM, 0);
         }
-        __builtin_amdgcn_sched_group_barrier(0x008, FW * PW * NX - PW * NX - 1 - FW, 0);
         __builtin_amdgcn_sched_barrier(0);
     };
     int s = 0;
-    for (; s + TURN <= nsteps; s += TURN) {             // whole turns: one basic block, no exits
+    for (; s + TURN < nsteps; s += TURN) {              // whole turns but the last: one basic block, no exits
 #pragma unroll
-        for (int u = 0; u < TURN; ++u) substep(s, u);
+        for (int u = 0; u < TURN; ++u) substep(s, u, u == TURN - 1);
     }
-    // the last, partial turn.  The accumulators are pinned before every exit test: otherwise the
+    // the last turn.  The accumulators are pinned before every exit test: otherwise the
     // matrix instructions sink below the branches and run in one burst behind all the loads.
 #pragma unroll
-    for (int u = 0; u < TURN - 1; ++u) {
+    for (int u = 0; u < TURN; ++u) {
         if (s + u >= nsteps) break;
-        substep(s, u);
+        substep(s, u, true);
 #pragma unroll
         for (int i = 0; i < FW; ++i)
 #pragma unroll

@@ -1,0 +1,99 @@
+"""The 4-bit matrix-core convolution on packed weight words, at the sizes where its staging and K loop can go wrong: every
+load width of the activations (1 to 4 words), odd block counts (half a K-step), channel tails, tiles that span images, rows
+and strides, given K and A, and inputs that take the general staging (dilated, several channel chunks)."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1603_05279_amd import xnor
+
+pytestmark = pytest.mark.gpu
+
+# n, c, h, w, k_out, kh, kw, stride, pad
+CASES = [
+    (1, 1, 1, 1, 1, 1, 1, 1, 0), (2, 33, 3, 5, 40, 1, 1, 1, 0), (70, 95, 1, 1, 33, 1, 1, 1, 0),
+    (3, 96, 9, 11, 100, 3, 3, 1, 1), (11, 128, 7, 7, 130, 3, 3, 1, 1), (2, 160, 13, 6, 257, 3, 3, 2, 1),
+    (5, 190, 6, 14, 64, 5, 3, (1, 2), (2, 1)), (2, 224, 10, 10, 300, 3, 3, 1, 2), (1, 256, 31, 29, 129, 3, 3, 1, 1),
+    (2, 384, 13, 13, 200, 3, 3, 1, 1), (1, 512, 40, 40, 32, 5, 5, 1, 2), (1, 32, 200, 3, 70, 7, 3, (3, 1), (3, 1)),
+]
+
+
+def block(case, algo, given_K=False, tile=0):
+    n, c, h, w, k, kh, kw, stride, pad = case
+    gen = torch.Generator(device="cuda").manual_seed(c * 1000 + h)
+    x = torch.randn((n, c, h, w), generator=gen, device="cuda")
+    wt = torch.randn((k, c, kh, kw), generator=gen, device="cuda")
+    desc = xnor.make_desc(n, c, h, w, k, kh, kw, stride, pad)
+    pw, bufs = xnor.PackedWeights(wt), xnor.ConvBuffers(desc, with_dot=True)
+    bufs.out.fill_(float("nan"))
+    bufs.dot.fill_(-(1 << 30))
+    xnor.xnor_binactiv(x, None, None, bufs.xbits, bufs.A, bufs.K if given_K else None, desc)
+    xnor.set_tuning(tile)
+    try:
+        xnor.xnor_conv2d(bufs.xbits, pw.wbits, pw.wmfma, bufs.K if given_K else None, None if given_K else bufs.A,
+                         pw.alpha, bufs.out, bufs.dot, desc, xnor.ALGOS[algo])
+    finally:
+        xnor.set_tuning(0)
+    torch.cuda.synchronize()
+    return bufs
+
+
+@pytest.mark.parametrize("tile", [0, 1, 2, 4, 5, 6, 11, 13, 14])
+@pytest.mark.parametrize("case", CASES)
+def test_same_integers_and_floats_as_the_vector_alu(case, tile):
+    print("case", case, tile, flush=True)
+    given_K = tile % 2 == 1
+    ref, got = block(case, "popcount", given_K), block(case, "mfma_f4", given_K, tile)
+    assert torch.equal(got.dot, ref.dot)
+    assert torch.equal(got.out, ref.out)               # the same two float products of the same integers
+
+
+@pytest.mark.parametrize("k,tile", [(64, 6), (256, 6), (257, 9), (384, 9), (100, 9), (385, 8), (512, 8), (70, 8), (600, 9)])
+def test_fused_tilings_that_hold_every_filter(k, tile):
+    n, c, h = 5, 96, 9
+    gen = torch.Generator(device="cuda").manual_seed(k)
+    xb = torch.randint(-(1 << 31), 1 << 31, (n, h, h, c // 32), generator=gen, device="cuda", dtype=torch.int64).int()
+    A = torch.rand((n, h, h), generator=gen, device="cuda")
+    wt = torch.randn((k, c, 3, 3), generator=gen, device="cuda")
+    sc, sh = torch.rand((k,), generator=gen, device="cuda") + 0.5, torch.randn((k,), generator=gen, device="cuda")
+    pw = xnor.PackedWeights(wt)
+    desc = xnor.make_desc(n, c, h, h, k, 3, 3, 1, 1)
+    ws = torch.empty((max(16, xnor.conv2d_binactiv_workspace_bytes(desc)),), dtype=torch.uint8, device="cuda")
+    res = []
+    for t in (13, tile):
+        nx = torch.full((n, h, h, xnor.words_per_pixel(k)), -1, dtype=torch.int32, device="cuda")
+        An, out = torch.full((n, h, h), float("nan"), device="cuda"), torch.empty((n, k, h, h), device="cuda")
+        xnor.set_tuning(t)
+        try:
+            xnor.xnor_conv2d_binactiv(xb, pw.wbits, pw.wmfma, None, A, pw.alpha, sc, sh, nx, An, out, ws, desc,
+                                      xnor.XNOR_ALGO_MFMA_F4)
+        finally:
+            xnor.set_tuning(0)
+        res.append((nx, An, out))
+    torch.cuda.synchronize()
+    assert torch.equal(res[0][0], res[1][0]) and torch.equal(res[0][2], res[1][2])
+    z = torch.abs(res[1][2].double() * sc.double().view(1, -1, 1, 1) + sh.double().view(1, -1, 1, 1)).mean(1)
+    # a float sum of k positive terms: at most k roundings, and one of each z
+    assert torch.allclose(res[1][1].double(), z, rtol=(k + 8) * 2.0 ** -24, atol=1e-6)
+
+
+def test_dilated_input_keeps_the_general_staging():
+    # backward convolution of a strided layer: zeros between the gradient's pixels; against the int8 matrix cores
+    n, c, h, k = 3, 64, 15, 96
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    desc = xnor.make_desc(n, c, h, h, k, 3, 3, 2, 1)
+    ho, wo = xnor.output_hw(desc)
+    w = torch.randn((k, c, 3, 3), generator=gen, device="cuda")
+    gb = torch.randint(-(1 << 31), 1 << 31, (n, ho, wo, 3), generator=gen, device="cuda", dtype=torch.int64).int()
+    gmax = torch.rand((n,), generator=gen, device="cuda")
+    wt, ones = torch.empty((c, 9, 3), dtype=torch.int32, device="cuda"), torch.empty((c,), device="cuda")
+    img = torch.empty((xnor.wmfma_bytes(c, k, 3, 3),), dtype=torch.uint8, device="cuda")
+    xnor.xnor_bingrad_pack_weights(w, wt, ones, img, k, c, 3, 3)
+    outs = []
+    for algo in ("mfma_f4", "mfma_i8"):
+        gin, dot = torch.empty((n, c, h, h), device="cuda"), torch.empty((n, c, h, h), dtype=torch.int32, device="cuda")
+        xnor.xnor_bingrad_conv2d(gb, wt, img, gmax, ones, torch.empty((n, h, h), device="cuda"), gin, dot, desc,
+                                 xnor.ALGOS[algo])
+        outs.append((gin, dot))
+    torch.cuda.synchronize()
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
