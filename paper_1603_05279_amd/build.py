@@ -1,4 +1,5 @@
-"""Builds paper_1603_05279_amd/libxnor.so from csrc/*.hip for gfx950 with hipcc.
+"""Builds paper_1603_05279_amd/libxnor.so from csrc/*.hip for gfx950 with hipcc, and the Python binding _binding.so from
+csrc/binding.cpp with g++.
 
 Every source is compiled to an object of its own (in parallel), then linked.  Only the `xnor_*` functions of
 the C ABI are exported: everything else is built with hidden visibility.
@@ -13,6 +14,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 OBJ = os.path.join(PKG, "_build")
 LIB = os.path.join(PKG, "libxnor.so")
+BINDING = os.path.join(PKG, "_binding.so")
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
@@ -36,8 +38,25 @@ def _run(cmd):
     r = subprocess.run(cmd, capture_output=True, text=True)
     err = "\n".join(l for l in r.stderr.splitlines() if NOISE not in l)
     if r.returncode != 0:
-        raise RuntimeError("hipcc failed: " + " ".join(cmd) + "\n" + err)
+        raise RuntimeError("compiler failed: " + " ".join(cmd) + "\n" + err)
     return err
+
+
+def build_binding(incremental: bool = False) -> str:
+    """The host-only extension module that marshals tensors for libxnor's entry points (torch's own headers and libraries)."""
+    import sysconfig
+    import torch
+    src, header = os.path.join(CSRC, "binding.cpp"), os.path.join(ROOT, "include", "xnor.h")
+    if incremental and os.path.exists(BINDING) and os.path.getmtime(BINDING) >= max(map(os.path.getmtime, (src, header))):
+        return BINDING
+    home = os.path.dirname(torch.__file__)
+    inc = [os.path.join(ROOT, "include"), sysconfig.get_paths()["include"], os.path.join(home, "include"),
+           os.path.join(home, "include", "torch", "csrc", "api", "include")]
+    libdir = os.path.join(home, "lib")
+    _run(["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden",
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}"] + [f for d in inc for f in ("-isystem", d)] +
+         [src, "-L" + libdir, "-Wl,-rpath," + libdir, "-ltorch_python", "-ltorch_cpu", "-lc10", "-ldl", "-o", BINDING])
+    return BINDING
 
 
 def build(verbose: bool = False, incremental: bool = False, extra_flags=(), lib: str = LIB, jobs: int = 8) -> str:
@@ -65,6 +84,8 @@ def build(verbose: bool = False, incremental: bool = False, extra_flags=(), lib:
                 "-Wl,--version-script=" + os.path.join(CSRC, "libxnor.map")] + objs + ["-o", lib])
     if verbose and err.strip():
         print(err)
+    if lib == LIB:
+        build_binding(incremental)
     return lib
 
 

@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libxnor (include/xnor.h): same names, argument marshalling only.
+"""Thin binding of libxnor (include/xnor.h): same names, argument marshalling only.  The calls that enqueue work go through
+csrc/binding.cpp, queries through ctypes.
 
 Tensors are torch CUDA tensors used as plain device buffers; every step of the path runs in
 the library's HIP kernels.  There is no fallback: a missing library raises at import of the
@@ -171,30 +172,36 @@ def output_hw(desc):
     return ho.value, wo.value
 
 
-def _ptr(t, dtype=None):
-    """Device address of a dense device tensor, as a plain integer (the declared argument types convert it)."""
-    if t is None:
-        return None
-    if not t.is_cuda:
-        raise ValueError("libxnor takes device tensors")
-    if not t.is_contiguous():
-        raise ValueError("libxnor takes densely packed tensors")
-    if dtype is not None and t.dtype != dtype:
-        raise ValueError(f"expected {dtype}, got {t.dtype}")
-    return t.data_ptr()
-
-
-_current_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
-
-
 def _stream(stream):
-    # the handle alone: building torch's Stream object on every call costs more than a kernel launch
-    # (with the plain integers of _ptr a call's Python share about 6 -> 3 us; one small block, two calls: 17.5 -> 12.0 us)
-    if stream is not None:
-        return stream.cuda_stream
-    if _current_raw_stream is not None:
-        return _current_raw_stream(torch.cuda.current_device())
-    return torch.cuda.current_stream().cuda_stream
+    return stream.cuda_stream if stream is not None else torch.cuda.current_stream().cuda_stream
+
+
+def _raise(fn, status):
+    raise XnorError(fn, status)
+
+
+def _current_raw_stream(device):
+    return torch.cuda.current_stream(device).cuda_stream
+
+
+class _Unbound:
+    """Stands in for the binding until the first call, which loads it; a missing build raises there."""
+
+    def __getattr__(self, name):
+        global _call
+        lib()
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise ImportError("the binding is missing: build it with paper_1603_05279_amd/build.py") from e
+        # (the raw handle alone: building torch's Stream object costs more than a kernel launch)
+        _binding.bind(_LIB_PATH, _raise, torch.cuda.current_device,
+                      getattr(torch._C, "_cuda_getCurrentRawStream", _current_raw_stream))
+        _call = _binding
+        return getattr(_binding, name)
+
+
+_call = _Unbound()
 
 
 def _check(fn, st):
@@ -203,37 +210,25 @@ def _check(fn, st):
 
 
 def xnor_binarize_pack(x, bn_scale, bn_shift, xbits, n, c, h, w, stream=None):
-    _check("xnor_binarize_pack", lib().xnor_binarize_pack(
-        _ptr(x, torch.float32), _ptr(bn_scale, torch.float32), _ptr(bn_shift, torch.float32),
-        _ptr(xbits, torch.int32), n, c, h, w, _stream(stream)))
+    _call.xnor_binarize_pack(x, bn_scale, bn_shift, xbits, n, c, h, w, stream)
 
 
 def xnor_compute_K(x, bn_scale, bn_shift, A, K, desc, stream=None):
-    _check("xnor_compute_K", lib().xnor_compute_K(
-        _ptr(x, torch.float32), _ptr(bn_scale, torch.float32), _ptr(bn_shift, torch.float32),
-        _ptr(A, torch.float32), _ptr(K, torch.float32), ctypes.byref(desc), _stream(stream)))
+    _call.xnor_compute_K(x, bn_scale, bn_shift, A, K, desc, stream)
 
 
 def xnor_binactiv(x, bn_scale, bn_shift, xbits, A, K, desc, stream=None):
-    _check("xnor_binactiv", lib().xnor_binactiv(
-        _ptr(x, torch.float32), _ptr(bn_scale, torch.float32), _ptr(bn_shift, torch.float32),
-        _ptr(xbits, torch.int32), _ptr(A, torch.float32), _ptr(K, torch.float32),
-        ctypes.byref(desc), _stream(stream)))
+    _call.xnor_binactiv(x, bn_scale, bn_shift, xbits, A, K, desc, stream)
 
 
 def xnor_binactiv_streamed(x, bn_scale, bn_shift, xbits, A, K, desc, stream=None):
-    _check("xnor_binactiv_streamed", lib().xnor_binactiv_streamed(
-        _ptr(x, torch.float32), _ptr(bn_scale, torch.float32), _ptr(bn_shift, torch.float32),
-        _ptr(xbits, torch.int32), _ptr(A, torch.float32), _ptr(K, torch.float32),
-        ctypes.byref(desc), _stream(stream)))
+    _call.xnor_binactiv_streamed(x, bn_scale, bn_shift, xbits, A, K, desc, stream)
 
 
 def xnor_pool_binactiv(x, bn_scale, bn_shift, xbits, A, n, c, h_in, w_in, pool, stride, pad=(0, 0), relu=False,
                        stream=None):
-    _check("xnor_pool_binactiv", lib().xnor_pool_binactiv(
-        _ptr(x, torch.float32), _ptr(bn_scale, torch.float32), _ptr(bn_shift, torch.float32),
-        _ptr(xbits, torch.int32), _ptr(A, torch.float32), n, c, h_in, w_in, pool[0], pool[1], stride[0], stride[1],
-        pad[0], pad[1], int(bool(relu)), _stream(stream)))
+    _call.xnor_pool_binactiv(x, bn_scale, bn_shift, xbits, A, n, c, h_in, w_in, pool[0], pool[1], stride[0],
+                             stride[1], pad[0], pad[1], int(bool(relu)), stream)
 
 
 def bwn_parts_bytes(n, c, h, w):
@@ -245,40 +240,28 @@ def bwn_wimg_bytes(k_out, c, kh, kw):
 
 
 def xnor_bwn_split(x, parts, n, c, h, w, stream=None):
-    _check("xnor_bwn_split", lib().xnor_bwn_split(_ptr(x, torch.float32), _ptr(parts, torch.uint8), n, c, h, w,
-                                                  _stream(stream)))
+    _call.xnor_bwn_split(x, parts, n, c, h, w, stream)
 
 
 def xnor_bwn_pack_weights(w, alpha, wimg, k_out, c, kh, kw, stream=None):
-    _check("xnor_bwn_pack_weights", lib().xnor_bwn_pack_weights(
-        _ptr(w, torch.float32), _ptr(alpha, torch.float32), _ptr(wimg, torch.uint8), k_out, c, kh, kw,
-        _stream(stream)))
+    _call.xnor_bwn_pack_weights(w, alpha, wimg, k_out, c, kh, kw, stream)
 
 
 def xnor_bwn_conv2d(parts, wimg, alpha, out, desc, stream=None):
-    _check("xnor_bwn_conv2d", lib().xnor_bwn_conv2d(
-        _ptr(parts, torch.uint8), _ptr(wimg, torch.uint8), _ptr(alpha, torch.float32), _ptr(out, torch.float32),
-        ctypes.byref(desc), _stream(stream)))
+    _call.xnor_bwn_conv2d(parts, wimg, alpha, out, desc, stream)
 
 
 def xnor_bingrad_pack_weights(w, wtbits, ones, wtmfma, k_out, c, kh, kw, stream=None):
-    _check("xnor_bingrad_pack_weights", lib().xnor_bingrad_pack_weights(
-        _ptr(w, torch.float32), _ptr(wtbits, torch.int32), _ptr(ones, torch.float32),
-        _ptr(wtmfma, torch.uint8), k_out, c, kh, kw, _stream(stream)))
+    _call.xnor_bingrad_pack_weights(w, wtbits, ones, wtmfma, k_out, c, kh, kw, stream)
 
 
 def xnor_bingrad_binarize(g_out, K, alpha, gbits, gmax, desc, stream=None):
-    _check("xnor_bingrad_binarize", lib().xnor_bingrad_binarize(
-        _ptr(g_out, torch.float32), _ptr(K, torch.float32), _ptr(alpha, torch.float32), _ptr(gbits, torch.int32),
-        _ptr(gmax, torch.float32), ctypes.byref(desc), _stream(stream)))
+    _call.xnor_bingrad_binarize(g_out, K, alpha, gbits, gmax, desc, stream)
 
 
 def xnor_bingrad_conv2d(gbits, wtbits, wtmfma, gmax, ones, scale_plane, g_in, dot_out, desc, algo=XNOR_ALGO_AUTO,
                         stream=None):
-    _check("xnor_bingrad_conv2d", lib().xnor_bingrad_conv2d(
-        _ptr(gbits, torch.int32), _ptr(wtbits, torch.int32), _ptr(wtmfma, torch.uint8), _ptr(gmax, torch.float32),
-        _ptr(ones, torch.float32), _ptr(scale_plane, torch.float32), _ptr(g_in, torch.float32),
-        _ptr(dot_out, torch.int32), ctypes.byref(desc), int(algo), _stream(stream)))
+    _call.xnor_bingrad_conv2d(gbits, wtbits, wtmfma, gmax, ones, scale_plane, g_in, dot_out, desc, int(algo), stream)
 
 
 def kbit_input_bytes(n, c, h, w):
@@ -290,48 +273,34 @@ def kbit_wimg_bytes(k_out, c, kh, kw):
 
 
 def xnor_kbit_pack_input(x, xq, ka, n, c, h, w, stream=None):
-    _check("xnor_kbit_pack_input", lib().xnor_kbit_pack_input(
-        _ptr(x, torch.float32), _ptr(xq, torch.uint8), int(ka), n, c, h, w, _stream(stream)))
+    _call.xnor_kbit_pack_input(x, xq, int(ka), n, c, h, w, stream)
 
 
 def xnor_kbit_pack_weights(w, scale, wq, ka, kw_bits, k_out, c, kh, kw, stream=None):
-    _check("xnor_kbit_pack_weights", lib().xnor_kbit_pack_weights(
-        _ptr(w, torch.float32), _ptr(scale, torch.float32), _ptr(wq, torch.uint8), int(ka), int(kw_bits),
-        k_out, c, kh, kw, _stream(stream)))
+    _call.xnor_kbit_pack_weights(w, scale, wq, int(ka), int(kw_bits), k_out, c, kh, kw, stream)
 
 
 def xnor_kbit_conv2d(xq, wq, scale, out, num_out, desc, ka, kw_bits, stream=None):
-    _check("xnor_kbit_conv2d", lib().xnor_kbit_conv2d(
-        _ptr(xq, torch.uint8), _ptr(wq, torch.uint8), _ptr(scale, torch.float32), _ptr(out, torch.float32),
-        _ptr(num_out, torch.int32), ctypes.byref(desc), int(ka), int(kw_bits), _stream(stream)))
+    _call.xnor_kbit_conv2d(xq, wq, scale, out, num_out, desc, int(ka), int(kw_bits), stream)
 
 
 def xnor_pack_weights(w, wbits, alpha, wmfma, k_out, c, kh, kw, stream=None):
-    _check("xnor_pack_weights", lib().xnor_pack_weights(
-        _ptr(w, torch.float32), _ptr(wbits, torch.int32), _ptr(alpha, torch.float32),
-        _ptr(wmfma, torch.uint8), k_out, c, kh, kw, _stream(stream)))
+    _call.xnor_pack_weights(w, wbits, alpha, wmfma, k_out, c, kh, kw, stream)
 
 
 def xnor_conv2d(xbits, wbits, wmfma, K, A, alpha, out, dot_out, desc, algo=XNOR_ALGO_AUTO, stream=None):
-    _check("xnor_conv2d", lib().xnor_conv2d(
-        _ptr(xbits, torch.int32), _ptr(wbits, torch.int32), _ptr(wmfma, torch.uint8),
-        _ptr(K, torch.float32), _ptr(A, torch.float32), _ptr(alpha, torch.float32), _ptr(out, torch.float32),
-        _ptr(dot_out, torch.int32), ctypes.byref(desc), int(algo), _stream(stream)))
+    _call.xnor_conv2d(xbits, wbits, wmfma, K, A, alpha, out, dot_out, desc, int(algo), stream)
 
 
 def xnor_conv2d_pool(xbits, wmfma, K, A, alpha, out_pool, desc, pool, pstride, relu=False, stream=None):
-    _check("xnor_conv2d_pool", lib().xnor_conv2d_pool(
-        _ptr(xbits, torch.int32), _ptr(wmfma, torch.uint8), _ptr(K, torch.float32), _ptr(A, torch.float32),
-        _ptr(alpha, torch.float32), _ptr(out_pool, torch.float32), ctypes.byref(desc), pool[0], pool[1], pstride[0],
-        pstride[1], int(bool(relu)), _stream(stream)))
+    _call.xnor_conv2d_pool(xbits, wmfma, K, A, alpha, out_pool, desc, pool[0], pool[1], pstride[0], pstride[1],
+                           int(bool(relu)), stream)
 
 
 def xnor_linear(xbits, wbits, wmfma, Krow, alpha, out, dot_out, batch, in_features, out_features,
                 algo=XNOR_ALGO_AUTO, stream=None):
-    _check("xnor_linear", lib().xnor_linear(
-        _ptr(xbits, torch.int32), _ptr(wbits, torch.int32), _ptr(wmfma, torch.uint8),
-        _ptr(Krow, torch.float32), _ptr(alpha, torch.float32), _ptr(out, torch.float32),
-        _ptr(dot_out, torch.int32), batch, in_features, out_features, int(algo), _stream(stream)))
+    _call.xnor_linear(xbits, wbits, wmfma, Krow, alpha, out, dot_out, batch, in_features, out_features, int(algo),
+                      stream)
 
 
 def conv2d_binactiv_workspace_bytes(desc):
@@ -340,12 +309,8 @@ def conv2d_binactiv_workspace_bytes(desc):
 
 def xnor_conv2d_binactiv(xbits, wbits, wmfma, K, A, alpha, bn_scale_next, bn_shift_next, xbits_next, A_next,
                          out, workspace, desc, algo=XNOR_ALGO_AUTO, stream=None):
-    _check("xnor_conv2d_binactiv", lib().xnor_conv2d_binactiv(
-        _ptr(xbits, torch.int32), _ptr(wbits, torch.int32), _ptr(wmfma, torch.uint8),
-        _ptr(K, torch.float32), _ptr(A, torch.float32), _ptr(alpha, torch.float32),
-        _ptr(bn_scale_next, torch.float32), _ptr(bn_shift_next, torch.float32),
-        _ptr(xbits_next, torch.int32), _ptr(A_next, torch.float32), _ptr(out, torch.float32),
-        _ptr(workspace, torch.uint8), ctypes.byref(desc), int(algo), _stream(stream)))
+    _call.xnor_conv2d_binactiv(xbits, wbits, wmfma, K, A, alpha, bn_scale_next, bn_shift_next, xbits_next, A_next,
+                               out, workspace, desc, int(algo), stream)
 
 
 NOALLOC_SCRATCH_BYTES = 4 << 20      # XNOR_NOALLOC_SCRATCH_BYTES of include/xnor.h
@@ -353,12 +318,8 @@ NOALLOC_SCRATCH_BYTES = 4 << 20      # XNOR_NOALLOC_SCRATCH_BYTES of include/xno
 
 def xnor_conv2d_binactiv_noalloc(xbits, wbits, wmfma, K, A, alpha, bn_scale_next, bn_shift_next, xbits_next,
                                  A_next, out, desc, algo=XNOR_ALGO_AUTO, stream=None):
-    _check("xnor_conv2d_binactiv_noalloc", lib().xnor_conv2d_binactiv_noalloc(
-        _ptr(xbits, torch.int32), _ptr(wbits, torch.int32), _ptr(wmfma, torch.uint8),
-        _ptr(K, torch.float32), _ptr(A, torch.float32), _ptr(alpha, torch.float32),
-        _ptr(bn_scale_next, torch.float32), _ptr(bn_shift_next, torch.float32),
-        _ptr(xbits_next, torch.int32), _ptr(A_next, torch.float32), _ptr(out, torch.float32),
-        ctypes.byref(desc), int(algo), _stream(stream)))
+    _call.xnor_conv2d_binactiv_noalloc(xbits, wbits, wmfma, K, A, alpha, bn_scale_next, bn_shift_next, xbits_next,
+                                       A_next, out, desc, int(algo), stream)
 
 
 # ---------------------------------------------------------------------------------------------
