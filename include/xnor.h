@@ -253,16 +253,18 @@ XNOR_API int xnor_conv2d_pool(const uint32_t *xbits, const void *wmfma, const fl
  * estimated by alpha * sign(W):
  *     out[n][k][oy][ox] = alpha_k * sum over in-bounds taps and channels of  I * sign(W)
  * (additions and subtractions of the inputs only; zero padding, correlation, no bias, as above).
- * The sums run on the bfloat16 matrix cores and are float sums of exact terms: xnor_bwn_split writes
- * every input as three bfloat16 numbers whose sum is the float exactly (finite inputs), the weights
- * are +-1.  Three calls:
+ * xnor_bwn_split writes every input as three bfloat16 numbers whose sum is the float exactly (finite inputs), the weights
+ * are +-1, and the sums run on the matrix cores in float: of those three parts, or (filters of 25 taps and more; of 9 and
+ * more where the layer fills the chip) of the same floats as five digits of 6-bit floats under one power of two per 32 channels of a
+ * pixel, which hold the largest of the 32 exactly and the others to half of its unit in the last place.  Three calls:
  *   xnor_bwn_split         x float32 [n][c][h][w]  ->  parts, xnor_bwn_parts_bytes(n, c, h, w) bytes (opaque)
  *   xnor_bwn_pack_weights  w float32 [k_out][c][kh][kw]  ->  alpha float32 [k_out] (as xnor_pack_weights),
  *                          wimg, xnor_bwn_wimg_bytes(k_out, c, kh, kw) bytes (opaque); once per layer
  *   xnor_bwn_conv2d        parts, wimg, alpha  ->  out float32 [n][k_out][h_out][w_out]; d describes the
  *                          convolution with the real channel count c
  * Differences between this result and one accumulated in double stay within float rounding of the
- * running sums (about 1e-7 * sqrt(c*kh*kw) of the magnitude of the terms).
+ * running sums (about 1e-7 * sqrt(c*kh*kw) of the magnitude of the terms); the digits' sums, with fewer additions, to
+ * about half of that.
  */
 XNOR_API size_t xnor_bwn_parts_bytes(int n, int c, int h, int w);
 XNOR_API size_t xnor_bwn_wimg_bytes(int k_out, int c, int kh, int kw);

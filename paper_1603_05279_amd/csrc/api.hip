@@ -349,7 +349,7 @@ size_t xnor_bwn_parts_bytes(int n, int c, int h, int w)
 size_t xnor_bwn_wimg_bytes(int k_out, int c, int kh, int kw)
 {
     if (k_out <= 0 || c <= 0 || kh <= 0 || kw <= 0 || (long long)kh * kw > 4096) return 0;
-    return wimg_bf16_bytes(k_out, (c + 15) / 16, kh * kw);
+    return wimg_bf16_bytes(k_out, (c + 15) / 16, kh * kw) + wimg_pop_bytes(k_out, c, kh * kw);
 }
 
 int xnor_bwn_split(const float *x, void *parts, int n, int c, int h, int w, void *hip_stream)
@@ -379,15 +379,15 @@ int xnor_bwn_conv2d(const void *parts, const void *wimg, const float *alpha, flo
 {
     if (!parts || !wimg || !alpha || !out) return XNOR_ERR_NULL;
     if (!d) return XNOR_ERR_NULL;
-    // the matrix-core kernel sees 3*ceil(c/16) operand words of 32 bytes per pixel
+    // the bfloat16 form sees 3*ceil(c/16) operand words of 32 bytes per pixel
     xnor_conv_desc dd = *d;
     if (d->c <= 0 || d->c > 0x7fffffff / 96) return XNOR_ERR_SHAPE;
     dd.c = 96 * ((d->c + 15) / 16);
-    ConvGeom g;
-    if (xnor_status s = make_geom(&dd, &g)) return s;
+    ConvGeom gp, g;
+    if (xnor_status s = make_geom(&dd, &gp)) return s;
+    if (xnor_status s = make_geom(d, &g)) return s;
     if (!aligned16(parts) || !aligned16(wimg) || !aligned16(alpha) || !aligned16(out)) return XNOR_ERR_ALIGN;
-    return launch_conv_mfma(2, static_cast<const uint32_t *>(parts), wimg, nullptr, nullptr, alpha, out, nullptr, g,
-                            (hipStream_t)hip_stream);
+    return launch_bwn_conv(parts, wimg, alpha, out, g, gp, (hipStream_t)hip_stream);
 }
 
 int xnor_bingrad_pack_weights(const float *w, uint32_t *wtbits, float *ones, void *wtmfma,

@@ -1,9 +1,8 @@
 // Binary-Weight-Network convolution (sec. 3.1): real-valued inputs, weights estimated as alpha * sign(W),
 //     I * W  ~  (I (+) B) alpha        (convolution with additions and subtractions only).
-// On this chip the +-1 weighted sums run on the bfloat16 matrix cores: a float is the exact sum of
-// three bfloat16 numbers, a +-1 weight times a bfloat16 is exact, and the matrix cores accumulate in
-// float, so the convolution kernel (conv_mfma.hip, third operand format) returns the float sum of
-// exact terms.  This file holds the two preparation kernels: the activation split and the weights.
+// The activations travel as three bfloat16 parts per float (their sum is the float exactly); the convolution kernel
+// (conv_mfma_kernel.h) stages them as digits of 6-bit floats (Enc<2>) or as they are (Enc<4>); the matrix cores
+// accumulate in float either way.  This file holds the two preparation kernels: the activation split and the weights.
 #include "xnor_internal.h"
 
 namespace xnor {
@@ -77,9 +76,11 @@ xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, 
 // Weight side: alpha_k = ||W_k||_1 / n (sec. 3.1) and the +-1 bfloat16 record image
 // [filter block of 32][tap][16-channel group] of 1 KiB records in matrix-operand lane order
 // (lane l: filter l & 31, channels 16*group + 8*(l >> 5) .. +7); a record multiplies all three
-// parts of its group.  One trailing all-zero record.  One workgroup per filter.
+// parts of its group.  One trailing all-zero record.  Behind it the signs as packed words [filter block of 32][tap][32-channel
+// word][32 filters], bit j = channel j of the word is negative (0 past the last channel and filter).  One workgroup per filter.
 __global__ __launch_bounds__(256) void bwn_pack_kernel(const float *__restrict__ w, float *__restrict__ alpha,
-                                                       uint16_t *__restrict__ wimg, int k_out, int c, int taps, int cg)
+                                                       uint16_t *__restrict__ wimg, uint32_t *__restrict__ words, int k_out,
+                                                       int c, int taps, int cg)
 {
     __shared__ float red[256];
     const int f = blockIdx.x, tid = threadIdx.x;
@@ -105,6 +106,14 @@ __global__ __launch_bounds__(256) void bwn_pack_kernel(const float *__restrict__
         const int slot = (row + 32 * (j >> 3)) * 8 + (j & 7);
         wimg[rec * 512 + slot] = v;
     }
+    const int cw = (c + 31) / 32;
+    for (int i = tid; i < (taps * cw + 1) / 2 * 64; i += 256) {       // lanes are the channels of two words
+        const int word = i >> 5, t = word / cw, ch = (word - t * cw) * 32 + (i & 31);
+        const bool neg = t < taps && ch < c && !(wf[(size_t)ch * taps + t] >= 0.0f);
+        const unsigned long long mask = __ballot(neg);
+        if ((tid & 31) == 0 && t < taps)
+            words[((size_t)fblk * taps * cw + word) * 32 + row] = (uint32_t)(tid & 32 ? mask >> 32 : mask);
+    }
 }
 
 __global__ __launch_bounds__(256) void bwn_clear_kernel(uint32_t *__restrict__ p, size_t ndwords)
@@ -116,10 +125,11 @@ xnor_status launch_bwn_pack(const float *w, float *alpha, void *wimg, int k_out,
 {
     const int cg = (c + 15) / 16;
     // rows of the last filter block past k_out and the trailing record must read as zero
-    const size_t bytes = wimg_bf16_bytes(k_out, cg, taps);
+    const size_t records = wimg_bf16_bytes(k_out, cg, taps), bytes = records + wimg_pop_bytes(k_out, c, taps);
     bwn_clear_kernel<<<dim3(1024), dim3(256), 0, stream>>>(static_cast<uint32_t *>(wimg), bytes / 4);
     if (xnor_status s = hip_status(hipGetLastError())) return s;
-    bwn_pack_kernel<<<dim3((unsigned)k_out), dim3(256), 0, stream>>>(w, alpha, static_cast<uint16_t *>(wimg), k_out, c,
+    bwn_pack_kernel<<<dim3((unsigned)k_out), dim3(256), 0, stream>>>(w, alpha, static_cast<uint16_t *>(wimg),
+                                                                     reinterpret_cast<uint32_t *>(static_cast<uint8_t *>(wimg) + records), k_out, c,
                                                                      taps, cg);
     return hip_status(hipGetLastError());
 }

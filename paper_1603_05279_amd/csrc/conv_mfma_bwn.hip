@@ -1,0 +1,29 @@
+// Binary-Weight-Network convolution: digits of the real inputs, or their bfloat16 parts as they are.
+#include "conv_mfma_kernel.h"
+
+namespace xnor {
+
+template xnor_status launch_fmt<2>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+template xnor_status launch_fmt<4>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+
+xnor_status launch_bwn_conv(const void *parts, const void *wimg, const float *alpha, float *out, const ConvGeom &g,
+                            const ConvGeom &gp, hipStream_t stream)
+{
+    const uint32_t *x = static_cast<const uint32_t *>(parts);
+    // Making the digits of a word costs a wave about 1.2 us per 64 words, and every tap multiplies them with 5 instructions
+    // instead of 12.  Digits win from 5 x 5 filters on, and from 3 x 3 where there are workgroups enough to convert under each
+    // other's matrix instructions (measured, bfloat16 parts against digits: 128 images of 256 x 13 x 13 -> 384, 3 x 3, 102 -> 78 us;
+    // 15 of 146 x 9 x 9 -> 368, 5 x 5, 38 -> 22; 23 of 96 x 33 x 22 -> 50, 3 x 3, 28.7 -> 24.8; but 6 of 288 x 23 x 20 -> 32,
+    // 3 x 3, 31 -> 35 and 21 of 264 x 11 x 11 -> 112, 1 x 1, 12.0 -> 13.5).
+    const long long wgs = (long long)((g.m_total + 127) / 128) * ((g.k_out + 127) / 128);
+    if (g.taps >= 25 || (g.taps >= 9 && wgs >= 128)) {
+        const uint8_t *words = static_cast<const uint8_t *>(wimg) + wimg_bf16_bytes(g.k_out, (g.c + 15) / 16, g.taps);
+        const xnor_status s = launch_fmt<2>(x, words, nullptr, nullptr, alpha, out, nullptr, g, stream, nullptr);
+        if (s != XNOR_ERR_UNSUPPORTED) return s;         // (the parts fit where the digits' LDS image does not)
+    }
+    return launch_fmt<4>(x, wimg, nullptr, nullptr, alpha, out, nullptr, gp, stream, nullptr);
+}
+
+}  // namespace xnor

@@ -1,7 +1,7 @@
 // k-bit quantisation (sec. 3.2, paragraph "k-bit Quantization"): q_k(x) = 2*([(2^k - 1)(x + 1)/2]/(2^k - 1) - 1/2)
 // in place of sign().  With L = 2^k - 1 and the level index u = [L (x + 1)/2], q_k = (2u - L)/L: an odd integer
 // in [-L, L] over L.  The convolution of ka-bit inputs with kw-bit weights is therefore an integer contraction
-// of the numerators divided by La*Lw, and runs as ONE int8 matrix-core convolution (conv_mfma.hip, operand
+// of the numerators divided by La*Lw, and runs as ONE int8 matrix-core convolution (conv_mfma_kernel.h, operand
 // format 3: int32 accumulation, exact) on the numerators stored as int8; zero padding stays exact.
 // (The same sum could be formed from ka*kw binary convolutions of the bit planes, q_k = sum_p 2^p s_p / L; on
 // this chip the int8 contraction is ka*kw times less matrix work at half the 4-bit rate.)

@@ -25,13 +25,13 @@ struct PoolPlan {
 };
 
 struct MfmaPlan {
-    int cc_words;     // channel words widened per chunk (divides cw)
+    int cc_words;     // channel words per chunk (divides cw; digit operands: the last chunk may lack one word, staged as zeros)
     int ps;           // bytes per pixel in LDS (an odd multiple of 16: conflict-free 16-byte reads)
     int max_rows;     // padded input rows a pixel tile can touch
     int region_bytes; // max_rows * row_pitch
     int row_pitch;    // LDS bytes per padded input row (>= wp * ps)
     int nsteps;       // K-steps per chunk
-    int tap_jump;     // weight records skipped when a chunk moves to the next tap
+    int tap_jump;     // weight records (packed words: words) skipped when a chunk moves to the next tap
     int ptiles;       // pixel tiles of the launch (the grid is padded beyond it)
     int lut_offset;   // LDS byte offset of the sign-byte widening table
     int ftiles;       // filter tiles of the launch
@@ -266,14 +266,77 @@ constexpr int ring_lcm(int a, int b)
     return m;
 }
 
-// Binary-Weight-Network operands (sec. 3.1: real inputs, +-1 weights).  The real activations arrive
+// Binary-Weight-Network operands (sec. 3.1: real inputs, +-1 weights).  A word is 32 channels of a pixel, staged as five
+// digits of 6-bit floats (E2M3) with one power-of-two scale 2^e, 2^e <= max |x| < 2^(e+1) over the word:
+//     x = 2^e * (d0 + d1 / 32 + d2 / 32^2 + d3 / 32^3 + d4 / 32^4),   |d| <= 2 in steps of 1/8 (all of them E2M3 values),
+// each digit the nearest to what the digits before it left (those remainders are exact).  The last digit's step is the unit in
+// the last place of the word's largest input: that one is represented exactly, the others to half of that unit, which
+// is what a float sum that the largest one enters can hold of them (every filter adds all 32, weights are never 0).
+// The matrix instruction multiplies E2M3 by the +-1 weights (E2M1, widened from packed bits as in the binary
+// convolution), applies the scales (activations: e, weights: the digit's 32^-k) and accumulates in float; 5 instructions of the
+// 4- and 6-bit rate per 64 channels take the place of 12 bfloat16 ones (three parts).
+// A word with an infinite or NaN input has the scale NaN: every result that it enters is NaN.  e is at least -106
+// (scales of all digits stay normal floats): inputs below keep an absolute error of 2^-130.
+template <> struct Enc<2> : Enc<1> {
+    static constexpr int DIGITS = 5;
+    static constexpr int BPB = 128;            // five 24-byte operands, the scale, 4 bytes of padding
+    static constexpr int SCALE_DWORD = 30;
+    static constexpr int MIN_FIELD = 21;       // biased exponent of the smallest scale
+    typedef unsigned v6u __attribute__((ext_vector_type(6)));
+    typedef int v32i __attribute__((ext_vector_type(32)));
+    typedef float v16 __attribute__((ext_vector_type(16)));
+    typedef float v32 __attribute__((ext_vector_type(32)));
+    // K position of channel ch in the 4-bit operands (widen_bits): 8 * (3 - ch % 4) + ch / 4.  The conversion of two
+    // 16-vectors puts lo[i] at position 2i and hi[i] at 2i + 1.
+    static constexpr int channel_at(int pos) { return 4 * (pos % 8) + 3 - pos / 8; }
+    // x: the word's channels in order.  out: the 32 dwords of the staged word.
+    static __device__ __forceinline__ void digits(const float (&x)[32], uint32_t (&out)[32])
+    {
+        uint32_t m = 0;
+#pragma unroll
+        for (int c = 0; c < 32; ++c) m = max(m, __builtin_bit_cast(uint32_t, x[c]) & 0x7fffffffu);
+        const uint32_t field = max(m >> 23, (uint32_t)MIN_FIELD);
+        v16 lo, hi;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            lo[i] = x[channel_at(2 * i)];
+            hi[i] = x[channel_at(2 * i + 1)];
+        }
+#pragma unroll
+        for (int k = 0; k < DIGITS; ++k) {
+            const float scale = __builtin_bit_cast(float, (field - 5u * k) << 23);
+            const v6u d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo, hi, scale);
+#pragma unroll
+            for (int i = 0; i < 6; ++i) out[6 * k + i] = d[i];
+            if (k + 1 < DIGITS) {
+                const v32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(d, scale);
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    lo[i] -= back[2 * i];
+                    hi[i] -= back[2 * i + 1];
+                }
+            }
+        }
+        out[SCALE_DWORD] = field;
+        out[31] = 0;
+    }
+    template <int K> static __device__ __forceinline__ acc_t mfma_digit(v4i w, const v32i &x, acc_t c)
+    {
+        const v8i w8 = __builtin_shufflevector(w, w, 0, 1, 2, 3, -1, -1, -1, -1);
+        const v8i x8 = __builtin_shufflevector(x, x, 6 * K, 6 * K + 1, 6 * K + 2, 6 * K + 3, 6 * K + 4, 6 * K + 5, -1, -1);
+        return __builtin_amdgcn_mfma_scale_f32_32x32x64_f8f6f4(w8, x8, c, 4, 2, 0, 127 - 5 * K, 0, x[SCALE_DWORD]);
+    }
+};
+
+// Binary-Weight-Network operands without conversion, for short K loops (few taps, few workgroups), where making the digits
+// above would take longer than their matrix instructions save.  The real activations arrive
 // pre-split into three bfloat16 parts (hi + mid + lo == the float exactly), 16 channels x one part
 // = one 32-byte "word" per pixel; the weights are +-1.0 (0 past the last channel or filter) in
 // bfloat16, one record per 16-channel group that multiplies all three parts (the record is fetched
 // once per K-step and feeds three matrix instructions per result block).  Products are exact,
 // accumulation is float: the result is the float sum of exact terms.  Layout-wise a word is like the
 // int8 encoding's (32 bytes per pixel and word, the half-wave picks its 16 bytes), with nothing to widen.
-template <> struct Enc<2> {
+template <> struct Enc<4> {
     static constexpr int BPS = 3;       // a K-step = one 16-channel group = the three parts' words, one weight record
     static constexpr int NX = 3;        // matrix instructions per step and result block (one per part)
     static constexpr bool HALF_SPLIT = true;
@@ -375,17 +438,17 @@ template <int FW> struct WStreamChunked {
 // resource of its own that ends with its words: prefetches beyond are answered with zeros.  When the block count is odd the
 // second half-wave of the last step holds no block: its code is 0 (operand 0.0).
 // Steps are consecutive (LINEAR) or, where a chunk holds part of the channel words, run on within a tap and skip
-// tap_jump steps to the next one (uniform bookkeeping in the scalar offset; steps past the end read the chunk's
+// tap_jump words to the next one (uniform bookkeeping in the scalar offset; steps past the end read the block's
 // first words, which nothing multiplies).
 template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     typedef uint32_t word_t;
     static constexpr bool WIDEN = true;
     __amdgpu_buffer_rsrc_t rsrc[FW];
-    int voff, w_rec, w_cnt, w_left, steps_per_tap, tap_jump;
+    int voff, w_blk, w_cnt, w_left, steps_per_tap, tap_jump;
     uint32_t last_code;          // code of the last step
-    __device__ __forceinline__ WStreamBits(const uint32_t *words, const int (&fblk)[FW], int nblk, int rec_start,
+    __device__ __forceinline__ WStreamBits(const uint32_t *words, const int (&fblk)[FW], int nblk, int first,
                                            int nsteps, bool odd_last, int lane, int steps_per_tap_, int tap_jump_)
-        : voff(lane * 4 + (LINEAR ? rec_start * 256 : 0)), w_rec(rec_start), w_cnt(0), w_left(nsteps),
+        : voff(lane * 4 + (LINEAR ? first * 128 : 0)), w_blk(first), w_cnt(0), w_left(nsteps),
           steps_per_tap(steps_per_tap_), tap_jump(tap_jump_), last_code(odd_last && lane >= 32 ? 0u : 0x88888888u)
     {
 #pragma unroll
@@ -397,7 +460,7 @@ template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     {
 #pragma unroll
         for (int i = 0; i < FW; ++i)
-            dst[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc[i], voff, LINEAR ? 0 : w_rec * 256, AUX);
+            dst[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc[i], voff, LINEAR ? 0 : w_blk * 128, AUX);
         if constexpr (LINEAR) {
             voff += 256;
         } else {
@@ -406,8 +469,8 @@ template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
             w_cnt += live;
             const int wrap = w_cnt == steps_per_tap ? 1 : 0;
             w_cnt = wrap ? 0 : w_cnt;
-            w_rec += live + (wrap ? tap_jump : 0);
-            w_rec = w_left > 0 ? w_rec : 0;
+            w_blk += 2 * live + (wrap ? tap_jump : 0);
+            w_blk = w_left > 0 ? w_blk : 0;
         }
     }
 };
@@ -512,6 +575,97 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
 #pragma unroll
             for (int j = 0; j < PW; ++j) asm volatile("" : "+v"(acc[i][j]));
     }
+}
+
+// The K loop of the digit operands (Enc<2>): a step is 64 channels, five matrix instructions per result block.  One pixel
+// block's digits (128 bytes per lane, eight reads) are read while the block before it is multiplied.
+template <int FW, int PW, int DW, class WS>
+__device__ __forceinline__ void mfma_kloop_digits(Enc<2>::acc_t (&acc)[FW][PW], const uint8_t *lds_x,
+                                                  const int (&pbase)[PW], const int *xoff_tab, int tab_lane, WS &ws,
+                                                  int nsteps)
+{
+    typedef Enc<2> E;
+    constexpr int RW = DW + 1;
+    static_assert(RW % 2 == 0 && RW + 3 <= KLOOP_TABLE_PAD, "rings");
+    // a wave tile of one result block alternates between two sums: a matrix instruction takes twice its rate to its result
+    constexpr bool TWO = FW * PW == 1;
+    E::acc_t odd;
+    if constexpr (TWO) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) odd[v] = 0.0f;
+    }
+    const int *tab = xoff_tab + tab_lane;
+    typename WS::word_t w[RW][FW];
+    v4i wide[2][FW];
+    uint32_t full = 0x88888888u, full_one = 0x22222222u;
+    asm("" : "+v"(full), "+v"(full_one));
+    auto widen = [&](v4i (&dst)[FW], const typename WS::word_t (&src)[FW], int s, bool tail) {
+        const uint32_t code = tail && s == nsteps - 1 ? ws.last_code : full;
+        const uint32_t one = tail && s == nsteps - 1 ? ws.last_code >> 2 : full_one;
+#pragma unroll
+        for (int i = 0; i < FW; ++i) dst[i] = E::widen_bits(src[i], code, one);
+    };
+    auto load_x = [&](E::v32i &dst, int at) {
+        v4i d[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) d[q] = *reinterpret_cast<const v4i *>(lds_x + at + 16 * q);
+#pragma unroll
+        for (int q = 0; q < 32; ++q) dst[q] = d[q / 4][q % 4];
+    };
+    E::v32i x[2];
+#pragma unroll
+    for (int u = 0; u < DW; ++u) ws.load(w[u]);
+    int off = tab[0], off_next = tab[E::BPS];
+    load_x(x[0], pbase[0] + off);
+    widen(wide[0], w[0], 0, true);
+    auto substep = [&](int s, int u, bool tail) {
+        ws.load(w[(u + DW) % RW]);
+        const int off_after = tab[(s + u + 2) * E::BPS];
+#pragma unroll
+        for (int j = 0; j < PW; ++j) {
+            const E::v32i &cur = x[(u * PW + j) & 1];
+            load_x(x[(u * PW + j + 1) & 1], j + 1 < PW ? pbase[j + 1] + off : pbase[0] + off_next);
+            auto digit = [&](auto k) {
+                constexpr int K = decltype(k)::value;
+#pragma unroll
+                for (int i = 0; i < FW; ++i) {
+                    E::acc_t &a = TWO && K % 2 ? odd : acc[i][j];
+                    a = E::mfma_digit<K>(wide[u & 1][i], cur, a);
+                }
+            };
+            digit(std::integral_constant<int, 0>{});
+            digit(std::integral_constant<int, 1>{});
+            digit(std::integral_constant<int, 2>{});
+            digit(std::integral_constant<int, 3>{});
+            digit(std::integral_constant<int, 4>{});
+            if (j == PW - 1) widen(wide[(u + 1) & 1], w[(u + 1) % RW], s + u + 1, tail);
+            // two reads behind each of the first four matrix instructions, the rest of the slots for the widening
+#pragma unroll
+            for (int q = 0; q < 5 * FW; ++q) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                if (q < 5) __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        off = off_next;
+        off_next = off_after;
+    };
+    int s = 0;
+    for (; s + RW < nsteps; s += RW) {
+#pragma unroll
+        for (int u = 0; u < RW; ++u) substep(s, u, u == RW - 1);
+    }
+#pragma unroll
+    for (int u = 0; u < RW; ++u) {
+        if (s + u >= nsteps) break;
+        substep(s, u, true);
+#pragma unroll
+        for (int i = 0; i < FW; ++i)
+#pragma unroll
+            for (int j = 0; j < PW; ++j) asm volatile("" : "+v"(acc[i][j]));
+    }
+    if constexpr (TWO) acc[0][0] += odd;
 }
 
 }  // namespace xnor

@@ -1,0 +1,21 @@
+// Host side shared by the sources that instantiate the matrix-core convolution kernel (conv_mfma_kernel.h), one source per
+// group of operand formats so that they compile side by side.
+#pragma once
+#include "xnor_internal.h"
+
+namespace xnor {
+
+// Tiling override and LDS budget of xnor_set_tuning (0 = the library's choice of tiling).
+int mfma_tile_override();
+int mfma_lds_budget();
+
+// One convolution with operand format FMT: 0 int8 signs, 1 4-bit signs, 2 digits of real inputs, 3 int8 levels, 4 bfloat16 parts.
+template <int FMT>
+xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, const float *A, const float *alpha, float *out,
+                       int32_t *dot_out, const ConvGeom &g, hipStream_t stream, const FuseArgs *fz);
+
+// A_next[m] = (part[0][m] + part[1][m] + ...) / k_out, planes added in order: second launch of the fused epilogue when the
+// filters span several workgroups
+xnor_status launch_sum_planes(const float *part, float *A_next, int m_total, int planes, float k_out, hipStream_t stream);
+
+}  // namespace xnor

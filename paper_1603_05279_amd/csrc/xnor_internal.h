@@ -123,7 +123,10 @@ xnor_status launch_conv_mfma_pool(const uint32_t *xbits, const void *wmfma, cons
                                   const float *alpha, float *out_pool, const ConvGeom &g, int ph, int pw, int sh,
                                   int sw, int relu, hipStream_t stream);
 void set_mfma_tuning(int tile, int lds_budget);
-// Binary-Weight-Network preparation kernels (bwn.hip); the convolution itself is launch_conv_mfma with fmt 2
+// Binary-Weight-Network preparation kernels (bwn.hip); the convolution itself is launch_bwn_conv
+// (g: the layer; gp: the same over the parts' 3 * ceil(c/16) words of 32 channels)
+xnor_status launch_bwn_conv(const void *parts, const void *wimg, const float *alpha, float *out, const ConvGeom &g,
+                            const ConvGeom &gp, hipStream_t stream);
 xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, hipStream_t stream);
 xnor_status launch_bwn_pack(const float *w, float *alpha, void *wimg, int k_out, int c, int taps, hipStream_t stream);
 // Sizes of the two matrix-core weight images (int8 first, 4-bit float second), 1 KiB records;
@@ -136,8 +139,9 @@ __host__ __device__ inline size_t wimg_f4_bytes(int k_out, int c, int taps)
 {
     return ((size_t)((k_out + 31) / 32) * (((size_t)taps * (size_t)((c + 31) / 32) + 1) / 2) + 1) * 1024u;
 }
-// Binary-Weight-Network image: one +-1 bfloat16 record per filter block, tap and 16-channel group
-// (groups = ceil(c/16)), plus the trailing all-zero record
+
+// Binary-Weight-Network images: one +-1 bfloat16 record per filter block, tap and 16-channel group (groups = ceil(c/16)) and
+// a trailing all-zero record, then packed words in the order of wimg_pop_bytes (a set bit is a negative weight)
 __host__ __device__ inline size_t wimg_bf16_bytes(int k_out, int groups, int taps)
 {
     return ((size_t)((k_out + 31) / 32) * (size_t)taps * (size_t)groups + 1) * 1024u;
