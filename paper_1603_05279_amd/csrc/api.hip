@@ -502,8 +502,8 @@ int xnor_kbit_pack_weights(const float *w, float *scale, void *wq, int ka, int k
         return XNOR_ERR_SHAPE;
     if (!aligned16(w) || !aligned16(scale) || !aligned16(wq)) return XNOR_ERR_ALIGN;
     const double s = (double)((1 << ka) - 1) * (double)((1 << kw_bits) - 1);
-    return launch_pack_weights(w, nullptr, scale, wq, k_out, c, kh * kw, (hipStream_t)hip_stream, 3, kw_bits,
-                               (float)(1.0 / s));
+    return launch_pack_weights(w, nullptr, scale, wq, k_out, c, kh * kw, (hipStream_t)hip_stream,
+                               kbit_narrow(ka, kw_bits, c, kh * kw) ? 4 : 3, kw_bits, (float)(1.0 / s));
 }
 
 int xnor_kbit_conv2d(const void *xq, const void *wq, const float *scale, float *out, int32_t *num_out,
@@ -517,8 +517,8 @@ int xnor_kbit_conv2d(const void *xq, const void *wq, const float *scale, float *
     if (lw * g.c * g.taps > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;       // the int32 accumulator holds every sum
     if (!aligned16(xq) || !aligned16(wq) || !aligned16(scale) || !aligned16(out) || !aligned16(num_out))
         return XNOR_ERR_ALIGN;
-    return launch_conv_mfma(3, static_cast<const uint32_t *>(xq), wq, nullptr, nullptr, scale, out, num_out, g,
-                            (hipStream_t)hip_stream);
+    return launch_conv_mfma(kbit_narrow(ka, kw_bits, g.c, g.taps) ? 5 : 3, static_cast<const uint32_t *>(xq), wq, nullptr, nullptr,
+                            scale, out, num_out, g, (hipStream_t)hip_stream);
 }
 
 int xnor_linear(const uint32_t *xbits, const uint32_t *wbits, const void *wmfma,

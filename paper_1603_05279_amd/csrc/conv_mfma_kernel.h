@@ -432,7 +432,9 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
 #pragma unroll
             for (int u = 0; u < FB; ++u)
                 if (dst[u] >= 0) {
-                    if constexpr (RAW) {
+                    if constexpr (FMT == 5) {
+                        *reinterpret_cast<v4i *>(lds + dst[u]) = ok[u] ? E::narrow(raw[u][0], raw[u][1]) : v4i{0, 0, 0, 0};
+                    } else if constexpr (RAW) {
                         *reinterpret_cast<v4u *>(lds + dst[u]) = raw[u][0];
                         *reinterpret_cast<v4u *>(lds + dst[u] + 16) = raw[u][1];
                     } else {
@@ -841,7 +843,7 @@ constexpr int LDS_LIMIT = 160 * 1024;
 // fuse_rows: rows of PT words for the fused epilogue's |z| sums and sign words (0 without it)
 // par_bytes: alpha (fused epilogue: also scale and shift) of the workgroup's filters
 // channel words per K-step and bytes of the widening table of an operand format (Enc<fmt>::BPS, LUT_BYTES)
-static constexpr int fmt_bps(int fmt) { return fmt == 1 || fmt == 2 ? 2 : fmt == 4 ? 3 : 1; }
+static constexpr int fmt_bps(int fmt) { return fmt == 1 || fmt == 2 || fmt == 5 ? 2 : fmt == 4 ? 3 : 1; }
 static constexpr int fmt_lut_bytes(int fmt) { return fmt == 0 ? 512 * 8 : 0; }     // int8 operands only
 static size_t plan_lds_bytes(const MfmaPlan &pl, int fmt, int wp, int PT, int fuse_rows, int par_bytes)
 {
@@ -858,7 +860,7 @@ static int plan_lut_offset(const MfmaPlan &pl, int fmt, int wp, int PT, int fuse
 static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fuse_rows, int par_bytes, MfmaPlan *pl,
                       int rows_override = 0, bool lone = false)
 {
-    const int bps = fmt_bps(fmt), bpb = fmt == 1 ? Enc<1>::BPB : fmt == 2 ? Enc<2>::BPB : 32;
+    const int bps = fmt_bps(fmt), bpb = fmt == 1 || fmt == 5 ? Enc<1>::BPB : fmt == 2 ? Enc<2>::BPB : 32;
     const int rows = rows_override ? rows_override : worst_region_rows(g, PT, PT);
     for (int ccw = g.cw; ccw >= 1; --ccw) {
         // (digit operands: the last chunk may lack one word)
@@ -956,6 +958,7 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     if (grid.y > 65535u) return XNOR_ERR_UNSUPPORTED;
     const size_t img_bytes = FMT == 1 || FMT == 2 ? wimg_pop_bytes(g.k_out, g.c, g.taps)
                              : FMT == 4 ? wimg_bf16_bytes(g.k_out, g.cw / 3, g.taps)
+                             : FMT == 5 ? wimg_f4_bytes(g.k_out, g.c, g.taps)
                                         : wimg_i8_bytes(g.k_out, g.c, g.taps);
     if (img_bytes > 0x7fffffffull) return XNOR_ERR_UNSUPPORTED;
     kern<<<grid, block, lds, stream>>>(ConvArgs{xbits, reinterpret_cast<const v4i *>(wimg), K, A, alpha, out, dot_out,

@@ -361,6 +361,26 @@ template <> struct Enc<3> : Enc<0> {
     static __device__ __forceinline__ void build_lut(uint8_t *, int, int) {}
 };
 
+// k-bit operands of at most two bits each: the numerators +-1 and +-3 are 4-bit floats (E2M1 0x2, 0x5 and their negatives), so the
+// contraction runs at twice the int8 rate on operands of half the size; its float sums are exact while they stay below 2^24.
+// Dword q of a word holds channel 8q + i in nibble 2i and channel 8q + 4 + i in nibble 2i + 1.
+template <> struct Enc<5> : Enc<1> {
+    // int8 numerators -> codes: (byte >> 1) & 3 is 0, 1, 2, 3 for 1, 3, -3, -1 (channels past the last one are 0 there, and
+    // 0 in the weights)
+    static constexpr uint32_t CODES = 0x0A0D0502u;
+    static __device__ __forceinline__ v4i narrow(v4u lo, v4u hi) {
+        v4i r;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t a = q < 2 ? lo[2 * q] : hi[2 * q - 4], b = q < 2 ? lo[2 * q + 1] : hi[2 * q - 3];
+            r[q] = (int)(__builtin_amdgcn_perm(0u, CODES, (a >> 1) & 0x03030303u) |
+                         __builtin_amdgcn_perm(0u, CODES, (b >> 1) & 0x03030303u) << 4);
+        }
+        return r;
+    }
+    static __device__ __forceinline__ uint32_t code(uint32_t byte) { return byte ? (CODES >> (4 * (byte & 6u))) & 15u : 0u; }
+};
+
 // Steps the offset table is padded by beyond the last K-step (copies of the last entry): operand
 // prefetches run ahead of the loop's end by at most one turn plus the activation depth.
 constexpr int KLOOP_TABLE_PAD = 20;

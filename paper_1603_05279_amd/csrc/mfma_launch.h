@@ -9,7 +9,8 @@ namespace xnor {
 int mfma_tile_override();
 int mfma_lds_budget();
 
-// One convolution with operand format FMT: 0 int8 signs, 1 4-bit signs, 2 digits of real inputs, 3 int8 levels, 4 bfloat16 parts.
+// One convolution with operand format FMT: 0 int8 signs, 1 4-bit signs, 2 digits of real inputs, 3 int8 levels, 4 bfloat16 parts, 5 levels
+// of at most two bits as 4-bit floats.
 template <int FMT>
 xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, const float *A, const float *alpha, float *out,
                        int32_t *dot_out, const ConvGeom &g, hipStream_t stream, const FuseArgs *fz);

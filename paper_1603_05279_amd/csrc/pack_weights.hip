@@ -22,6 +22,7 @@ namespace xnor {
 // MODE 3 (k-bit quantised weights as int8 levels): the int8 image alone is written, its bytes the odd-integer
 // numerators 2u - L of q_aux(w) (L = 2^aux - 1) instead of +-1; wbits may be NULL; alpha[k] = `alpha_fill`
 // (the caller's 1 / (La * Lw)).
+// MODE 4: the same levels, at most two bits, as 4-bit records (Enc<5>) in place of the int8 image.
 // In mode 1 alpha is written as 1 (the scaling of that convolution is applied elsewhere).
 __device__ __forceinline__ int qk_level_index(float x, int L)
 {
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
         const int t0 = (int)tchunk * run, wd0 = (int)wg << pl.words_log2;
         const int f0 = (int)fg * PACK_ROWS, ch0 = wd0 * 32;
         const int nch = 32 << pl.words_log2, gt = run << pl.words_log2;          // channels; (word, tap) pairs
-        // ---- weights -> one byte each (modes 0, 1: 1 = positive; mode 3: the level's numerator; 0 outside) ----
+        // ---- weights -> one byte each (modes 0, 1: 1 = positive; modes 3, 4: the level's numerator; 0 outside) ----
         // A row is a filter with its channels (mode 1: a channel with its filters), `sub` runs of `run` taps in memory
         // order; its bytes lie in LDS the same way, tap run by tap run.
         const int rows = MODE == 1 ? nch : PACK_ROWS, sub = MODE == 1 ? PACK_ROWS : nch;
@@ -136,7 +137,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
                 for (int u = 0; u < 8; ++u)
                     if (dst[u] >= 0)
                         bytes[dst[u]] = !ok[u] ? 0
-                                        : MODE == 3 ? (uint8_t)(int8_t)(2 * qk_level_index(v[u], levels) - levels)
+                                        : MODE >= 3 ? (uint8_t)(int8_t)(2 * qk_level_index(v[u], levels) - levels)
                                                     : (uint8_t)(v[u] >= 0.0f);
             }
         };
@@ -147,9 +148,9 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
             return MODE == 1 ? bytes[ch * pitch + f * run + (run - 1 - tl)] : bytes[f * pitch + ch * run + tl];
         };
         if (MODE != 0 && wg == 0 && tchunk == 0 && tid < PACK_ROWS && f0 + tid < k_out)
-            alpha[f0 + tid] = MODE == 3 ? alpha_fill : 1.0f;
+            alpha[f0 + tid] = MODE >= 3 ? alpha_fill : 1.0f;
         __syncthreads();
-        if constexpr (MODE != 3) {
+        if constexpr (MODE < 3) {
             // lanes are the 32 channels of a word of filters f and f + 1
             for (int q0 = wave; q0 < gt * (PACK_ROWS / 2); q0 += 4 * 4) {
                 uint32_t byte[4];
@@ -182,6 +183,26 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
         if (!wmfma) continue;
         // ---- images: every (word, tap) pair is a contiguous run of each --------------------------------------
         const int fb = f0 >> 5, row0 = f0 & 31;
+        if constexpr (MODE == 4) {
+            const int blocks = taps * cw, recs = (blocks + 1) / 2;
+            for (int i = tid; i < gt * PACK_ROWS; i += 256) {
+                const int pair = i / PACK_ROWS, f = i % PACK_ROWS;
+                const int g = (int)pl.div_tap.div_small((uint32_t)pair), tl = pair - g * run;
+                if (t0 + tl >= taps || wd0 + g >= cw) continue;
+                uint32_t v[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int ch = 0; ch < 32; ++ch)
+                    v[ch >> 3] |= Enc<5>::code(at(f, g * 32 + ch, tl)) << (8 * (ch & 3) + (ch & 4));
+                const int b = (t0 + tl) * cw + wd0 + g;
+                int8_t *rec = wmfma + ((size_t)fb * recs + (b >> 1)) * 1024;
+                *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32 * (b & 1)) * 16) = make_uint4(v[0], v[1], v[2], v[3]);
+                if (b == blocks - 1 && !(b & 1))    // an odd number of blocks: the last record's other half is zero
+                    *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32) * 16) = make_uint4(0, 0, 0, 0);
+            }
+            if (blk == 0 && tid < 64)               // the trailing all-zero record
+                *reinterpret_cast<uint4 *>(wmfma + wimg_f4_bytes(k_out, c, taps) - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
+            continue;
+        }
         for (int i = tid; i < gt * PACK_ROWS * 2; i += 256) {
             const int pair = i / (PACK_ROWS * 2), f = i % PACK_ROWS, half = (i / PACK_ROWS) & 1;
             const int g = (int)pl.div_tap.div_small((uint32_t)pair), tl = pair - g * run;
@@ -266,6 +287,7 @@ xnor_status launch_pack_weights(const float *w, uint32_t *wbits, float *alpha, v
 #define XNOR_PACK(M) pack_weights_kernel<M><<<grid, block, 0, stream>>>(w, wbits, alpha, (int8_t *)wmfma, k_out, c, taps, cw, (1 << aux) - 1, alpha_fill, pl)
     if (mode == 1) XNOR_PACK(1);
     else if (mode == 3) XNOR_PACK(3);
+    else if (mode == 4) XNOR_PACK(4);
     else XNOR_PACK(0);
 #undef XNOR_PACK
     return hip_status(hipGetLastError());

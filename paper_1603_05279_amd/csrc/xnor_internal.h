@@ -76,7 +76,15 @@ xnor_status launch_pack_weights(const float *w, uint32_t *wbits, float *alpha, v
                                 int k_out, int c, int taps, hipStream_t stream, int mode = 0, int aux = 1,
                                 float alpha_fill = 1.0f);
 // (mode 0: sign(W) and alpha; 1: transposed, rotated filters of the backward convolution; 3: int8 level
-// numerators of the aux-bit quantised weights, int8 image only, alpha = alpha_fill)
+// numerators of the aux-bit quantised weights, int8 image only, alpha = alpha_fill; 4: the same as a 4-bit image)
+// k-bit layers that run on 4-bit operands: at most two bits each, float sums below 2^24, and an LDS image that fits wherever
+// the int8 one does (that one may take a single channel word at a time, 48 bytes per pixel; this one an even number of
+// words, 48 bytes for two, or all of them).  Fixed by what packer and convolution both know.
+inline bool kbit_narrow(int ka, int kw_bits, int c, int taps)
+{
+    const int cw = (c + 31) / 32;
+    return ka <= 2 && kw_bits <= 2 && 9ll * c * taps < (1ll << 24) && (cw % 2 == 0 || cw <= 3);
+}
 // k-bit quantisation (kbit.hip): int8 level numerators of q_k(x), [n][hw][Cw][32] (channels innermost)
 xnor_status launch_kbit_pack_input(const float *x, int8_t *xq, int k, int n, int c, int hw, hipStream_t stream);
 // Binary gradient (bingrad.hip): sign words of gd = g * alpha_k * K over the filters + per-image max |gd|;
