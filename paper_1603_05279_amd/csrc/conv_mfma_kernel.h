@@ -284,7 +284,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         if (wbase > 0 || !DIRECT || E::LUT_BYTES > 0) __syncthreads();   // tables visible / previous chunk fully consumed
         const bool stageA = !RAW && wbase == 0 && !K;
         if constexpr (DIRECT) {
-            const int px_a = g.h * g.w;
+            const int px_a = g.real_h * g.real_w;
             const uint32_t left = (uint32_t)(g.n - (int)img_a) * (uint32_t)px_a;       // (validated: n * h * w fits 31 bits)
             // (the images a tile can touch stay below 2 GiB; the resource may end early, never late)
             const __amdgpu_buffer_rsrc_t xrsrc = __builtin_amdgcn_make_buffer_rsrc(
@@ -294,8 +294,9 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                 const_cast<float *>(A) + (size_t)img_a * px_a, 0, stageA ? (int)(min(left, 0x1fffffffu) * 4u) : 0, 0x00020000);
             const int items = nrows * g.wp * pl.quads;
             const int y0 = (int)oy_a * g.sh;
-            auto stage = [&](auto vecc) {
+            auto stage = [&](auto vecc, auto dilc) {
                 constexpr int V = decltype(vecc)::value;
+                constexpr bool DILATED = decltype(dilc)::value;
                 constexpr int FB = 4;           // items in flight per thread: a tile rarely has more
                 for (int base = 0; base < items; base += NT * FB) {
                     uint32_t bits[FB][V];
@@ -310,9 +311,16 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                         const uint32_t rr = pl.sd_wp.div(px);
                         const uint32_t xc = px - mul24(rr, (uint32_t)g.wp);
                         const uint32_t yy = (uint32_t)y0 + rr, img = pl.sd_hp.div(yy);
-                        const uint32_t y = yy - mul24(img, (uint32_t)g.hp) - (uint32_t)g.ph, x = xc - (uint32_t)g.pw;
+                        uint32_t y = yy - mul24(img, (uint32_t)g.hp) - (uint32_t)g.ph, x = xc - (uint32_t)g.pw;
                         ok[u] = (int)it < items && y < (uint32_t)g.h && x < (uint32_t)g.w;
-                        const uint32_t pix = mul24(mul24(img, (uint32_t)g.h) + y, (uint32_t)g.w) + x;
+                        if constexpr (DILATED) {       // zeros between the real pixels and beyond the last ones
+                            const uint32_t yr = pl.sd_dil_h.div(y), xr = pl.sd_dil_w.div(x);
+                            ok[u] = ok[u] && mul24(yr, (uint32_t)g.dil_h) == y && mul24(xr, (uint32_t)g.dil_w) == x &&
+                                    yr < (uint32_t)g.real_h && xr < (uint32_t)g.real_w;
+                            y = yr;
+                            x = xr;
+                        }
+                        const uint32_t pix = mul24(mul24(img, (uint32_t)g.real_h) + y, (uint32_t)g.real_w) + x;
                         const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + q * (V * 4u) : 0x80000000u;
                         if constexpr (V == 4) {
                             const v4u r = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
@@ -350,10 +358,15 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                     }
                 }
             };
-            if (pl.vec == 4) stage(std::integral_constant<int, 4>{});
-            else if (pl.vec == 3) stage(std::integral_constant<int, 3>{});
-            else if (pl.vec == 2) stage(std::integral_constant<int, 2>{});
-            else stage(std::integral_constant<int, 1>{});
+            auto by_width = [&](auto dilated) {
+                if (pl.vec == 4) stage(std::integral_constant<int, 4>{}, dilated);
+                else if (pl.vec == 3) stage(std::integral_constant<int, 3>{}, dilated);
+                else if (pl.vec == 2) stage(std::integral_constant<int, 2>{}, dilated);
+                else stage(std::integral_constant<int, 1>{}, dilated);
+            };
+            // (dilated inputs: backward convolutions, which have the plain epilogue)
+            if (!FUSE && !POOL && pl.dilated) by_width(std::bool_constant<!FUSE && !POOL>{});
+            else by_width(std::false_type{});
         } else {
         const int items = nrows * g.wp * ccw;
         if constexpr (FMT == 2) {
@@ -413,7 +426,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                 const int xv = (int)(px - rr * g.wp) - g.pw;                 // column of the (virtual) input
                 const int xcol = (int)g.div_dil_w.div_small((uint32_t)max(xv, 0));  // column of the real tensor
                 const int rowbase = rowinfo[rr];
-                ok[u] = rowbase >= 0 && xv >= 0 && xv < g.w && xcol * g.dil_w == xv && xcol < g.real_w;
+                ok[u] = rowbase >= 0 && xv >= 0 && xv < g.w && xcol * g.dil_w == xv && xcol < g.real_w && wbase + wl < g.cw;
                 dst[u] = it < items ? (int)(rr * pl.row_pitch + (px - rr * g.wp) * pl.ps + wl * E::BPB) : -1;
                 nch[u] = g.c - (wbase + wl) * 32;
                 bits[u] = 0;
@@ -863,8 +876,8 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
     const int bps = fmt_bps(fmt), bpb = fmt == 1 || fmt == 5 ? Enc<1>::BPB : fmt == 2 ? Enc<2>::BPB : 32;
     const int rows = rows_override ? rows_override : worst_region_rows(g, PT, PT);
     for (int ccw = g.cw; ccw >= 1; --ccw) {
-        // (digit operands: the last chunk may lack one word)
-        if (fmt == 2 ? (g.cw + ccw - 1) / ccw * ccw > g.cw + 1 : g.cw % ccw != 0) continue;
+        // (packed words and digits: the last chunk may lack one word, staged as zeros)
+        if (fmt == 1 || fmt == 2 ? (g.cw + ccw - 1) / ccw * ccw > g.cw + 1 : g.cw % ccw != 0) continue;
         // packed words and digits take two channel words per step: chunks must keep the words of a step together
         if (ccw != g.cw && (ccw % bps)) continue;
         const long long row_bytes = (long long)ccw * bpb;

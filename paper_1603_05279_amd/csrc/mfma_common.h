@@ -25,7 +25,7 @@ struct PoolPlan {
 };
 
 struct MfmaPlan {
-    int cc_words;     // channel words per chunk (divides cw; digit operands: the last chunk may lack one word, staged as zeros)
+    int cc_words;     // channel words per chunk (divides cw; packed words and digits: the last chunk may lack one word, staged as zeros)
     int ps;           // bytes per pixel in LDS (an odd multiple of 16: conflict-free 16-byte reads)
     int max_rows;     // padded input rows a pixel tile can touch
     int region_bytes; // max_rows * row_pitch
@@ -38,6 +38,8 @@ struct MfmaPlan {
     int wmajor;       // 1: 1-D grid that keeps the pixel tiles of a filter tile on one XCD
     int vec;          // > 0: channel words per load of the direct staging loop (1 to 4, divides cc_words); 0: the general loop
     int quads;        // cc_words / vec
+    int dilated;      // direct staging: the input is dilated
+    SmallDiv sd_dil_h, sd_dil_w;
     SmallDiv sd_quads, sd_wp, sd_hp, sd_wo, sd_ho;   // direct staging: item, padded and output coordinates of a tile
     int stream_out;   // 1: float results are stored with the non-temporal hint (they exceed a quarter of the last-level cache)
     FastDiv div_wp, div_hp, div_ccw, div_cw;
@@ -47,12 +49,12 @@ struct MfmaPlan {
 // Direct staging: an item of the staging loop is `vec` channel words of one pixel, read by one load and widened together.
 // Coordinates are divided down from the tile's first image with 24-bit multiplies, memory is read through a bounds-checked
 // buffer that starts at that image (positions outside an image get an offset beyond it and come back as zero): no 64-bit
-// arithmetic, no branch per item.  Needs an input that is not dilated, one chunk that holds every channel word, and a tile whose images' pixels, packed words and
+// arithmetic, no branch per item.  Needs one chunk that holds every channel word, and a tile whose images' pixels, packed words and
 // padded pixels fit the ranges of those divisions and offsets; anything else takes the general loop.
 inline void set_direct_staging(MfmaPlan *pl, const ConvGeom &g, int fmt, int run)
 {
     pl->vec = pl->quads = 0;
-    if (fmt > 1 || pl->cc_words != g.cw || g.dil_h != 1 || g.dil_w != 1) return;
+    if (fmt > 1 || pl->cc_words != g.cw) return;
     const int vec = pl->cc_words % 4 == 0 ? 4 : pl->cc_words == 3 ? 3 : pl->cc_words % 2 == 0 ? 2 : 1;
     const int quads = pl->cc_words / vec;
     const long long howo = (long long)g.ho * g.wo, hw = (long long)g.h * g.w;
@@ -61,7 +63,9 @@ inline void set_direct_staging(MfmaPlan *pl, const ConvGeom &g, int fmt, int run
     if (images * hw >= (1 << 24) || images * hw * g.cw * 4 >= 0x7fffffffLL || g.cw >= (1 << 22) ||
         px * quads >= (1 << 24) || pl->row_pitch >= (1 << 23) || howo + run >= (1 << 24))
         return;
-    if (!SmallDiv::make((uint32_t)quads, (uint64_t)(px * quads), &pl->sd_quads) ||
+    pl->dilated = g.dil_h != 1 || g.dil_w != 1;
+    if (!SmallDiv::make((uint32_t)g.dil_h, (uint64_t)g.h, &pl->sd_dil_h) || !SmallDiv::make((uint32_t)g.dil_w, (uint64_t)g.w, &pl->sd_dil_w) ||
+        !SmallDiv::make((uint32_t)quads, (uint64_t)(px * quads), &pl->sd_quads) ||
         !SmallDiv::make((uint32_t)g.wp, (uint64_t)px, &pl->sd_wp) ||
         !SmallDiv::make((uint32_t)g.hp, (uint64_t)g.hp + pl->max_rows, &pl->sd_hp) ||
         !SmallDiv::make((uint32_t)g.wo, (uint64_t)(howo + run), &pl->sd_wo) ||

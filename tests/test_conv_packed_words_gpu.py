@@ -1,6 +1,6 @@
 """The 4-bit matrix-core convolution on packed weight words, at the sizes where its staging and K loop can go wrong: every
 load width of the activations (1 to 4 words), odd block counts (half a K-step), channel tails, tiles that span images, rows
-and strides, given K and A, and inputs that take the general staging (dilated, several channel chunks)."""
+and strides, given K and A, dilated inputs, and channel chunks, the last of which may lack a word."""
 import numpy as np
 import pytest
 import torch
@@ -14,7 +14,7 @@ CASES = [
     (1, 1, 1, 1, 1, 1, 1, 1, 0), (2, 33, 3, 5, 40, 1, 1, 1, 0), (70, 95, 1, 1, 33, 1, 1, 1, 0),
     (3, 96, 9, 11, 100, 3, 3, 1, 1), (11, 128, 7, 7, 130, 3, 3, 1, 1), (2, 160, 13, 6, 257, 3, 3, 2, 1),
     (5, 190, 6, 14, 64, 5, 3, (1, 2), (2, 1)), (2, 224, 10, 10, 300, 3, 3, 1, 2), (1, 256, 31, 29, 129, 3, 3, 1, 1),
-    (2, 384, 13, 13, 200, 3, 3, 1, 1), (1, 512, 40, 40, 32, 5, 5, 1, 2), (1, 32, 200, 3, 70, 7, 3, (3, 1), (3, 1)),
+    (2, 384, 13, 13, 200, 3, 3, 1, 1), (1, 512, 40, 40, 32, 5, 5, 1, 2), (1, 288, 41, 41, 40, 5, 5, 2, 2), (1, 32, 200, 3, 70, 7, 3, (3, 1), (3, 1)),
 ]
 
 
@@ -77,23 +77,27 @@ def test_fused_tilings_that_hold_every_filter(k, tile):
     assert torch.allclose(res[1][1].double(), z, rtol=(k + 8) * 2.0 ** -24, atol=1e-6)
 
 
-def test_dilated_input_keeps_the_general_staging():
-    # backward convolution of a strided layer: zeros between the gradient's pixels; against the int8 matrix cores
-    n, c, h, k = 3, 64, 15, 96
-    gen = torch.Generator(device="cuda").manual_seed(3)
-    desc = xnor.make_desc(n, c, h, h, k, 3, 3, 2, 1)
+@pytest.mark.parametrize("c,k,h,stride", [(64, 96, 15, (2, 2)), (40, 33, 14, (3, 2)), (32, 160, 16, (2, 1)), (70, 512, 45, (2, 2))])
+def test_dilated_input(c, k, h, stride):
+    # backward convolution of a strided layer: zeros between the gradient's pixels, in one chunk of words and in several;
+    # against a library convolution's transpose, whose integers float64 holds exactly
+    n = 3
+    gen = torch.Generator(device="cuda").manual_seed(c)
+    desc = xnor.make_desc(n, c, h, h, k, 3, 3, stride, 1)
     ho, wo = xnor.output_hw(desc)
     w = torch.randn((k, c, 3, 3), generator=gen, device="cuda")
-    gb = torch.randint(-(1 << 31), 1 << 31, (n, ho, wo, 3), generator=gen, device="cuda", dtype=torch.int64).int()
-    gmax = torch.rand((n,), generator=gen, device="cuda")
-    wt, ones = torch.empty((c, 9, 3), dtype=torch.int32, device="cuda"), torch.empty((c,), device="cuda")
-    img = torch.empty((xnor.wmfma_bytes(c, k, 3, 3),), dtype=torch.uint8, device="cuda")
+    g = torch.randn((n, k, ho, wo), generator=gen, device="cuda")
+    gb = torch.empty((n, ho, wo, xnor.words_per_pixel(k)), dtype=torch.int32, device="cuda")
+    gmax = torch.empty((n,), device="cuda")
+    xnor.xnor_bingrad_binarize(g, None, None, gb, gmax, desc)
+    wt = torch.empty((c, 9, xnor.words_per_pixel(k)), dtype=torch.int32, device="cuda")
+    ones, img = torch.empty((c,), device="cuda"), torch.empty((xnor.wmfma_bytes(c, k, 3, 3),), dtype=torch.uint8, device="cuda")
     xnor.xnor_bingrad_pack_weights(w, wt, ones, img, k, c, 3, 3)
-    outs = []
+    sign = lambda t: torch.where(t >= 0, 1.0, -1.0).double().cpu()
+    ref = torch.nn.grad.conv2d_input((n, c, h, h), sign(w), sign(g), stride, 1)
     for algo in ("mfma_f4", "mfma_i8"):
         gin, dot = torch.empty((n, c, h, h), device="cuda"), torch.empty((n, c, h, h), dtype=torch.int32, device="cuda")
         xnor.xnor_bingrad_conv2d(gb, wt, img, gmax, ones, torch.empty((n, h, h), device="cuda"), gin, dot, desc,
                                  xnor.ALGOS[algo])
-        outs.append((gin, dot))
-    torch.cuda.synchronize()
-    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+        assert torch.equal(dot.cpu().double(), ref)
+        assert torch.equal(gin, dot.float() * gmax.view(-1, 1, 1, 1))
