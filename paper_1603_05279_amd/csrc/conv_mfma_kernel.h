@@ -959,7 +959,10 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     pl.ptiles = (g.m_total + PT - 1) / PT;
     pl.ftiles = (g.k_out + FT - 1) / FT;
     // (measured on whole benchmark steps: 64 MiB 382 us, 40 MiB 403 us, 120 MiB 408 us, never 428 us)
-    pl.stream_out = (long long)g.m_total * g.k_out * 4 > (64ll << 20);
+    // (only where the rows of 32 pixels that a wave stores cover whole 64-byte pieces: a non-temporal store of part of one is
+    // not merged with its neighbour's.  200 images of 27 x 27, 64 -> 256 channels, 142 MiB: 105 us with the hint, 32 without;
+    // 256 images of 14 x 14, 128 -> 512: 77 and 32; 100 of 55 x 55, 128 -> 96: 72 and 40; 28 x 28 and 56 x 56 keep it)
+    pl.stream_out = (long long)g.m_total * g.k_out * 4 > (64ll << 20) && howo % 16 == 0;
     // weight-heavy: the weight image outweighs the packed activations and there are filter tiles to spread
     pl.wmajor = pl.ftiles >= 8 && (long long)g.k_out * g.taps * g.c > 4LL * g.n * g.h * g.w * g.c;
     dim3 grid((unsigned)pl.ptiles, (unsigned)pl.ftiles), block(64 * WF * WP * KS);

@@ -101,3 +101,11 @@ def test_dilated_input(c, k, h, stride):
                                  xnor.ALGOS[algo])
         assert torch.equal(dot.cpu().double(), ref)
         assert torch.equal(gin, dot.float() * gmax.view(-1, 1, 1, 1))
+
+
+@pytest.mark.parametrize("h", [28, 30, 31])              # with the non-temporal hint: 28 x 28 only
+def test_results_larger_than_the_hint_threshold(h):
+    n = (64 << 20) // (256 * 4 * h * h) + 1              # just above 64 MiB of results
+    ref, got = (block((n, 64, h, h, 256, 1, 1, 1, 0), algo) for algo in ("popcount", "mfma_f4"))
+    assert torch.equal(got.dot, ref.dot)
+    assert torch.equal(got.out, ref.out)
