@@ -88,7 +88,7 @@ template <class T> __device__ __forceinline__ global_t<T> *in_global(T *p) { ret
 // KS > 1: KS groups of WF x WP waves share the K loop of the same tile (group k takes the k-th run of steps) and add
 // their accumulators through LDS at the end: more weight loads in flight and more waves for the staging where a
 // problem offers few output tiles and a long K (fully connected layers).  Consecutive-record streams only.
-template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, bool LINEAR, bool POOL = false, int KS = 1>
+template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, bool LINEAR, bool POOL = false, int KS = 1, bool DIRECT_CHUNKS = false>
 __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 4 ? 6 : 8) && WF * WP * KS <= 8 ? 2 : 1)) void conv_mfma_kernel(
     ConvArgs args)
 {
@@ -103,7 +103,9 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
     // operands staged as they are (no sign bits to widen, no K): bfloat16 parts and int8 levels
     constexpr bool RAW = FMT >= 2;
     // packed bits staged through set_direct_staging's plan
-    constexpr bool DIRECT = LINEAR && !RAW;
+    constexpr bool DIRECT = (LINEAR || DIRECT_CHUNKS) && !RAW;
+    constexpr bool ONE = LINEAR && !RAW;        // ... and one chunk holds every channel word
+    static_assert(!DIRECT_CHUNKS || (FMT == 1 && !LINEAR), "chunks of packed words");
     typedef typename E::acc_t acc_t;
     static_assert(KS == 1 || (LINEAR && !FUSE && !POOL), "waves along K: plain epilogue, consecutive records");
     constexpr int NT = 64 * WF * WP * KS;
@@ -274,14 +276,13 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
     const int steps_per_tap = pl.tap_jump ? ccw / E::BPS : 0x7fffffff;
-    // (direct staging: one chunk holds every channel word)
-    for (int wbase = 0; DIRECT ? wbase < 1 : wbase < args.g.cw; wbase += DIRECT ? 1 : ccw) {
+    for (int wbase = 0; ONE ? wbase < 1 : wbase < args.g.cw; wbase += ONE ? 1 : ccw) {
         // (read per chunk: otherwise everything a chunk derives from them is hoisted in front of the first one and held)
         const ConvArgs now = reload_args();
         const ConvGeom &g = now.g;
         const MfmaPlan &pl = now.pl;
         const v4i *wimg = now.wimg;
-        if (wbase > 0 || !DIRECT || E::LUT_BYTES > 0) __syncthreads();   // tables visible / previous chunk fully consumed
+        if (wbase > 0 || !ONE || E::LUT_BYTES > 0) __syncthreads();   // tables visible / previous chunk fully consumed
         const bool stageA = !RAW && wbase == 0 && !K;
         if constexpr (DIRECT) {
             const int px_a = g.real_h * g.real_w;
@@ -321,7 +322,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                             x = xr;
                         }
                         const uint32_t pix = mul24(mul24(img, (uint32_t)g.real_h) + y, (uint32_t)g.real_w) + x;
-                        const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + q * (V * 4u) : 0x80000000u;
+                        const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + q * (V * 4u) + (ONE ? 0u : (uint32_t)wbase * 4u) : 0x80000000u;
                         if constexpr (V == 4) {
                             const v4u r = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
                             bits[u][0] = r[0]; bits[u][1] = r[1]; bits[u][2] = r[2]; bits[u][3] = r[3];
@@ -334,7 +335,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                         } else {
                             bits[u][0] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)off, 0, 0);
                         }
-                        wl[u] = (int)q * V;
+                        wl[u] = (ONE ? 0 : wbase) + (int)q * V;
                         const bool first = stageA && q == 0 && (int)it < items;
                         adst[u] = first ? (int)px : -1;
                         if (stageA)
@@ -351,7 +352,8 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
 #pragma unroll
                             for (int v = 0; v < V; ++v) {
                                 const int nch = g.c % 32 == 0 ? 32 : g.c - (wl[u] + v) * 32;
-                                E::widen_word_lut(lds + dst[u] + v * E::BPB, lut, bits[u][v], ok[u], nch);
+                                E::widen_word_lut(lds + dst[u] + v * E::BPB, lut, bits[u][v],
+                                                  ok[u] && (ONE || wl[u] + v < g.cw), nch);
                             }
                             if (stageA && adst[u] >= 0) a_lds[adst[u]] = av[u];
                         }
@@ -871,7 +873,7 @@ static int plan_lut_offset(const MfmaPlan &pl, int fmt, int wp, int PT, int fuse
 }
 
 static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fuse_rows, int par_bytes, MfmaPlan *pl,
-                      int rows_override = 0, bool lone = false)
+                      int rows_override = 0, bool lone = false, int most_chunks = 0x7fffffff)
 {
     const int bps = fmt_bps(fmt), bpb = fmt == 1 || fmt == 5 ? Enc<1>::BPB : fmt == 2 ? Enc<2>::BPB : 32;
     const int rows = rows_override ? rows_override : worst_region_rows(g, PT, PT);
@@ -907,6 +909,12 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         const long long budget = ccw == g.cw ? (lds_budget > whole ? lds_budget : whole) : lds_budget;
         if (total > budget && !last) continue;
         if (total > LDS_LIMIT) return false;
+        MfmaPlan one;
+        if ((g.cw + ccw - 1) / ccw > most_chunks &&
+            make_plan(g, PT, fmt, lds_budget, fuse_rows, par_bytes, &one, rows_override, true) && one.cc_words == g.cw) {
+            *pl = one;
+            return true;
+        }
         pl->div_wp = FastDiv::make((uint32_t)g.wp);
         pl->div_hp = FastDiv::make((uint32_t)g.hp);
         pl->div_ccw = FastDiv::make((uint32_t)ccw);
@@ -941,21 +949,27 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     constexpr int FROWS = FUSE ? WF + FT / 32 : 0, PARB = (FUSE ? 3 : 1) * FT * 4;
     const long long wg_count = (long long)((g.m_total + PT - 1) / PT) * ((g.k_out + FT - 1) / FT);
     const int budget = std::max(mfma_lds_budget(), FMT == 2 && FW * PW > 6 ? 150 * 1024 : 0);      // (one workgroup per CU)
-    if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256))
+    // 4-bit operands, tiles of four result blocks and more per wave: three chunks and more (two words each, as a count that has no
+    // larger even divisor gives) cost more than holding every word with one workgroup per CU: 85 images of 320x31x31, 3x3
+    // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, two blocks per wave: 34.5 and 39.5)
+    if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW >= 4 ? 2 : 0x7fffffff))
         return XNOR_ERR_UNSUPPORTED;
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
-    // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not
+    // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
+    // third, chunks staged directly
     // (a chunk of a 1x1 filter is a run of consecutive records too)
     set_direct_staging(&pl, g, FMT, PT);
-    const bool linear = FMT > 1 ? pl.tap_jump == 0 || g.taps == 1 : pl.vec > 0;
+    const bool linear = FMT > 1 ? pl.tap_jump == 0 || g.taps == 1 : pl.vec > 0 && pl.cc_words == g.cw;
     // waves along K: consecutive weight records only, and the partial sums need the activation region's room
     if (KS > 1 && (!linear || (size_t)pl.region_bytes < (size_t)(KS - 1) * WF * WP * FW * PW * 16 * 64 * 4))
         return XNOR_ERR_UNSUPPORTED;
-    auto kern = linear ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, true, false, KS>
-                       : conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, KS != 1, false, KS>;
-    static std::atomic<bool> attr_done[2];       // per instantiation (zero-initialised: false)
-    if (xnor_status s = allow_full_lds(kern, attr_done[linear])) return s;
+    const bool direct_chunks = FMT == 1 && !linear && pl.vec > 0;
+    auto kern = linear          ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, true, false, KS>
+                : direct_chunks ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, KS != 1, false, KS, FMT == 1 && KS == 1>
+                                : conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, KS != 1, false, KS>;
+    static std::atomic<bool> attr_done[3];       // per instantiation (zero-initialised: false)
+    if (xnor_status s = allow_full_lds(kern, attr_done[linear ? 1 : direct_chunks ? 2 : 0])) return s;
     pl.ptiles = (g.m_total + PT - 1) / PT;
     pl.ftiles = (g.k_out + FT - 1) / FT;
     // (measured on whole benchmark steps: 64 MiB 382 us, 40 MiB 403 us, 120 MiB 408 us, never 428 us)

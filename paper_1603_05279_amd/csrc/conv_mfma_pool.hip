@@ -19,11 +19,12 @@ static xnor_status launch_cfg_pool(const uint32_t *xbits, const void *wimg, cons
     lds = std::max(lds, (size_t)WAVES * 16 * (PT + 1) * sizeof(float));       // the epilogue's per-wave y tiles
     if (lds > (size_t)LDS_LIMIT) return XNOR_ERR_UNSUPPORTED;
     set_direct_staging(&pl, g, 1, PT);
-    const bool linear = pl.vec > 0;
-    auto kern = linear ? conv_mfma_kernel<1, FW, PW, WF, WP, false, true, true>
-                       : conv_mfma_kernel<1, FW, PW, WF, WP, false, false, true>;
-    static std::atomic<bool> attr_done[2];
-    if (xnor_status s = allow_full_lds(kern, attr_done[linear])) return s;
+    const int build = pl.vec == 0 ? 0 : pl.cc_words == g.cw ? 1 : 2;
+    auto kern = build == 1   ? conv_mfma_kernel<1, FW, PW, WF, WP, false, true, true>
+                : build == 2 ? conv_mfma_kernel<1, FW, PW, WF, WP, false, false, true, 1, true>
+                             : conv_mfma_kernel<1, FW, PW, WF, WP, false, false, true>;
+    static std::atomic<bool> attr_done[3];
+    if (xnor_status s = allow_full_lds(kern, attr_done[build])) return s;
     const long long ptiles = (long long)g.n * pool.groups;
     if (ptiles > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;
     pl.ptiles = (int)ptiles;
