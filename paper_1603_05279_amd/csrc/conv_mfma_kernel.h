@@ -1046,6 +1046,9 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
             if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) tile = 6;
         } else if (FMT == 1 && fz && g.k_out <= 512) tile = g.k_out <= 384 ? 9 : 8;
         else tile = g.k_out % 256 == 0 ? 5 : fz ? 13 : 1;      // (fused epilogue: 128 x 64 ahead of 128 x 128)
+        // 4-bit operands: less than a workgroup per CU of 128 x 128, 128 x 64 is ahead of it (3 images of 352x48x48 -> 310 14.6 -> 13.4 us,
+        // 8 of 416x28x28 -> 390 15.8 -> 14.2, 36 of 64x14x14 -> 384 8.1 -> 7.6, 9 of 192x28x28 -> 300 1x1 7.4 -> 6.8)
+        if (FMT == 1 && tile == 1 && !fz && g.k_out > 256 && wgs(128, 128) < cus) tile = 13;
         const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
                              : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
                              : tile == 9 ? wgs(384, 96) : tile == 12 ? wgs(512, 64) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
