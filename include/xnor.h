@@ -316,17 +316,20 @@ XNOR_API int xnor_bingrad_conv2d(const uint32_t *gbits, const uint32_t *wtbits, 
  * k = 1, which is decided by the comparison x >= 0 so that q_1 is the sign rule for every float, also for
  * -2^-25 < x < 0 where x + 1 rounds to 1).
  * q_k = (2u - L)/L with L = 2^k - 1, so the convolution of ka-bit inputs with kw-bit weights is an exact integer
- * sum of numerator products divided by La * Lw; it runs on the int8 matrix cores:
+ * sum of numerator products divided by La * Lw; it runs on the int8 matrix cores, or, inputs and weights of at most two
+ * bits each, on their 4-bit floats (the same integers, exact as float sums below 2^24):
  *   out[n][k_out][h_out][w_out] = sum q_ka(x) * q_kw(w) over the in-bounds window, no K, no alpha.
  * ka, kw in 1..7 (the numerators of 7-bit levels, -127..127, are the widest that fit int8).  Device pointers,
  * 16-byte aligned, caller-owned; enqueued on hip_stream.
  *   xnor_kbit_pack_input    x float32 [n][c][h][w] -> xq, xnor_kbit_input_bytes(n, c, h, w) bytes: the numerators
  *                           2u - La as int8, [n][h][w][ceil(c/32)][32], 0 past the last channel
  *   xnor_kbit_pack_weights  w float32 [k_out][c][kh][kw] -> wq, xnor_kbit_wimg_bytes(k_out, c, kh, kw) bytes
- *                           (opaque), scale float32 [k_out] (written with 1 / (La * Lw)); once per layer
+ *                           (opaque), scale float32 [k_out] (written with 1 / (La * Lw)); once per layer.  ka enters
+ *                           scale alone: wq serves inputs of every width
  *   xnor_kbit_conv2d        num_out int32 [n][k_out][h_out][w_out] (may be NULL) = the integer numerator
  *                           sum (2u_x - La)(2u_w - Lw), out = float(num) * scale (two float roundings: within
- *                           2e-7 relative of num / (La * Lw)).  XNOR_ERR_UNSUPPORTED when La * Lw * c * kh * kw
+ *                           2e-7 relative of num / (La * Lw)).  ka and kw_bits are the widths that xq and wq were
+ *                           packed with.  XNOR_ERR_UNSUPPORTED when La * Lw * c * kh * kw
  *                           does not fit 31 bits.
  */
 XNOR_API size_t xnor_kbit_input_bytes(int n, int c, int h, int w);

@@ -478,7 +478,7 @@ size_t xnor_kbit_input_bytes(int n, int c, int h, int w)
 size_t xnor_kbit_wimg_bytes(int k_out, int c, int kh, int kw)
 {
     if (k_out <= 0 || c <= 0 || kh <= 0 || kw <= 0 || (long long)kh * kw > 4096) return 0;
-    return wimg_i8_bytes(k_out, c, kh * kw);
+    return wimg_i8_bytes(k_out, c, kh * kw) + wimg_f4_bytes(k_out, c, kh * kw);
 }
 
 int xnor_kbit_pack_input(const float *x, void *xq, int ka, int n, int c, int h, int w, void *hip_stream)
@@ -502,8 +502,9 @@ int xnor_kbit_pack_weights(const float *w, float *scale, void *wq, int ka, int k
         return XNOR_ERR_SHAPE;
     if (!aligned16(w) || !aligned16(scale) || !aligned16(wq)) return XNOR_ERR_ALIGN;
     const double s = (double)((1 << ka) - 1) * (double)((1 << kw_bits) - 1);
-    return launch_pack_weights(w, nullptr, scale, wq, k_out, c, kh * kw, (hipStream_t)hip_stream,
-                               kbit_narrow(ka, kw_bits, c, kh * kw) ? 4 : 3, kw_bits, (float)(1.0 / s));
+    // (ka enters the scale alone: the image serves inputs of any width)
+    return launch_pack_weights(w, nullptr, scale, wq, k_out, c, kh * kw, (hipStream_t)hip_stream, kw_bits <= 2 ? 4 : 3,
+                               kw_bits, (float)(1.0 / s));
 }
 
 int xnor_kbit_conv2d(const void *xq, const void *wq, const float *scale, float *out, int32_t *num_out,

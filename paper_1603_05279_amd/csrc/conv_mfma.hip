@@ -40,8 +40,8 @@ xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, 
     const uint8_t *img = static_cast<const uint8_t *>(wmfma);
     // fmt 3: int8 level numerators (xbits = 32-byte words of 32 channels, wmfma = an int8 record image); no K
     if (fmt == 3) return fz ? XNOR_ERR_UNSUPPORTED : launch_fmt<3>(xbits, img, nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
-    // fmt 5: the same for kbit_narrow() layers (wmfma = their 4-bit record image)
-    if (fmt == 5) return fz ? XNOR_ERR_UNSUPPORTED : launch_fmt<5>(xbits, img, nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
+    // fmt 5: the same for kbit_narrow() layers, on the 4-bit record image behind it
+    if (fmt == 5) return fz ? XNOR_ERR_UNSUPPORTED : launch_fmt<5>(xbits, img + wimg_i8_bytes(g.k_out, g.c, g.taps), nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
     // float accumulation of the 4-bit path is exact while every sum stays below 2^24
     if (fmt != 0 && (long long)g.c * g.taps >= (1ll << 24)) return XNOR_ERR_UNSUPPORTED;
     if (fmt == 0) return launch_fmt<0>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);

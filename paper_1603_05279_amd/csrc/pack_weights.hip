@@ -22,7 +22,7 @@ namespace xnor {
 // MODE 3 (k-bit quantised weights as int8 levels): the int8 image alone is written, its bytes the odd-integer
 // numerators 2u - L of q_aux(w) (L = 2^aux - 1) instead of +-1; wbits may be NULL; alpha[k] = `alpha_fill`
 // (the caller's 1 / (La * Lw)).
-// MODE 4: the same levels, at most two bits, as 4-bit records (Enc<5>) in place of the int8 image.
+// MODE 4 (at most two bits): the same, and behind the int8 image its levels as 4-bit records (Enc<5>).
 // In mode 1 alpha is written as 1 (the scaling of that convolution is applied elsewhere).
 __device__ __forceinline__ int qk_level_index(float x, int L)
 {
@@ -183,6 +183,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
         if (!wmfma) continue;
         // ---- images: every (word, tap) pair is a contiguous run of each --------------------------------------
         const int fb = f0 >> 5, row0 = f0 & 31;
+        int8_t *w4 = wmfma + wimg_i8_bytes(k_out, c, taps);
         if constexpr (MODE == 4) {
             const int blocks = taps * cw, recs = (blocks + 1) / 2;
             for (int i = tid; i < gt * PACK_ROWS; i += 256) {
@@ -194,14 +195,13 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
                 for (int ch = 0; ch < 32; ++ch)
                     v[ch >> 3] |= Enc<5>::code(at(f, g * 32 + ch, tl)) << (8 * (ch & 3) + (ch & 4));
                 const int b = (t0 + tl) * cw + wd0 + g;
-                int8_t *rec = wmfma + ((size_t)fb * recs + (b >> 1)) * 1024;
+                int8_t *rec = w4 + ((size_t)fb * recs + (b >> 1)) * 1024;
                 *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32 * (b & 1)) * 16) = make_uint4(v[0], v[1], v[2], v[3]);
                 if (b == blocks - 1 && !(b & 1))    // an odd number of blocks: the last record's other half is zero
                     *reinterpret_cast<uint4 *>(rec + (size_t)(row0 + f + 32) * 16) = make_uint4(0, 0, 0, 0);
             }
             if (blk == 0 && tid < 64)               // the trailing all-zero record
-                *reinterpret_cast<uint4 *>(wmfma + wimg_f4_bytes(k_out, c, taps) - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
-            continue;
+                *reinterpret_cast<uint4 *>(w4 + wimg_f4_bytes(k_out, c, taps) - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
         }
         for (int i = tid; i < gt * PACK_ROWS * 2; i += 256) {
             const int pair = i / (PACK_ROWS * 2), f = i % PACK_ROWS, half = (i / PACK_ROWS) & 1;
@@ -209,7 +209,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
             const int t = t0 + tl, wd = wd0 + g;
             if (t >= taps || wd >= cw) continue;
             uint32_t v[4];
-            if constexpr (MODE == 3) {
+            if constexpr (MODE >= 3) {
                 const int ch = g * 32 + half * 16;
 #pragma unroll
                 for (int j = 0; j < 4; ++j)
@@ -229,8 +229,7 @@ __global__ __launch_bounds__(256) void pack_weights_kernel(
             *reinterpret_cast<uint4 *>(wmfma + rec * 1024 + (size_t)(row0 + f + 32 * half) * 16) =
                 make_uint4(v[0], v[1], v[2], v[3]);
         }
-        int8_t *w4 = wmfma + wimg_i8_bytes(k_out, c, taps);
-        if (MODE == 3) {
+        if (MODE >= 3) {
             if (blk == 0 && tid < 64)           // the trailing all-zero record
                 *reinterpret_cast<uint4 *>(w4 - 1024 + (size_t)tid * 16) = make_uint4(0, 0, 0, 0);
             continue;

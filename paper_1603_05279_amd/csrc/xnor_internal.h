@@ -76,10 +76,11 @@ xnor_status launch_pack_weights(const float *w, uint32_t *wbits, float *alpha, v
                                 int k_out, int c, int taps, hipStream_t stream, int mode = 0, int aux = 1,
                                 float alpha_fill = 1.0f);
 // (mode 0: sign(W) and alpha; 1: transposed, rotated filters of the backward convolution; 3: int8 level
-// numerators of the aux-bit quantised weights, int8 image only, alpha = alpha_fill; 4: the same as a 4-bit image)
+// numerators of the aux-bit quantised weights, int8 image only, alpha = alpha_fill; 4: the same, aux <= 2, and behind it
+// the 4-bit image)
 // k-bit layers that run on 4-bit operands: at most two bits each, float sums below 2^24, and an LDS image that fits wherever
 // the int8 one does (that one may take a single channel word at a time, 48 bytes per pixel; this one an even number of
-// words, 48 bytes for two, or all of them).  Fixed by what packer and convolution both know.
+// words, 48 bytes for two, or all of them).  The packer writes both images for weights of at most two bits.
 inline bool kbit_narrow(int ka, int kw_bits, int c, int taps)
 {
     const int cw = (c + 31) / 32;

@@ -2,8 +2,11 @@
 channel chunks: the integer sum bit-exact against the oracle, also where the two forms border on each other."""
 import numpy as np
 import pytest
+import torch
 
 from oracle import xnor_oracle as xo
+from paper_1603_05279_amd import xnor
+from tests.helpers import to_dev
 from tests.test_kbit_gpu import run
 
 pytestmark = pytest.mark.gpu
@@ -31,3 +34,23 @@ def test_numerators_and_results(case, bits):
     r = xo.kbit_conv2d(x, W, ka, kb, stride, pad)
     assert np.array_equal(num.astype(np.int64), r["num"])
     np.testing.assert_allclose(out, r["out"], rtol=1e-6, atol=0)
+
+
+@pytest.mark.parametrize("kb,packed_ka", [(1, 1), (2, 2), (2, 5), (1, 7), (3, 2)])
+def test_one_weight_image_serves_inputs_of_every_width(kb, packed_ka):
+    # ka reaches the packer for `scale` alone: the same image under inputs of 1, 2 (4-bit operands) and 3, 7 bits (int8)
+    n, c, h, k = 2, 65, 7, 40
+    rng = np.random.default_rng(10 * kb + packed_ka)
+    x = rng.uniform(-1.1, 1.1, (n, c, h, h)).astype(np.float32)
+    W = rng.uniform(-1.1, 1.1, (k, c, 3, 3)).astype(np.float32)
+    desc = xnor.make_desc(n, c, h, h, k, 3, 3, 1, 1)
+    wq = torch.full((xnor.kbit_wimg_bytes(k, c, 3, 3),), 0x5A, dtype=torch.uint8, device="cuda")
+    scale, out = torch.empty((k,), device="cuda"), torch.empty((n, k, h, h), device="cuda")
+    num = torch.empty((n, k, h, h), dtype=torch.int32, device="cuda")
+    xnor.xnor_kbit_pack_weights(to_dev(W), scale, wq, packed_ka, kb, k, c, 3, 3)
+    for ka in (1, 2, 3, 7):
+        xq = torch.empty((xnor.kbit_input_bytes(n, c, h, h),), dtype=torch.uint8, device="cuda")
+        xnor.xnor_kbit_pack_input(to_dev(x), xq, ka, n, c, h, h)
+        xnor.xnor_kbit_conv2d(xq, wq, scale, out, num, desc, ka, kb)
+        r = xo.kbit_conv2d(x, W, ka, kb, (1, 1), (1, 1))
+        assert np.array_equal(num.cpu().numpy().astype(np.int64), r["num"]), ka
