@@ -39,9 +39,17 @@ xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, 
 {
     const uint8_t *img = static_cast<const uint8_t *>(wmfma);
     // fmt 3: int8 level numerators (xbits = 32-byte words of 32 channels, wmfma = an int8 record image); no K
-    if (fmt == 3) return fz ? XNOR_ERR_UNSUPPORTED : launch_fmt<3>(xbits, img, nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
-    // fmt 5: the same for kbit_narrow() layers, on the 4-bit record image behind it
-    if (fmt == 5) return fz ? XNOR_ERR_UNSUPPORTED : launch_fmt<5>(xbits, img + wimg_i8_bytes(g.k_out, g.c, g.taps), nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
+    // fmt 5: the same for kbit_narrow() layers, on the 4-bit record image behind it.  Three words per pixel it stages at once
+    // or not at all, where int8 may take one at a time: rows too wide for that run on int8.
+    if (fmt == 3 || fmt == 5) {
+        if (fz) return XNOR_ERR_UNSUPPORTED;
+        if (fmt == 5) {
+            const xnor_status s = launch_fmt<5>(xbits, img + wimg_i8_bytes(g.k_out, g.c, g.taps), nullptr, nullptr, alpha, out,
+                                                dot_out, g, stream, nullptr);
+            if (s != XNOR_ERR_UNSUPPORTED) return s;
+        }
+        return launch_fmt<3>(xbits, img, nullptr, nullptr, alpha, out, dot_out, g, stream, nullptr);
+    }
     // float accumulation of the 4-bit path is exact while every sum stays below 2^24
     if (fmt != 0 && (long long)g.c * g.taps >= (1ll << 24)) return XNOR_ERR_UNSUPPORTED;
     if (fmt == 0) return launch_fmt<0>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);

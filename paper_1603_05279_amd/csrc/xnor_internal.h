@@ -78,9 +78,8 @@ xnor_status launch_pack_weights(const float *w, uint32_t *wbits, float *alpha, v
 // (mode 0: sign(W) and alpha; 1: transposed, rotated filters of the backward convolution; 3: int8 level
 // numerators of the aux-bit quantised weights, int8 image only, alpha = alpha_fill; 4: the same, aux <= 2, and behind it
 // the 4-bit image)
-// k-bit layers that run on 4-bit operands: at most two bits each, float sums below 2^24, and an LDS image that fits wherever
-// the int8 one does (that one may take a single channel word at a time, 48 bytes per pixel; this one an even number of
-// words, 48 bytes for two, or all of them).  The packer writes both images for weights of at most two bits.
+// k-bit layers that run on 4-bit operands (where their LDS image fits: launch_conv_mfma): at most two bits each, float sums
+// below 2^24, and channel words in pairs, or at most three of them.  The packer writes both images for weights of at most two bits.
 inline bool kbit_narrow(int ka, int kw_bits, int c, int taps)
 {
     const int cw = (c + 31) / 32;

@@ -16,6 +16,7 @@ CASES = [
     (1, 31, 4, 5, 3, 1, 1, (1, 1), (0, 0)), (2, 32, 7, 7, 33, 3, 3, (1, 1), (1, 1)), (3, 65, 9, 6, 40, 3, 2, (2, 1), (1, 0)),
     (2, 96, 13, 13, 130, 3, 3, (1, 1), (1, 1)), (1, 140, 6, 6, 20, 3, 3, (1, 1), (1, 1)),      # five words: int8
     (2, 192, 11, 11, 257, 3, 3, (1, 1), (1, 1)), (1, 512, 40, 40, 32, 5, 5, (1, 1), (2, 2)),   # several chunks
+    (1, 70, 5, 900, 130, 1, 1, (1, 1), (0, 0)), (2, 96, 16, 300, 3, 3, 3, (1, 1), (0, 0)),      # rows too wide for three words: int8
 ]
 
 
