@@ -464,11 +464,12 @@ template <int FW> struct WStreamChunked {
 // Weight stream of the 4-bit operands: the packed words themselves, [filter block][(tap, channel word)][32 filters], two
 // (tap, word) blocks = 256 bytes per K-step and filter block, one word per lane, widened in registers while the matrix
 // pipes work on the step before (a matrix instruction leaves its wave seven issue slots).  Each filter block has a
-// resource of its own that ends with its words: prefetches beyond are answered with zeros.  When the block count is odd the
-// second half-wave of the last step holds no block: its code is 0 (operand 0.0).
+// resource of its own that ends with its words: reads beyond are answered with zeros, as above only while the step lies in the
+// vector offset.  When the block count is odd the second half-wave of the last step holds no block: its code is 0 (operand 0.0).
 // Steps are consecutive (LINEAR) or, where a chunk holds part of the channel words, run on within a tap and skip
-// tap_jump words to the next one (uniform bookkeeping in the scalar offset; steps past the end read the block's
-// first words, which nothing multiplies).
+// tap_jump words to the next one (uniform bookkeeping, one vector addition per step; steps past the end read the block's
+// first words, which nothing multiplies).  There too the second half-wave of a filter's very last step may lie beyond its
+// words: a last chunk that lacks a word, an odd block count in one chunk.
 template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     typedef uint32_t word_t;
     static constexpr bool WIDEN = true;
@@ -489,7 +490,7 @@ template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     {
 #pragma unroll
         for (int i = 0; i < FW; ++i)
-            dst[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc[i], voff, LINEAR ? 0 : w_blk * 128, AUX);
+            dst[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc[i], LINEAR ? voff : voff + w_blk * 128, 0, AUX);
         if constexpr (LINEAR) {
             voff += 256;
         } else {
