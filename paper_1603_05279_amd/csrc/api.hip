@@ -193,12 +193,12 @@ xnor_status conv_dispatch(const ConvGeom &g, const uint32_t *xbits, const uint32
     case XNOR_ALGO_MFMA_I8:
     case XNOR_ALGO_MFMA_F4:
         if (!wmfma) return XNOR_ERR_NULL;
-        return launch_conv_mfma(algo == XNOR_ALGO_MFMA_F4 ? 1 : 0, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
+        return launch_conv_mfma(algo == XNOR_ALGO_MFMA_F4 ? 1 : 0, xbits, wmfma, K, A, alpha, out, dot_out, g, st, nullptr, true);
     case XNOR_ALGO_AUTO: {
         if (linear_popcount_applies(g, wmfma != nullptr))
             return launch_linear_popcount(xbits, wbits, K ? K : A, alpha, out, dot_out, g, st);
         if (wmfma) {        // 4-bit operands, then int8 (sums of 2^24 and more terms), then the vector ALU
-            xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
+            xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, dot_out, g, st, nullptr, dilated);
             if (s != XNOR_ERR_UNSUPPORTED) return s;
             s = launch_conv_mfma(0, xbits, wmfma, K, A, alpha, out, dot_out, g, st);
             if (s != XNOR_ERR_UNSUPPORTED) return s;
@@ -284,7 +284,7 @@ int xnor_conv2d_binactiv(const uint32_t *xbits, const uint32_t *wbits, const voi
     fz.xbits_next = xbits_next; fz.A_next = A_next; fz.workspace = static_cast<float *>(workspace);
     hipStream_t st = (hipStream_t)hip_stream;
     if (algo != XNOR_ALGO_MFMA_I8) {
-        const xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, nullptr, g, st, &fz);
+        const xnor_status s = launch_conv_mfma(1, xbits, wmfma, K, A, alpha, out, nullptr, g, st, &fz, true);
         if (s != XNOR_ERR_UNSUPPORTED || algo == XNOR_ALGO_MFMA_F4) return s;
     }
     return launch_conv_mfma(0, xbits, wmfma, K, A, alpha, out, nullptr, g, st, &fz);
@@ -459,7 +459,8 @@ int xnor_bingrad_conv2d(const uint32_t *gbits, const uint32_t *wtbits, const voi
         gi.k_per_image = 1;
         xnor_status s = XNOR_ERR_UNSUPPORTED;
         if (algo != XNOR_ALGO_MFMA_I8)
-            s = launch_conv_mfma(1, gbits, wtmfma, gmax, nullptr, ones, g_in, dot_out, gi, st);
+            s = launch_conv_mfma(1, gbits, wtmfma, gmax, nullptr, ones, g_in, dot_out, gi, st, nullptr,
+                                 dilated || algo == XNOR_ALGO_MFMA_F4);
         if (s == XNOR_ERR_UNSUPPORTED && algo != XNOR_ALGO_MFMA_F4)
             s = launch_conv_mfma(0, gbits, wtmfma, gmax, nullptr, ones, g_in, dot_out, gi, st);
         if (s != XNOR_ERR_UNSUPPORTED || algo != XNOR_ALGO_AUTO || dilated) return s;

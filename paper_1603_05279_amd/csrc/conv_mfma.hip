@@ -35,7 +35,7 @@ xnor_status launch_sum_planes(const float *part, float *A_next, int m_total, int
 
 xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, const float *K, const float *A,
                              const float *alpha, float *out, int32_t *dot_out,
-                             const ConvGeom &g, hipStream_t stream, const FuseArgs *fz)
+                             const ConvGeom &g, hipStream_t stream, const FuseArgs *fz, bool last)
 {
     const uint8_t *img = static_cast<const uint8_t *>(wmfma);
     // fmt 3: int8 level numerators (xbits = 32-byte words of 32 channels, wmfma = an int8 record image); no K
@@ -54,7 +54,7 @@ xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, 
     if (fmt != 0 && (long long)g.c * g.taps >= (1ll << 24)) return XNOR_ERR_UNSUPPORTED;
     if (fmt == 0) return launch_fmt<0>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);
     img += wimg_i8_bytes(g.k_out, g.c, g.taps) + wimg_f4_bytes(g.k_out, g.c, g.taps);
-    return launch_fmt<1>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);
+    return launch_fmt<1>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz, last);
 }
 
 }  // namespace xnor

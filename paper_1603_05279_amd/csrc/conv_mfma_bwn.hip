@@ -4,9 +4,9 @@
 namespace xnor {
 
 template xnor_status launch_fmt<2>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 template xnor_status launch_fmt<4>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 
 xnor_status launch_bwn_conv(const void *parts, const void *wimg, const float *alpha, float *out, const ConvGeom &g,
                             const ConvGeom &gp, hipStream_t stream)

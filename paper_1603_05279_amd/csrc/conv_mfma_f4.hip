@@ -4,6 +4,6 @@
 namespace xnor {
 
 template xnor_status launch_fmt<1>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 
 }  // namespace xnor

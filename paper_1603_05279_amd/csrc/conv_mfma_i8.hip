@@ -4,10 +4,10 @@
 namespace xnor {
 
 template xnor_status launch_fmt<0>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 template xnor_status launch_fmt<3>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 template xnor_status launch_fmt<5>(const uint32_t *, const void *, const float *, const float *, const float *, float *,
-                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *);
+                                   int32_t *, const ConvGeom &, hipStream_t, const FuseArgs *, bool);
 
 }  // namespace xnor

@@ -1003,9 +1003,9 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
 template <int FMT>
 xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, const float *A,
                               const float *alpha, float *out, int32_t *dot_out, const ConvGeom &g,
-                              hipStream_t stream, const FuseArgs *fz)
+                              hipStream_t stream, const FuseArgs *fz, bool last)
 {
-    int tile = mfma_tile_override();
+    int tile = mfma_tile_override(), stead = 0;      // stead: the tile that a rule for smaller launches has replaced
     if (tile == 0) {
         // Measured rules (fp4, all benchmark layers).  Up to 64 filters: 64 x 256 when that still gives every
         // CU two workgroups, else 64 x 128; up to 128 filters: 128 x 64, else 64 x 128 (fused epilogue:
@@ -1043,12 +1043,12 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         else if (g.k_out <= 128) tile = fz ? 1 : wgs(128, 64) >= 2 * cus ? 13 : 11;
         else if (g.k_out <= 256) {
             tile = waste(wgs(256, 96)) <= waste(wgs(256, 128)) ? 4 : 5;
-            if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) tile = 6;
+            if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) { tile = 6; stead = 4; }
         } else if (FMT == 1 && fz && g.k_out <= 512) tile = g.k_out <= 384 ? 9 : 8;
         else tile = g.k_out % 256 == 0 ? 5 : fz ? 13 : 1;      // (fused epilogue: 128 x 64 ahead of 128 x 128)
         // 4-bit operands: less than a workgroup per CU of 128 x 128, 128 x 64 is ahead of it (3 images of 352x48x48 -> 310 14.6 -> 13.4 us,
         // 8 of 416x28x28 -> 390 15.8 -> 14.2, 36 of 64x14x14 -> 384 8.1 -> 7.6, 9 of 192x28x28 -> 300 1x1 7.4 -> 6.8)
-        if (FMT == 1 && tile == 1 && !fz && g.k_out > 256 && wgs(128, 128) < cus) tile = 13;
+        if (FMT == 1 && tile == 1 && !fz && g.k_out > 256 && wgs(128, 128) < cus) { tile = 13; stead = 1; }
         const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
                              : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
                              : tile == 9 ? wgs(384, 96) : tile == 12 ? wgs(512, 64) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
@@ -1071,6 +1071,7 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
             return fz ? launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz)        \
                       : launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr); \
         return XNOR_ERR_UNSUPPORTED;
+    auto launch = [&](int tile) -> xnor_status {
     switch (tile) {
         XNOR_TILE_F(1, 2, 2, 2, 2);   // 128 filters x 128 pixels
         XNOR_TILE_F(2, 2, 2, 1, 4);   //  64 x 256
@@ -1102,8 +1103,19 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         return XNOR_ERR_UNSUPPORTED;
     default: return XNOR_ERR_UNSUPPORTED;
     }
+    };
 #undef XNOR_TILE_F
 #undef XNOR_TILE_F4
+    xnor_status s = launch(tile);
+    if (FMT != 1 || mfma_tile_override() != 0) return s;
+    // 4-bit operands: the rows under the chosen tile may not fit the LDS with what the tile keeps beside them (384 and 512
+    // filters of the fused epilogue: 5 and 6 KiB of alpha, scale and shift, a word per pixel and 32 filters; 64 x 6 x 6, one 6 x 6
+    // window, fused with 384 filters: 190 KB for 384 x 96, 123 KB for 128 x 64).  Where nothing else takes the call, fewer
+    // pixels and filters do.  Where the vector ALU does, it stays ahead of them as often as not (7 x 40 x 804, 7 x 7 -> 300,
+    // 24 images: 893 us against 3215; 160 x 21 x 119, 11 x 11 stride 2 -> 512, 19 images: 362 against 206).
+    for (const int other : {stead, last ? 13 : 0, last ? 14 : 0})
+        if (s == XNOR_ERR_UNSUPPORTED && other) s = launch(other);
+    return s;
 }
 
 }  // namespace xnor

@@ -121,10 +121,10 @@ struct FuseArgs {
 };
 
 // fmt 0: int8 operands, fmt 1: 4-bit float operands (both images live in the wmfma buffer).
-// fz != NULL selects the fused epilogue above; `out` may then be NULL.
+// fz != NULL selects the fused epilogue above; `out` may then be NULL.  last: no form but the int8 one follows a refusal.
 xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, const float *K, const float *A,
                              const float *alpha, float *out, int32_t *dot_out,
-                             const ConvGeom &g, hipStream_t stream, const FuseArgs *fz = nullptr);
+                             const ConvGeom &g, hipStream_t stream, const FuseArgs *fz = nullptr, bool last = false);
 // the same convolution (4-bit operands) with max-pooling (window ph x pw, stride sh x sw, no padding, optional
 // ReLU first) applied in the epilogue: out_pool [n][k_out][hpo][wpo], the unpooled tensor is never written
 xnor_status launch_conv_mfma_pool(const uint32_t *xbits, const void *wmfma, const float *K, const float *A,

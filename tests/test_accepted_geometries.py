@@ -21,3 +21,26 @@ def test_kbit_layers_of_two_bits_are_taken_where_three_bits_are(case):
     d = ctypes.byref(xnor.make_desc(*case))
     for ka, kb in ((1, 1), (1, 2), (2, 2), (2, 3), (3, 3)):
         assert xnor.lib().xnor_kbit_conv2d(FAKE, FAKE, FAKE, FAKE, None, d, ka, kb, None) == ERR_HIP
+
+
+# (the fused epilogue of 257 to 512 filters keeps up to 6 KiB of per-filter values and a word per pixel and 32 filters in LDS)
+@pytest.mark.parametrize("case", [
+    (15360, 64, 6, 6, 384, 6, 6, 1, 0), (6, 64, 8, 297, 384, 5, 5, 1, (3, 1)), (64, 7, 6, 700, 300, 5, 5, 2, 0), (39, 32, 54, 1076, 512, 3, 3, 2, 1),
+    (2, 7, 16, 560, 256, 7, 7, 1, 0), (136, 64, 11, 301, 320, 5, 5, 1, 2)])
+def test_fused_layers_with_wide_rows(case):
+    d = ctypes.byref(xnor.make_desc(*case))
+    for algo in (xnor.XNOR_ALGO_AUTO, xnor.XNOR_ALGO_MFMA_F4):
+        assert xnor.lib().xnor_conv2d_binactiv(FAKE, FAKE, FAKE, None, FAKE, FAKE, None, None, FAKE, FAKE, None, FAKE, d, algo, None) == ERR_HIP
+
+
+@pytest.mark.parametrize("case", [(2, 7, 8, 620, 300, 7, 7, 1, 1), (2, 64, 6, 400, 300, 5, 5, 1, 2), (168, 256, 14, 530, 256, 3, 3, (1, 2), 0)])
+def test_plain_layers_with_wide_rows(case):
+    d = ctypes.byref(xnor.make_desc(*case))
+    for K, A in ((None, FAKE), (FAKE, None)):
+        assert xnor.lib().xnor_conv2d(FAKE, FAKE, FAKE, K, A, FAKE, FAKE, None, d, xnor.XNOR_ALGO_MFMA_F4, None) == ERR_HIP
+
+
+@pytest.mark.parametrize("case", [(7, 160, 6, 302, 256, 5, 7, 2, (2, 4)), (2, 352, 8, 213, 320, 7, 7, 1, 3), (300, 160, 8, 900, 256, 2, 2, 2, 0)])
+def test_backward_layers_with_wide_rows(case):
+    d = ctypes.byref(xnor.make_desc(*case))
+    assert xnor.lib().xnor_bingrad_conv2d(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, None, d, xnor.XNOR_ALGO_MFMA_F4, None) == ERR_HIP

@@ -110,3 +110,27 @@ def test_results_larger_than_the_hint_threshold(h):
     ref, got = (block((n, 64, h, h, 256, 1, 1, 1, 0), algo) for algo in ("popcount", "mfma_f4"))
     assert torch.equal(got.dot, ref.dot)
     assert torch.equal(got.out, ref.out)
+
+
+# n, c, h, w, k_out, kh, kw, stride, pad: rows that the tile of the layer's size cannot stage (a smaller one does)
+@pytest.mark.parametrize("case", [(64, 7, 6, 700, 300, 5, 5, 2, 0), (2, 7, 16, 560, 256, 7, 7, 1, 0), (2, 7, 8, 620, 300, 7, 7, 1, 1)])
+def test_layers_whose_tile_does_not_fit_take_a_smaller_one(case):
+    n, c, h, w, k, kh, kw, stride, pad = case
+    ref, got = block(case, "popcount"), block(case, "mfma_f4")
+    assert torch.equal(got.dot, ref.dot) and torch.equal(got.out, ref.out)
+    gen = torch.Generator(device="cuda").manual_seed(c * 1000 + h)
+    torch.randn((n, c, h, w), generator=gen, device="cuda")                  # (block's input and weights)
+    pw = xnor.PackedWeights(torch.randn((k, c, kh, kw), generator=gen, device="cuda"))
+    desc = xnor.make_desc(n, c, h, w, k, kh, kw, stride, pad)
+    ho, wo = xnor.output_hw(desc)
+    sc, sh = torch.rand((k,), generator=gen, device="cuda") + 0.5, torch.randn((k,), generator=gen, device="cuda")
+    ws = torch.empty((xnor.conv2d_binactiv_workspace_bytes(desc),), dtype=torch.uint8, device="cuda")
+    nx = torch.full((n, ho, wo, xnor.words_per_pixel(k)), -1, dtype=torch.int32, device="cuda")
+    An, out = torch.full((n, ho, wo), float("nan"), device="cuda"), torch.empty((n, k, ho, wo), device="cuda")
+    xnor.xnor_conv2d_binactiv(ref.xbits, pw.wbits, pw.wmfma, None, ref.A, pw.alpha, sc, sh, nx, An, out, ws, desc)
+    assert torch.equal(out, ref.out)
+    bits, A2 = torch.empty_like(nx), torch.empty_like(An)
+    xnor.xnor_binactiv(ref.out, sc, sh, bits, A2, None, xnor.make_desc(n, k, ho, wo, 1, 1, 1))
+    assert torch.equal(nx, bits)
+    # two float sums of k positive terms in different orders: at most k roundings each
+    assert torch.allclose(An, A2, rtol=2 * k * 2.0 ** -24, atol=0)
