@@ -939,7 +939,7 @@ template <class Kern> static xnor_status allow_full_lds(Kern kern, std::atomic<b
 template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, int KS = 1>
 static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const float *K, const float *A,
                               const float *alpha, float *out, int32_t *dot_out, const ConvGeom &g,
-                              hipStream_t stream, const FuseArgs *fz)
+                              hipStream_t stream, const FuseArgs *fz, bool whole = false)
 {
     constexpr int FT = 32 * FW * WF, PT = 32 * PW * WP;
     // results are stored through a buffer resource with 32-bit offsets from the tile's first image
@@ -954,6 +954,7 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, two blocks per wave: 34.5 and 39.5)
     if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW >= 4 ? 2 : 0x7fffffff))
         return XNOR_ERR_UNSUPPORTED;
+    if (whole && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
@@ -1047,7 +1048,9 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         } else if (FMT == 1 && fz && g.k_out <= 512) tile = g.k_out <= 384 ? 9 : 8;
         else tile = g.k_out % 256 == 0 ? 5 : fz ? 13 : 1;      // (fused epilogue: 128 x 64 ahead of 128 x 128)
         // 4-bit operands: less than a workgroup per CU of 128 x 128, 128 x 64 is ahead of it (3 images of 352x48x48 -> 310 14.6 -> 13.4 us,
-        // 8 of 416x28x28 -> 390 15.8 -> 14.2, 36 of 64x14x14 -> 384 8.1 -> 7.6, 9 of 192x28x28 -> 300 1x1 7.4 -> 6.8)
+        // 8 of 416x28x28 -> 390 15.8 -> 14.2, 36 of 64x14x14 -> 384 8.1 -> 7.6, 9 of 192x28x28 -> 300 1x1 7.4 -> 6.8), but for those
+        // that hold every channel word with one workgroup per CU and would take chunks with two (11 images of 480x29x29, 5x5 -> 300
+        // 25.6 and 36.9; 2 of 362x53x53 -> 416 13.7 and 17.6: below)
         if (FMT == 1 && tile == 1 && !fz && g.k_out > 256 && wgs(128, 128) < cus) { tile = 13; stead = 1; }
         const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
                              : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
@@ -1064,14 +1067,14 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         if constexpr (FMT < 2) {                                                                          \
             if (fz) return launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz); \
         }                                                                                                 \
-        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr);
+        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, whole);
 #define XNOR_TILE_F4(ID, FW, PW, WF, WP)                                                                  \
     case ID:                                                                                              \
         if constexpr (FMT == 1)                                                                           \
             return fz ? launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz)        \
                       : launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr); \
         return XNOR_ERR_UNSUPPORTED;
-    auto launch = [&](int tile) -> xnor_status {
+    auto launch = [&](int tile, bool whole = false) -> xnor_status {       // whole: not in chunks of the channel words
     switch (tile) {
         XNOR_TILE_F(1, 2, 2, 2, 2);   // 128 filters x 128 pixels
         XNOR_TILE_F(2, 2, 2, 1, 4);   //  64 x 256
@@ -1106,7 +1109,9 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     };
 #undef XNOR_TILE_F
 #undef XNOR_TILE_F4
-    xnor_status s = launch(tile);
+    xnor_status s = launch(tile, stead == 1);
+    if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(1, true);
+    if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(13);
     if (FMT != 1 || mfma_tile_override() != 0) return s;
     // 4-bit operands: the rows under the chosen tile may not fit the LDS with what the tile keeps beside them (384 and 512
     // filters of the fused epilogue: 5 and 6 KiB of alpha, scale and shift, a word per pixel and 32 filters; 64 x 6 x 6, one 6 x 6

@@ -15,7 +15,7 @@ CASES = [
     (3, 96, 9, 11, 100, 3, 3, 1, 1), (11, 128, 7, 7, 130, 3, 3, 1, 1), (2, 160, 13, 6, 257, 3, 3, 2, 1),
     (5, 190, 6, 14, 64, 5, 3, (1, 2), (2, 1)), (2, 224, 10, 10, 300, 3, 3, 1, 2), (1, 256, 31, 29, 129, 3, 3, 1, 1),
     (2, 384, 13, 13, 200, 3, 3, 1, 1), (1, 512, 40, 40, 32, 5, 5, 1, 2), (1, 288, 41, 41, 40, 5, 5, 2, 2), (3, 275, 9, 12, 70, 3, 3, 1, 1),
-    (2, 384, 54, 54, 33, 5, 5, 1, 2), (5, 320, 31, 31, 320, 3, 3, 2, 1), (1, 330, 48, 48, 140, 3, 3, 1, 1), (1, 32, 200, 3, 70, 7, 3, (3, 1), (3, 1)),
+    (2, 384, 54, 54, 33, 5, 5, 1, 2), (2, 362, 53, 53, 416, 3, 3, 1, 1), (5, 320, 31, 31, 320, 3, 3, 2, 1), (1, 330, 48, 48, 140, 3, 3, 1, 1), (1, 32, 200, 3, 70, 7, 3, (3, 1), (3, 1)),
 ]
 
 
