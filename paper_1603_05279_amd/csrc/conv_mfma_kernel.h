@@ -309,6 +309,8 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                         if (base + u * NT >= items) break;                              // (uniform)
                         const uint32_t it = (uint32_t)(base + u * NT + tid);
                         const uint32_t px = pl.sd_quads.div(it), q = it - mul24(px, (uint32_t)pl.quads);
+                        // first word of the item's load
+                        const uint32_t w0 = ONE && V == 4 ? min(q * V, (uint32_t)(pl.cc_words - V)) : q * V;
                         const uint32_t rr = pl.sd_wp.div(px);
                         const uint32_t xc = px - mul24(rr, (uint32_t)g.wp);
                         const uint32_t yy = (uint32_t)y0 + rr, img = pl.sd_hp.div(yy);
@@ -322,7 +324,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                             x = xr;
                         }
                         const uint32_t pix = mul24(mul24(img, (uint32_t)g.real_h) + y, (uint32_t)g.real_w) + x;
-                        const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + q * (V * 4u) + (ONE ? 0u : (uint32_t)wbase * 4u) : 0x80000000u;
+                        const uint32_t off = ok[u] ? mul24(pix, (uint32_t)g.cw * 4u) + w0 * 4u + (ONE ? 0u : (uint32_t)wbase * 4u) : 0x80000000u;
                         if constexpr (V == 4) {
                             const v4u r = __builtin_amdgcn_raw_buffer_load_b128(xrsrc, (int)off, 0, 0);
                             bits[u][0] = r[0]; bits[u][1] = r[1]; bits[u][2] = r[2]; bits[u][3] = r[3];
@@ -335,14 +337,14 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                         } else {
                             bits[u][0] = __builtin_amdgcn_raw_buffer_load_b32(xrsrc, (int)off, 0, 0);
                         }
-                        wl[u] = (ONE ? 0 : wbase) + (int)q * V;
+                        wl[u] = (ONE ? 0 : wbase) + (int)w0;
                         const bool first = stageA && q == 0 && (int)it < items;
                         adst[u] = first ? (int)px : -1;
                         if (stageA)
                             av[u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
                                                                   arsrc, (int)(ok[u] && q == 0 ? pix * 4u : 0x80000000u), 0, 0));
                         dst[u] = (int)it < items ? (int)(mul24(rr, (uint32_t)pl.row_pitch) + mul24(xc, (uint32_t)pl.ps) +
-                                                         q * (uint32_t)(V * E::BPB))
+                                                         w0 * (uint32_t)E::BPB)
                                                  : -1;
                     }
 #pragma unroll

@@ -36,8 +36,8 @@ struct MfmaPlan {
     int lut_offset;   // LDS byte offset of the sign-byte widening table
     int ftiles;       // filter tiles of the launch
     int wmajor;       // 1: 1-D grid that keeps the pixel tiles of a filter tile on one XCD
-    int vec;          // > 0: channel words per load of the direct staging loop (1 to 4, divides cc_words); 0: the general loop
-    int quads;        // cc_words / vec
+    int vec;          // > 0: channel words per load of the direct staging loop (1 to 4); 0: the general loop
+    int quads;        // loads per pixel: cc_words / vec, rounded up
     int dilated;      // direct staging: the input is dilated
     SmallDiv sd_dil_h, sd_dil_w;
     SmallDiv sd_quads, sd_wp, sd_hp, sd_wo, sd_ho;   // direct staging: item, padded and output coordinates of a tile
@@ -56,12 +56,17 @@ inline void set_direct_staging(MfmaPlan *pl, const ConvGeom &g, int fmt, int run
 {
     pl->vec = pl->quads = 0;
     if (fmt > 1 || (fmt != 1 && pl->cc_words != g.cw)) return;
-    // (a pixel's words start at a multiple of the load in every chunk; an odd count's last chunk may lack a word: single words)
-    const int vec = pl->cc_words == g.cw && g.cw % 3 == 0 && g.cw % 2 ? 3
-                    : pl->cc_words % 4 == 0 && g.cw % 4 == 0         ? 4
-                    : pl->cc_words % 2 == 0 && g.cw % 2 == 0         ? 2
-                                                                     : 1;
-    const int quads = pl->cc_words / vec;
+    // Odd counts in one chunk: four words too (a load is aligned to a word, not to its size), the last load of a pixel moved back
+    // onto the last four, so that some words are loaded and written twice, with the same value.  One word per item
+    // repeats the coordinates for each: 16 images of 352x28x28 -> 128 1x1 7.8 -> 6.7 us, 3x3 11.3 -> 9.7, 5x5 17.7 -> 15.0.
+    // (chunks of an odd count: the last one may lack a word, single words)
+    const bool odd = pl->cc_words == g.cw && g.cw % 2;
+    const int vec = odd && g.cw % 3 == 0                     ? 3
+                    : odd                                    ? (g.cw > 4 ? 4 : 1)
+                    : pl->cc_words % 4 == 0 && g.cw % 4 == 0 ? 4
+                    : pl->cc_words % 2 == 0 && g.cw % 2 == 0 ? 2
+                                                             : 1;
+    const int quads = (pl->cc_words + vec - 1) / vec;
     const long long howo = (long long)g.ho * g.wo, hw = (long long)g.h * g.w;
     const long long images = run / howo + 2;                        // that a tile can touch
     const long long px = (long long)pl->max_rows * g.wp;
