@@ -185,7 +185,8 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
     const int nrows = r_hi - r_lo + 1;
 
     // alpha (fused epilogue: also scale and shift) of this workgroup's filters: requested first, written behind the widening
-    // table ([FT] each) once the staging loads are on their way; filters past the last one repeat it and are masked later
+    // table ([FT] each), raw operands at once, the others when the staging loads are on their way; filters past the last one
+    // repeat it and are masked later
     constexpr int NP = (FT + NT - 1) / NT;
     float par[NP][FUSE ? 3 : 1];
 #pragma unroll
@@ -199,6 +200,18 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
     }
     float *par_lds = reinterpret_cast<float *>(lds + pl.lut_offset + E::LUT_BYTES);
     E::build_lut(lds + pl.lut_offset, tid, NT);
+    auto store_par = [&] {
+#pragma unroll
+        for (int u = 0; u < NP; ++u)
+            if (NP * NT == FT || tid + u * NT < FT) {
+                par_lds[tid + u * NT] = par[u][0];
+                if constexpr (FUSE) {
+                    par_lds[FT + tid + u * NT] = par[u][1];
+                    par_lds[2 * FT + tid + u * NT] = par[u][2];
+                }
+            }
+    };
+    if constexpr (RAW) store_par();
     if constexpr (!DIRECT)
     for (int rr = tid; rr < nrows; rr += NT) {
         const uint32_t R = (uint32_t)(r_lo + rr);
@@ -277,8 +290,9 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
     const int steps_per_tap = pl.tap_jump ? ccw / E::BPS : 0x7fffffff;
     for (int wbase = 0; ONE ? wbase < 1 : wbase < args.g.cw; wbase += ONE ? 1 : ccw) {
-        // (read per chunk: otherwise everything a chunk derives from them is hoisted in front of the first one and held)
-        const ConvArgs now = reload_args();
+        // (read per chunk: otherwise everything a chunk derives from them is hoisted in front of the first one and held.  Raw
+        // operands hold little: there the loads cost more, 4 images of 32x12x12 -> 497, 1x1, int8 levels 4.6 us with them, 4.3 without)
+        const ConvArgs now = RAW ? args : reload_args();
         const ConvGeom &g = now.g;
         const MfmaPlan &pl = now.pl;
         const v4i *wimg = now.wimg;
@@ -430,7 +444,8 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                 const int xv = (int)(px - rr * g.wp) - g.pw;                 // column of the (virtual) input
                 const int xcol = (int)g.div_dil_w.div_small((uint32_t)max(xv, 0));  // column of the real tensor
                 const int rowbase = rowinfo[rr];
-                ok[u] = rowbase >= 0 && xv >= 0 && xv < g.w && xcol * g.dil_w == xv && xcol < g.real_w && wbase + wl < g.cw;
+                // (only packed words have a last chunk that may lack one)
+                ok[u] = rowbase >= 0 && xv >= 0 && xv < g.w && xcol * g.dil_w == xv && xcol < g.real_w && (FMT != 1 || wbase + wl < g.cw);
                 dst[u] = it < items ? (int)(rr * pl.row_pitch + (px - rr * g.wp) * pl.ps + wl * E::BPB) : -1;
                 nch[u] = g.c - (wbase + wl) * 32;
                 bits[u] = 0;
@@ -470,17 +485,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                 a_lds[it] = rowbase >= 0 && xcol >= 0 && xcol < g.w ? in_global(A)[(size_t)rowbase + xcol] : 0.0f;
             }
         }
-        if (wbase == 0) {
-#pragma unroll
-            for (int u = 0; u < NP; ++u)
-                if (NP * NT == FT || tid + u * NT < FT) {
-                    par_lds[tid + u * NT] = par[u][0];
-                    if constexpr (FUSE) {
-                        par_lds[FT + tid + u * NT] = par[u][1];
-                        par_lds[2 * FT + tid + u * NT] = par[u][2];
-                    }
-                }
-        }
+        if (!RAW && wbase == 0) store_par();
         __syncthreads();
         // K of the tile's output pixels, an equal share per wave: the kh x kw taps of A in row-major order over the
         // staged rows (halo entries add +0.0f, the same bits as skipping them), divided by kh*kw
@@ -544,7 +549,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         }
     }
     {
-    const ConvArgs late = reload_args();
+    const ConvArgs late = RAW ? args : reload_args();
     const ConvGeom &g = late.g;
     const MfmaPlan &pl = late.pl;
     const FuseArgs &fz = late.fz;
