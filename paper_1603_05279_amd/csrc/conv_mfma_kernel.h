@@ -946,7 +946,7 @@ template <class Kern> static xnor_status allow_full_lds(Kern kern, std::atomic<b
 template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, int KS = 1>
 static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const float *K, const float *A,
                               const float *alpha, float *out, int32_t *dot_out, const ConvGeom &g,
-                              hipStream_t stream, const FuseArgs *fz, bool whole = false)
+                              hipStream_t stream, const FuseArgs *fz, bool strict = false)
 {
     constexpr int FT = 32 * FW * WF, PT = 32 * PW * WP;
     // results are stored through a buffer resource with 32-bit offsets from the tile's first image
@@ -961,8 +961,20 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, two blocks per wave: 34.5 and 39.5)
     if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW >= 4 ? 2 : 0x7fffffff))
         return XNOR_ERR_UNSUPPORTED;
-    if (whole && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
+    // strict: packed words only in one chunk (the caller has another tile for the others), digits only where they are ahead
+    if (FMT != 2 && strict && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
+    if (FMT == 2 && strict) {
+        // With one workgroup on a CU that has several to run nothing hides the conversion: a word's digits have to save 24 matrix
+        // instructions per 32 x 32 results over their taps, 84 where the words come in chunks (a 512-filter tile holds the CU
+        // whatever it stages).  Parts against digits, us (saved per word): 2 images of 35x50x50, 3x3 -> 448 (18) 13.4 / 20.7;
+        // 18 of 64x50x50, 3x3 -> 236 (31) 37.2 / 32.9; 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; in chunks 7 of 68x44x44, 3x3 -> 288
+        // (15) 26.7 / 45.3; 5 of 160x51x51, 5x5 -> 60 (75) 49.1 / 61.4; 20 of 192x34x34, 5x5 -> 32 (87) 82.3 / 73.6.  512 filters: 19 of
+        // 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
+        const bool wide = FW * PW > 6, chunks = !wide && pl.cc_words != g.cw;
+        if ((wide || (lds > 80 * 1024 && wg_count > 256)) && bwn_digits_save(g) < (chunks ? 84LL : 24LL) * g.cw)
+            return XNOR_ERR_UNSUPPORTED;
+    }
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
     // third, chunks staged directly
@@ -1074,14 +1086,14 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         if constexpr (FMT < 2) {                                                                          \
             if (fz) return launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz); \
         }                                                                                                 \
-        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, whole);
+        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict);
 #define XNOR_TILE_F4(ID, FW, PW, WF, WP)                                                                  \
     case ID:                                                                                              \
         if constexpr (FMT == 1)                                                                           \
             return fz ? launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz)        \
                       : launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr); \
         return XNOR_ERR_UNSUPPORTED;
-    auto launch = [&](int tile, bool whole = false) -> xnor_status {       // whole: not in chunks of the channel words
+    auto launch = [&](int tile, bool strict = false) -> xnor_status {
     switch (tile) {
         XNOR_TILE_F(1, 2, 2, 2, 2);   // 128 filters x 128 pixels
         XNOR_TILE_F(2, 2, 2, 1, 4);   //  64 x 256
@@ -1092,7 +1104,7 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         XNOR_TILE_F(13, 1, 2, 4, 1);  // 128 x  64
         XNOR_TILE_F(14, 1, 1, 4, 1);  // 128 x  32
     case 12:                          // 512 x  64, one workgroup of four waves per CU (digit operands)
-        if constexpr (FMT == 2) return launch_cfg<FMT, 4, 2, 4, 1, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr);
+        if constexpr (FMT == 2) return launch_cfg<FMT, 4, 2, 4, 1, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict);
         return XNOR_ERR_UNSUPPORTED;
     case 8:                           // 512 x  64, eight waves, and 384 x 96, six: one workgroup holds every filter of the
     case 9:                           // fused epilogue (4-bit operands)
@@ -1116,7 +1128,7 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     };
 #undef XNOR_TILE_F
 #undef XNOR_TILE_F4
-    xnor_status s = launch(tile, stead == 1);
+    xnor_status s = launch(tile, FMT == 2 ? !last && mfma_tile_override() == 0 : stead == 1);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(1, true);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(13);
     if (FMT != 1 || mfma_tile_override() != 0) return s;

@@ -44,3 +44,9 @@ def test_plain_layers_with_wide_rows(case):
 def test_backward_layers_with_wide_rows(case):
     d = ctypes.byref(xnor.make_desc(*case))
     assert xnor.lib().xnor_bingrad_conv2d(FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, FAKE, None, d, xnor.XNOR_ALGO_MFMA_F4, None) == ERR_HIP
+
+
+# (up to 16 channels: the parts are the faster form, and their image does not fit)
+@pytest.mark.parametrize("case", [(1072, 8, 7, 8, 512, 7, 7, (1, 2), (6, 0)), (112, 10, 278, 72, 512, 3, 3, (4, 2), (2, 0)), (8, 5, 34, 85, 512, 7, 5, (2, 3), (2, 4))])
+def test_binary_weight_layers_that_only_digits_stage(case):
+    assert xnor.lib().xnor_bwn_conv2d(FAKE, FAKE, FAKE, FAKE, ctypes.byref(xnor.make_desc(*case)), None) == ERR_HIP

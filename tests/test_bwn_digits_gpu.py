@@ -30,6 +30,7 @@ CASES = [
     (3, 33, 8, 8, 130, 5, 5, (1, 1), (2, 2)), (2, 65, 13, 13, 257, 5, 5, (1, 1), (2, 2)), (1, 96, 27, 27, 64, 5, 5, (1, 1), (2, 2)),
     (2, 160, 14, 14, 100, 5, 5, (2, 2), (1, 2)), (1, 290, 20, 20, 40, 5, 7, (1, 1), (2, 3)), (1, 512, 9, 9, 512, 5, 5, (1, 1), (2, 2)),
     (40, 64, 24, 24, 128, 3, 3, (1, 1), (1, 1)),                 # 3 x 3 with workgroups enough for digits
+    (8, 5, 34, 85, 512, 7, 5, (2, 3), (2, 4)),                   # parts are faster and do not fit
 ]
 
 
