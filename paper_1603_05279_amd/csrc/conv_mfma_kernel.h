@@ -966,14 +966,16 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
     if (FMT == 2 && strict) {
         // With one workgroup on a CU that has several to run nothing hides the conversion: a word's digits have to save 24 matrix
-        // instructions per 32 x 32 results over their taps, 84 where the words come in chunks (a 512-filter tile holds the CU
-        // whatever it stages).  Parts against digits, us (saved per word): 2 images of 35x50x50, 3x3 -> 448 (18) 13.4 / 20.7;
+        // instructions per 32 x 32 results over their taps (a 512-filter tile holds the CU whatever it stages).  Where the words
+        // come in chunks they have to save 84, or the tile one per staged word.  Parts against digits, us (saved per word): 2 images of 35x50x50, 3x3 -> 448 (18) 13.4 / 20.7;
         // 18 of 64x50x50, 3x3 -> 236 (31) 37.2 / 32.9; 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; in chunks 7 of 68x44x44, 3x3 -> 288
-        // (15) 26.7 / 45.3; 5 of 160x51x51, 5x5 -> 60 (75) 49.1 / 61.4; 20 of 192x34x34, 5x5 -> 32 (87) 82.3 / 73.6.  512 filters: 19 of
-        // 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
+        // (15) 26.7 / 45.3; 5 of 160x51x51, 5x5 -> 60 (75) 49.1 / 61.4; 20 of 192x34x34, 5x5 -> 32 (87) 82.3 / 73.6;
+        // 64 of 96x27x27, 5x5 -> 256 (67, 5.5 per staged word) 117 / 92.  512 filters: 19 of 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
         const bool wide = FW * PW > 6, chunks = !wide && pl.cc_words != g.cw;
-        if ((wide || (lds > 80 * 1024 && wg_count > 256)) && bwn_digits_save(g) < (chunks ? 84LL : 24LL) * g.cw)
-            return XNOR_ERR_UNSUPPORTED;
+        const long long saved = bwn_digits_save(g), staged = (long long)pl.max_rows * g.wp * g.cw;
+        const bool ahead = chunks ? saved >= 84LL * g.cw || saved * std::min(FT / 32, g.fblocks) * (PT / 32) >= staged
+                                  : saved >= 24LL * g.cw;
+        if ((wide || (lds > 80 * 1024 && wg_count > 256)) && !ahead) return XNOR_ERR_UNSUPPORTED;
     }
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
