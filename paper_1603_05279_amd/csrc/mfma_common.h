@@ -286,6 +286,8 @@ constexpr int ring_lcm(int a, int b)
 // each digit the nearest to what the digits before it left (those remainders are exact).  The last digit's step is the unit in
 // the last place of the word's largest input: that one is represented exactly, the others to half of that unit, which
 // is what a float sum that the largest one enters can hold of them (every filter adds all 32, weights are never 0).
+// Where |x| >= 2^127 the first digit is at most 1.875 and the next ones reach 4 in steps of 1/4: inputs from 1.9375 * 2^127 on
+// are held to a unit in the last place.
 // The matrix instruction multiplies E2M3 by the +-1 weights (E2M1, widened from packed bits as in the binary
 // convolution), applies the scales (activations: e, weights: the digit's 32^-k) and accumulates in float; 5 instructions of the
 // 4- and 6-bit rate per 64 channels take the place of 12 bfloat16 ones (three parts).
@@ -319,7 +321,16 @@ template <> struct Enc<2> : Enc<1> {
 #pragma unroll
         for (int k = 0; k < DIGITS; ++k) {
             const float scale = __builtin_bit_cast(float, (field - 5u * k) << 23);
-            const v6u d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(lo, hi, scale);
+            v16 l = lo, h = hi;
+            if (k == 0 && field == 254u) {       // the top binade: a first digit of 2 would stand for 2^128, which is no float
+                const float top = 1.875f * 0x1p127f;
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    l[i] = __builtin_fminf(__builtin_fmaxf(l[i], -top), top);
+                    h[i] = __builtin_fminf(__builtin_fmaxf(h[i], -top), top);
+                }
+            }
+            const v6u d = __builtin_amdgcn_cvt_scalef32_2xpk16_fp6_f32(l, h, scale);
 #pragma unroll
             for (int i = 0; i < 6; ++i) out[6 * k + i] = d[i];
             if (k + 1 < DIGITS) {
