@@ -18,6 +18,7 @@ namespace {
 struct PythonError {};
 
 PyObject *g_raise = nullptr;            // xnor.py's error for a non-zero status: raise(name, status)
+PyObject *g_desc = nullptr;             // xnor.py's descriptor class
 PyObject *g_current_device = nullptr, *g_raw_stream = nullptr;      // torch's, for calls without a stream
 
 [[noreturn]] void fail(PyObject *type, const char *message)
@@ -51,11 +52,15 @@ int num(PyObject *o)
     return (int)v;
 }
 
-// A descriptor (ctypes structure) through the buffer protocol; held for the duration of the call.
+// A descriptor (xnor.py's ctypes structure, nothing else that holds as many bytes) through the buffer protocol; held for the
+// duration of the call.
 struct Desc {
     Py_buffer view{};
     explicit Desc(PyObject *o)
     {
+        const int is = PyObject_IsInstance(o, g_desc);
+        if (is < 0) throw PythonError{};
+        if (!is) fail(PyExc_TypeError, "expected a convolution descriptor");
         if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) != 0) throw PythonError{};
         if (view.len != (Py_ssize_t)sizeof(xnor_conv_desc)) {
             PyBuffer_Release(&view);
@@ -162,12 +167,12 @@ template <class F> PyObject *guarded(const char *name, F call)
     }
 XNOR_CALLS(XNOR_WRAPPER)
 
-// bind(path of the library, raise(name, status), current_device(), raw_stream(device))
+// bind(path of the library, raise(name, status), current_device(), raw_stream(device), descriptor class)
 PyObject *bind(PyObject *, PyObject *args)
 {
     const char *path;
-    PyObject *raise, *device, *raw;
-    if (!PyArg_ParseTuple(args, "sOOO", &path, &raise, &device, &raw)) return nullptr;
+    PyObject *raise, *device, *raw, *desc;
+    if (!PyArg_ParseTuple(args, "sOOOO", &path, &raise, &device, &raw, &desc)) return nullptr;
     void *lib = dlopen(path, RTLD_NOW | RTLD_LOCAL);
     if (!lib) {
         PyErr_SetString(PyExc_ImportError, dlerror());
@@ -180,9 +185,9 @@ PyObject *bind(PyObject *, PyObject *args)
         return nullptr;                                                                 \
     }
     XNOR_CALLS(XNOR_LOOKUP)
-    Py_INCREF(raise); Py_INCREF(device); Py_INCREF(raw);
-    Py_XDECREF(g_raise); Py_XDECREF(g_current_device); Py_XDECREF(g_raw_stream);
-    g_raise = raise; g_current_device = device; g_raw_stream = raw;
+    Py_INCREF(raise); Py_INCREF(device); Py_INCREF(raw); Py_INCREF(desc);
+    Py_XDECREF(g_raise); Py_XDECREF(g_current_device); Py_XDECREF(g_raw_stream); Py_XDECREF(g_desc);
+    g_raise = raise; g_current_device = device; g_raw_stream = raw; g_desc = desc;
     Py_RETURN_NONE;
 }
 

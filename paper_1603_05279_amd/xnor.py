@@ -196,7 +196,7 @@ class _Unbound:
             raise ImportError("the binding is missing: build it with paper_1603_05279_amd/build.py") from e
         # (the raw handle alone: building torch's Stream object costs more than a kernel launch)
         _binding.bind(_LIB_PATH, _raise, torch.cuda.current_device,
-                      getattr(torch._C, "_cuda_getCurrentRawStream", _current_raw_stream))
+                      getattr(torch._C, "_cuda_getCurrentRawStream", _current_raw_stream), ConvDesc)
         _call = _binding
         return getattr(_binding, name)
 

@@ -1,4 +1,6 @@
 """Argument checks of the binding (csrc/binding.cpp): what is refused before any entry point runs (no GPU)."""
+import ctypes
+
 import pytest
 import torch
 
@@ -15,6 +17,17 @@ def test_tensor_arguments_are_checked_before_the_call():
         xnor.xnor_binactiv(None, None, None, None, None, None, 5)
     with pytest.raises(TypeError):
         xnor.xnor_binarize_pack(None, None, None, None, 1.5, 1, 1, 1)
+
+
+class _OtherStructure(ctypes.Structure):
+    _fields_ = [("v", ctypes.c_int * (ctypes.sizeof(xnor.ConvDesc) // 4))]
+
+
+@pytest.mark.parametrize("other", [bytes(ctypes.sizeof(xnor.ConvDesc)), bytearray(ctypes.sizeof(xnor.ConvDesc)), _OtherStructure(),
+                                   torch.zeros(ctypes.sizeof(xnor.ConvDesc), dtype=torch.uint8).numpy(), None])
+def test_only_a_descriptor_is_a_descriptor(other):
+    with pytest.raises(TypeError, match="descriptor"):
+        xnor.xnor_binactiv(None, None, None, None, None, None, other, stream=_Stream())
 
 
 class _Stream:
