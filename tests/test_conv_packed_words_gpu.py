@@ -134,3 +134,54 @@ def test_layers_whose_tile_does_not_fit_take_a_smaller_one(case):
     assert torch.equal(nx, bits)
     # two float sums of k positive terms in different orders: at most k roundings each
     assert torch.allclose(An, A2, rtol=2 * k * 2.0 ** -24, atol=0)
+
+
+def packed_block(c, h, k, r, n, seed):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    desc = xnor.make_desc(n, c, h, h, k, r, r, 1, r // 2)
+    bits = torch.randint(-(1 << 31), 1 << 31, (n, h, h, xnor.words_per_pixel(c)), generator=gen, device="cuda", dtype=torch.int64).int()
+    if c % 32:
+        bits[..., -1] &= (1 << (c % 32)) - 1
+    A = torch.rand((n, h, h), generator=gen, device="cuda")
+    pw = xnor.PackedWeights(torch.randn((k, c, r, r), generator=gen, device="cuda"))
+    ref = torch.full((n, k, h, h), float("nan"), device="cuda")
+    xnor.xnor_conv2d(bits, pw.wbits, pw.wmfma, None, A, pw.alpha, ref, None, desc, xnor.XNOR_ALGO_POPCOUNT)
+    sc, sh = torch.rand((k,), generator=gen, device="cuda") + 0.5, torch.randn((k,), generator=gen, device="cuda")
+    return desc, bits, A, pw, ref, sc, sh
+
+
+# (seven rows of 52 pixels under 64 results: 87 KB and more with every word, more than two workgroups of a CU may take; 15 words: the
+# last chunk lacks one)
+@pytest.mark.parametrize("tile,k", [(1, 100), (2, 64), (4, 200), (5, 256), (6, 225), (8, 500), (9, 384), (11, 33), (13, 128), (14, 97)])
+@pytest.mark.parametrize("c", [480, 512])
+def test_fused_epilogue_on_chunks_of_channel_words(c, tile, k):
+    print("case", c, tile, k, flush=True)
+    n, h = 32, 48
+    desc, bits, A, pw, ref, sc, sh = packed_block(c, h, k, 5, n, c + tile)
+    nx = torch.full((n, h, h, xnor.words_per_pixel(k)), -1, dtype=torch.int32, device="cuda")
+    An, out = torch.full((n, h, h), float("nan"), device="cuda"), torch.full_like(ref, float("nan"))
+    ws = torch.empty((max(16, xnor.conv2d_binactiv_workspace_bytes(desc)),), dtype=torch.uint8, device="cuda")
+    xnor.set_tuning(tile)
+    try:
+        xnor.xnor_conv2d_binactiv(bits, pw.wbits, pw.wmfma, None, A, pw.alpha, sc, sh, nx, An, out, ws, desc, xnor.XNOR_ALGO_MFMA_F4)
+    finally:
+        xnor.set_tuning(0)
+    assert torch.equal(out, ref)
+    bits2, A2 = torch.empty_like(nx), torch.empty_like(An)
+    xnor.xnor_binactiv(ref, sc, sh, bits2, A2, None, xnor.make_desc(n, k, h, h, 1, 1, 1))
+    assert torch.equal(nx, bits2)
+    # two float sums of k positive terms in different orders: at most k roundings each
+    assert torch.allclose(An, A2, rtol=2 * k * 2.0 ** -24, atol=0)
+
+
+# rows under three pooled ones: tiles of 96, 160 and 192 pixels; 17 words: the last chunk lacks one
+@pytest.mark.parametrize("h,r", [(28, 7), (38, 5), (60, 3)])
+@pytest.mark.parametrize("c", [544, 768, 1000])
+def test_pooled_epilogue_on_chunks_of_channel_words(c, h, r):
+    print("case", c, h, r, flush=True)
+    n, k = 3, 70
+    desc, bits, A, pw, ref, _, _ = packed_block(c, h, k, r, n, c + h)
+    hp = (h - 3) // 2 + 1
+    pooled = torch.full((n, k, hp, hp), float("nan"), device="cuda")
+    xnor.xnor_conv2d_pool(bits, pw.wmfma, None, A, pw.alpha, pooled, desc, (3, 3), (2, 2))
+    assert torch.equal(pooled, torch.nn.functional.max_pool2d(ref, 3, 2))
