@@ -150,14 +150,15 @@ def packed_block(c, h, k, r, n, seed):
     return desc, bits, A, pw, ref, sc, sh
 
 
-# (seven rows of 52 pixels under 64 results: 87 KB and more with every word, more than two workgroups of a CU may take; 15 words: the
-# last chunk lacks one)
-@pytest.mark.parametrize("tile,k", [(1, 100), (2, 64), (4, 200), (5, 256), (6, 225), (8, 500), (9, 384), (11, 33), (13, 128), (14, 97)])
+# Images whose rows under a tile do not fit two workgroups of a CU with every word (wide wave tiles: and do in two chunks); 15 words: the
+# last chunk lacks one
+@pytest.mark.parametrize("tile,k,n,h,r", [(1, 100, 40, 30, 3), (2, 64, 260, 16, 3), (4, 200, 32, 48, 5), (5, 256, 40, 30, 3), (6, 225, 32, 48, 5),
+                                          (8, 500, 32, 48, 5), (9, 384, 32, 48, 5), (11, 33, 32, 48, 5), (13, 128, 32, 48, 5),
+                                          (14, 97, 32, 48, 5)])
 @pytest.mark.parametrize("c", [480, 512])
-def test_fused_epilogue_on_chunks_of_channel_words(c, tile, k):
+def test_fused_epilogue_on_chunks_of_channel_words(c, tile, k, n, h, r):
     print("case", c, tile, k, flush=True)
-    n, h = 32, 48
-    desc, bits, A, pw, ref, sc, sh = packed_block(c, h, k, 5, n, c + tile)
+    desc, bits, A, pw, ref, sc, sh = packed_block(c, h, k, r, n, c + tile)
     nx = torch.full((n, h, h, xnor.words_per_pixel(k)), -1, dtype=torch.int32, device="cuda")
     An, out = torch.full((n, h, h), float("nan"), device="cuda"), torch.full_like(ref, float("nan"))
     ws = torch.empty((max(16, xnor.conv2d_binactiv_workspace_bytes(desc)),), dtype=torch.uint8, device="cuda")
