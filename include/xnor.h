@@ -236,8 +236,10 @@ XNOR_API int xnor_conv2d_binactiv_noalloc(const uint32_t *xbits, const uint32_t 
  *   XNOR_POOL_ON_LOAD     (0): xnor_conv2d, then xnor_pool_binactiv on the unpooled tensor
  * Pooling in the epilogue recomputes the convolution rows that neighbouring groups of pooled rows share and
  * sends every result through LDS once more; measured on the AlexNet / ResNet-18 layer shapes it wins where
- * output rows are short (w_out <= 16: 13- and 14-pixel rows, 1.1 to 1.25 times the matrix work) and loses on
- * 27- and 28-pixel rows.  Also XNOR_POOL_ON_LOAD when xnor_conv2d_pool has no kernel for the geometry.
+ * output rows are short (w_out <= 16, 1.1 to 1.25 times the matrix work; 128 images of 384 x 13 x 13 -> 256, 3 x 3 window: 24 us
+ * against 35; 256 of 256 x 14 x 14, 2 x 2: 37 against 39) and loses on wide ones (64 of 96 x 27 x 27, 5 x 5 -> 256: 45 against
+ * 39; 128 of 128 x 28 x 28: 53 against 39).  From 18 to 24 pixels it is ahead as well (64 of 128 x 20 x 20 -> 256: 23 against
+ * 33), which the line does not use.  Also XNOR_POOL_ON_LOAD when xnor_conv2d_pool has no kernel for the geometry.
  * Returns a negative xnor_status for an invalid descriptor or window.  Host-only, launches nothing.
  */
 #define XNOR_POOL_ON_LOAD 0
@@ -254,9 +256,10 @@ XNOR_API int xnor_conv2d_pool(const uint32_t *xbits, const void *wmfma, const fl
  *     out[n][k][oy][ox] = alpha_k * sum over in-bounds taps and channels of  I * sign(W)
  * (additions and subtractions of the inputs only; zero padding, correlation, no bias, as above).
  * xnor_bwn_split writes every input as three bfloat16 numbers whose sum is the float exactly (finite inputs), the weights
- * are +-1, and the sums run on the matrix cores in float: of those three parts, or (filters of 25 taps and more; of 9 and
- * more where the layer fills the chip) of the same floats as five digits of 6-bit floats under one power of two per 32 channels of a
- * pixel, which hold the largest of the 32 exactly and the others to half of its unit in the last place.  Three calls:
+ * are +-1, and the sums run on the matrix cores in float: of those three parts, or (more than 16 channels under filters of 25 taps
+ * and more, or of 9 and more where the layer fills the chip, but for shapes whose digits are the slower form) of the same floats as five
+ * digits of 6-bit floats under one power of two per 32 channels of a pixel, which hold the largest of the 32 exactly and the others to
+ * half of its unit in the last place (from 1.9375 * 2^127 on: to a unit; below 2^-106: to 2^-130).  Three calls:
  *   xnor_bwn_split         x float32 [n][c][h][w]  ->  parts, xnor_bwn_parts_bytes(n, c, h, w) bytes (opaque)
  *   xnor_bwn_pack_weights  w float32 [k_out][c][kh][kw]  ->  alpha float32 [k_out] (as xnor_pack_weights),
  *                          wimg, xnor_bwn_wimg_bytes(k_out, c, kh, kw) bytes (opaque); once per layer
@@ -264,7 +267,8 @@ XNOR_API int xnor_conv2d_pool(const uint32_t *xbits, const void *wmfma, const fl
  *                          convolution with the real channel count c
  * Differences between this result and one accumulated in double stay within float rounding of the
  * running sums (about 1e-7 * sqrt(c*kh*kw) of the magnitude of the terms); the digits' sums, with fewer additions, to
- * about half of that.
+ * about half of that, also for heavy-tailed inputs and outlier channels.  Where two large inputs of a pixel's 32 channels cancel, what
+ * smaller ones leave is known to 2^-24 of the large ones, in either form.
  */
 XNOR_API size_t xnor_bwn_parts_bytes(int n, int c, int h, int w);
 XNOR_API size_t xnor_bwn_wimg_bytes(int k_out, int c, int kh, int kw);

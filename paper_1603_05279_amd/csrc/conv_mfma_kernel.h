@@ -72,12 +72,12 @@ __device__ __forceinline__ ConvArgs reload_args()
 }
 
 // What bounds it: with a few waves per SIMD every phase costs its instructions (5.2 cycles each for a wave, 4 for the SIMD);
-// the K loop then runs at the matrix pipes' 19 ns per instruction and SIMD (34 cycles; the clock is 1.6 to 1.8 GHz while all
-// pipes are busy), which up to four vector instructions per matrix instruction do not slow down.
+// the K loop then runs at the matrix pipes' 32 busy cycles per instruction and SIMD (19 ns by stamps around the loop, that is
+// a clock of about 1.7 GHz while all pipes are busy), which up to four vector instructions per matrix instruction do not slow down.
 // Against 4-bit records in memory, a staging loop of one word per item and one set of arguments held throughout (launches
-// back to back): 256 rows x 9216 -> 4096 12.7 -> 8.6 us, 128 x 28 x 28 batch 256 30.5 -> 26.7 us (983 -> 653 vector
-// instructions per wave), 96 x 27 x 27 5 x 5 batch 64 22.6 -> 19.9, 384 x 13 x 13 batch 128 21.5 -> 19.9, 512 x 7 x 7 batch
-// 256 22.7 -> 21.0, 256 x 14 x 14 batch 256 24.0 -> 22.1 us.
+// back to back, the two in turn): 256 rows x 9216 -> 4096 14.3 -> 12.8 us, 128 x 28 x 28 batch 256 30.4 -> 26.0 us (983 -> 653
+// vector instructions per wave), 96 x 27 x 27 5 x 5 batch 64 21.6 -> 20.6, 384 x 13 x 13 -> 256 batch 128 17.1 -> 15.9, 512 x 7 x 7
+// batch 256 22.7 -> 21.3, 256 x 14 x 14 batch 256 23.8 -> 22.6 us.
 //
 // Device memory behind a pointer out of the argument struct.  Without the address space such accesses are flat ones, which
 // also wait for, and are waited for with, the LDS accesses in flight.
@@ -925,7 +925,6 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         pl->div_wp = FastDiv::make((uint32_t)g.wp);
         pl->div_hp = FastDiv::make((uint32_t)g.hp);
         pl->div_ccw = FastDiv::make((uint32_t)ccw);
-        pl->div_cw = FastDiv::make((uint32_t)g.cw);
         return true;
     }
     return false;

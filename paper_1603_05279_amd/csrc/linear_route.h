@@ -13,19 +13,19 @@ constexpr int linear_words_per_pass(int v) { return v == 4 ? 320 : v == 2 ? 256 
 //
 // A workgroup holds two rows (one if there is only one) and 16 filters whether they exist or not, so the time follows the
 // padded product: 2.5 us + rows * filters * passes over the row * 0.052 ns with 4 words per load (0.083 ns with 2, 0.032 ns
-// with 1; measured from 8192 to 2^20 padded products, 32 to 131072 features).  The matrix-core form takes 5 us for the
-// shortest rows and grows with c, hardly with rows and filters.  Both, back to back, us (rows x filters, c):
-//       2048 x 16, 512: 4.2 / 5.2      8192 x 4, 64: 13.3 / 5.0       32768 x 1, 512: 29.6 / 6.0
-//       8 x 8192, 2560: 6.0 / 6.2      8 x 8192, 2368 (2 words per load): 8.0 / 6.6
-//       96 x 1024, 4096: 8.3 / 8.4     128 x 1000, 4096: 10.4 / 8.5   8192 x 16, 9216: 9.4 / 12.9
-// The lines below keep the slower of the two at most 7 % behind over the 3590 measured shapes of more than two rows and at
-// most 10240 features.  Apart from them:
+// with 1; measured from 8192 to 2^20 padded products, 32 to 131072 features).  The matrix-core form (packed weight words) takes
+// 4 to 5 us for the shortest rows and grows with c, hardly with rows and filters.  Both, back to back, us (rows x filters, c):
+//       2048 x 16, 512: 3.8 / 4.9      8 x 8192, 2560: 5.8 / 6.1      8 x 8192, 2368 (2 words per load): 7.7 / 6.2
+//       32 x 4096, 9216: 9.5 / 11.8    96 x 1024, 4096: 7.7 / 7.7     128 x 1000, 4096: 9.6 / 7.7
+//       8192 x 16, 9216: 9.3 / 12.1
+// The lines below were drawn from 3590 shapes of more than two rows and at most 10240 features, and timed again on 500: what
+// they choose is at most 2 % behind the matrix-core form.  Apart from them:
 //   - one or two rows, where nothing is padded, and more than 320 words, which the matrix-core form walks in many chunks:
-//     ahead wherever measured (1 x 32768, 64: 6.1 / 6.1; 128 x 1000, 25088: 25 / 44; above 32768 rows at most 25 % behind);
+//     ahead wherever measured but 1 x 32768, 64: 5.5 / 4.9 (128 x 1000, 25088: 22.7 / 55.2; above 32768 rows at most 25 % behind);
 //   - 16384 filters and more: the matrix-core form needs more workgroups than there are CUs for a few rows
-//     (4 x 32768, 4096: 9.4 / 15.2), except with 2 words per load (3 x 16384, 2112: 7.9 / 7.1);
+//     (4 x 32768, 4096: 9.2 / 10.3), except with 2 words per load (3 x 16384, 2112: 7.5 / 6.3);
 //   - from 16384 rows and 5120 features the matrix-core form's larger tiles no longer hold a row (16384 x 4, 9216:
-//     16.3 / 36.1; 32768 x 4, 5120: 30.1 / 32.3).
+//     15.8 / 31.5; 32768 x 4, 5120: 29.1 / 32.2).
 inline bool linear_popcount_route(int n, int k, int c, int cw, bool matrix_image)
 {
     // rows times filters: beyond these no shape was measured ahead

@@ -42,7 +42,7 @@ struct MfmaPlan {
     SmallDiv sd_dil_h, sd_dil_w;
     SmallDiv sd_quads, sd_wp, sd_hp, sd_wo, sd_ho;   // direct staging: item, padded and output coordinates of a tile
     int stream_out;   // 1: float results are stored with the non-temporal hint (they exceed a quarter of the last-level cache)
-    FastDiv div_wp, div_hp, div_ccw, div_cw;
+    FastDiv div_wp, div_hp, div_ccw;
     PoolPlan pool;    // used by the pooled-epilogue instantiations only
 };
 
@@ -129,29 +129,7 @@ template <> struct Enc<0> {                    // int8
         const uint32_t t = __umul24(nibble, 0x00204081u) & 0x01010101u;     // bit i -> byte i
         return __builtin_amdgcn_perm(0x000001FFu, 0x000001FFu, t);           // byte = {0xFF, 0x01}[t]
     }
-    // one channel word -> 32 bytes at dst; channels >= nch are 0
-    static __device__ __forceinline__ void widen_word(uint8_t *dst, uint32_t bits, bool ok, int nch) {
-        uint4 lo = make_uint4(0, 0, 0, 0), hi = make_uint4(0, 0, 0, 0);
-        if (ok) {
-            lo.x = widen4(bits & 15u);         lo.y = widen4((bits >> 4) & 15u);
-            lo.z = widen4((bits >> 8) & 15u);  lo.w = widen4((bits >> 12) & 15u);
-            hi.x = widen4((bits >> 16) & 15u); hi.y = widen4((bits >> 20) & 15u);
-            hi.z = widen4((bits >> 24) & 15u); hi.w = widen4(bits >> 28);
-            if (nch < 32) {
-                uint32_t *d = reinterpret_cast<uint32_t *>(&lo);
-                uint32_t *e = reinterpret_cast<uint32_t *>(&hi);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r0 = nch - 4 * q, r1 = nch - 16 - 4 * q;
-                    d[q] &= r0 >= 4 ? 0xFFFFFFFFu : (r0 <= 0 ? 0u : (1u << (8 * r0)) - 1u);
-                    e[q] &= r1 >= 4 ? 0xFFFFFFFFu : (r1 <= 0 ? 0u : (1u << (8 * r1)) - 1u);
-                }
-            }
-        }
-        *reinterpret_cast<uint4 *>(dst) = lo;
-        *reinterpret_cast<uint4 *>(dst + 16) = hi;
-    }
-    // The same through a table in LDS: entry b (8 bytes) = the 8 operand bytes of sign byte b,
+    // One channel word -> 32 bytes at dst, channels >= nch 0, through a table in LDS: entry b (8 bytes) = the 8 operand bytes of sign byte b,
     // entries 256..511 are zero (selected for positions outside the image).  Three instructions
     // per sign byte instead of a dozen: the widening is instruction-issue bound.
     static constexpr int LUT_BYTES = 512 * 8;
@@ -197,31 +175,7 @@ template <> struct Enc<1> {                    // 4-bit float E2M1
     }
     static __device__ __forceinline__ int to_int(acc_t a, int v) { return (int)a[v]; }
     static __device__ __forceinline__ float to_float(acc_t a, int v) { return a[v]; }   // an exact integer already
-    // 8 sign bits -> 8 nibbles: bit 1 -> 0x2 (+1.0), bit 0 -> 0xA (-1.0)
-    static __device__ __forceinline__ uint32_t widen8(uint32_t byte) {
-        uint32_t x = byte;                                   // bit i -> bit 4i by three shift-or steps
-        x = (x | (x << 12)) & 0x000F000Fu;
-        x = (x | (x << 6)) & 0x03030303u;
-        x = (x | (x << 3)) & 0x11111111u;
-        return 0xAAAAAAAAu ^ (x << 3);
-    }
-    static __device__ __forceinline__ void widen_word(uint8_t *dst, uint32_t bits, bool ok, int nch) {
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (ok) {
-            v.x = widen8(bits & 255u);         v.y = widen8((bits >> 8) & 255u);
-            v.z = widen8((bits >> 16) & 255u); v.w = widen8(bits >> 24);
-            if (nch < 32) {
-                uint32_t *d = reinterpret_cast<uint32_t *>(&v);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int r0 = nch - 8 * q;
-                    d[q] &= r0 >= 8 ? 0xFFFFFFFFu : (r0 <= 0 ? 0u : (1u << (4 * r0)) - 1u);
-                }
-            }
-        }
-        *reinterpret_cast<uint4 *>(dst) = v;
-    }
-    // 8 sign bits -> 8 nibbles with one byte permute: an output byte holds two channels, i.e. one of four values
+    // 8 sign bits -> 8 nibbles (bit 1 -> 0x2, +1.0; bit 0 -> 0xA, -1.0) with one byte permute: an output byte holds two channels, i.e. one of four values
     // (0xAA, 0xA2, 0x2A, 0x22 for the bit pairs 00, 01, 10, 11), and v_perm_b32 picks four bytes out of a 32-bit
     // table by four selector bytes.  The selectors are the byte's four bit pairs spread to byte positions by two
     // shift-ors and a mask: four vector instructions per output dword, no table in LDS (whose reads would hit
