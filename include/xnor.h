@@ -255,11 +255,12 @@ XNOR_API int xnor_conv2d_pool(const uint32_t *xbits, const void *wmfma, const fl
  * estimated by alpha * sign(W):
  *     out[n][k][oy][ox] = alpha_k * sum over in-bounds taps and channels of  I * sign(W)
  * (additions and subtractions of the inputs only; zero padding, correlation, no bias, as above).
- * xnor_bwn_split writes every input as three bfloat16 numbers whose sum is the float exactly (finite inputs), the weights
- * are +-1, and the sums run on the matrix cores in float: of those three parts, or (more than 16 channels under filters of 25 taps
- * and more, or of 9 and more where the layer fills the chip, but for shapes whose digits are the slower form) of the same floats as five
- * digits of 6-bit floats under one power of two per 32 channels of a pixel, which hold the largest of the 32 exactly and the others to
- * half of its unit in the last place (from 1.9375 * 2^127 on: to a unit; below 2^-106: to 2^-130).  Three calls:
+ * The weights are +-1 and the sums run on the matrix cores in float.  Inputs of more than 32 channels are five digits of 6-bit floats
+ * under one power of two per 32 channels of a pixel, which hold the largest of the 32 exactly and the others to half of its unit in the
+ * last place (from 1.9375 * 2^127 on: to a unit; below 2^-106: to 2^-130).  Up to 32 channels xnor_bwn_split writes every input as three
+ * bfloat16 numbers whose sum is the float exactly (finite inputs), and the sums are of those three parts, or (more than 16 channels
+ * under filters of 25 taps and more, or of 9 and more where the layer fills the chip, but for shapes whose digits are the slower form)
+ * of the same floats as digits.  Three calls:
  *   xnor_bwn_split         x float32 [n][c][h][w]  ->  parts, xnor_bwn_parts_bytes(n, c, h, w) bytes (opaque)
  *   xnor_bwn_pack_weights  w float32 [k_out][c][kh][kw]  ->  alpha float32 [k_out] (as xnor_pack_weights),
  *                          wimg, xnor_bwn_wimg_bytes(k_out, c, kh, kw) bytes (opaque); once per layer

@@ -1,18 +1,11 @@
 // Binary-Weight-Network convolution (sec. 3.1): real-valued inputs, weights estimated as alpha * sign(W),
 //     I * W  ~  (I (+) B) alpha        (convolution with additions and subtractions only).
-// The activations travel as three bfloat16 parts per float (their sum is the float exactly); the convolution kernel
-// (conv_mfma_kernel.h) stages them as digits of 6-bit floats (Enc<2>) or as they are (Enc<4>); the matrix cores
-// accumulate in float either way.  This file holds the two preparation kernels: the activation split and the weights.
-#include "xnor_internal.h"
+// The activations travel as five digits of 6-bit floats (Enc<2>, more than 32 channels) or as three bfloat16 parts per float (their sum
+// is the float exactly); the convolution kernel (conv_mfma_kernel.h) stages the digits as they are, the parts as they are (Enc<4>) or as
+// digits; the matrix cores accumulate in float.  This file holds the preparation kernels: the activation split and the weights.
+#include "mfma_common.h"
 
 namespace xnor {
-
-__device__ __forceinline__ uint32_t bf16_rne(float v)      // round to nearest even (finite inputs)
-{
-    const uint32_t u = __builtin_bit_cast(uint32_t, v);
-    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
-}
-__device__ __forceinline__ float bf16_value(uint32_t h) { return __builtin_bit_cast(float, h << 16); }
 
 // x [n][c][hw] float  ->  parts [n][hw][Cg][3][16] bfloat16, Cg = ceil(c/16): for every pixel and group
 // of 16 channels three 32-byte words (hi, mid, lo) with hi + mid + lo == x exactly; channels >= c are 0.
@@ -63,8 +56,66 @@ __global__ __launch_bounds__(256) void bwn_split_kernel(const float *__restrict_
     }
 }
 
+// x [n][c][hw] float  ->  digits [n][hw][ceil(c/32)][128 bytes] (Enc<2>).  A wave makes one channel word of 64 pixels that follow
+// each other in the batch, a pixel per lane: 32 loads in flight, 64 neighbouring floats each; the words turn in LDS (rows of 144 bytes: 16-byte
+// accesses of neighbouring lanes on different banks), so that every pixel's 128 bytes leave as one run.  Waves share nothing.
+// What bounds it: memory, 4 bytes read and 4 written per input (128 images of 256x13x13: 8.3 us, 5.3 TB/s; three parts per input, 10
+// bytes, took 11 us).  Made here a digit is made once; made by the convolution while it stages a tile, every filter tile and every halo
+// repeated it: conversion and staging were half of that kernel's time (the same inputs, 3x3 -> 384: convolution 64 -> 55 us).
+constexpr int DIGITS_ROW = 144;
+__global__ __launch_bounds__(256) void bwn_digits_kernel(const float *__restrict__ x, uint8_t *__restrict__ out, int c, int hw, int cw,
+                                                         uint32_t pixels, uint32_t tiles, FastDiv div_tiles, FastDiv div_hw)
+{
+    extern __shared__ __attribute__((aligned(16))) uint8_t stage[];
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Neighbouring pixel tiles share cache lines (channel rows are not line aligned): in every whole window of 64 workgroups each of
+    // the 8 XCDs, which take workgroups in turn, has a run of 8
+    const uint32_t b = blockIdx.x, win = b >> 6 << 6;
+    const uint32_t blk = win + 64u <= gridDim.x ? win + ((b & 7u) << 3) + ((b >> 3) & 7u) : b;
+    const uint32_t group = div_tiles.div(blk), tile = blk - group * tiles;
+    const int word = (int)(group * (blockDim.x >> 6)) + wave;
+    if (word >= cw) return;
+    const uint32_t m0 = tile * 64u, m = min(m0 + lane, pixels - 1u), img = div_hw.div(m);
+    const float *xi = x + ((size_t)img * c + (size_t)word * 32) * hw + (m - img * (uint32_t)hw);
+    const int left = c - word * 32;
+    float v[32];
+#pragma unroll
+    for (int j = 0; j < 32; ++j) v[j] = xi[(size_t)min(j, left - 1) * hw];
+    if (left < 32) {
+#pragma unroll
+        for (int j = 1; j < 32; ++j) v[j] = j < left ? v[j] : 0.0f;
+    }
+    uint32_t d[32];
+    Enc<2>::digits(v, d);
+    uint8_t *slab = stage + wave * 64 * DIGITS_ROW;
+    uint4 *dst = reinterpret_cast<uint4 *>(slab + lane * DIGITS_ROW);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) dst[q] = make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+    __builtin_amdgcn_wave_barrier();          // (LDS serves one wave's instructions in order)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+        const uint32_t px = i * 8 + (lane >> 3), unit = lane & 7;
+        const uint4 r = *reinterpret_cast<const uint4 *>(slab + px * DIGITS_ROW + unit * 16);
+        if (m0 + px < pixels) *reinterpret_cast<uint4 *>(out + ((size_t)(m0 + px) * cw + word) * 128 + unit * 16) = r;
+    }
+}
+
+static xnor_status launch_bwn_digits(const float *x, void *out, int n, int c, int hw, hipStream_t stream)
+{
+    const int cw = (c + 31) / 32;
+    const int groups = (cw + 3) / 4, waves = (cw + groups - 1) / groups;         // up to four words per workgroup, evenly
+    const long long pixels = (long long)n * hw, tiles = (pixels + 63) / 64;
+    if (tiles * groups > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;
+    bwn_digits_kernel<<<dim3((unsigned)(tiles * groups)), dim3(64 * waves), (size_t)waves * 64 * DIGITS_ROW, stream>>>(
+        x, static_cast<uint8_t *>(out), c, hw, cw, (uint32_t)pixels, (uint32_t)tiles, FastDiv::make((uint32_t)tiles),
+        FastDiv::make((uint32_t)hw));
+    return hip_status(hipGetLastError());
+}
+
 xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, hipStream_t stream)
 {
+    if (bwn_in_digits(c)) return launch_bwn_digits(x, parts, n, c, hw, stream);
     const int cg = (c + 15) / 16;
     const int gblocks = (cg + SPLIT_G - 1) / SPLIT_G;
     if (gblocks > 65535 || n > 65535) return XNOR_ERR_UNSUPPORTED;

@@ -89,7 +89,7 @@ template <class T> __device__ __forceinline__ global_t<T> *in_global(T *p) { ret
 // their accumulators through LDS at the end: more weight loads in flight and more waves for the staging where a
 // problem offers few output tiles and a long K (fully connected layers).  Consecutive-record streams only.
 template <int FMT, int FW, int PW, int WF, int WP, bool FUSE, bool LINEAR, bool POOL = false, int KS = 1, bool DIRECT_CHUNKS = false>
-__global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 4 ? 6 : 8) && WF * WP * KS <= 8 ? 2 : 1)) void conv_mfma_kernel(
+__global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 4 || FMT == 6 ? 6 : 8) && WF * WP * KS <= 8 ? 2 : 1)) void conv_mfma_kernel(
     ConvArgs args)
 {
     const uint32_t *xbits = args.xbits;
@@ -117,7 +117,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
     // (Packed words cost one register per step: five steps throughout.)
     // A wave tile of a single result block (fully connected layers: few output tiles, long K) issues one matrix
     // instruction per record: only a deep ring keeps enough bytes in flight to cover the L2 latency.
-    constexpr int DW = FMT == 2 || FMT == 4 ? 3 : (FW * PW == 1 && FMT < 2 && !FUSE) ? 7 : (FMT == 1) ? 5 : (FUSE || FT <= 64) ? 3 : 5;      // (bfloat16 parts: a step is three times as long)
+    constexpr int DW = FMT == 2 || FMT == 4 || FMT == 6 ? 3 : (FW * PW == 1 && FMT < 2 && !FUSE) ? 7 : (FMT == 1) ? 5 : (FUSE || FT <= 64) ? 3 : 5;      // (bfloat16 parts: a step is three times as long)
     extern __shared__ __attribute__((aligned(16))) uint8_t lds[];
     int *rowinfo = reinterpret_cast<int *>(lds + pl.region_bytes);
     int *xoff_tab = rowinfo + pl.max_rows;     // [(nsteps + KLOOP_TABLE_PAD) * BPS]
@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         for (int j = 0; j < PW; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0;
-    const int steps_per_tap = pl.tap_jump ? ccw / E::BPS : 0x7fffffff;
+    const int steps_per_tap = pl.tap_jump ? max(ccw / E::BPS, 1) : 0x7fffffff;
     for (int wbase = 0; ONE ? wbase < 1 : wbase < args.g.cw; wbase += ONE ? 1 : ccw) {
         // (read per chunk: otherwise everything a chunk derives from them is hoisted in front of the first one and held.  Raw
         // operands hold little: there the loads cost more, 4 images of 32x12x12 -> 497, 1x1, int8 levels 4.6 us with them, 4.3 without)
@@ -296,6 +296,30 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         const ConvGeom &g = now.g;
         const MfmaPlan &pl = now.pl;
         const v4i *wimg = now.wimg;
+        // packed weight words, widened in the K loop: the first steps' are requested ahead of the staging, which hides their latency
+        // (a register per step and filter block)
+        constexpr bool WORDS = FMT == 1 || FMT == 2;
+        const int per = (nsteps + KS - 1) / KS;
+        const int s0 = KS > 1 ? __builtin_amdgcn_readfirstlane(wk * per) : 0;
+        const int ns = KS > 1 ? max(0, min(per, nsteps - s0)) : nsteps;
+        auto words_of = [&] {
+            int fblk[FW];
+#pragma unroll
+            for (int i = 0; i < FW; ++i)
+                fblk[i] = __builtin_amdgcn_readfirstlane(min(f0 / 32 + wf * FW + i, g.fblocks - 1));
+            const bool odd = (g.taps * ccw) % 2 != 0 && s0 + ns == nsteps;
+            return WStreamBits<FW, LINEAR, KS != 1 ? 2 : 0>(reinterpret_cast<const uint32_t *>(wimg), fblk, g.taps * g.cw,
+                                                            wbase + s0 * E::BPS, ns, odd, lane, steps_per_tap, pl.tap_jump,
+                                                            FMT == 2 && ccw == 1 ? g.cw : 1);
+        };
+        typedef typename std::conditional<WORDS, uint32_t, v4i>::type weight_t;
+        weight_t w[DW + 1][FW];
+        typename std::conditional<WORDS, WStreamBits<FW, LINEAR, KS != 1 ? 2 : 0>, int>::type words{};
+        if constexpr (WORDS) {
+            words = words_of();
+#pragma unroll
+            for (int u = 0; u < DW; ++u) words.load(w[u]);
+        }
         if (wbase > 0 || !ONE || E::LUT_BYTES > 0) __syncthreads();   // tables visible / previous chunk fully consumed
         const bool stageA = !RAW && wbase == 0 && !K;
         if constexpr (DIRECT) {
@@ -388,30 +412,51 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         } else {
         const int items = nrows * g.wp * ccw;
         if constexpr (FMT == 2) {
-            // 32 channels of a pixel per item: two groups of three bfloat16 parts (192 bytes), summed back to floats (exact),
-            // to digits
-            const int groups = (g.c + 15) / 16;
-            for (int it = tid; it < items; it += NT) {
-                const uint32_t px = pl.div_ccw.div_small((uint32_t)it);
-                const int wl = it - (int)px * ccw;
-                const uint32_t rr = pl.div_wp.div_small(px);
-                const int xcol = (int)(px - rr * g.wp) - g.pw;
+            if (g.cw > 1) {
+                // digits as the split wrote them: 16 of a word's 128 bytes per item, a pixel's words of the chunk one after the other
+                constexpr int FB = 4;          // items in flight per thread
+                const int units = items * 8;
+                for (int it0 = tid; it0 < units; it0 += NT * FB) {
+                    v4u d[FB];
+                    int dst[FB];
+#pragma unroll
+                    for (int u = 0; u < FB; ++u) {
+                        const int it = it0 + u * NT;
+                        const uint32_t item = (uint32_t)min(it, units - 1) >> 3, unit = (uint32_t)it & 7u;
+                        const uint32_t px = pl.div_ccw.div_small(item);
+                        const int wl = (int)(item - px * ccw);
+                        const uint32_t rr = pl.div_wp.div_small(px);
+                        const int xcol = (int)(px - rr * g.wp) - g.pw;
+                        const int rowbase = rowinfo[rr];
+                        const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w && wbase + wl < g.cw;
+                        dst[u] = it < units ? (int)(rr * pl.row_pitch + (px - rr * g.wp) * pl.ps + wl * E::BPB + unit * 16) : -1;
+                        const uint32_t word = ok ? (uint32_t)(rowbase + xcol) * (uint32_t)g.cw + (uint32_t)(wbase + wl) : 0u;
+                        d[u] = in_global(reinterpret_cast<const v4u *>(xbits))[(size_t)word * 8 + unit];
+                        if (!ok) d[u] = v4u{0, 0, unit == 7u ? 127u : 0u, 0};
+                    }
+#pragma unroll
+                    for (int u = 0; u < FB; ++u)
+                        if (dst[u] >= 0) *reinterpret_cast<v4u *>(lds + dst[u]) = d[u];
+                }
+            } else {
+            // at most 32 channels of a pixel per item: one or two groups of three bfloat16 parts (96 bytes each), summed back to
+            // floats (exact), to digits
+            const bool second = g.c > 16;
+            for (int px = tid; px < items; px += NT) {
+                const uint32_t rr = pl.div_wp.div_small((uint32_t)px);
+                const int xcol = px - (int)rr * g.wp - g.pw;
                 const int rowbase = rowinfo[rr];
-                const int grp = 2 * (wbase + wl);
-                const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w && grp < groups;
-                v4u *dst = reinterpret_cast<v4u *>(lds + rr * pl.row_pitch + (px - rr * g.wp) * pl.ps + wl * E::BPB);
+                const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w;
+                v4u *dst = reinterpret_cast<v4u *>(lds + rr * pl.row_pitch + (px - (int)rr * g.wp) * pl.ps);
                 if (!ok) {
 #pragma unroll
                     for (int q = 0; q < 8; ++q) dst[q] = v4u{0, 0, q == 7 ? 127u : 0u, 0};
                     continue;
                 }
-                const auto *src = in_global(reinterpret_cast<const v4u *>(xbits)) + (((size_t)rowbase + xcol) * groups + grp) * 6;
+                const auto *src = in_global(reinterpret_cast<const v4u *>(xbits)) + ((size_t)rowbase + xcol) * (second ? 12 : 6);
                 v4u p[12];
 #pragma unroll
-                for (int q = 0; q < 6; ++q) p[q] = src[q];
-                const int second = grp + 1 < groups ? 6 : 0;      // (no second group: the first one again, cleared below)
-#pragma unroll
-                for (int q = 0; q < 6; ++q) p[6 + q] = src[second + q];
+                for (int q = 0; q < 12; ++q) p[q] = src[q < 6 || second ? q : q - 6];     // (no second group: the first one again, cleared below)
                 float x[32];
 #pragma unroll
                 for (int c = 0; c < 32; ++c) {
@@ -426,6 +471,27 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                 E::digits(x, out);
 #pragma unroll
                 for (int q = 0; q < 8; ++q) dst[q] = v4u{out[4 * q], out[4 * q + 1], out[4 * q + 2], out[4 * q + 3]};
+            }
+            }
+        } else if constexpr (FMT == 6) {
+            // the three parts of 16 channels of a pixel per item, from their half of a word of digits
+            const int cg = ccw / 3, words = (g.cw / 3 + 1) / 2;
+            for (int it = tid; it < items / 3; it += NT) {
+                const int px = it / cg, grp = wbase / 3 + it - px * cg;
+                const uint32_t rr = pl.div_wp.div_small((uint32_t)px);
+                const int xcol = px - (int)rr * g.wp - g.pw;
+                const int rowbase = rowinfo[rr];
+                v4u parts[6] = {};
+                if (rowbase >= 0 && xcol >= 0 && xcol < g.w) {
+                    const auto *src = in_global(reinterpret_cast<const v4u *>(xbits)) + (((size_t)rowbase + xcol) * words + grp / 2) * 8;
+                    v4u word[8];
+#pragma unroll
+                    for (int q = 0; q < 8; ++q) word[q] = src[q];
+                    E::parts_of_digits(word, grp & 1, parts);
+                }
+                v4u *dst = reinterpret_cast<v4u *>(lds + rr * pl.row_pitch + (px - (int)rr * g.wp) * pl.ps + (it - px * cg) * 3 * E::BPB);
+#pragma unroll
+                for (int q = 0; q < 6; ++q) dst[q] = parts[q];
             }
         } else {
         constexpr int FB = RAW ? 4 : 8;        // items in flight per thread: loads first, then widening (every batch costs one round trip to L2 or HBM)
@@ -517,35 +583,28 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
 
         // ---- software-pipelined K loop over this chunk's steps --------------------------------
         // record of step s: rec0 + s + (s / steps_per_tap) * tap_jump
-        if constexpr (FMT == 1 || FMT == 2) {
-            // packed words, widened in the K loop
-            int fblk[FW];
+        auto request = [&](auto &ws) {
 #pragma unroll
-            for (int i = 0; i < FW; ++i)
-                fblk[i] = __builtin_amdgcn_readfirstlane(min(f0 / 32 + wf * FW + i, g.fblocks - 1));
-            const int nblk = g.taps * g.cw;
-            const int per = (nsteps + KS - 1) / KS;
-            const int s0 = KS > 1 ? __builtin_amdgcn_readfirstlane(wk * per) : 0;
-            const int ns = KS > 1 ? max(0, min(per, nsteps - s0)) : nsteps;
-            const bool odd = (g.taps * ccw) % 2 != 0 && s0 + ns == nsteps;
-            WStreamBits<FW, LINEAR, KS != 1 ? 2 : 0> ws(reinterpret_cast<const uint32_t *>(wimg), fblk, nblk,
-                                                        wbase + s0 * E::BPS, ns, odd, lane, steps_per_tap, pl.tap_jump);
-            if constexpr (FMT == 2) mfma_kloop_digits<FW, PW, DW>(acc, lds, pbase, xoff_tab, tab_lane, ws, ns);
-            else mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab + s0 * E::BPS, tab_lane, ws, ns);
+            for (int u = 0; u < DW; ++u) ws.load(w[u]);
+        };
+        if constexpr (FMT == 2) {
+            mfma_kloop_digits<FW, PW, DW>(acc, lds, pbase, xoff_tab, tab_lane, words, w, ns);
+        } else if constexpr (WORDS) {
+            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab + s0 * E::BPS, tab_lane, words, w, ns);
         } else if constexpr (LINEAR && KS > 1) {
-            const int per = (nsteps + KS - 1) / KS;
-            const int s0 = __builtin_amdgcn_readfirstlane(wk * per);
-            const int ns = max(0, min(per, nsteps - s0));
             // (problems that take this form are all weights: an image read once per call, which passes every XCD's L2 on its
             // way and should not settle in the last-level cache: fully connected layer inside a step 27.3 -> 24.3 us)
             WStreamLinear<FW, 2> ws(wimg, wrec0, wbase / E::BPS + s0, ns, wlane);
-            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab + s0 * E::BPS, tab_lane, ws, ns);
+            request(ws);
+            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab + s0 * E::BPS, tab_lane, ws, w, ns);
         } else if constexpr (LINEAR) {      // the chunk holds every channel word: consecutive records
             WStreamLinear<FW> ws(wimg, wrec0, wbase / E::BPS, nsteps, wlane);
-            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab, tab_lane, ws, nsteps);
+            request(ws);
+            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab, tab_lane, ws, w, nsteps);
         } else {
             WStreamChunked<FW> ws(wrsrc, wrec0, zero_rec, wbase / E::BPS, nsteps, steps_per_tap, pl.tap_jump, wlane);
-            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab, tab_lane, ws, nsteps);
+            request(ws);
+            mfma_kloop<E, FW, PW, DW, 1>(acc, lds, pbase, xoff_tab, tab_lane, ws, w, nsteps);
         }
     }
     {
@@ -865,7 +924,7 @@ constexpr int LDS_LIMIT = 160 * 1024;
 // fuse_rows: rows of PT words for the fused epilogue's |z| sums and sign words (0 without it)
 // par_bytes: alpha (fused epilogue: also scale and shift) of the workgroup's filters
 // channel words per K-step and bytes of the widening table of an operand format (Enc<fmt>::BPS, LUT_BYTES)
-static constexpr int fmt_bps(int fmt) { return fmt == 1 || fmt == 2 || fmt == 5 ? 2 : fmt == 4 ? 3 : 1; }
+static constexpr int fmt_bps(int fmt) { return fmt == 1 || fmt == 2 || fmt == 5 ? 2 : fmt == 4 || fmt == 6 ? 3 : 1; }
 static constexpr int fmt_lut_bytes(int fmt) { return fmt == 0 ? 512 * 8 : 0; }     // int8 operands only
 static size_t plan_lds_bytes(const MfmaPlan &pl, int fmt, int wp, int PT, int fuse_rows, int par_bytes)
 {
@@ -887,8 +946,9 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
     for (int ccw = g.cw; ccw >= 1; --ccw) {
         // (packed words and digits: the last chunk may lack one word, staged as zeros)
         if (fmt == 1 || fmt == 2 ? (g.cw + ccw - 1) / ccw * ccw > g.cw + 1 : g.cw % ccw != 0) continue;
-        // packed words and digits take two channel words per step: chunks must keep the words of a step together
-        if (ccw != g.cw && (ccw % bps)) continue;
+        // packed words and digits take two channel words per step: chunks must keep the words of a step together (a single word of
+        // digits: two taps per step)
+        if (ccw != g.cw && (ccw % bps) && !(fmt == 2 && ccw == 1)) continue;
         const long long row_bytes = (long long)ccw * bpb;
         const long long ps = row_bytes + ((row_bytes / 16) % 2 == 0 ? 16 : 0);
         // LDS row pitch: at least wp pixels, padded so that stepping from the last output pixel of a row
@@ -904,7 +964,7 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         pl->ps = (int)ps;
         pl->max_rows = rows;
         pl->nsteps = (g.taps * ccw + bps - 1) / bps;
-        pl->tap_jump = (ccw == g.cw) ? 0 : (g.cw - ccw) / (fmt == 1 || fmt == 2 ? 1 : bps);
+        pl->tap_jump = (ccw == g.cw) ? 0 : fmt == 2 && ccw == 1 ? 2 * g.cw - 2 : (g.cw - ccw) / (fmt == 1 || fmt == 2 ? 1 : bps);
         if (region >= (1ll << 30)) continue;
         pl->region_bytes = (int)region;
         const long long total = (long long)plan_lds_bytes(*pl, fmt, g.wp, PT, fuse_rows, par_bytes);
@@ -915,6 +975,7 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         const long long whole = lone ? 156 * 1024 : 80 * 1024;
         const long long budget = ccw == g.cw ? (lds_budget > whole ? lds_budget : whole) : lds_budget;
         if (total > budget && !last) continue;
+        if (total > LDS_LIMIT && fmt == 2 && ccw > 1) continue;
         if (total > LDS_LIMIT) return false;
         MfmaPlan one;
         if ((g.cw + ccw - 1) / ccw > most_chunks &&
@@ -960,21 +1021,15 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, two blocks per wave: 34.5 and 39.5)
     if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW >= 4 ? 2 : 0x7fffffff))
         return XNOR_ERR_UNSUPPORTED;
-    // strict: packed words only in one chunk (the caller has another tile for the others), digits only where they are ahead
+    // strict: packed words only in one chunk (the caller has another tile for the others), digits of parts only where they are ahead
     if (FMT != 2 && strict && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
     if (FMT == 2 && strict) {
-        // With one workgroup on a CU that has several to run nothing hides the conversion: a word's digits have to save 24 matrix
-        // instructions per 32 x 32 results over their taps (a 512-filter tile holds the CU whatever it stages).  Where the words
-        // come in chunks they have to save 84, or the tile one per staged word.  Parts against digits, us (saved per word): 2 images of 35x50x50, 3x3 -> 448 (18) 13.4 / 20.7;
-        // 18 of 64x50x50, 3x3 -> 236 (31) 37.2 / 32.9; 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; in chunks 7 of 68x44x44, 3x3 -> 288
-        // (15) 26.7 / 45.3; 5 of 160x51x51, 5x5 -> 60 (75) 49.1 / 61.4; 20 of 192x34x34, 5x5 -> 32 (87) 82.3 / 73.6;
-        // 64 of 96x27x27, 5x5 -> 256 (67, 5.5 per staged word) 117 / 92.  512 filters: 19 of 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
-        const bool wide = FW * PW > 6, chunks = !wide && pl.cc_words != g.cw;
-        const long long saved = bwn_digits_save(g), staged = (long long)pl.max_rows * g.wp * g.cw;
-        const bool ahead = chunks ? saved >= 84LL * g.cw || saved * std::min(FT / 32, g.fblocks) * (PT / 32) >= staged
-                                  : saved >= 24LL * g.cw;
-        if ((wide || (lds > 80 * 1024 && wg_count > 256)) && !ahead) return XNOR_ERR_UNSUPPORTED;
+        // Inputs that come as parts (at most 32 channels).  With one workgroup on a CU that has several to run nothing hides the
+        // conversion: a word's digits have to save 24 matrix instructions per 32 x 32 results over their taps (a 512-filter tile holds
+        // the CU whatever it stages).  Parts against digits, us (saved per word): 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; 512 filters:
+        // 19 of 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
+        if ((FW * PW > 6 || (lds > 80 * 1024 && wg_count > 256)) && bwn_digits_save(g) < 24) return XNOR_ERR_UNSUPPORTED;
     }
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
@@ -1008,7 +1063,7 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     }
     if (grid.y > 65535u) return XNOR_ERR_UNSUPPORTED;
     const size_t img_bytes = FMT == 1 || FMT == 2 ? wimg_pop_bytes(g.k_out, g.c, g.taps)
-                             : FMT == 4 ? wimg_bf16_bytes(g.k_out, g.cw / 3, g.taps)
+                             : FMT == 4 || FMT == 6 ? wimg_bf16_bytes(g.k_out, g.cw / 3, g.taps)
                              : FMT == 5 ? wimg_f4_bytes(g.k_out, g.c, g.taps)
                                         : wimg_i8_bytes(g.k_out, g.c, g.taps);
     if (img_bytes > 0x7fffffffull) return XNOR_ERR_UNSUPPORTED;
@@ -1026,7 +1081,7 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
                               const float *alpha, float *out, int32_t *dot_out, const ConvGeom &g,
                               hipStream_t stream, const FuseArgs *fz, bool last)
 {
-    int tile = mfma_tile_override(), stead = 0;      // stead: the tile that a rule for smaller launches has replaced
+    int tile = FMT == 6 ? 0 : mfma_tile_override(), stead = 0;      // stead: the tile that a rule for smaller launches has replaced
     if (tile == 0) {
         // Measured rules (fp4, all benchmark layers).  Up to 64 filters: 64 x 256 when that still gives every
         // CU two workgroups, else 64 x 128; up to 128 filters: 128 x 64, else 64 x 128 (fused epilogue:
@@ -1045,16 +1100,20 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         };
         const int cus = 256;
         auto waste = [&](long long w) { return (double)((w + cus - 1) / cus * cus) / (double)w; };
-        if (FMT == 2 || FMT == 4) {
+        if (FMT == 6) tile = g.k_out <= 64 ? 2 : 1;
+        else if (FMT == 2 || FMT == 4) {
             // real activations (bfloat16 parts): the K loop is 24 times longer per channel, so the
             // tiles with the larger register blocks win wherever the filter count fills them
             // (measured): up to 64 filters 64 x 256, up to 128 filters 128 x 128; beyond that the tile
             // among 256 x 96 (when one tile holds every filter), 128 x 128 and 128 x 64 that leaves the
             // fewest CUs idle in the last round, the larger one on a tie
-            // (digits, 385 to 512 filters: 512 x 64, so that an input word is converted once: 512 x 7 x 7, batch 256, 115 -> 99 us)
+            // (digits, 385 to 512 filters: 512 x 64, whose waves read every staged digit for four filter blocks, or 256 x 96, whichever
+            // has less to do on the CU that does most (8 and 6 blocks per wave and workgroup): 256 of 512x7x7, 3x3 -> 512 73 / 98 us,
+            // 64 of 256x14x14, 1x1 -> 400 16.2 / 18.1; 28 of 192x12x50, 3x3 -> 416 69 / 60, 5 of 96x48x48, 3x3 -> 448 21.7 / 18.5)
             if (g.k_out <= 64) tile = 2;
             else if (g.k_out <= 128) tile = 1;
-            else if (FMT == 2 && g.k_out > 384 && g.k_out <= 512) tile = 12;
+            else if (FMT == 2 && g.k_out > 384 && g.k_out <= 512)
+                tile = (wgs(512, 64) + cus - 1) / cus * 8 <= (wgs(256, 96) + cus - 1) / cus * 6 ? 12 : 4;
             else {
                 const double w4 = g.k_out <= 256 ? waste(wgs(256, 96)) : 1e30;
                 const double w1 = waste(wgs(128, 128)), w13 = waste(wgs(128, 64));
@@ -1075,8 +1134,9 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
                              : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
                              : tile == 9 ? wgs(384, 96) : tile == 12 ? wgs(512, 64) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
-        if (w0 < (FMT == 2 || FMT == 4 ? 128 : 160)) {
-            if (wgs(64, 128) >= cus) tile = 11;
+        if (w0 < (FMT == 2 || FMT == 4 || FMT == 6 ? 128 : 160)) {
+            if (FMT == 6) tile = 14;
+            else if (wgs(64, 128) >= cus) tile = 11;
             else if (wgs(128, 64) >= cus) tile = 13;
             else tile = (FMT < 2 && !fz && g.taps == 1) ? 15 : 14;       // 128 x 32 (measured ahead of 64 x 64 at equal workgroup count), with eight waves where the records are consecutive
         }
@@ -1084,10 +1144,12 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     // every tiling is built with and without the fused epilogue (bfloat16 parts and k-bit levels: without only)
 #define XNOR_TILE_F(ID, FW, PW, WF, WP)                                                                   \
     case ID:                                                                                              \
+        if constexpr (FMT == 6 && ID != 1 && ID != 2 && ID != 14) return XNOR_ERR_UNSUPPORTED;            \
+        else {                                                                                            \
         if constexpr (FMT < 2) {                                                                          \
             if (fz) return launch_cfg<FMT, FW, PW, WF, WP, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz); \
         }                                                                                                 \
-        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict);
+        return launch_cfg<FMT, FW, PW, WF, WP, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict); }
 #define XNOR_TILE_F4(ID, FW, PW, WF, WP)                                                                  \
     case ID:                                                                                              \
         if constexpr (FMT == 1)                                                                           \
@@ -1132,6 +1194,10 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     xnor_status s = launch(tile, FMT == 2 ? !last && mfma_tile_override() == 0 : stead == 1);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(1, true);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(13);
+    // (digits, wide rows: fewer pixels)
+    if (FMT == 2 && g.cw > 1 && mfma_tile_override() == 0)
+        for (const int other : {11, 14})
+            if (s == XNOR_ERR_UNSUPPORTED) s = launch(other);
     if (FMT != 1 || mfma_tile_override() != 0) return s;
     // 4-bit operands: the rows under the chosen tile may not fit the LDS with what the tile keeps beside them (384 and 512
     // filters of the fused epilogue: 5 and 6 KiB of alpha, scale and shift, a word per pixel and 32 filters; 64 x 6 x 6, one 6 x 6

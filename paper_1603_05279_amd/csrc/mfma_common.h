@@ -332,6 +332,42 @@ template <> struct Enc<4> {
     static __device__ __forceinline__ void build_lut(uint8_t *, int, int) {}
 };
 
+// The same parts, made from digits (Enc<2>) while they are staged: for rows so wide that one channel word's digits do not fit the
+// LDS and a part of 16 channels does.
+template <> struct Enc<6> : Enc<4> {
+    // word: the 32 dwords of 32 channels' digits; half: which 16 of them; out: their hi, mid and lo parts, 16 bfloat16 numbers each
+    static __device__ __forceinline__ void parts_of_digits(const v4u (&word)[8], int half, v4u (&out)[6])
+    {
+        typedef Enc<2> D;
+        const uint32_t field = word[D::SCALE_DWORD / 4][D::SCALE_DWORD % 4];
+        float x[32];
+#pragma unroll
+        for (int k = D::DIGITS - 1; k >= 0; --k) {
+            D::v6u d;
+#pragma unroll
+            for (int i = 0; i < 6; ++i) d[i] = word[(6 * k + i) / 4][(6 * k + i) % 4];
+            const D::v32 back = __builtin_amdgcn_cvt_scalef32_pk32_f32_fp6(d, __builtin_bit_cast(float, (field - 5u * k) << 23));
+#pragma unroll
+            for (int i = 0; i < 32; ++i) {        // (smallest first: every sum is a float)
+                const int ch = D::channel_at(i);
+                x[ch] = k == D::DIGITS - 1 ? back[i] : x[ch] + back[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            float a = half ? x[16 + 2 * i] : x[2 * i], b = half ? x[17 + 2 * i] : x[2 * i + 1];
+            if (field == 255u) a = b = __builtin_nanf("");       // a word with an infinite or NaN input
+#pragma unroll
+            for (int part = 0; part < 3; ++part) {
+                const uint32_t ha = bf16_rne(a), hb = bf16_rne(b);
+                out[2 * part + i / 4][i % 4] = ha | (hb << 16);
+                a -= bf16_value(ha);
+                b -= bf16_value(hb);
+            }
+        }
+    }
+};
+
 // k-bit quantised operands (sec. 3.2, "k-bit Quantization"): activations and weights arrive as the odd-integer
 // numerators 2u - L of their levels in int8 (32 channels = one 32-byte word per pixel, 0 past the last
 // channel), so the int8 matrix instruction accumulates the exact integer sum of products; nothing to widen.
@@ -438,7 +474,8 @@ template <int FW> struct WStreamChunked {
 // vector offset.  When the block count is odd the second half-wave of the last step holds no block: its code is 0 (operand 0.0).
 // Steps are consecutive (LINEAR) or, where a chunk holds part of the channel words, run on within a tap and skip
 // tap_jump words to the next one (uniform bookkeeping, one vector addition per step; steps past the end read the block's
-// first words, which nothing multiplies).  There too the second half-wave of a filter's very last step may lie beyond its
+// first words, which nothing multiplies).  Where a chunk holds one of several channel words a step takes it of two taps, whose blocks
+// lie half_blk apart.  There too the second half-wave of a filter's very last step may lie beyond its
 // words: a last chunk that lacks a word, an odd block count in one chunk.
 template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     typedef uint32_t word_t;
@@ -446,9 +483,10 @@ template <int FW, bool LINEAR, int AUX = 0> struct WStreamBits {
     __amdgpu_buffer_rsrc_t rsrc[FW];
     int voff, w_blk, w_cnt, w_left, steps_per_tap, tap_jump;
     uint32_t last_code;          // code of the last step
+    __device__ __forceinline__ WStreamBits() = default;
     __device__ __forceinline__ WStreamBits(const uint32_t *words, const int (&fblk)[FW], int nblk, int first,
-                                           int nsteps, bool odd_last, int lane, int steps_per_tap_, int tap_jump_)
-        : voff(lane * 4 + (LINEAR ? first * 128 : 0)), w_blk(first), w_cnt(0), w_left(nsteps),
+                                           int nsteps, bool odd_last, int lane, int steps_per_tap_, int tap_jump_, int half_blk = 1)
+        : voff((lane & 31) * 4 + (lane >> 5) * half_blk * 128 + (LINEAR ? first * 128 : 0)), w_blk(first), w_cnt(0), w_left(nsteps),
           steps_per_tap(steps_per_tap_), tap_jump(tap_jump_), last_code(odd_last && lane >= 32 ? 0u : 0x88888888u)
     {
 #pragma unroll
@@ -486,7 +524,7 @@ template <bool ACC, class A> __device__ __forceinline__ void pin_acc(A &acc)
 
 // One chunk's K loop of a wave: acc[i][j] += W(filter block i, step s) x X(pixel block j, step s)
 // for s = 0 .. nsteps-1, weights from the stream `ws` (one of those above), activations from LDS
-// through the per-step offset table (padded by KLOOP_TABLE_PAD steps).  Operands are requested DW
+// through the per-step offset table (padded by KLOOP_TABLE_PAD steps).  The first DW steps' weights are on their way already (w).  Operands are requested DW
 // steps (weights: buffer loads with a scalar offset, L2 latency) and DX steps (activations) ahead
 // of their use and live in register rings of DW+1 and DX+1 slots; the body is unrolled until both
 // rings are back at slot 0.  Packed weight words are widened one step ahead of their use.  A wave issues one
@@ -499,7 +537,7 @@ template <bool ACC, class A> __device__ __forceinline__ void pin_acc(A &acc)
 template <class E, int FW, int PW, int DW, int DX, class WS>
 __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], const uint8_t *lds_x,
                                            const int (&pbase)[PW], const int *xoff_tab, int tab_lane, WS &ws,
-                                           int nsteps)
+                                           typename WS::word_t (&w)[DW + 1][FW], int nsteps)
 {
     constexpr int RW = DW + 1, RX = DX + 1;
     constexpr int TURN = ring_lcm(RW, RX);     // sub-steps after which both rings are back at slot 0
@@ -525,7 +563,6 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
                 for (int i = 0; i < FW; ++i) acc[i][j] = E::mfma(w[i], x[j][q], acc[i][j]);
     };
 
-    word_t w[RW][FW];
     v4i x[RX][PW][NX], wide[2][FW];
     int tq[2];
     // (in registers: an and-or takes no two literals)
@@ -540,8 +577,6 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
             for (int i = 0; i < FW; ++i) dst[i] = E::widen_bits(src[i], code, one);
         }
     };
-#pragma unroll
-    for (int u = 0; u < DW; ++u) ws.load(w[u]);
 #pragma unroll
     for (int u = 0; u < DX; ++u) load_x(x[u], load_t(u));
     tq[0] = load_t(DX);
@@ -591,7 +626,7 @@ __device__ __forceinline__ void mfma_kloop(typename E::acc_t (&acc)[FW][PW], con
 template <int FW, int PW, int DW, class WS>
 __device__ __forceinline__ void mfma_kloop_digits(Enc<2>::acc_t (&acc)[FW][PW], const uint8_t *lds_x,
                                                   const int (&pbase)[PW], const int *xoff_tab, int tab_lane, WS &ws,
-                                                  int nsteps)
+                                                  typename WS::word_t (&w)[DW + 1][FW], int nsteps)
 {
     typedef Enc<2> E;
     constexpr int RW = DW + 1;
@@ -604,7 +639,6 @@ __device__ __forceinline__ void mfma_kloop_digits(Enc<2>::acc_t (&acc)[FW][PW], 
         for (int v = 0; v < 16; ++v) odd[v] = 0.0f;
     }
     const int *tab = xoff_tab + tab_lane;
-    typename WS::word_t w[RW][FW];
     v4i wide[2][FW];
     uint32_t full = 0x88888888u, full_one = 0x22222222u;
     asm("" : "+v"(full), "+v"(full_one));
@@ -622,8 +656,6 @@ __device__ __forceinline__ void mfma_kloop_digits(Enc<2>::acc_t (&acc)[FW][PW], 
         for (int q = 0; q < 32; ++q) dst[q] = d[q / 4][q % 4];
     };
     E::v32i x[2];
-#pragma unroll
-    for (int u = 0; u < DW; ++u) ws.load(w[u]);
     int off = tab[0], off_next = tab[E::BPS];
     load_x(x[0], pbase[0] + off);
     widen(wide[0], w[0], 0, true);

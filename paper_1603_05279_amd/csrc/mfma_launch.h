@@ -10,7 +10,7 @@ int mfma_tile_override();
 int mfma_lds_budget();
 
 // One convolution with operand format FMT: 0 int8 signs, 1 4-bit signs, 2 digits of real inputs, 3 int8 levels, 4 bfloat16 parts, 5 levels
-// of at most two bits as 4-bit floats.  last: no other form follows where this one refuses the geometry.
+// of at most two bits as 4-bit floats, 6 bfloat16 parts made of digits.  last: no other form follows where this one refuses the geometry.
 template <int FMT>
 xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, const float *A, const float *alpha, float *out,
                        int32_t *dot_out, const ConvGeom &g, hipStream_t stream, const FuseArgs *fz, bool last = false);

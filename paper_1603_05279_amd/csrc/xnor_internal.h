@@ -61,6 +61,13 @@ __device__ __forceinline__ float box_K(const float *__restrict__ A, const ConvGe
     return s / (float)(g.kh * g.kw);
 }
 
+__device__ __forceinline__ uint32_t bf16_rne(float v)      // round to nearest even (finite inputs)
+{
+    const uint32_t u = __builtin_bit_cast(uint32_t, v);
+    return (u + 0x7FFFu + ((u >> 16) & 1u)) >> 16;
+}
+__device__ __forceinline__ float bf16_value(uint32_t h) { return __builtin_bit_cast(float, h << 16); }
+
 inline xnor_status hip_status(hipError_t e) { return e == hipSuccess ? XNOR_OK : XNOR_ERR_HIP; }
 
 // kernels' host launchers (each returns an xnor_status, enqueues on `stream`, never synchronises)
@@ -135,6 +142,12 @@ void set_mfma_tuning(int tile, int lds_budget);
 // (g: the layer; gp: the same over the parts' 3 * ceil(c/16) words of 32 channels)
 xnor_status launch_bwn_conv(const void *parts, const void *wimg, const float *alpha, float *out, const ConvGeom &g,
                             const ConvGeom &gp, hipStream_t stream);
+// Form of the buffer that xnor_bwn_split writes, by channels alone (it knows no filters): true: the digits of Enc<2>, 128 bytes per
+// pixel and 32 channels, which fit the parts' room (96 bytes per 16 channels) from 33 channels on, where they also take fewer matrix
+// instructions whatever the filters; false: three bfloat16 parts.  Passes over 30 layers, split and convolution, parts or digits made
+// while staging against stored digits: 16 of 33 and more channels at 0.64 to 1.04 of the time, 0.88 in the mean (42 of 300x29x13, 3x3 -> 18
+// 54.0 -> 34.7 us, 59 of 500x7x7, 1x1 -> 192 20.3 -> 17.2, one of 74x6x31, 3x3 -> 224 11.1 -> 11.6).
+inline bool bwn_in_digits(int c) { return c > 32; }
 xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, hipStream_t stream);
 xnor_status launch_bwn_pack(const float *w, float *alpha, void *wimg, int k_out, int c, int taps, hipStream_t stream);
 // Sizes of the two matrix-core weight images (int8 first, 4-bit float second), 1 KiB records;
