@@ -54,6 +54,10 @@ xnor_status launch_conv_mfma(int fmt, const uint32_t *xbits, const void *wmfma, 
     if (fmt != 0 && (long long)g.c * g.taps >= (1ll << 24)) return XNOR_ERR_UNSUPPORTED;
     if (fmt == 0) return launch_fmt<0>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz);
     img += wimg_i8_bytes(g.k_out, g.c, g.taps) + wimg_f4_bytes(g.k_out, g.c, g.taps);
+    if (!fz && mfma_tile_override() == 0 && linear_words_applies(g)) {
+        const xnor_status s = launch_linear_words(xbits, reinterpret_cast<const uint32_t *>(img), K ? K : A, alpha, out, dot_out, g, stream);
+        if (s != XNOR_ERR_UNSUPPORTED) return s;
+    }
     return launch_fmt<1>(xbits, img, K, A, alpha, out, dot_out, g, stream, fz, last);
 }
 

@@ -236,6 +236,7 @@ __global__ __launch_bounds__(256) void linear_popcount_kernel(
 bool linear_popcount_applies(const ConvGeom &g, bool matrix_image)
 {
     if (g.h != 1 || g.w != 1 || g.taps != 1 || g.ph != 0 || g.pw != 0 || g.dil_h != 1 || g.dil_w != 1) return false;
+    if (matrix_image && linear_words_applies(g)) return linear_few_rows_ahead_of_words(g.n, g.k_out, g.c, g.cw);
     return linear_popcount_route(g.n, g.k_out, g.c, g.cw, matrix_image);
 }
 

@@ -107,6 +107,14 @@ xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, c
 bool linear_popcount_applies(const ConvGeom &g, bool matrix_image);
 xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits, const float *Krow, const float *alpha,
                                    float *out, int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
+// the layers linear_words_kernel takes: a 1x1 image and filter, rows of four words and more, sums that a float holds
+inline bool linear_words_applies(const ConvGeom &g)
+{
+    return g.h == 1 && g.w == 1 && g.taps == 1 && g.ph == 0 && g.pw == 0 && g.dil_h == 1 && g.dil_w == 1 && g.cw >= 4 && g.c < (1 << 24) - 32 && g.n < (1 << 30);
+}
+// words: the scalar-path image (wimg_pop_bytes)
+xnor_status launch_linear_words(const uint32_t *xbits, const uint32_t *words, const float *Krow, const float *alpha, float *out,
+                                int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
 // Third image of the wmfma buffer (after the int8 and 4-bit images): the packed weight words in
 // scalar-path order, [filter block of 32][tap][channel word][32 filters], so that the 32 words a
 // wave needs for one (tap, channel word) are one aligned 128-byte scalar load.
