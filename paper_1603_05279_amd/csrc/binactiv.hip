@@ -368,6 +368,148 @@ xnor_status launch_binactiv(const float *x, const float *bn_scale, const float *
     return launch_binactiv_impl<false>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
 }
 
+// Max-pooling of stride 2 (3 x 3 and 2 x 2 windows, rows of at most 64 pixels with their padding) in front of the layer: the same layer as
+// the pooled form above, R pooled rows of an image per workgroup.  Lanes run along the columns of an input row, as many channels side by side as
+// fit a wave (`lanes` = 8, 16, 32 or 64 lanes each); every lane takes 8 channels (a byte of its pixel's words), loads the rows under the R
+// windows once, all of them in flight, and takes the maxima down its column in registers; two lane shifts bring in the neighbouring columns.
+// Even columns then hold a pooled pixel each.  Nothing is staged, no window is read from LDS.
+// What bounds it: memory, once there are workgroups and loads enough.  Against 64 pooled pixels per workgroup whose input rows went
+// through LDS, two channels at a time, us: 64 of 256x27x27, 3x3 15.3 -> 11.7; 128 of 256x13x13, 3x3 12.1 -> 6.5; 256 of 128x28x28, 3x3
+// 29.5 -> 18.8; 256 of 512x7x7, 2x2 18.4 -> 6.6; 256 of 256x14x14, 2x2 12.6 -> 11.3; 1 of 64x14x14, 3x3 5.9 -> 3.8; 20 of 200x56x56, 3x3
+// 15.4 -> 15.2.
+// Maxima start at -inf and skip NaN, as above.
+__device__ __forceinline__ float next_lane(float v)      // the value of the lane above (the last lane keeps its own)
+{
+    const int i = __builtin_bit_cast(int, v);
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(i, i, 0x130, 0xf, 0xf, false));      // wave_shl:1
+}
+
+template <int PH, int R, int NW>
+__global__ __launch_bounds__(64 * NW, NW == 16 ? 8 : 6) void pool_rows_kernel(
+    const float *__restrict__ x, const float *__restrict__ bn_scale, const float *__restrict__ bn_shift,
+    uint32_t *__restrict__ xbits, float *__restrict__ A, int c, int cw, int ho, int tiles_per_image, int nblocks, int lanes_log2, PoolGeom pg)
+{
+    constexpr int NR = 2 * (R - 1) + PH;          // input rows under the tile
+    const unsigned b = blockIdx.x, win = (b >> 6) << 6;      // (runs of 8 tiles per XCD: neighbouring tiles share input rows)
+    const int blk = (int)(win + 64u <= (unsigned)nblocks ? win + ((b & 7u) << 3) + ((b >> 3) & 7u) : b);
+    extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int side = 64 >> lanes_log2;            // channel groups side by side
+    const int npx = R * pg.wo;
+    uint8_t *wbytes = smem;                                                            // [npx][cw words][4 bytes]
+    float *part = reinterpret_cast<float *>(smem + (size_t)npx * cw * 4);              // [NW * side][npx]
+    float *bn = part + NW * side * npx;                                                // scale, shift [cw * 32] each
+    const int img = blk / tiles_per_image;
+    const int oy0 = (blk - img * tiles_per_image) * R;
+    const int rows_out = min(R, ho - oy0);
+    const int col = lane & ((1 << lanes_log2) - 1), slot = wave * side + (lane >> lanes_log2);
+    const int in_hw = pg.h * pg.w, xc = col - pg.pad_w;
+    const bool in_row = xc >= 0 && xc < pg.w;
+    const int ox = col >> 1;
+    const bool out_lane = !(col & 1) && ox < pg.wo;
+    const float *rowp[NR];
+    bool row_ok[NR];
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+        const int iy = oy0 * 2 - pg.pad_h + r;
+        row_ok[r] = iy >= 0 && iy < pg.h;
+        rowp[r] = x + (size_t)img * c * in_hw + (size_t)min(max(iy, 0), pg.h - 1) * pg.w;
+    }
+    const bool padded = pg.pad_h != 0 || pg.pad_w != 0;
+    const int groups = (c + 7) >> 3;
+    const float inf = __builtin_inff();
+    for (int ch = tid; ch < cw * 32; ch += 64 * NW) {
+        bn[ch] = bn_scale ? bn_scale[min(ch, c - 1)] : 1.0f;               // (without normalisation y == fma(y, 1, 0))
+        bn[cw * 32 + ch] = bn_scale ? bn_shift[min(ch, c - 1)] : 0.0f;
+    }
+    float asum[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) asum[r] = 0.0f;
+    for (int g0 = 0; g0 < groups; g0 += NW * side) {
+        const int gidx = g0 + slot;
+        const int ch0 = min(gidx, groups - 1) * 8, last = c - 1 - ch0, real = gidx < groups ? last + 1 : 0;
+        float v[8][NR];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const uint32_t off = (uint32_t)(ch0 + min(j, last)) * (uint32_t)in_hw + (uint32_t)min(max(xc, 0), pg.w - 1);
+#pragma unroll
+            for (int r = 0; r < NR; ++r) v[j][r] = rowp[r][off];
+        }
+        if (g0 == 0) __syncthreads();             // (scale and shift; the loads are on their way)
+        uint32_t byte[R];
+#pragma unroll
+        for (int r = 0; r < R; ++r) byte[r] = 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (padded) {
+#pragma unroll
+                for (int r = 0; r < NR; ++r) v[j][r] = row_ok[r] && in_row ? v[j][r] : -inf;
+            }
+            const bool ok = j < real;
+            const float sc = bn[ch0 + j], sh = bn[cw * 32 + ch0 + j];
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                float m = __builtin_fmaxf(v[j][2 * r], v[j][2 * r + 1]);
+                if (PH == 3) m = __builtin_fmaxf(m, v[j][2 * r + PH - 1]);
+                m = __builtin_fmaxf(m, next_lane(m));
+                if (PH == 3) m = __builtin_fmaxf(m, next_lane(m));
+                m = __builtin_fmaxf(m, -inf);
+                if (pg.relu) m = m > 0.0f ? m : 0.0f;
+                const float y = __builtin_fmaf(m, sc, sh);
+                byte[r] |= (ok && y >= 0.0f ? 1u : 0u) << j;
+                asum[r] += ok ? __builtin_fabsf(y) : 0.0f;
+            }
+        }
+        if (gidx < groups && out_lane) {
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r < rows_out) wbytes[(size_t)(r * pg.wo + ox) * cw * 4 + gidx] = (uint8_t)byte[r];
+        }
+    }
+    if (out_lane) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) part[slot * npx + r * pg.wo + ox] = asum[r];
+    }
+    __syncthreads();
+    const int live = rows_out * pg.wo, slots = min(groups, NW * side);
+    const size_t p0 = ((size_t)img * ho + oy0) * pg.wo;
+    for (int p = tid; p < live; p += 64 * NW) {
+        float s = part[p];
+        for (int q = 1; q < slots; ++q) s += part[q * npx + p];            // fixed order
+        A[p0 + p] = s / (float)c;
+    }
+    const uint32_t *words = reinterpret_cast<const uint32_t *>(wbytes);
+    const uint32_t tail_mask = 0xFFFFFFFFu >> (8 * (cw * 4 - groups));      // bytes of the last word no group wrote
+    for (int i = tid; i < live * cw; i += 64 * NW) xbits[p0 * cw + i] = words[i] & (i % cw == cw - 1 ? tail_mask : 0xFFFFFFFFu);
+}
+
+template <int PH>
+static xnor_status launch_pool_rows(const float *x, const float *bn_scale, const float *bn_shift, uint32_t *xbits, float *A, int n, int c,
+                                    int ho, const PoolGeom &pg, hipStream_t stream)
+{
+    const int cw = (c + 31) / 32, groups = (c + 7) / 8, width = pg.w + 2 * pg.pad_w;
+    if (width > 64 || (long long)c * pg.h * pg.w >= (1ll << 30)) return XNOR_ERR_UNSUPPORTED;
+    int lanes_log2 = 3;
+    while ((1 << lanes_log2) < width) ++lanes_log2;
+    const int side = 64 >> lanes_log2;
+    // One pooled row per workgroup where two leave CUs without one.  Waves: those that the channels fill, up to 8 (several workgroups of 64 to
+    // 72 registers then share a CU, one loads while another computes: 64 of 256x27x27 11.7 us, with 16 waves 14.8; 256 of 128x28x28
+    // 18.8 / 32.4), 16 where there are CUs to spare (2 of 480x40x40 11.3 / 9.7, 4 of 100x33x33 4.9 / 4.6).
+    const int R = (long long)n * ((ho + 1) / 2) < 256 ? 1 : 2, waves = (groups + side - 1) / side;
+    const int NW = waves > 8 && (long long)n * ((ho + R - 1) / R) < 256 ? 16 : waves > 4 ? 8 : 4;
+    const int tiles = (ho + R - 1) / R;
+    const long long blocks = (long long)n * tiles;
+    const size_t lds = (size_t)R * pg.wo * 4 * (cw + NW * side) + (size_t)cw * 64 * 4;
+    if (blocks > 0x7ffffff0LL || lds > 48 * 1024) return XNOR_ERR_UNSUPPORTED;
+#define XNOR_PR(RR, W) \
+    pool_rows_kernel<PH, RR, W><<<dim3((unsigned)blocks), dim3(64 * W), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, cw, ho, tiles, (int)blocks, lanes_log2, pg)
+    if (R == 1) { if (NW == 16) XNOR_PR(1, 16); else if (NW == 8) XNOR_PR(1, 8); else XNOR_PR(1, 4); }
+    else        { if (NW == 16) XNOR_PR(2, 16); else if (NW == 8) XNOR_PR(2, 8); else XNOR_PR(2, 4); }
+#undef XNOR_PR
+    return hip_status(hipGetLastError());
+}
+
 xnor_status launch_pool_binactiv(const float *x, const float *bn_scale, const float *bn_shift,
                                  uint32_t *xbits, float *A, int n, int c, int h, int w, int ph, int pw,
                                  int sh, int sw, int pad_h, int pad_w, int relu, hipStream_t stream)
@@ -377,6 +519,11 @@ xnor_status launch_pool_binactiv(const float *x, const float *bn_scale, const fl
     pg.relu = relu;
     const int ho = (h + 2 * pad_h - ph) / sh + 1, wo = (w + 2 * pad_w - pw) / sw + 1;
     pg.wo = wo;
+    if (ph == pw && (ph == 2 || ph == 3) && sh == 2 && sw == 2 && xbits && A) {
+        const xnor_status s = ph == 3 ? launch_pool_rows<3>(x, bn_scale, bn_shift, xbits, A, n, c, ho, pg, stream)
+                                      : launch_pool_rows<2>(x, bn_scale, bn_shift, xbits, A, n, c, ho, pg, stream);
+        if (s != XNOR_ERR_UNSUPPORTED) return s;
+    }
     // LDS staging of the input rows a 64-pixel tile touches (compile-time windows only): at most
     // ceil-ish (64 + wo - 2)/wo + 1 pooled rows, hence (rows - 1)*sh + ph input rows of w floats
     pg.stage = 0;

@@ -95,3 +95,25 @@ def test_argument_errors():
         with pytest.raises(xnor.XnorError) as e:
             xnor.xnor_pool_binactiv(x, None, None, xb, A, 1, 4, 5, 5, a["pool"], a["stride"], a["pad"])
         assert e.value.status == status, kw
+
+
+# n, c, h, w, window, pad: rows of 8, 16, 32 and 64 lanes and one wider, channels that fill no group of eight or more than one pass of the waves,
+# odd and single pooled rows, one and two of them per workgroup
+@pytest.mark.parametrize("n,c,h,w,window,pad", [
+    (1, 1, 3, 3, 3, 0), (3, 7, 6, 8, 3, 0), (2, 9, 7, 6, 2, 1), (1, 100, 9, 16, 3, 0), (2, 130, 15, 14, 3, 1), (300, 17, 5, 5, 2, 0),
+    (2, 64, 13, 17, 3, 0), (70, 33, 11, 32, 2, 0), (3, 257, 12, 30, 3, 1), (2, 200, 9, 64, 3, 0), (40, 72, 16, 62, 3, 1), (2, 48, 8, 64, 2, 1),
+    (130, 96, 7, 33, 3, 0), (2, 40, 9, 65, 3, 0), (1, 900, 5, 7, 2, 0),
+])
+@pytest.mark.parametrize("with_bn,relu", [(True, False), (False, True)])
+def test_pooling_of_stride_two(n, c, h, w, window, pad, with_bn, relu):
+    print("case", n, c, h, w, window, pad, flush=True)
+    rng = np.random.default_rng(n + c + h + w)
+    x = rng.standard_normal((n, c, h, w)).astype(np.float32)
+    x[rng.random(x.shape) < 0.05] = 0.0
+    x[rng.random(x.shape) < 0.02] = np.nan
+    x.flat[-1] = -np.inf
+    bn = (rng.uniform(0.5, 1.5, c).astype(np.float32), (0.3 * rng.standard_normal(c)).astype(np.float32)) if with_bn else None
+    bits, A = run(x, (window, window), (2, 2), (pad, pad), bn, relu)
+    y, s, A_ref = xo.binactiv(xo.max_pool(x, (window, window), (2, 2), (pad, pad), relu), *(bn if bn is not None else (None, None)))
+    assert np.array_equal(bits, pack_signs_channels_last(s))
+    np.testing.assert_allclose(A, A_ref, rtol=RTOL, atol=ATOL)
