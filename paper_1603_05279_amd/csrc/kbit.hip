@@ -6,56 +6,79 @@
 // (The same sum could be formed from ka*kw binary convolutions of the bit planes, q_k = sum_p 2^p s_p / L; on
 // this chip the int8 contraction is ka*kw times less matrix work at half the 4-bit rate.)
 #include "xnor_internal.h"
+#include <type_traits>
 
 namespace xnor {
 
-__device__ __forceinline__ int qk_level(float x, int L)
+// Level indices u of four inputs, one per byte: u = floor(((x + 1) * 0.5) * L + 0.5), x clamped to [-1, 1] (NaN -> -1), each operation
+// rounded to float in this order (contraction is disabled for the build): the float value decides the level.  Halving is exact, so
+// (x + 1) * (L / 2) is the same float; the value lies in [0.5, L + 0.5], where conversion to integer is the floor and stays within 0 .. L.
+// One bit: the comparison of the sign rule (x + 1 rounds to 1 for -2^-25 < x < 0, which would give +1).
+template <bool ONE_BIT> __device__ __forceinline__ uint32_t qk_indices(const float *x, float half_L)
 {
-    // u = floor(((x + 1) * 0.5) * L + 0.5), x clamped to [-1, 1] (NaN -> -1); each operation rounded to
-    // float in this order (contraction is disabled for the build): the float value decides the level
-    float t = x >= -1.0f ? x : -1.0f;
-    t = t <= 1.0f ? t : 1.0f;
-    const float v = ((t + 1.0f) * 0.5f) * (float)L + 0.5f;
-    // one bit: the comparison of the sign rule (x + 1 rounds to 1 for -2^-25 < x < 0, which would give +1)
-    if (L == 1) return x >= 0.0f ? 1 : 0;
-    return min(max((int)__builtin_floorf(v), 0), L);
+    uint32_t u = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t q = ONE_BIT ? (x[i] >= 0.0f ? 1u : 0u)
+                                   : (uint32_t)((__builtin_amdgcn_fmed3f(x[i], -1.0f, 1.0f) + 1.0f) * half_L + 0.5f);
+        u |= q << (8 * i);
+    }
+    return u;
+}
+
+// The numerators 2u - L of four level indices (u at most 127), byte by byte: 2u with its top bit forced on is at least 128 and borrows
+// nothing from its neighbour; the top bit is put right afterwards.
+__device__ __forceinline__ uint32_t qk_numerators(uint32_t u, uint32_t L4)
+{
+    const uint32_t x = u << 1, top = 0x80808080u;
+    return ((x | top) - L4) ^ (~x & top);
 }
 
 // x [n][c][hw] float -> xq [n][hw][cw][32] int8: byte j of word wd = 2u - L of channel wd*32 + j (0 past the
-// last channel).  One workgroup = 64 consecutive pixels of one image x 8 channel words; lanes along pixels
+// last channel).  One workgroup = 64 pixels that follow each other in the batch x 8 channel words; lanes along pixels
 // (every channel row is read as coalesced 256-byte segments), the 4 waves share the 32 groups of 8 channels,
 // a group's 8 bytes go to LDS (row stride 8*32 + 16 bytes: neighbouring lanes fall on different banks), from
 // where each pixel's words leave as one contiguous run, 16 bytes per lane.
+// What bounds it: memory, 4 bytes read and 1 written per input, once the levels take few instructions (7 per input; 18 with a clamp of the index
+// and bytes put together one by one).  256 images of 256x14x14: 15.8 -> 12.6 us, 128 of 100x28x28 13.1 -> 10.8, 256 of 512x7x7 9.0 -> 6.9.
 constexpr int KB_WORDS = 8, KB_ROW = KB_WORDS * 32 + 16;
-__global__ __launch_bounds__(256) void kbit_levels_kernel(const float *__restrict__ x, int8_t *__restrict__ xq,
-                                                          int c, int hw, int cw, int L)
+__global__ __launch_bounds__(256) void kbit_levels_kernel(const float *__restrict__ x, int8_t *__restrict__ xq, int c, int hw, int cw, int L,
+                                                          uint32_t pixels, uint32_t tiles, FastDiv div_tiles, FastDiv div_hw)
 {
     __shared__ __attribute__((aligned(16))) uint8_t stage[64 * KB_ROW];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int p0 = blockIdx.x * 64, w0 = blockIdx.y * KB_WORDS, img = blockIdx.z;
-    const int nwords = min(KB_WORDS, cw - w0);
-    const int pc = min(p0 + lane, hw - 1);
-    const float *xi = x + (size_t)img * c * hw + pc;
+    // (runs of 8 workgroups per XCD: neighbouring pixel tiles share cache lines)
+    const uint32_t b = blockIdx.x, win = b >> 6 << 6;
+    const uint32_t blk = win + 64u <= gridDim.x ? win + ((b & 7u) << 3) + ((b >> 3) & 7u) : b;
+    const uint32_t part = div_tiles.div(blk), m0 = (blk - part * tiles) * 64u;
+    const int w0 = (int)part * KB_WORDS, nwords = min(KB_WORDS, cw - w0);
+    const uint32_t m = min(m0 + lane, pixels - 1u), img = div_hw.div(m);
+    const float *xi = x + (size_t)img * c * hw + (m - img * (uint32_t)hw);
+    const uint32_t L4 = (uint32_t)L * 0x01010101u;
+    const float half_L = 0.5f * (float)L;
+    auto levels = [&](auto one_bit) {
 #pragma unroll 2
-    for (int gidx = wave; gidx < nwords * 4; gidx += 4) {           // groups of 8 channels of this workgroup
-        const int ch0 = w0 * 32 + gidx * 8;
-        float v[8];
+        for (int gidx = wave; gidx < nwords * 4; gidx += 4) {           // groups of 8 channels of this workgroup
+            const int ch0 = w0 * 32 + gidx * 8, real = c - ch0;
+            float v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = xi[(size_t)min(ch0 + j, c - 1) * hw];
-        uint32_t lo = 0, hi = 0;
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int a = ch0 + j < c ? 2 * qk_level(v[j], L) - L : 0;
-            if (j < 4) lo |= ((uint32_t)a & 255u) << (8 * j);
-            else hi |= ((uint32_t)a & 255u) << (8 * (j - 4));
+            for (int j = 0; j < 8; ++j) v[j] = xi[(size_t)min(ch0 + j, c - 1) * hw];
+            uint32_t lo = qk_numerators(qk_indices<one_bit.value>(v, half_L), L4);
+            uint32_t hi = qk_numerators(qk_indices<one_bit.value>(v + 4, half_L), L4);
+            if (real < 8) {                                             // channels past the last one: 0
+                lo = real <= 0 ? 0u : real < 4 ? lo & ((1u << (8 * real)) - 1u) : lo;
+                hi = real <= 4 ? 0u : hi & ((1u << (8 * (real - 4))) - 1u);
+            }
+            *reinterpret_cast<uint2 *>(stage + lane * KB_ROW + gidx * 8) = make_uint2(lo, hi);
         }
-        *reinterpret_cast<uint2 *>(stage + lane * KB_ROW + gidx * 8) = make_uint2(lo, hi);
-    }
+    };
+    if (L == 1) levels(std::true_type{});
+    else levels(std::false_type{});
     __syncthreads();
     const int upp = nwords * 2;                       // 16-byte units per pixel
-    const int npx = min(64, hw - p0);
-    int8_t *out = xq + (((size_t)img * hw + p0) * cw + w0) * 32;
+    const int npx = (int)min(64u, pixels - m0);
+    int8_t *out = xq + ((size_t)m0 * cw + w0) * 32;
     for (int i = tid; i < npx * upp; i += 256) {
         const int px = i / upp, u = i - px * upp;
         *reinterpret_cast<uint4 *>(out + (size_t)px * cw * 32 + u * 16) =
@@ -66,10 +89,12 @@ __global__ __launch_bounds__(256) void kbit_levels_kernel(const float *__restric
 xnor_status launch_kbit_pack_input(const float *x, int8_t *xq, int k, int n, int c, int hw, hipStream_t stream)
 {
     const int cw = (c + 31) / 32;
-    const int wblocks = (cw + KB_WORDS - 1) / KB_WORDS;
-    if (wblocks > 65535 || n > 65535) return XNOR_ERR_UNSUPPORTED;
-    dim3 grid((unsigned)((hw + 63) / 64), (unsigned)wblocks, (unsigned)n);
-    kbit_levels_kernel<<<grid, dim3(256), 0, stream>>>(x, xq, c, hw, cw, (1 << k) - 1);
+    const int parts = (cw + KB_WORDS - 1) / KB_WORDS;
+    if (parts > 65535 || n > 65535) return XNOR_ERR_UNSUPPORTED;
+    const long long pixels = (long long)n * hw, tiles = (pixels + 63) / 64;
+    if (tiles * parts > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;
+    kbit_levels_kernel<<<dim3((unsigned)(tiles * parts)), dim3(256), 0, stream>>>(
+        x, xq, c, hw, cw, (1 << k) - 1, (uint32_t)pixels, (uint32_t)tiles, FastDiv::make((uint32_t)tiles), FastDiv::make((uint32_t)hw));
     return hip_status(hipGetLastError());
 }
 
