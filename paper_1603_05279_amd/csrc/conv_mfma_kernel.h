@@ -1016,10 +1016,10 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     constexpr int FROWS = FUSE ? WF + FT / 32 : 0, PARB = (FUSE ? 3 : 1) * FT * 4;
     const long long wg_count = (long long)((g.m_total + PT - 1) / PT) * ((g.k_out + FT - 1) / FT);
     const int budget = std::max(mfma_lds_budget(), FMT == 2 && FW * PW > 6 ? 150 * 1024 : 0);      // (one workgroup per CU)
-    // 4-bit operands, tiles of four result blocks and more per wave: three chunks and more (two words each, as a count that has no
+    // 4-bit operands, tiles of 16 result blocks and more: three chunks and more (two words each, as a count that has no
     // larger even divisor gives) cost more than holding every word with one workgroup per CU: 85 images of 320x31x31, 3x3
-    // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, two blocks per wave: 34.5 and 39.5)
-    if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW >= 4 ? 2 : 0x7fffffff))
+    // stride 2 -> 320, five chunks 30.4 us, whole 28.6.  (64 x 128, eight blocks: 34.5 and 39.5)
+    if (!make_plan(g, PT, FMT, budget, FROWS, PARB, &pl, 0, wg_count <= 256, FMT == 1 && FW * PW * WF * WP >= 16 ? 2 : 0x7fffffff))
         return XNOR_ERR_UNSUPPORTED;
     // strict: packed words only in one chunk (the caller has another tile for the others), digits of parts only where they are ahead
     if (FMT != 2 && strict && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
@@ -1091,8 +1091,9 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         // workgroups; 4-bit operands 256 x 64 in place of 256 x 96 where that idles no more of them (three workgroups per
         // CU instead of two: 96 x 27 x 27 batch 64 20.4 -> 19.9 us).  More filters: 256 x 128 when the filter count is a
         // multiple of 256, else 128 x 128; fused epilogue with 4-bit operands up to 512 filters: 384 x 96 or 512 x 64, so
-        // that one workgroup holds every filter and no second launch adds partial sums (128 images of 13 x 13, 384 filters:
-        // 256 channels 17.1 -> 16.1 us, 384 channels 20.4 -> 19.8; 512 filters on 7 x 7, batch 256: 22.1 -> 18.3).
+        // that one workgroup holds every filter and no second launch adds partial sums (512 filters on 7 x 7, batch 256: 22.1 -> 18.3),
+        // 384 in twelve waves of 32, three per SIMD (in six of 64 two SIMDs had twice the work of the others: 128 images of 13 x 13, 256
+        // channels 17.6 -> 15.2 us, 384 channels 20.0 -> 17.3; 250 images 37 -> 33; 140 of 200x13x13, 3x3 -> 300 15.4 -> 12.9).
         // Problems with few output tiles (fully connected layers: few "pixels", long K) take the largest
         // smaller tile that still gives every CU a workgroup.
         auto wgs = [&](int ft, int pt) {
@@ -1123,7 +1124,11 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         else if (g.k_out <= 128) tile = fz ? 1 : wgs(128, 64) >= 2 * cus ? 13 : 11;
         else if (g.k_out <= 256) {
             tile = waste(wgs(256, 96)) <= waste(wgs(256, 128)) ? 4 : 5;
-            if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) { tile = 6; stead = 4; }
+            // fused epilogue, at most one workgroup per CU: eight waves of 32 filters in place of four of 64, so that a SIMD has two to
+            // choose from (128 of 384x13x13, 3x3 -> 256 15.2 -> 13.7 us, 100 of 256x14x14, 3x3 -> 256 12.8 -> 11.4, 110 of 300x13x13, 1x1 ->
+            // 130 9.5 -> 7.9; with several workgroups per CU the wider waves are ahead: 128 of 96x27x27, 5x5 -> 256 33 / 42)
+            if (FMT == 1 && fz && wgs(256, 96) <= cus) { tile = 3; stead = 4; }
+            else if (FMT == 1 && tile == 4 && waste(wgs(256, 64)) <= waste(wgs(256, 96))) { tile = 6; stead = 4; }
         } else if (FMT == 1 && fz && g.k_out <= 512) tile = g.k_out <= 384 ? 9 : 8;
         else tile = g.k_out % 256 == 0 ? 5 : fz ? 13 : 1;      // (fused epilogue: 128 x 64 ahead of 128 x 128)
         // 4-bit operands: less than a workgroup per CU of 128 x 128, 128 x 64 is ahead of it (3 images of 352x48x48 -> 310 14.6 -> 13.4 us,
@@ -1131,10 +1136,11 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
         // that hold every channel word with one workgroup per CU and would take chunks with two (11 images of 480x29x29, 5x5 -> 300
         // 25.6 and 36.9; 2 of 362x53x53 -> 416 13.7 and 17.6: below)
         if (FMT == 1 && tile == 1 && !fz && g.k_out > 256 && wgs(128, 128) < cus) { tile = 13; stead = 1; }
-        const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 ? wgs(256, 96)
+        const long long w0 = tile == 11 ? wgs(64, 128) : tile == 2 ? wgs(64, 256) : tile == 4 || tile == 3 ? wgs(256, 96)
                              : tile == 5 ? wgs(256, 128) : tile == 6 ? wgs(256, 64) : tile == 8 ? wgs(512, 64)
                              : tile == 9 ? wgs(384, 96) : tile == 12 ? wgs(512, 64) : tile == 13 ? wgs(128, 64) : wgs(128, 128);
-        if (w0 < (FMT == 2 || FMT == 4 || FMT == 6 ? 128 : 160)) {
+        // (fused tiles of eight waves and more, which hold every filter: 90 of 256x13x13, 3x3 -> 320, 159 workgroups, 13.8 us, in 128 x 64 15.9)
+        if (w0 < (FMT == 2 || FMT == 4 || FMT == 6 || tile == 3 || tile == 8 || tile == 9 ? 128 : 160)) {
             if (FMT == 6) tile = 14;
             else if (wgs(64, 128) >= cus) tile = 11;
             else if (wgs(128, 64) >= cus) tile = 13;
@@ -1169,11 +1175,13 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     case 12:                          // 512 x  64, one workgroup of four waves per CU (digit operands)
         if constexpr (FMT == 2) return launch_cfg<FMT, 4, 2, 4, 1, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict);
         return XNOR_ERR_UNSUPPORTED;
-    case 8:                           // 512 x  64, eight waves, and 384 x 96, six: one workgroup holds every filter of the
-    case 9:                           // fused epilogue (4-bit operands)
+    case 3:                           // 256 x  96, eight waves,
+    case 8:                           // 512 x  64, eight, and
+    case 9:                           // 384 x  96, twelve: one workgroup holds every filter of the fused epilogue (4-bit operands)
         if constexpr (FMT == 1) {
+            if (fz && tile == 3) return launch_cfg<FMT, 1, 3, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
             if (fz && tile == 8) return launch_cfg<FMT, 2, 2, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
-            if (fz) return launch_cfg<FMT, 2, 3, 6, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
+            if (fz) return launch_cfg<FMT, 1, 3, 12, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
         }
         return XNOR_ERR_UNSUPPORTED;
     case 15:                          // 128 x  32, two groups of four waves along K (no fused epilogue, packed-bit operands)
