@@ -1146,6 +1146,19 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
             else if (wgs(128, 64) >= cus) tile = 13;
             else tile = (FMT < 2 && !fz && g.taps == 1) ? 15 : 14;       // 128 x 32 (measured ahead of 64 x 64 at equal workgroup count), with eight waves where the records are consecutive
         }
+        // Fused epilogue, 129 to 512 filters, few pixels: tiles of 32 pixels whose eight or sixteen waves hold every filter save the second
+        // launch that adds partial sums (2.5 us), while their waves share the SIMDs for a K loop that is not longer than that (graphs of
+        // one kernel, against the best of the other tiles): 1 of 64x6x6, 3x3 -> 200 4.9 / 6.5 us, 40 of 128x14x14, 3x3 -> 200 5.9 / 8.4, 20 of
+        // 256x14x14, 3x3 -> 256 7.1 / 8.7, 76 of 300x14x14, 1x1 -> 256 6.8 / 8.0; 2 of 480x14x14, 5x5 -> 160 (188 steps) 16.8 / 15.2; more than two
+        // workgroups per CU, 100 of 128x14x14 -> 200 9.9 / 8.5.  Sixteen waves: 40 of 100x12x12, 1x1 -> 300 6.3 / 7.7, 3 of 200x9x9, 1x1 -> 400
+        // 6.3 / 7.0, 10 of 96x8x8, 3x3 -> 384 (27 steps) 7.2 / 7.2, 1 of 300x6x6, 5x5 -> 500 18.0 / 11.7; 51 of 256x14x14, 1x1 -> 400, 313
+        // workgroups, 11.1 / 8.0.
+        const int steps = (g.taps * g.cw + 1) / 2;
+        if (FMT == 1 && fz && g.k_out > 128) {
+            const int small = g.k_out <= 256 && wgs(256, 32) <= 2 * cus && steps <= 150 ? 7
+                              : g.k_out > 256 && g.k_out <= 512 && wgs(512, 32) <= cus && steps <= 24 ? 10 : 0;
+            if (small) { stead = stead ? stead : tile; tile = small; }
+        }
     }
     // every tiling is built with and without the fused epilogue (bfloat16 parts and k-bit levels: without only)
 #define XNOR_TILE_F(ID, FW, PW, WF, WP)                                                                   \
@@ -1175,10 +1188,14 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     case 12:                          // 512 x  64, one workgroup of four waves per CU (digit operands)
         if constexpr (FMT == 2) return launch_cfg<FMT, 4, 2, 4, 1, false>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, nullptr, strict);
         return XNOR_ERR_UNSUPPORTED;
-    case 3:                           // 256 x  96, eight waves,
+    case 7:                           // 256 x  32, eight waves,
+    case 10:                          // 512 x  32, sixteen,
+    case 3:                           // 256 x  96, eight,
     case 8:                           // 512 x  64, eight, and
     case 9:                           // 384 x  96, twelve: one workgroup holds every filter of the fused epilogue (4-bit operands)
         if constexpr (FMT == 1) {
+            if (fz && tile == 7) return launch_cfg<FMT, 1, 1, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
+            if (fz && tile == 10) return launch_cfg<FMT, 1, 1, 16, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
             if (fz && tile == 3) return launch_cfg<FMT, 1, 3, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
             if (fz && tile == 8) return launch_cfg<FMT, 2, 2, 8, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);
             if (fz) return launch_cfg<FMT, 1, 3, 12, 1, true>(xbits, wimg, K, A, alpha, out, dot_out, g, stream, fz);

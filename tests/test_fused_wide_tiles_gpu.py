@@ -1,4 +1,4 @@
-"""Fused epilogue in the tiles whose eight and twelve waves hold 32 filters each (256 x 96 and 384 x 96 pixels): the result, the sign words and
+"""Fused epilogue in the tiles whose 8 to 16 waves hold 32 filters each (256 x 96, 384 x 96, 256 x 32, 512 x 32 pixels): the result, the sign words and
 A of the next block at the edges of their filters and pixels, against the vector-ALU convolution and the stand-alone BinActiv."""
 import pytest
 import torch
@@ -9,10 +9,12 @@ from tests.test_conv_packed_words_gpu import packed_block
 pytestmark = pytest.mark.gpu
 
 
-# n, c, h, k, filter size; tile 0: the library's choice (both tiles among them)
+# n, c, h, k, filter size; tile 0: the library's choice (each of the tiles among them)
 @pytest.mark.parametrize("tile,n,c,h,k,r", [
     (3, 1, 32, 4, 1, 3), (3, 9, 70, 7, 129, 3), (3, 2, 200, 13, 255, 5), (3, 3, 96, 20, 256, 1), (9, 1, 64, 5, 33, 3), (9, 9, 100, 7, 257, 3),
     (9, 2, 33, 19, 353, 5), (9, 5, 256, 13, 384, 1), (0, 100, 64, 13, 200, 3), (0, 90, 40, 13, 320, 3),
+    (7, 1, 32, 3, 1, 3), (7, 5, 70, 7, 129, 3), (7, 2, 480, 9, 255, 5), (7, 3, 96, 11, 256, 1), (10, 1, 64, 5, 33, 3), (10, 5, 100, 7, 257, 3),
+    (10, 2, 33, 9, 511, 5), (10, 4, 480, 14, 512, 1), (0, 3, 64, 9, 130, 3), (0, 3, 200, 9, 400, 1),
 ])
 @pytest.mark.parametrize("with_out", [True, False])
 def test_fused_tiles(tile, n, c, h, k, r, with_out):
