@@ -6,13 +6,16 @@
 
 namespace xnor {
 
-// One workgroup = 64 consecutive pixels of one image x all channels.  Lanes run along the pixels
-// (contiguous in NCHW, so every channel row is read as 256-byte coalesced segments); the 4 waves
-// share the channels in groups of 8 (wave w takes groups w, w+4, ...), so any channel count keeps
+// One workgroup = up to 64 pixels that follow each other in the batch x all channels.  Lanes run along the pixels
+// (contiguous in NCHW, so every channel row is read as 256-byte coalesced segments); the NW waves
+// share the channels in groups of 8 (wave w takes groups w, w+NW, ...), so any channel count keeps
 // all waves busy with many independent loads in flight.  A group's 8 sign bits are one byte of
-// the pixel's packed word: it is assembled in LDS, from where the 64 x Cw words of the tile leave
-// as one contiguous, fully coalesced run.  |y| is accumulated per wave in float; the 4 partial
+// the pixel's packed word: it is assembled in LDS, from where the words of the tile leave
+// as one contiguous, fully coalesced run.  |y| is accumulated per wave in float; the NW partial
 // sums per pixel meet in LDS in a fixed order, so results do not depend on timing.
+// What bounds it: memory (256 of 64x56x56: 33.1 us, 6.2 TB/s), on small inputs the launch and one trip to memory.  Against tiles within an image
+// and 4 or 16 waves, us in a graph: 128 of 256x13x13 7.1 -> 4.7, 200 of 17x31x31 6.4 -> 4.3, 3 of 384x50x50 5.8 -> 4.2, 256 of 512x7x7
+// 5.2 -> 4.05, 256 of 128x28x28 18.9 -> 17.0, 256 of 64x56x56 34.7 -> 33.1, 9 of 83x29x23 3.7 -> 2.65.
 // Max-pooling in front of the layer (block order BinConv -> Pool -> next block's BatchNorm -> BinActiv,
 // sec. 3.2): `hw` then counts pooled pixels and every value is the maximum of its window of the
 // h x w input plane.  Out-of-range window positions are skipped; the maximum starts at -inf and skips
@@ -23,10 +26,11 @@ struct PoolGeom {
     int pad_h, pad_w;
     int relu;               // max(., 0) before the normalisation (the optional ReLU of sec. 3.2)
     int stage;              // > 0: floats per channel of the per-wave LDS staging buffer (see the kernel)
+    int px_tile;            // unpooled form: pixels per workgroup, at most 64
     int streamed;           // unpooled form: the caller says the input is not in any cache (read with the non-temporal hint)
 };
 
-// NW = waves per workgroup.  The pooled form runs 16: a pooled image has few pixels (13 x 13 after
+// NW = waves per workgroup (launch_binactiv_impl).  The pooled form runs 16: a pooled image has few pixels (13 x 13 after
 // the 27 x 27 layer), so 64-pixel tiles alone would leave CUs idle and each wave with hundreds of
 // dependent window loads; more waves share the channels instead.
 // PH x PW > 0: pooling window known at compile time (3 x 3 and 2 x 2 are built): all window loads of
@@ -36,7 +40,7 @@ template <bool WRITE_BITS, bool WRITE_A, bool BN, bool POOL, int NW, int PH = 0,
 __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
     const float *__restrict__ x, const float *__restrict__ bn_scale,
     const float *__restrict__ bn_shift, uint32_t *__restrict__ xbits, float *__restrict__ A,
-    int c, int hw, int cw, int tiles_per_image, int nblocks, PoolGeom pg)
+    int c, int hw, int cw, int tiles_per_image, int nblocks, uint32_t pixels, int px_tile, FastDiv div_hw, PoolGeom pg)
 {
     // Workgroups are dealt to the 8 XCDs round-robin by index.  Neighbouring pixel tiles share the
     // cache lines that straddle their boundary (channel rows are not line aligned), so within
@@ -53,13 +57,16 @@ __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
     // the wave index as a scalar: channel indices derived from it are then scalar too, and the
     // per-channel scale and shift come through the scalar cache instead of 64-lane loads
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    const int img = blk / tiles_per_image;
-    const int tile = blk - img * tiles_per_image;
-    const int p0 = tile * 64;
-    const int p = p0 + lane;
-    const bool live = p < hw;
-    const int pc = live ? p : hw - 1;
-    const float *xi = x + (size_t)img * c * hw + pc;                       // unpooled: this lane's pixel
+    // unpooled: 64 pixels that follow each other in the batch (planes of 49, 169 or 196 pixels would leave every last wave of an image with
+    // few of them); pooled: of an image
+    const int img = POOL ? blk / tiles_per_image : 0;
+    const int p0 = POOL ? (blk - img * tiles_per_image) * 64 : 0;
+    const uint32_t first = POOL ? (uint32_t)img * (uint32_t)hw + (uint32_t)p0 : (uint32_t)blk * (uint32_t)px_tile;      // of the batch
+    const int npx = POOL ? min(64, hw - p0) : (int)min((uint32_t)px_tile, pixels - first);
+    const bool live = lane < npx;
+    const int pc = min(p0 + lane, hw - 1);
+    const uint32_t m = first + (uint32_t)min(lane, npx - 1), img_l = div_hw.div(m);
+    const float *xi = x + (size_t)img_l * c * hw + (m - img_l * (uint32_t)hw);      // unpooled: this lane's pixel
     const float *xs = x + (size_t)img * c * pg.h * pg.w;                  // pooled: the image (wave-uniform)
     const int in_hw = POOL ? pg.h * pg.w : hw;
     int iy0 = 0, ix0 = 0;       // window origin of this lane's pooled pixel
@@ -192,15 +199,17 @@ __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
             }
         }
         uint32_t byte = 0;
+        auto sign_and_sum = [&](int real) {                   // channels of the group that exist
 #pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int ch = min(ch0 + j, c - 1);
-            float y = v[j];
-            if (BN) y = __builtin_fmaf(y, bn_scale[ch], bn_shift[ch]);
-            const bool ok = ch0 + j < c;
-            byte |= ((ok && y >= 0.0f) ? 1u : 0u) << j;
-            asum += ok ? __builtin_fabsf(y) : 0.0f;
-        }
+            for (int j = 0; j < 8; ++j) {
+                if (j >= real) break;
+                const float y = BN ? __builtin_fmaf(v[j], bn_scale[ch0 + j], bn_shift[ch0 + j]) : v[j];
+                byte |= y >= 0.0f ? 1u << j : 0u;
+                asum += __builtin_fabsf(y);
+            }
+        };
+        if (ch0 + 8 <= c) sign_and_sum(8);
+        else sign_and_sum(c - ch0);
         if (WRITE_BITS) wbytes[(lane * cw) * 4 + gidx] = (uint8_t)byte;   // byte gidx of the pixel's word run
     }
     if (WRITE_A) part[wave][lane] = asum;
@@ -209,12 +218,11 @@ __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
         float s = part[0][lane];
 #pragma unroll
         for (int q = 1; q < NW; ++q) s += part[q][lane];
-        A[(size_t)img * hw + p] = s / (float)c;
+        A[first + lane] = s / (float)c;
     }
     if (WRITE_BITS) {
-        const int npx = min(64, hw - p0);
         const uint32_t *wsrc = reinterpret_cast<const uint32_t *>(wbytes);
-        uint32_t *dst = xbits + ((size_t)img * hw + p0) * cw;
+        uint32_t *dst = xbits + (size_t)first * cw;
         const int nwords = npx * cw;
         const int tail_bytes = cw * 4 - groups;          // bytes of the last word no group wrote
         const uint32_t tail_mask = 0xFFFFFFFFu >> (8 * tail_bytes);
@@ -290,11 +298,11 @@ __global__ __launch_bounds__(64 * NWV) void binactiv_vec_kernel(
 
 template <bool WB, bool WA, bool BN, bool POOL, int NW, int PH, int PW>
 static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream, const float *x,
-                                       const float *bn_scale, const float *bn_shift, uint32_t *xbits, float *A, int c,
+                                       const float *bn_scale, const float *bn_shift, uint32_t *xbits, float *A, int n, int c,
                                        int hw, int cw, int tiles, int blocks, const PoolGeom &pg)
 {
     // (the cache policy is an instruction field: a kernel of its own for streamed inputs)
-    const bool stream_in = !POOL && (pg.streamed || (long long)(blocks / tiles) * c * hw * 4 > (64ll << 20));
+    const bool stream_in = !POOL && (pg.streamed || (long long)n * c * hw * 4 > (64ll << 20));
     auto kern = stream_in ? binactiv_kernel<WB, WA, BN, POOL, NW, PH, PW, !POOL> : binactiv_kernel<WB, WA, BN, POOL, NW, PH, PW, false>;
     if (lds > 48 * 1024) {      // the pooled form's staging buffer can pass the default dynamic LDS limit
         static std::atomic<bool> attr_done;      // false -> true only; a repeated attribute call is harmless
@@ -305,7 +313,8 @@ static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream
             attr_done.store(true, std::memory_order_release);
         }
     }
-    kern<<<grid, dim3(64 * NW), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, hw, cw, tiles, blocks, pg);
+    kern<<<grid, dim3(64 * NW), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, hw, cw, tiles, blocks, (uint32_t)((long long)n * hw), pg.px_tile,
+                                               FastDiv::make((uint32_t)hw), pg);
     return hip_status(hipGetLastError());
 }
 
@@ -319,14 +328,18 @@ static xnor_status launch_binactiv_impl(const float *x, const float *bn_scale, c
                                         uint32_t *xbits, float *A, int n, int c, int hw, const PoolGeom &pg,
                                         hipStream_t stream)
 {
-    const int cw = (c + 31) / 32;
     const int tiles = (hw + 63) / 64;
-    const long long blocks = (long long)n * tiles;
+    const long long blocks = POOL ? (long long)n * tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
     if (blocks > 0x7ffffff0LL) return XNOR_ERR_SHAPE;
-    // 16 waves per workgroup for the pooled form and wherever 4-wave workgroups would leave the CUs with fewer
-    // than 8 waves each (small planes: a 7 x 7 image is one 64-pixel tile): more loads in flight per CU
-    if (!POOL && blocks * 4 < 256 * 8 && c >= 128)
-        return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
+    // 16 waves per workgroup for the pooled form and where few workgroups have many channels (30 of 512x20x20: 4.55 us, with 8 waves 5.95; 3
+    // of 384x50x50 4.2 / 4.45); 8 where the channels give each of them a group (256 of 64x56x56 33.1, with 4 waves 34.0; 128 of 256x13x13
+    // 4.7 / 5.7; 9 of 83x29x23 2.65 / 3.0; 16 waves 53 and 4.95 for the first two), else 4 (200 of 17x31x31 4.3, with 8 waves 5.2).
+    if constexpr (!POOL) {
+        const int groups = (c + 7) / 8;
+        if (blocks <= 256 && groups >= 24)
+            return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
+        if (groups >= 8) return launch_binactiv_nw<POOL, PH, PW, 8>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
+    }
     return launch_binactiv_nw<POOL, PH, PW, POOL ? 16 : 4>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
 }
 
@@ -337,13 +350,13 @@ static xnor_status launch_binactiv_nw(const float *x, const float *bn_scale, con
 {
     const int cw = (c + 31) / 32;
     const int tiles = (hw + 63) / 64;
-    const long long blocks = (long long)n * tiles;
+    const long long blocks = POOL ? (long long)n * tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
     size_t lds = NW * 64 * sizeof(float) + (size_t)64 * cw * 4;
     if (lds > 64 * 1024) return XNOR_ERR_UNSUPPORTED;       // more than ~500k channels per pixel
     lds += (size_t)NW * 2 * pg.stage * sizeof(float);
     dim3 grid((unsigned)blocks);
 #define XNOR_BA(B, AA, N) \
-    return launch_binactiv_one<B, AA, N, POOL, NW, PH, PW>(grid, lds, stream, x, bn_scale, bn_shift, xbits, A, c, hw, cw, \
+    return launch_binactiv_one<B, AA, N, POOL, NW, PH, PW>(grid, lds, stream, x, bn_scale, bn_shift, xbits, A, n, c, hw, cw, \
                                                            tiles, (int)blocks, pg)
     const bool bn = bn_scale != nullptr;
     if (xbits && A) { if (bn) XNOR_BA(true, true, true); else XNOR_BA(true, true, false); }
@@ -365,6 +378,14 @@ xnor_status launch_binactiv(const float *x, const float *bn_scale, const float *
     }
     PoolGeom pg{};
     pg.streamed = streamed;
+    const long long pixels = (long long)n * hw, per_cu = (pixels + 256 * 64 - 1) / (256 * 64);
+    pg.px_tile = 64;
+    // Up to 8 workgroups per CU, the same number on each where that leaves them at least 48 pixels: 256 of 512x7x7, 196 workgroups of 64
+    // 5.3 us, 256 of 49 4.05; 256 of 256x14x14 10.9 and 9.6; but 128 of 256x13x13, 338 of 64 4.7, 512 of 43 5.0.
+    if (per_cu <= 8) {
+        const long long even = (pixels + 256 * per_cu - 1) / (256 * per_cu);
+        if (even >= 48 && even < 64) pg.px_tile = (int)even;
+    }
     return launch_binactiv_impl<false>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
 }
 
