@@ -106,7 +106,7 @@ static xnor_status launch_bwn_digits(const float *x, void *out, int n, int c, in
     const int cw = (c + 31) / 32;
     const int groups = (cw + 3) / 4, waves = (cw + groups - 1) / groups;         // up to four words per workgroup, evenly
     const long long pixels = (long long)n * hw, tiles = (pixels + 63) / 64;
-    if (tiles * groups > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;
+    if (n > 65535 || tiles * groups > 0x7fffffffLL) return XNOR_ERR_UNSUPPORTED;      // (images: one limit for every width)
     bwn_digits_kernel<<<dim3((unsigned)(tiles * groups)), dim3(64 * waves), (size_t)waves * 64 * DIGITS_ROW, stream>>>(
         x, static_cast<uint8_t *>(out), c, hw, cw, (uint32_t)pixels, (uint32_t)tiles, FastDiv::make((uint32_t)tiles),
         FastDiv::make((uint32_t)hw));

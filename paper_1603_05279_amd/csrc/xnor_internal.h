@@ -107,11 +107,6 @@ xnor_status launch_conv_popcount(const uint32_t *xbits, const uint32_t *wbits, c
 bool linear_popcount_applies(const ConvGeom &g, bool matrix_image);
 xnor_status launch_linear_popcount(const uint32_t *xbits, const uint32_t *wbits, const float *Krow, const float *alpha,
                                    float *out, int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
-// the layers linear_words_kernel takes: a 1x1 image and filter, rows of four words and more, sums that a float holds
-inline bool linear_words_applies(const ConvGeom &g)
-{
-    return g.h == 1 && g.w == 1 && g.taps == 1 && g.ph == 0 && g.pw == 0 && g.dil_h == 1 && g.dil_w == 1 && g.cw >= 4 && g.c < (1 << 24) - 32 && g.n < (1 << 30);
-}
 // words: the scalar-path image (wimg_pop_bytes)
 xnor_status launch_linear_words(const uint32_t *xbits, const uint32_t *words, const float *Krow, const float *alpha, float *out,
                                 int32_t *dot_out, const ConvGeom &g, hipStream_t stream);
@@ -121,6 +116,14 @@ xnor_status launch_linear_words(const uint32_t *xbits, const uint32_t *words, co
 __host__ __device__ inline size_t wimg_pop_bytes(int k_out, int c, int taps)
 {
     return (size_t)((k_out + 31) / 32) * (size_t)taps * (size_t)((c + 31) / 32) * 128u;
+}
+
+// The layers linear_words_kernel takes: a 1x1 image and filter, rows of four words and more, sums that a float holds; images and results
+// beyond the ranges of the convolution's buffer resources are refused here as there.
+inline bool linear_words_applies(const ConvGeom &g)
+{
+    return g.h == 1 && g.w == 1 && g.taps == 1 && g.ph == 0 && g.pw == 0 && g.dil_h == 1 && g.dil_w == 1 && g.cw >= 4 && g.c < (1 << 24) - 32 &&
+           g.n < (1 << 30) && 34LL * g.k_out * 4 < 0x7ffffff0LL && wimg_pop_bytes(g.k_out, g.c, 1) <= 0x7fffffffull;
 }
 
 // Next block's BatchNorm + BinActiv applied in the convolution's epilogue (block order of sec. 3.2):
