@@ -307,8 +307,8 @@ template <> struct Enc<2> : Enc<1> {
     }
 };
 
-// Binary-Weight-Network operands without conversion, for short K loops (few taps, few workgroups), where making the digits
-// above would take longer than their matrix instructions save.  The real activations arrive
+// Binary-Weight-Network operands without conversion, for inputs of at most 32 channels and short K loops (few taps, few workgroups), where
+// making the digits above while staging would take longer than their matrix instructions save.  The real activations arrive
 // pre-split into three bfloat16 parts (hi + mid + lo == the float exactly), 16 channels x one part
 // = one 32-byte "word" per pixel; the weights are +-1.0 (0 past the last channel or filter) in
 // bfloat16, one record per 16-channel group that multiplies all three parts (the record is fetched
