@@ -455,7 +455,7 @@ def main():
     roofline.update({
         "traffic": sum(traffic) if all(t is not None for t in traffic) else None,
         "traffic_source": PROFILED_TRAFFIC_SOURCE + " (rocprofv3 FETCH_SIZE / WRITE_SIZE, not measured in this run)",
-        "kernel": "conv_mfma_kernel (xnor_conv2d / xnor_linear, 4-bit-float matrix instructions), all launches of one step",
+        "kernel": "conv_mfma_kernel and linear_words_kernel (xnor_conv2d / xnor_linear, 4-bit-float matrix instructions), all launches of one step",
         "launches_per_step": len(rows), "algorithmic_bytes": nbytes, "flop": flop,
         "avg_launch_us": conv_s * 1e6 / len(rows), "timing": f"HIP events around {max(50, args.launches)} back-to-back "
         "launches per layer, rotating buffer sets" if args.buffers == "rotating" else "HIP events, one buffer set",
