@@ -1219,10 +1219,13 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     xnor_status s = launch(tile, FMT == 2 ? !last && mfma_tile_override() == 0 : stead == 1);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(1, true);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(13);
-    // (digits, wide rows: fewer pixels)
+    // Real inputs, wide rows: fewer pixels span fewer of them (512 x 64 in place of 256 x 96 for digits made while staging too; parts made of
+    // digits: nothing else takes the call, and 32 pixels fit wherever any tile does)
+    if (FMT == 2 && tile == 4 && g.k_out > 384 && mfma_tile_override() == 0 && s == XNOR_ERR_UNSUPPORTED) s = launch(12);
     if (FMT == 2 && g.cw > 1 && mfma_tile_override() == 0)
         for (const int other : {11, 14})
             if (s == XNOR_ERR_UNSUPPORTED) s = launch(other);
+    if (FMT == 6 && tile != 14 && s == XNOR_ERR_UNSUPPORTED) s = launch(14);
     if (FMT != 1 || mfma_tile_override() != 0) return s;
     // 4-bit operands: the rows under the chosen tile may not fit the LDS with what the tile keeps beside them (384 and 512
     // filters of the fused epilogue: 5 and 6 KiB of alpha, scale and shift, a word per pixel and 32 filters; 64 x 6 x 6, one 6 x 6

@@ -50,3 +50,20 @@ def test_backward_layers_with_wide_rows(case):
 @pytest.mark.parametrize("case", [(1072, 8, 7, 8, 512, 7, 7, (1, 2), (6, 0)), (112, 10, 278, 72, 512, 3, 3, (4, 2), (2, 0)), (8, 5, 34, 85, 512, 7, 5, (2, 3), (2, 4))])
 def test_binary_weight_layers_that_only_digits_stage(case):
     assert xnor.lib().xnor_bwn_conv2d(FAKE, FAKE, FAKE, FAKE, ctypes.byref(xnor.make_desc(*case)), None) == ERR_HIP
+
+
+# Real inputs of more than 32 channels on rows so wide that the larger tiles' do not fit as digits (144 bytes a pixel and word) nor as parts
+# (112): 129 to 640 filters, for which tiles of 64 to 96 pixels would, of many workgroups
+@pytest.mark.parametrize("case", [
+    (1, 64, 384, 384, 256, 3, 3, 2, 1), (32, 64, 384, 384, 256, 3, 3, 2, 1), (52, 96, 170, 176, 192, 3, 3, 2, 1),
+    (75, 128, 53, 189, 192, 3, 3, 2, 1), (32, 96, 160, 160, 256, 5, 5, 2, 2), (128, 64, 192, 192, 256, 7, 7, 2, 3), (2, 64, 92, 92, 160, 7, 7, 1, 3),
+    (4, 64, 184, 184, 160, 5, 5, 1, 2), (8, 48, 46, 92, 256, 7, 7, 1, 3), (1, 48, 98, 98, 640, 11, 11, 1, 5), (797, 35, 26, 345, 156, 1, 1, 3, 0),
+    (2, 996, 93, 93, 2844, 7, 7, 2, (6, 3)), (301, 51, 36, 36, 441, 11, 1, 3, (5, 0)), (3, 34, 74, 160, 4278, 3, 7, 2, (0, 6))])
+def test_binary_weight_layers_with_wide_rows(case):
+    assert xnor.lib().xnor_bwn_conv2d(FAKE, FAKE, FAKE, FAKE, ctypes.byref(xnor.make_desc(*case)), None) == ERR_HIP
+
+
+# (385 to 512 filters, up to 32 channels: 96 pixels do not fit as digits, 64 do)
+@pytest.mark.parametrize("case", [(840, 25, 3, 23, 466, 5, 5, 3, (4, 3)), (207, 2, 36, 27, 433, 5, 7, 3, (0, 3))])
+def test_binary_weight_layers_of_many_filters(case):
+    assert xnor.lib().xnor_bwn_conv2d(FAKE, FAKE, FAKE, FAKE, ctypes.byref(xnor.make_desc(*case)), None) == ERR_HIP

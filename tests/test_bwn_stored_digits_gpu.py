@@ -18,6 +18,8 @@ CASES = [
     (2, 257, 9, 9, 40, 1, 1, (1, 1), (0, 0)), (1, 512, 14, 14, 512, 3, 3, (1, 1), (1, 1)),
     (1, 64, 9, 160, 40, 5, 5, (1, 1), (2, 2)), (1, 96, 8, 170, 70, 5, 4, (1, 1), (2, 1)),      # one word per chunk
     (1, 33, 9, 150, 20, 7, 7, (1, 1), (3, 3)), (1, 72, 9, 150, 20, 7, 7, (1, 1), (3, 3)),      # parts again
+    (1, 33, 110, 150, 70, 7, 7, (1, 1), (3, 3)), (1, 40, 112, 300, 20, 3, 3, (1, 1), (1, 1)),    # in tiles of 128 x 128 and 64 x 256
+    (2, 64, 92, 92, 160, 7, 7, (1, 1), (3, 3)),                                                # and of 128 x 32 where 128 x 128 does not fit
 ]
 
 
