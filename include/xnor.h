@@ -255,17 +255,17 @@ XNOR_API int xnor_conv2d_pool(const uint32_t *xbits, const void *wmfma, const fl
  * estimated by alpha * sign(W):
  *     out[n][k][oy][ox] = alpha_k * sum over in-bounds taps and channels of  I * sign(W)
  * (additions and subtractions of the inputs only; zero padding, correlation, no bias, as above).
- * The weights are +-1 and the sums run on the matrix cores in float.  Inputs of more than 32 channels are five digits of 6-bit floats
- * under one power of two per 32 channels of a pixel, which hold the largest of the 32 exactly and the others to half of its unit in the
- * last place (from 1.9375 * 2^127 on: to a unit; below 2^-106: to 2^-130).  Up to 32 channels xnor_bwn_split writes every input as three
- * bfloat16 numbers whose sum is the float exactly (finite inputs), and the sums are of those three parts, or (more than 16 channels
- * under filters of 25 taps and more, or of 9 and more where the layer fills the chip, but for shapes whose digits are the slower form)
- * of the same floats as digits.  Three calls:
+ * The weights are +-1 and the sums run on the matrix cores in float.  Inputs of more than 48 channels on rows of at most 64 pixels are
+ * five digits of 6-bit floats under one power of two per 32 channels of a pixel, which hold the largest of the 32 exactly and the others
+ * to half of its unit in the last place (from 1.9375 * 2^127 on: to a unit; below 2^-106: to 2^-130).  Otherwise xnor_bwn_split writes
+ * every input as three bfloat16 numbers whose sum is the float exactly (finite inputs), and the sums are of those three parts, or (more
+ * than 16 channels under filters of 25 taps and more, or of 9 and more where the layer fills the chip, but for shapes whose digits are
+ * the slower form) of the same floats as digits.  Three calls:
  *   xnor_bwn_split         x float32 [n][c][h][w]  ->  parts, xnor_bwn_parts_bytes(n, c, h, w) bytes (opaque)
  *   xnor_bwn_pack_weights  w float32 [k_out][c][kh][kw]  ->  alpha float32 [k_out] (as xnor_pack_weights),
  *                          wimg, xnor_bwn_wimg_bytes(k_out, c, kh, kw) bytes (opaque); once per layer
  *   xnor_bwn_conv2d        parts, wimg, alpha  ->  out float32 [n][k_out][h_out][w_out]; d describes the
- *                          convolution with the real channel count c
+ *                          convolution with the real channel count c, and the same n, c, h and w as the split was given
  * Differences between this result and one accumulated in double stay within float rounding of the
  * running sums (about 1e-7 * sqrt(c*kh*kw) of the magnitude of the terms); the digits' sums, with fewer additions, to
  * about half of that, also for heavy-tailed inputs and outlier channels.  Where two large inputs of a pixel's 32 channels cancel, what

@@ -36,6 +36,7 @@ xnor_status make_geom(const xnor_conv_desc *d, ConvGeom *g)
     g->div_howo = FastDiv::make((uint32_t)(ho * wo));
     g->div_kw = FastDiv::make((uint32_t)d->kw);
     g->k_per_image = 0;
+    g->stored_digits = 0;
     g->dil_h = g->dil_w = 1;
     g->real_h = g->h; g->real_w = g->w;
     g->div_dil_h = g->div_dil_w = FastDiv::make(1u);
@@ -359,7 +360,7 @@ int xnor_bwn_split(const float *x, void *parts, int n, int c, int h, int w, void
     if ((long long)h * w > 0x7fffffffLL || (long long)n * h * w * ((c + 15) / 16) * 3 > 0x7fffffffLL)
         return XNOR_ERR_SHAPE;
     if (!aligned16(x) || !aligned16(parts)) return XNOR_ERR_ALIGN;
-    return launch_bwn_split(x, parts, n, c, h * w, (hipStream_t)hip_stream);
+    return launch_bwn_split(x, parts, n, c, h, w, (hipStream_t)hip_stream);
 }
 
 int xnor_bwn_pack_weights(const float *w, float *alpha, void *wimg, int k_out, int c, int kh, int kw,

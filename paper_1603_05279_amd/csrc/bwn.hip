@@ -1,6 +1,6 @@
 // Binary-Weight-Network convolution (sec. 3.1): real-valued inputs, weights estimated as alpha * sign(W),
 //     I * W  ~  (I (+) B) alpha        (convolution with additions and subtractions only).
-// The activations travel as five digits of 6-bit floats (Enc<2>, more than 32 channels) or as three bfloat16 parts per float (their sum
+// The activations travel as five digits of 6-bit floats (Enc<2>, bwn_in_digits) or as three bfloat16 parts per float (their sum
 // is the float exactly); the convolution kernel (conv_mfma_kernel.h) stages the digits as they are, the parts as they are (Enc<4>) or as
 // digits; the matrix cores accumulate in float.  This file holds the preparation kernels: the activation split and the weights.
 #include "mfma_common.h"
@@ -113,9 +113,10 @@ static xnor_status launch_bwn_digits(const float *x, void *out, int n, int c, in
     return hip_status(hipGetLastError());
 }
 
-xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, hipStream_t stream)
+xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int h, int w, hipStream_t stream)
 {
-    if (bwn_in_digits(c)) return launch_bwn_digits(x, parts, n, c, hw, stream);
+    const int hw = h * w;
+    if (bwn_in_digits(c, w)) return launch_bwn_digits(x, parts, n, c, hw, stream);
     const int cg = (c + 15) / 16;
     const int gblocks = (cg + SPLIT_G - 1) / SPLIT_G;
     if (gblocks > 65535 || n > 65535) return XNOR_ERR_UNSUPPORTED;

@@ -412,7 +412,7 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
         } else {
         const int items = nrows * g.wp * ccw;
         if constexpr (FMT == 2) {
-            if (g.cw > 1) {
+            if (g.stored_digits) {
                 // digits as the split wrote them: 16 of a word's 128 bytes per item, a pixel's words of the chunk one after the other
                 constexpr int FB = 4;          // items in flight per thread
                 const int units = items * 8;
@@ -439,24 +439,30 @@ __global__ __launch_bounds__(64 * WF * WP * KS, (FW * PW <= (FMT == 2 || FMT == 
                         if (dst[u] >= 0) *reinterpret_cast<v4u *>(lds + dst[u]) = d[u];
                 }
             } else {
-            // at most 32 channels of a pixel per item: one or two groups of three bfloat16 parts (96 bytes each), summed back to
-            // floats (exact), to digits
-            const bool second = g.c > 16;
-            for (int px = tid; px < items; px += NT) {
-                const uint32_t rr = pl.div_wp.div_small((uint32_t)px);
-                const int xcol = px - (int)rr * g.wp - g.pw;
+            // 32 channels of a pixel per item: two groups of three bfloat16 parts (192 bytes), summed back to floats (exact),
+            // to digits
+            const int groups = (g.c + 15) / 16;
+            for (int it = tid; it < items; it += NT) {
+                const uint32_t px = pl.div_ccw.div_small((uint32_t)it);
+                const int wl = it - (int)px * ccw;
+                const uint32_t rr = pl.div_wp.div_small(px);
+                const int xcol = (int)(px - rr * g.wp) - g.pw;
                 const int rowbase = rowinfo[rr];
-                const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w;
-                v4u *dst = reinterpret_cast<v4u *>(lds + rr * pl.row_pitch + (px - (int)rr * g.wp) * pl.ps);
+                const int grp = 2 * (wbase + wl);
+                const bool ok = rowbase >= 0 && xcol >= 0 && xcol < g.w && grp < groups;
+                v4u *dst = reinterpret_cast<v4u *>(lds + rr * pl.row_pitch + (px - rr * g.wp) * pl.ps + wl * E::BPB);
                 if (!ok) {
 #pragma unroll
                     for (int q = 0; q < 8; ++q) dst[q] = v4u{0, 0, q == 7 ? 127u : 0u, 0};
                     continue;
                 }
-                const auto *src = in_global(reinterpret_cast<const v4u *>(xbits)) + ((size_t)rowbase + xcol) * (second ? 12 : 6);
+                const auto *src = in_global(reinterpret_cast<const v4u *>(xbits)) + (((size_t)rowbase + xcol) * groups + grp) * 6;
                 v4u p[12];
 #pragma unroll
-                for (int q = 0; q < 12; ++q) p[q] = src[q < 6 || second ? q : q - 6];     // (no second group: the first one again, cleared below)
+                for (int q = 0; q < 6; ++q) p[q] = src[q];
+                const int second = grp + 1 < groups ? 6 : 0;      // (no second group: the first one again, cleared below)
+#pragma unroll
+                for (int q = 0; q < 6; ++q) p[6 + q] = src[second + q];
                 float x[32];
 #pragma unroll
                 for (int c = 0; c < 32; ++c) {
@@ -947,8 +953,8 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         // (packed words and digits: the last chunk may lack one word, staged as zeros)
         if (fmt == 1 || fmt == 2 ? (g.cw + ccw - 1) / ccw * ccw > g.cw + 1 : g.cw % ccw != 0) continue;
         // packed words and digits take two channel words per step: chunks must keep the words of a step together (a single word of
-        // digits: two taps per step)
-        if (ccw != g.cw && (ccw % bps) && !(fmt == 2 && ccw == 1)) continue;
+        // stored digits: two taps per step)
+        if (ccw != g.cw && (ccw % bps) && !(g.stored_digits && ccw == 1)) continue;
         const long long row_bytes = (long long)ccw * bpb;
         const long long ps = row_bytes + ((row_bytes / 16) % 2 == 0 ? 16 : 0);
         // LDS row pitch: at least wp pixels, padded so that stepping from the last output pixel of a row
@@ -975,7 +981,7 @@ static bool make_plan(const ConvGeom &g, int PT, int fmt, int lds_budget, int fu
         const long long whole = lone ? 156 * 1024 : 80 * 1024;
         const long long budget = ccw == g.cw ? (lds_budget > whole ? lds_budget : whole) : lds_budget;
         if (total > budget && !last) continue;
-        if (total > LDS_LIMIT && fmt == 2 && ccw > 1) continue;
+        if (total > LDS_LIMIT && g.stored_digits && ccw > 1) continue;
         if (total > LDS_LIMIT) return false;
         MfmaPlan one;
         if ((g.cw + ccw - 1) / ccw > most_chunks &&
@@ -1025,11 +1031,17 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     if (FMT != 2 && strict && pl.cc_words != g.cw) return XNOR_ERR_UNSUPPORTED;
     const size_t lds = plan_lds_bytes(pl, FMT, g.wp, PT, FROWS, PARB);
     if (FMT == 2 && strict) {
-        // Inputs that come as parts (at most 32 channels).  With one workgroup on a CU that has several to run nothing hides the
-        // conversion: a word's digits have to save 24 matrix instructions per 32 x 32 results over their taps (a 512-filter tile holds
-        // the CU whatever it stages).  Parts against digits, us (saved per word): 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; 512 filters:
-        // 19 of 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
-        if ((FW * PW > 6 || (lds > 80 * 1024 && wg_count > 256)) && bwn_digits_save(g) < 24) return XNOR_ERR_UNSUPPORTED;
+        // With one workgroup on a CU that has several to run nothing hides the conversion: a word's digits have to save 24 matrix
+        // instructions per 32 x 32 results over their taps (a 512-filter tile holds the CU whatever it stages).  Where the words
+        // come in chunks they have to save 84, or the tile one per staged word.  Parts against digits, us (saved per word): 2 images of 35x50x50, 3x3 -> 448 (18) 13.4 / 20.7;
+        // 18 of 64x50x50, 3x3 -> 236 (31) 37.2 / 32.9; 88 of 32x18x43, 5x5 -> 32 (25) 35.9 / 25.3; in chunks 7 of 68x44x44, 3x3 -> 288
+        // (15) 26.7 / 45.3; 5 of 160x51x51, 5x5 -> 60 (75) 49.1 / 61.4; 20 of 192x34x34, 5x5 -> 32 (87) 82.3 / 73.6;
+        // 64 of 96x27x27, 5x5 -> 256 (67, 5.5 per staged word) 117 / 92.  512 filters: 19 of 37x30x30, 3x3 -> 428 (18) 25.9 / 33.9; 5 of 96x48x48, 3x3 -> 448 (24) 31.9 / 24.8.
+        const bool wide = FW * PW > 6, chunks = !wide && pl.cc_words != g.cw;
+        const long long saved = bwn_digits_save(g), staged = (long long)pl.max_rows * g.wp * g.cw;
+        const bool ahead = chunks ? saved >= 84LL * g.cw || saved * std::min(FT / 32, g.fblocks) * (PT / 32) >= staged
+                                  : saved >= 24LL * g.cw;
+        if ((wide || (lds > 80 * 1024 && wg_count > 256)) && !ahead) return XNOR_ERR_UNSUPPORTED;
     }
     pl.lut_offset = plan_lut_offset(pl, FMT, g.wp, PT, FROWS, PARB);
     // two builds of every tiling: weight records consecutive (one chunk holds all channel words) or not; 4-bit operands: a
@@ -1041,7 +1053,8 @@ static xnor_status launch_cfg(const uint32_t *xbits, const void *wimg, const flo
     if (KS > 1 && (!linear || (size_t)pl.region_bytes < (size_t)(KS - 1) * WF * WP * FW * PW * 16 * 64 * 4))
         return XNOR_ERR_UNSUPPORTED;
     const bool direct_chunks = FMT == 1 && !linear && pl.vec > 0;
-    auto kern = linear          ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, true, false, KS>
+    // (parts made of digits: where all of a pixel's fitted, a word of its digits would)
+    auto kern = linear          ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, FMT != 6, false, KS>
                 : direct_chunks ? conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, KS != 1, false, KS, FMT == 1 && KS == 1>
                                 : conv_mfma_kernel<FMT, FW, PW, WF, WP, FUSE, KS != 1, false, KS>;
     static std::atomic<bool> attr_done[3];       // per instantiation (zero-initialised: false)
@@ -1108,13 +1121,15 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
             // (measured): up to 64 filters 64 x 256, up to 128 filters 128 x 128; beyond that the tile
             // among 256 x 96 (when one tile holds every filter), 128 x 128 and 128 x 64 that leaves the
             // fewest CUs idle in the last round, the larger one on a tie
-            // (digits, 385 to 512 filters: 512 x 64, whose waves read every staged digit for four filter blocks, or 256 x 96, whichever
-            // has less to do on the CU that does most (8 and 6 blocks per wave and workgroup): 256 of 512x7x7, 3x3 -> 512 73 / 98 us,
-            // 64 of 256x14x14, 1x1 -> 400 16.2 / 18.1; 28 of 192x12x50, 3x3 -> 416 69 / 60, 5 of 96x48x48, 3x3 -> 448 21.7 / 18.5)
+            // (digits, 385 to 512 filters: 512 x 64, so that several words of parts are converted once: 512 x 7 x 7, batch 256, 115 -> 99 us.
+            // Digits as the split wrote them, or of a single word of parts: 512 x 64, whose waves read every staged digit for four filter blocks,
+            // or 256 x 96, whichever has less to do on the CU that does most (8 and 6 blocks per wave and workgroup): 256 of 512x7x7, 3x3 -> 512
+            // 73 / 98 us, 64 of 256x14x14, 1x1 -> 400 16.2 / 18.1; 28 of 192x12x50, 3x3 -> 416 69 / 60, 5 of 96x48x48, 3x3 -> 448 21.7 / 18.5; one
+            // word, 3 of 26x52x52, 5x5 -> 415 26.1 / 21.0, 11 of 30x30x30, 5x5 -> 385 24.7 / 21.2)
             if (g.k_out <= 64) tile = 2;
             else if (g.k_out <= 128) tile = 1;
             else if (FMT == 2 && g.k_out > 384 && g.k_out <= 512)
-                tile = (wgs(512, 64) + cus - 1) / cus * 8 <= (wgs(256, 96) + cus - 1) / cus * 6 ? 12 : 4;
+                tile = (!g.stored_digits && g.cw > 1) || (wgs(512, 64) + cus - 1) / cus * 8 <= (wgs(256, 96) + cus - 1) / cus * 6 ? 12 : 4;
             else {
                 const double w4 = g.k_out <= 256 ? waste(wgs(256, 96)) : 1e30;
                 const double w1 = waste(wgs(128, 128)), w13 = waste(wgs(128, 64));
@@ -1219,13 +1234,13 @@ xnor_status launch_fmt(const uint32_t *xbits, const void *wimg, const float *K, 
     xnor_status s = launch(tile, FMT == 2 ? !last && mfma_tile_override() == 0 : stead == 1);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(1, true);
     if (stead == 1 && s == XNOR_ERR_UNSUPPORTED) s = launch(13);
-    // Real inputs, wide rows: fewer pixels span fewer of them (512 x 64 in place of 256 x 96 for digits made while staging too; parts made of
-    // digits: nothing else takes the call, and 32 pixels fit wherever any tile does)
-    if (FMT == 2 && tile == 4 && g.k_out > 384 && mfma_tile_override() == 0 && s == XNOR_ERR_UNSUPPORTED) s = launch(12);
-    if (FMT == 2 && g.cw > 1 && mfma_tile_override() == 0)
+    // Real inputs, many rows under a tile: fewer pixels span fewer of them.  (Parts, where nothing else takes the call: 32 pixels fit wherever
+    // any tile does)
+    if (FMT == 2 && tile == 4 && !g.stored_digits && g.k_out > 384 && mfma_tile_override() == 0 && s == XNOR_ERR_UNSUPPORTED) s = launch(12);
+    if (FMT == 2 && g.stored_digits && mfma_tile_override() == 0)
         for (const int other : {11, 14})
             if (s == XNOR_ERR_UNSUPPORTED) s = launch(other);
-    if (FMT == 6 && tile != 14 && s == XNOR_ERR_UNSUPPORTED) s = launch(14);
+    if ((FMT == 6 || (FMT == 4 && last && mfma_tile_override() == 0)) && tile != 14 && s == XNOR_ERR_UNSUPPORTED) s = launch(14);
     if (FMT != 1 || mfma_tile_override() != 0) return s;
     // 4-bit operands: the rows under the chosen tile may not fit the LDS with what the tile keeps beside them (384 and 512
     // filters of the fused epilogue: 5 and 6 KiB of alpha, scale and shift, a word per pixel and 32 filters; 64 x 6 x 6, one 6 x 6

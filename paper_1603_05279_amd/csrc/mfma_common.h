@@ -307,8 +307,8 @@ template <> struct Enc<2> : Enc<1> {
     }
 };
 
-// Binary-Weight-Network operands without conversion, for inputs of at most 32 channels and short K loops (few taps, few workgroups), where
-// making the digits above while staging would take longer than their matrix instructions save.  The real activations arrive
+// Binary-Weight-Network operands without conversion, where the split writes parts (bwn_in_digits) and the K loop is so short (few taps, few
+// workgroups) that making the digits above while staging would take longer than their matrix instructions save.  The real activations arrive
 // pre-split into three bfloat16 parts (hi + mid + lo == the float exactly), 16 channels x one part
 // = one 32-byte "word" per pixel; the weights are +-1.0 (0 past the last channel or filter) in
 // bfloat16, one record per 16-channel group that multiplies all three parts (the record is fetched
@@ -332,8 +332,8 @@ template <> struct Enc<4> {
     static __device__ __forceinline__ void build_lut(uint8_t *, int, int) {}
 };
 
-// The same parts, made from digits (Enc<2>) while they are staged: for rows so wide that one channel word's digits do not fit the
-// LDS and a part of 16 channels does.
+// The same parts, made from digits (Enc<2>) while they are staged: for filters so tall that one channel word's digits of the rows under a
+// tile do not fit the LDS and a part of 16 channels does.
 template <> struct Enc<6> : Enc<4> {
     // word: the 32 dwords of 32 channels' digits; half: which 16 of them; out: their hi, mid and lo parts, 16 bfloat16 numbers each
     static __device__ __forceinline__ void parts_of_digits(const v4u (&word)[8], int half, v4u (&out)[6])

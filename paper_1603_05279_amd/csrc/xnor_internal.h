@@ -23,6 +23,7 @@ struct ConvGeom {
     // divisions are exact and in range, and zero otherwise.  1 / h / w for ordinary convolutions.
     int dil_h, dil_w, real_h, real_w;
     FastDiv div_dil_h, div_dil_w;
+    int stored_digits; // real inputs: the buffer holds digits (Enc<2>), not bfloat16 parts
     int k_per_image;   // 1: the K given to the matrix-core kernels is one value per image [n] instead of a plane [n][ho][wo]
 };
 
@@ -153,13 +154,18 @@ void set_mfma_tuning(int tile, int lds_budget);
 // (g: the layer; gp: the same over the parts' 3 * ceil(c/16) words of 32 channels)
 xnor_status launch_bwn_conv(const void *parts, const void *wimg, const float *alpha, float *out, const ConvGeom &g,
                             const ConvGeom &gp, hipStream_t stream);
-// Form of the buffer that xnor_bwn_split writes, by channels alone (it knows no filters): true: the digits of Enc<2>, 128 bytes per
-// pixel and 32 channels, which fit the parts' room (96 bytes per 16 channels) from 33 channels on, where they also take fewer matrix
-// instructions whatever the filters; false: three bfloat16 parts.  Passes over 30 layers, split and convolution, parts or digits made
-// while staging against stored digits: 16 of 33 and more channels at 0.64 to 1.04 of the time, 0.88 in the mean (42 of 300x29x13, 3x3 -> 18
-// 54.0 -> 34.7 us, 59 of 500x7x7, 1x1 -> 192 20.3 -> 17.2, one of 74x6x31, 3x3 -> 224 11.1 -> 11.6).
-inline bool bwn_in_digits(int c) { return c > 32; }
-xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int hw, hipStream_t stream);
+// Form of the buffer that xnor_bwn_split writes, by channels and row length alone (it knows no filters): true: the digits of Enc<2>, 128
+// bytes per pixel and 32 channels, which fit the parts' room (96 bytes per 16 channels) from 33 channels on; false: three bfloat16 parts, which
+// the convolution takes as they are or makes digits of.  Passes, split and convolution, parts against digits, us: 7 of 261x14x14, 3x3 -> 480
+// 38.1 / 18.5, 15 of 321x12x38, 3x3 -> 16 46.7 / 34.7; 55 drawn layers of 49 to 512 channels, rows up to 56: digits 0.88 of the time in the mean,
+// behind only in launches of a few hundred pixels, whose waves make twice the channels (one of 74x6x31, 3x3 -> 224 10.4 / 10.9).
+// 33 to 48 channels leave half of the second word empty: 105 layers 1.0 in the mean, as many behind as ahead (134 of 42x22x22, 3x3 -> 136 45 / 38,
+// 5 of 43x47x47, 3x3 -> 37 14.1 / 16.5, 2 of 48x15x36, 1x1 -> 144 7.8 / 8.6), so their inputs stay exact.
+// A tile stages whole rows, 144 bytes per pixel and word against 112 for a part of 16 channels: of 25 layers of rows of 48 and 64 none was
+// slower in digits, of 95 of rows of 80 to 384 thirty, by up to three times (one of 64x384x384, 3x3 -> 192 203 / 368, one of 256x150x144, 7x7
+// stride 2 -> 64 145 / 225, 3 of 200x80x80, 3x3 -> 64 56 / 60).
+inline bool bwn_in_digits(int c, int w) { return c > 48 && w <= 64; }
+xnor_status launch_bwn_split(const float *x, void *parts, int n, int c, int h, int w, hipStream_t stream);
 xnor_status launch_bwn_pack(const float *w, float *alpha, void *wimg, int k_out, int c, int taps, hipStream_t stream);
 // Sizes of the two matrix-core weight images (int8 first, 4-bit float second), 1 KiB records;
 // each image ends with one all-zero record that padded K-steps multiply by.
