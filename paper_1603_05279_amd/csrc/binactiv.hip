@@ -318,6 +318,10 @@ static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream
     return hip_status(hipGetLastError());
 }
 
+// LDS of a workgroup: a partial sum per wave and pixel, the words of 64 pixels
+constexpr size_t BINACTIV_LDS = 64 * 1024;
+static size_t binactiv_lds(int waves, int cw) { return (size_t)waves * 64 * sizeof(float) + (size_t)64 * cw * 4; }
+
 template <bool POOL, int PH, int PW, int NW>
 static xnor_status launch_binactiv_nw(const float *x, const float *bn_scale, const float *bn_shift,
                                       uint32_t *xbits, float *A, int n, int c, int hw, const PoolGeom &pg,
@@ -335,11 +339,12 @@ static xnor_status launch_binactiv_impl(const float *x, const float *bn_scale, c
     // of 384x50x50 4.2 / 4.45); 8 where the channels give each of them a group (256 of 64x56x56 33.1, with 4 waves 34.0; 128 of 256x13x13
     // 4.7 / 5.7; 9 of 83x29x23 2.65 / 3.0; 16 waves 53 and 4.95 for the first two), else 4 (200 of 17x31x31 4.3, with 8 waves 5.2).
     if constexpr (!POOL) {
-        const int groups = (c + 7) / 8;
-        if (blocks <= 256 && groups >= 24)
+        // (from 7681 channels on, where fewer of them leave room for the words)
+        const int groups = (c + 7) / 8, cw = (c + 31) / 32;
+        if (blocks <= 256 && groups >= 24 && binactiv_lds(16, cw) <= BINACTIV_LDS)
             return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
         // (9 to 15 groups leave waves without work on every second turn: 64 of 96x27x27 from memory, 765 workgroups, 4 waves 5.35, 8 waves 5.7)
-        if (groups == 8 || groups >= 16 || (groups > 8 && blocks <= 512))
+        if ((groups == 8 || groups >= 16 || (groups > 8 && blocks <= 512)) && binactiv_lds(8, cw) <= BINACTIV_LDS)
             return launch_binactiv_nw<POOL, PH, PW, 8>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
     }
     return launch_binactiv_nw<POOL, PH, PW, POOL ? 16 : 4>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
@@ -353,8 +358,8 @@ static xnor_status launch_binactiv_nw(const float *x, const float *bn_scale, con
     const int cw = (c + 31) / 32;
     const int tiles = (hw + 63) / 64;
     const long long blocks = POOL ? (long long)n * tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
-    size_t lds = NW * 64 * sizeof(float) + (size_t)64 * cw * 4;
-    if (lds > 64 * 1024) return XNOR_ERR_UNSUPPORTED;       // more than ~500k channels per pixel
+    size_t lds = binactiv_lds(NW, cw);
+    if (lds > BINACTIV_LDS) return XNOR_ERR_UNSUPPORTED;    // more than 8064 channels per pixel (four waves; pooled, sixteen: 7680)
     lds += (size_t)NW * 2 * pg.stage * sizeof(float);
     dim3 grid((unsigned)blocks);
 #define XNOR_BA(B, AA, N) \

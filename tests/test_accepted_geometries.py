@@ -67,3 +67,12 @@ def test_binary_weight_layers_with_wide_rows(case):
 @pytest.mark.parametrize("case", [(840, 25, 3, 23, 466, 5, 5, 3, (4, 3)), (207, 2, 36, 27, 433, 5, 7, 3, (0, 3))])
 def test_binary_weight_layers_of_many_filters(case):
     assert xnor.lib().xnor_bwn_conv2d(FAKE, FAKE, FAKE, FAKE, ctypes.byref(xnor.make_desc(*case)), None) == ERR_HIP
+
+
+# (sixteen waves leave room for 7680 channels, eight for 7936, four for 8064)
+@pytest.mark.parametrize("n,c,h,w", [(1, 7681, 1, 2), (512, 7700, 2, 2), (1, 7936, 7, 7), (256, 7971, 13, 21), (512, 8000, 8, 8), (512, 8000, 2, 2), (3, 8064, 1, 3)])
+def test_binactiv_up_to_the_channels_that_four_waves_hold(n, c, h, w):
+    d = ctypes.byref(xnor.make_desc(n, c, h, w, 1, 1, 1))
+    assert xnor.lib().xnor_binactiv(FAKE, None, None, FAKE, FAKE, None, d, None) == ERR_HIP
+    assert xnor.lib().xnor_binarize_pack(FAKE, None, None, FAKE, n, c, h, w, None) == ERR_HIP
+    assert xnor.lib().xnor_compute_K(FAKE, None, None, FAKE, FAKE, d, None) == ERR_HIP

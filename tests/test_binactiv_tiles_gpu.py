@@ -14,6 +14,7 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,c,h,w", [
     (1, 1, 1, 2), (3, 7, 3, 7), (130, 9, 1, 3), (5, 64, 7, 9), (2, 57, 8, 8), (7, 191, 5, 13), (7, 185, 5, 13), (1, 1000, 2, 1),
     (256, 70, 7, 7), (255, 65, 14, 14), (64, 33, 13, 13), (200, 96, 13, 13),
+    (2, 7680, 1, 3), (2, 7690, 1, 3), (1, 7936, 7, 10), (3, 7940, 8, 8), (3, 8064, 1, 3),     # the widest rows of 16, 8 and 4 waves
 ])
 @pytest.mark.parametrize("bn", [False, True])
 def test_matches_oracle(n, c, h, w, bn):
