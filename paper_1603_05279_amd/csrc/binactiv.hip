@@ -343,8 +343,11 @@ static xnor_status launch_binactiv_impl(const float *x, const float *bn_scale, c
         const int groups = (c + 7) / 8, cw = (c + 31) / 32;
         if (blocks <= 256 && groups >= 24 && binactiv_lds(16, cw) <= BINACTIV_LDS)
             return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
-        // (9 to 15 groups leave waves without work on every second turn: 64 of 96x27x27 from memory, 765 workgroups, 4 waves 5.35, 8 waves 5.7)
-        if ((groups == 8 || groups >= 16 || (groups > 8 && blocks <= 512)) && binactiv_lds(8, cw) <= BINACTIV_LDS)
+        // (9 to 12 groups leave most of eight waves without work on the second turn.  A CU holds four such workgroups and eight of four waves: from
+        // 1025 to 2048 the latter take one round where eight waves take two, 1.05 of their time in the mean of 31 cached inputs, up to 1.10, 0.99 of
+        // 35 from memory; up to 1024 eight waves are level, 64 of 96x27x27 4.0 and 4.0, from memory 6.4 and 6.45, or ahead, 261 of 72x7x7
+        // 2.95 / 3.2; above 2048 ahead, 351 of 96x27x27 18.3 / 19.6)
+        if ((groups == 8 || groups > 12 || (groups > 8 && (blocks <= 1024 || blocks > 2048))) && binactiv_lds(8, cw) <= BINACTIV_LDS)
             return launch_binactiv_nw<POOL, PH, PW, 8>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
     }
     return launch_binactiv_nw<POOL, PH, PW, POOL ? 16 : 4>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
