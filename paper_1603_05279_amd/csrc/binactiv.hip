@@ -528,7 +528,7 @@ static xnor_status launch_pool_rows(const float *x, const float *bn_scale, const
     // 72 registers then share a CU, one loads while another computes: 64 of 256x27x27 11.7 us, with 16 waves 14.8; 256 of 128x28x28
     // 18.8 / 32.4), 16 where there are CUs to spare (2 of 480x40x40 11.3 / 9.7, 4 of 100x33x33 4.9 / 4.6).
     const int R = (long long)n * ((ho + 1) / 2) < 256 ? 1 : 2, waves = (groups + side - 1) / side;
-    const int NW = waves > 8 && (long long)n * ((ho + R - 1) / R) < 256 ? 16 : waves > 4 ? 8 : 4;
+    const int NW = R == 1 && waves > 8 && (long long)n * ho < 256 ? 16 : waves > 4 ? 8 : 4;
     const int tiles = (ho + R - 1) / R;
     const long long blocks = (long long)n * tiles;
     const size_t lds = (size_t)R * pg.wo * 4 * (cw + NW * side) + (size_t)cw * 64 * 4;
@@ -536,7 +536,7 @@ static xnor_status launch_pool_rows(const float *x, const float *bn_scale, const
 #define XNOR_PR(RR, W) \
     pool_rows_kernel<PH, RR, W><<<dim3((unsigned)blocks), dim3(64 * W), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, cw, ho, tiles, (int)blocks, lanes_log2, pg)
     if (R == 1) { if (NW == 16) XNOR_PR(1, 16); else if (NW == 8) XNOR_PR(1, 8); else XNOR_PR(1, 4); }
-    else        { if (NW == 16) XNOR_PR(2, 16); else if (NW == 8) XNOR_PR(2, 8); else XNOR_PR(2, 4); }
+    else        { if (NW == 8) XNOR_PR(2, 8); else XNOR_PR(2, 4); }
 #undef XNOR_PR
     return hip_status(hipGetLastError());
 }
