@@ -305,12 +305,12 @@ static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream
     const bool stream_in = !POOL && (pg.streamed || (long long)n * c * hw * 4 > (64ll << 20));
     auto kern = stream_in ? binactiv_kernel<WB, WA, BN, POOL, NW, PH, PW, !POOL> : binactiv_kernel<WB, WA, BN, POOL, NW, PH, PW, false>;
     if (lds > 48 * 1024) {      // the pooled form's staging buffer can pass the default dynamic LDS limit
-        static std::atomic<bool> attr_done;      // false -> true only; a repeated attribute call is harmless
-        if (!attr_done.load(std::memory_order_acquire)) {
+        static std::atomic<bool> attr_done[2];   // per kernel; false -> true only, a repeated attribute call is harmless
+        if (!attr_done[stream_in].load(std::memory_order_acquire)) {
             if (hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                     160 * 1024) != hipSuccess)
                 return XNOR_ERR_HIP;
-            attr_done.store(true, std::memory_order_release);
+            attr_done[stream_in].store(true, std::memory_order_release);
         }
     }
     kern<<<grid, dim3(64 * NW), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, hw, cw, tiles, blocks, (uint32_t)((long long)n * hw), pg.px_tile,
