@@ -13,19 +13,11 @@ constexpr int linear_words_per_pass(int v) { return v == 4 ? 320 : v == 2 ? 256 
 //
 // A workgroup holds two rows (one if there is only one) and 16 filters whether they exist or not, so the time follows the
 // padded product: 2.5 us + rows * filters * passes over the row * 0.052 ns with 4 words per load (0.083 ns with 2, 0.032 ns
-// with 1; measured from 8192 to 2^20 padded products, 32 to 131072 features).  The matrix-core form (packed weight words) takes
-// 4 to 5 us for the shortest rows and grows with c, hardly with rows and filters.  Both, back to back, us (rows x filters, c):
-//       2048 x 16, 512: 3.8 / 4.9      8 x 8192, 2560: 5.8 / 6.1      8 x 8192, 2368 (2 words per load): 7.7 / 6.2
-//       32 x 4096, 9216: 9.5 / 11.8    96 x 1024, 4096: 7.7 / 7.7     128 x 1000, 4096: 9.6 / 7.7
-//       8192 x 16, 9216: 9.3 / 12.1
-// The lines below were drawn from 3590 shapes of more than two rows and at most 10240 features, and timed again on 500: what
-// they choose is at most 2 % behind the matrix-core form.  Apart from them:
-//   - one or two rows, where nothing is padded, and more than 320 words, which the matrix-core form walks in many chunks:
-//     ahead wherever measured but 1 x 32768, 64: 5.5 / 4.9 (128 x 1000, 25088: 22.7 / 55.2; above 32768 rows at most 25 % behind);
-//   - 16384 filters and more: the matrix-core form needs more workgroups than there are CUs for a few rows
-//     (4 x 32768, 4096: 9.2 / 10.3), except with 2 words per load (3 x 16384, 2112: 7.5 / 6.3);
-//   - from 16384 rows and 5120 features the matrix-core form's larger tiles no longer hold a row (16384 x 4, 9216:
-//     15.8 / 31.5; 32768 x 4, 5120: 29.1 / 32.2).
+// with 1; measured from 8192 to 2^20 padded products, 32 to 131072 features).
+// With an image, rows of up to three words are against the matrix-core convolution, 4 to 5 us whatever rows and filters (rows x filters, c,
+// us back to back): 2048 x 8, 96 3.2 / 4.3, 300 x 100, 96 3.6 / 4.3, 64 x 512, 32 3.3 / 4.2, 1000 x 30, 40 5.1 / 4.2, 9000 x 3, 96 7.1 / 4.7.  One or
+// two rows, where nothing is padded, are ahead but for 1 x 32768, 64: 6.0 / 5.0.  Longer rows come here only where the images pass what
+// linear_words_kernel and the convolution address (2 GiB).
 inline bool linear_popcount_route(int n, int k, int c, int cw, bool matrix_image)
 {
     // rows times filters: beyond these no shape was measured ahead
@@ -38,9 +30,7 @@ inline bool linear_popcount_route(int n, int k, int c, int cw, bool matrix_image
     // against the vector-ALU convolution (5.3 us + 6.5 ns per feature: 32768 x 1, 512: 30.8 / 7.4, 2048: 31.0 / 18.7,
     // 4096: 30.6 / 32.1)
     if (!matrix_image) return cost <= 53500 + 124 * (int64_t)c;
-    if (cw > 320 || (k >= 16384 && v != 2)) return true;
-    if (n >= 16384 && c >= 5120) return padded <= 524288 && (v != 2 || cw <= 256);
-    return cost <= (c < 4096 ? 40960 + 15 * (int64_t)c : c < 6144 ? 122880 : 28 * (int64_t)c);
+    return cw > 320 || cost <= 40960 + 15 * (int64_t)c;
 }
 
 // Rows of four packed words and more with a matrix image have a third form, linear_words_kernel.  Its tiles (filters, rows of 32): what a
@@ -62,7 +52,8 @@ inline LinearWordsTile linear_words_tile(int n, int k)
 // Few rows against it, both in graphs of one kernel: the few-rows kernel 2.1 us + padded product * passes * 0.055 ns (as above), the other
 // 2.4 us and 0.2 us per 1024 features for a round of 1 x 1, 1.1 us and as many features' worth for every further one.  us, few rows /
 // words: 8 x 4096, 4096 features 3.8 / 3.2, 9216 3.8 / 4.1; 4 x 4096, 4096 2.9 / 3.2; 16 x 1000, 1024 2.9 / 2.6; 256 x 100, 4096 3.8 / 3.4,
-// 9216 3.8 / 4.3; 32 x 4096, 9216 9.4 / 4.3; 1 x 4096, 9216 2.3 / 4.1; 64 x 1000, 25088 12.8 / 7.4.
+// 9216 3.8 / 4.3; 32 x 4096, 9216 9.4 / 4.3; 1 x 4096, 9216 2.3 / 4.1; 64 x 1000, 25088 12.8 / 7.4.  Timed again on 252 shapes of 1 to 65535 rows and
+// 97 to 131072 features, one of them is chosen more than 10 % behind (5 x 3237, 34701 10.4 / 9.3), 0.3 % in the mean.
 inline bool linear_few_rows_ahead_of_words(int n, int k, int c, int cw)
 {
     if (n > 65535) return false;                                   // (grid limit)
