@@ -30,8 +30,10 @@ CASES = [
     (5, 64, 14, 14, 64, 3, 3, (1, 1), (1, 1)),      # exactly two words, no workspace needed
     (3, 96, 27, 27, 40, 5, 5, (1, 1), (2, 2)),      # several pixel tiles
     (9, 100, 7, 7, 70, 3, 3, (1, 1), (1, 1)),       # tile spans several images
-    (2, 64, 13, 13, 200, 3, 3, (1, 1), (1, 1)),     # two filter tiles: partial sums through the workspace
-    (2, 40, 10, 12, 300, 3, 3, (1, 1), (1, 1)),     # three filter tiles, ragged last one
+    (2, 64, 13, 13, 200, 3, 3, (1, 1), (1, 1)),     # int8: two filter tiles, partial sums through the workspace; 4-bit: one
+    (2, 40, 10, 12, 300, 3, 3, (1, 1), (1, 1)),     # int8: three filter tiles, ragged last one; 4-bit: one
+    (1, 400, 7, 9, 200, 5, 5, (1, 1), (2, 2)),      # long K loops: two and three filter tiles of either
+    (2, 192, 10, 12, 300, 3, 3, (1, 1), (1, 1)),
     (2, 256, 13, 13, 96, 3, 3, (1, 1), (1, 1)),     # several channel chunks in LDS
 ]
 

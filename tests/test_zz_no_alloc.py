@@ -1,7 +1,7 @@
 """xnor_conv2d_binactiv_noalloc (library-owned scratch, no workspace argument) against xnor_conv2d_binactiv
 (caller workspace) through the C ABI: same sign words, same A_next, same y, bit for bit, on two calls in a
-row, the second with a smaller input (the scratch keeps the first call's contents).  Both shapes have more than
-one filter tile, so the partial |z| sums really travel through the scratch."""
+row, the second with a smaller input (the scratch keeps the first call's contents).  All shapes but the last have more than
+one filter tile (the caller's workspace is seen to be written), so the partial |z| sums really travel through the scratch."""
 import ctypes
 
 import numpy as np
@@ -14,7 +14,7 @@ from tests.helpers import to_dev
 pytestmark = pytest.mark.gpu
 
 
-def both_entry_points(rng, n, c, h, w, k_out, kh, pad, bn):
+def both_entry_points(rng, n, c, h, w, k_out, kh, pad, bn, one_tile):
     x = rng.standard_normal((n, c, h, w)).astype(np.float32)
     wt = (0.05 * rng.standard_normal((k_out, c, kh, kh))).astype(np.float32)
     desc = xnor.make_desc(n, c, h, w, k_out, kh, kh, 1, pad)
@@ -35,9 +35,11 @@ def both_entry_points(rng, n, c, h, w, k_out, kh, pad, bn):
             xnor.xnor_conv2d_binactiv_noalloc(bufs.xbits, pw.wbits, pw.wmfma, None, bufs.A, pw.alpha, sc, sf, xb, An,
                                               out, desc, xnor.XNOR_ALGO_AUTO)
         else:
-            ws = torch.empty((ws_bytes,), dtype=torch.uint8, device="cuda")
+            ws = torch.full((ws_bytes,), 255, dtype=torch.uint8, device="cuda")
             xnor.xnor_conv2d_binactiv(bufs.xbits, pw.wbits, pw.wmfma, None, bufs.A, pw.alpha, sc, sf, xb, An, out,
                                       ws, desc, xnor.XNOR_ALGO_AUTO)
+            planes = ws.view(torch.float32).view(-1, n * ho * wo)          # NaN before; one plane of sums per filter tile
+            assert torch.isnan(planes[0]).all() if one_tile else not torch.isnan(planes[:2]).any()
         torch.cuda.synchronize()
         res.append((xb.cpu().numpy(), An.cpu().numpy(), out.cpu().numpy()))
     return res
@@ -45,8 +47,9 @@ def both_entry_points(rng, n, c, h, w, k_out, kh, pad, bn):
 
 def test_noalloc_entry_point_matches_the_workspace_one_twice_in_a_row():
     rng = np.random.default_rng(707)
-    # first call: 384 filters over 3 x 13 x 13 pixels; second, smaller: 200 filters over 2 x 7 x 9 pixels
-    for shape in [(3, 96, 13, 13, 384, 3, 1, True), (2, 40, 7, 9, 200, 3, 1, False)]:
+    # first call: 384 filters over 3 x 13 x 13 pixels; second, smaller: 200 filters over 2 x 7 x 9 pixels (K loops too long for the tiles that
+    # hold every filter); last: one of those tiles
+    for shape in [(3, 192, 13, 13, 384, 3, 1, True, False), (2, 400, 7, 9, 200, 5, 2, False, False), (3, 96, 13, 13, 384, 3, 1, True, True)]:
         (xb0, an0, y0), (xb1, an1, y1) = both_entry_points(rng, *shape)
         assert not np.isnan(an0).any() and not np.isnan(y0).any()
         assert np.array_equal(xb0, xb1), "sign words differ"
