@@ -11,7 +11,8 @@
 namespace xnor {
 
 // Level indices u of four inputs, one per byte: u = floor(((x + 1) * 0.5) * L + 0.5), x clamped to [-1, 1] (NaN -> -1), each operation
-// rounded to float in this order (contraction is disabled for the build): the float value decides the level.  Halving is exact, so
+// rounded to float in this order (contraction is disabled for the build): the float value decides the level.  Rounding keeps order, so x + 1 is
+// clamped instead, to [0, 2]: the addition quiets a signaling NaN, which the median of three would answer with 2.  Halving is exact, so
 // (x + 1) * (L / 2) is the same float; the value lies in [0.5, L + 0.5], where conversion to integer is the floor and stays within 0 .. L.
 // One bit: the comparison of the sign rule (x + 1 rounds to 1 for -2^-25 < x < 0, which would give +1).
 template <bool ONE_BIT> __device__ __forceinline__ uint32_t qk_indices(const float *x, float half_L)
@@ -20,7 +21,7 @@ template <bool ONE_BIT> __device__ __forceinline__ uint32_t qk_indices(const flo
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t q = ONE_BIT ? (x[i] >= 0.0f ? 1u : 0u)
-                                   : (uint32_t)((__builtin_amdgcn_fmed3f(x[i], -1.0f, 1.0f) + 1.0f) * half_L + 0.5f);
+                                   : (uint32_t)(__builtin_amdgcn_fmed3f(x[i] + 1.0f, 0.0f, 2.0f) * half_L + 0.5f);
         u |= q << (8 * i);
     }
     return u;

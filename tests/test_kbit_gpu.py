@@ -78,6 +78,17 @@ def test_one_bit_each_is_the_binary_dot_map():
     assert np.array_equal(out, ref.astype(np.float32))
 
 
+@pytest.mark.parametrize("k", range(1, 8))
+def test_levels_of_special_values(k):
+    # NaN, quiet or signaling, counts as -1; infinities, the ends of the range and their neighbours, denormal numbers, zeros of both signs
+    words = [0x7F800001, 0xFF800001, 0x7FBFFFFF, 0x7FC00000, 0xFFC00001, 0x7F800000, 0xFF800000, 0x3F800000, 0x3F800001, 0x3F7FFFFF,
+             0xBF800000, 0xBF800001, 0xBF7FFFFF, 0x80000000, 0, 1, 0x80000001, 0x33000000, 0xB3000000, 0x7F7FFFFF, 0xFF7FFFFF]
+    x = np.resize(np.array(words, np.uint32), 64 * 40).view(np.float32).reshape(5, 64, 4, 2)
+    xq = torch.full((xnor.kbit_input_bytes(*x.shape),), 99, dtype=torch.uint8, device="cuda")
+    xnor.xnor_kbit_pack_input(to_dev(x), xq, k, *x.shape)
+    assert np.array_equal(xq.cpu().numpy().view(np.int8).ravel(), levels_image(xo.qk_levels(x, k)).ravel())
+
+
 def test_level_ties_and_errors():
     # inputs exactly halfway between two levels round up, like the oracle; NaN counts as -1
     k = 2
