@@ -6,16 +6,16 @@
 
 namespace xnor {
 
-// One workgroup = up to 64 pixels that follow each other in the batch x all channels.  Lanes run along the pixels
-// (contiguous in NCHW, so every channel row is read as 256-byte coalesced segments); the NW waves
+// One workgroup = up to 64 pixels that follow each other in an image x all channels (small planes: in the batch, launch_binactiv).  Lanes run
+// along the pixels (contiguous in NCHW, so every channel row is read as 256-byte coalesced segments); the NW waves
 // share the channels in groups of 8 (wave w takes groups w, w+NW, ...), so any channel count keeps
 // all waves busy with many independent loads in flight.  A group's 8 sign bits are one byte of
 // the pixel's packed word: it is assembled in LDS, from where the words of the tile leave
 // as one contiguous, fully coalesced run.  |y| is accumulated per wave in float; the NW partial
 // sums per pixel meet in LDS in a fixed order, so results do not depend on timing.
-// What bounds it: memory (256 of 64x56x56: 33.1 us, 6.2 TB/s), on small inputs the launch and one trip to memory.  Against tiles within an image
-// and 4 or 16 waves, us in a graph: 128 of 256x13x13 7.1 -> 4.7, 200 of 17x31x31 6.4 -> 4.3, 3 of 384x50x50 5.8 -> 4.2, 256 of 512x7x7
-// 5.2 -> 4.05, 256 of 128x28x28 18.9 -> 17.0, 256 of 64x56x56 34.7 -> 33.1, 9 of 83x29x23 3.7 -> 2.65.
+// What bounds it: memory (256 of 64x56x56: 32.7 us, 6.3 TB/s), on small inputs the launch and one trip to memory.  Masks only in a last group that
+// lacks channels, and the waves of binactiv_waves, against masks in every group and 4 or 16 waves, us in a graph: 128 of 256x13x13, normalised
+// 7.1 -> 4.4, 256 of 128x28x28 18.3 -> 17.1, 256 of 512x7x7 5.1 -> 4.3, 256 of 64x56x56 34.5 -> 32.7, 9 of 83x29x23 3.2 -> 2.9.
 // Max-pooling in front of the layer (block order BinConv -> Pool -> next block's BatchNorm -> BinActiv,
 // sec. 3.2): `hw` then counts pooled pixels and every value is the maximum of its window of the
 // h x w input plane.  Out-of-range window positions are skipped; the maximum starts at -inf and skips
@@ -26,7 +26,8 @@ struct PoolGeom {
     int pad_h, pad_w;
     int relu;               // max(., 0) before the normalisation (the optional ReLU of sec. 3.2)
     int stage;              // > 0: floats per channel of the per-wave LDS staging buffer (see the kernel)
-    int px_tile;            // unpooled form: pixels per workgroup, at most 64
+    int px_tile;            // pixels per workgroup, at most 64
+    int tiles;              // workgroups per image; 0 (unpooled form): the pixels of the whole batch in one row
     int streamed;           // unpooled form: the caller says the input is not in any cache (read with the non-temporal hint)
 };
 
@@ -40,7 +41,7 @@ template <bool WRITE_BITS, bool WRITE_A, bool BN, bool POOL, int NW, int PH = 0,
 __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
     const float *__restrict__ x, const float *__restrict__ bn_scale,
     const float *__restrict__ bn_shift, uint32_t *__restrict__ xbits, float *__restrict__ A,
-    int c, int hw, int cw, int tiles_per_image, int nblocks, uint32_t pixels, int px_tile, FastDiv div_hw, PoolGeom pg)
+    int c, int hw, int cw, int nblocks, int px_tile, uint32_t len, FastDiv div_tiles, FastDiv div_hw, PoolGeom pg)
 {
     // Workgroups are dealt to the 8 XCDs round-robin by index.  Neighbouring pixel tiles share the
     // cache lines that straddle their boundary (channel rows are not line aligned), so within
@@ -57,16 +58,15 @@ __global__ __launch_bounds__(64 * NW) void binactiv_kernel(
     // the wave index as a scalar: channel indices derived from it are then scalar too, and the
     // per-channel scale and shift come through the scalar cache instead of 64-lane loads
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-    // unpooled: 64 pixels that follow each other in the batch (planes of 49, 169 or 196 pixels would leave every last wave of an image with
-    // few of them); pooled: of an image
-    const int img = POOL ? blk / tiles_per_image : 0;
-    const int p0 = POOL ? (blk - img * tiles_per_image) * 64 : 0;
-    const uint32_t first = POOL ? (uint32_t)img * (uint32_t)hw + (uint32_t)p0 : (uint32_t)blk * (uint32_t)px_tile;      // of the batch
-    const int npx = POOL ? min(64, hw - p0) : (int)min((uint32_t)px_tile, pixels - first);
+    // a row of `tiles` tiles over `len` pixels: an image, or (unpooled form, planes of less than 64 pixels) the whole batch
+    const uint32_t row = div_tiles.div((uint32_t)blk);
+    const uint32_t p0 = ((uint32_t)blk - row * div_tiles.d) * (uint32_t)px_tile, first = row * len + p0;
+    const int npx = (int)min((uint32_t)px_tile, len - p0);
     const bool live = lane < npx;
-    const int pc = min(p0 + lane, hw - 1);
-    const uint32_t m = first + (uint32_t)min(lane, npx - 1), img_l = div_hw.div(m);
+    const uint32_t m = first + (uint32_t)min(lane, npx - 1);              // of the batch
+    const uint32_t img_l = POOL ? row : div_hw.div(m);
     const float *xi = x + (size_t)img_l * c * hw + (m - img_l * (uint32_t)hw);      // unpooled: this lane's pixel
+    const int img = (int)row, pc = (int)(m - row * len);                  // pooled: the image, this lane's pixel there
     const float *xs = x + (size_t)img * c * pg.h * pg.w;                  // pooled: the image (wave-uniform)
     const int in_hw = POOL ? pg.h * pg.w : hw;
     int iy0 = 0, ix0 = 0;       // window origin of this lane's pooled pixel
@@ -299,7 +299,7 @@ __global__ __launch_bounds__(64 * NWV) void binactiv_vec_kernel(
 template <bool WB, bool WA, bool BN, bool POOL, int NW, int PH, int PW>
 static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream, const float *x,
                                        const float *bn_scale, const float *bn_shift, uint32_t *xbits, float *A, int n, int c,
-                                       int hw, int cw, int tiles, int blocks, const PoolGeom &pg)
+                                       int hw, int cw, int blocks, const PoolGeom &pg)
 {
     // (the cache policy is an instruction field: a kernel of its own for streamed inputs)
     const bool stream_in = !POOL && (pg.streamed || (long long)n * c * hw * 4 > (64ll << 20));
@@ -313,14 +313,40 @@ static xnor_status launch_binactiv_one(dim3 grid, size_t lds, hipStream_t stream
             attr_done[stream_in].store(true, std::memory_order_release);
         }
     }
-    kern<<<grid, dim3(64 * NW), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, hw, cw, tiles, blocks, (uint32_t)((long long)n * hw), pg.px_tile,
-                                               FastDiv::make((uint32_t)hw), pg);
+    const bool per_image = pg.tiles > 0;
+    kern<<<grid, dim3(64 * NW), lds, stream>>>(x, bn_scale, bn_shift, xbits, A, c, hw, cw, blocks, pg.px_tile,
+                                               per_image ? (uint32_t)hw : (uint32_t)((long long)n * hw),
+                                               FastDiv::make((uint32_t)(per_image ? pg.tiles : blocks)), FastDiv::make((uint32_t)hw), pg);
     return hip_status(hipGetLastError());
+}
+
+static long long binactiv_blocks(int n, int hw, const PoolGeom &pg)
+{
+    return pg.tiles ? (long long)n * pg.tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
 }
 
 // LDS of a workgroup: a partial sum per wave and pixel, the words of 64 pixels
 constexpr size_t BINACTIV_LDS = 64 * 1024;
 static size_t binactiv_lds(int waves, int cw) { return (size_t)waves * 64 * sizeof(float) + (size_t)64 * cw * 4; }
+
+// Waves per workgroup of the unpooled form, each at least a group of 8 channels.  A CU holds 2048 threads: 256 CUs take 2048 workgroups of four
+// waves in one round, 1024 of eight, 512 of sixteen.  Few workgroups want many loads in flight each, more of them want one round.  Over 700
+// layers, time against the best of the three in the mean, four / eight / sixteen waves, inputs cached and from memory:
+//   8 to 15 groups, up to 256 workgroups 1.06 / 1.00 / 1.03 and 1.06 / 1.00 / 1.02, to 2048 1.00 / 1.10 / 1.25 and 1.01 / 1.01 / 1.16, more 1.02 / 1.00 / 1.41
+//   16 to 23, up to 256 1.10 / 1.00 / 1.05 and 1.15 / 1.01 / 1.02, to 512 1.00 / 1.05 / 1.18 and 1.03 / 1.01 / 1.02, to 1024 1.00 / 1.08 / 1.30 and
+//   1.01 / 1.00 / 1.11, more 1.02 / 1.00 / 1.18 and 1.05 / 1.00 / 1.17
+//   24 to 39, up to 256 1.20 / 1.00 / 1.02 and 1.32 / 1.04 / 1.00, to 512 1.13 / 1.00 / 1.09 and 1.08 / 1.02 / 1.00, to 1024 1.01 / 1.01 / 1.06 and
+//   1.01 / 1.04 / 1.06, more 1.08 / 1.01 / 1.07 and 1.08 / 1.01 / 1.06
+//   40 and more, up to 256 1.37 / 1.05 / 1.00 and 1.64 / 1.14 / 1.00, to 512 1.12 / 1.01 / 1.01 and 1.22 / 1.01 / 1.03, more 1.06 / 1.07 / 1.02 and
+//   1.06 / 1.08 / 1.02
+static int binactiv_waves(int groups, long long blocks)
+{
+    if (groups < 8) return 4;
+    if (blocks <= 256) return groups >= 24 ? 16 : 8;
+    if (groups >= 40 && blocks > 512) return 16;
+    if (groups >= 16 && blocks <= 512) return 8;
+    return blocks <= (groups < 16 ? 2048 : 1024) ? 4 : 8;
+}
 
 template <bool POOL, int PH, int PW, int NW>
 static xnor_status launch_binactiv_nw(const float *x, const float *bn_scale, const float *bn_shift,
@@ -332,23 +358,15 @@ static xnor_status launch_binactiv_impl(const float *x, const float *bn_scale, c
                                         uint32_t *xbits, float *A, int n, int c, int hw, const PoolGeom &pg,
                                         hipStream_t stream)
 {
-    const int tiles = (hw + 63) / 64;
-    const long long blocks = POOL ? (long long)n * tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
+    const long long blocks = binactiv_blocks(n, hw, pg);
     if (blocks > 0x7ffffff0LL) return XNOR_ERR_SHAPE;
-    // 16 waves per workgroup for the pooled form and where few workgroups have many channels (30 of 512x20x20: 4.55 us, with 8 waves 5.95; 3
-    // of 384x50x50 4.2 / 4.45); 8 where the channels give each of them a group (256 of 64x56x56 33.1, with 4 waves 34.0; 128 of 256x13x13
-    // 4.7 / 5.7; 9 of 83x29x23 2.65 / 3.0; 16 waves 53 and 4.95 for the first two), else 4 (200 of 17x31x31 4.3, with 8 waves 5.2).
+    // 16 waves per workgroup for the pooled form.
     if constexpr (!POOL) {
-        // (from 7681 channels on, where fewer of them leave room for the words)
         const int groups = (c + 7) / 8, cw = (c + 31) / 32;
-        if (blocks <= 256 && groups >= 24 && binactiv_lds(16, cw) <= BINACTIV_LDS)
-            return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
-        // (9 to 12 groups leave most of eight waves without work on the second turn.  A CU holds four such workgroups and eight of four waves: from
-        // 1025 to 2048 the latter take one round where eight waves take two, 1.05 of their time in the mean of 31 cached inputs, up to 1.10, 0.99 of
-        // 35 from memory; up to 1024 eight waves are level, 64 of 96x27x27 4.0 and 4.0, from memory 6.4 and 6.45, or ahead, 261 of 72x7x7
-        // 2.95 / 3.2; above 2048 ahead, 351 of 96x27x27 18.3 / 19.6)
-        if ((groups == 8 || groups > 12 || (groups > 8 && (blocks <= 1024 || blocks > 2048))) && binactiv_lds(8, cw) <= BINACTIV_LDS)
-            return launch_binactiv_nw<POOL, PH, PW, 8>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
+        int nw = binactiv_waves(groups, blocks);
+        while (nw > 4 && binactiv_lds(nw, cw) > BINACTIV_LDS) nw /= 2;         // (from 7681 channels on fewer waves leave room for the words)
+        if (nw == 16) return launch_binactiv_nw<POOL, PH, PW, 16>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
+        if (nw == 8) return launch_binactiv_nw<POOL, PH, PW, 8>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
     }
     return launch_binactiv_nw<POOL, PH, PW, POOL ? 16 : 4>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
 }
@@ -359,15 +377,14 @@ static xnor_status launch_binactiv_nw(const float *x, const float *bn_scale, con
                                       hipStream_t stream)
 {
     const int cw = (c + 31) / 32;
-    const int tiles = (hw + 63) / 64;
-    const long long blocks = POOL ? (long long)n * tiles : ((long long)n * hw + pg.px_tile - 1) / pg.px_tile;
+    const long long blocks = binactiv_blocks(n, hw, pg);
     size_t lds = binactiv_lds(NW, cw);
     if (lds > BINACTIV_LDS) return XNOR_ERR_UNSUPPORTED;    // more than 8064 channels per pixel (four waves; pooled, sixteen: 7680)
     lds += (size_t)NW * 2 * pg.stage * sizeof(float);
     dim3 grid((unsigned)blocks);
 #define XNOR_BA(B, AA, N) \
     return launch_binactiv_one<B, AA, N, POOL, NW, PH, PW>(grid, lds, stream, x, bn_scale, bn_shift, xbits, A, n, c, hw, cw, \
-                                                           tiles, (int)blocks, pg)
+                                                           (int)blocks, pg)
     const bool bn = bn_scale != nullptr;
     if (xbits && A) { if (bn) XNOR_BA(true, true, true); else XNOR_BA(true, true, false); }
     else if (xbits) { if (bn) XNOR_BA(true, false, true); else XNOR_BA(true, false, false); }
@@ -388,13 +405,25 @@ xnor_status launch_binactiv(const float *x, const float *bn_scale, const float *
     }
     PoolGeom pg{};
     pg.streamed = streamed;
-    const long long pixels = (long long)n * hw, per_cu = (pixels + 256 * 64 - 1) / (256 * 64);
-    pg.px_tile = 64;
-    // Up to 8 workgroups per CU, the same number on each where that leaves them at least 48 pixels: 256 of 512x7x7, 196 workgroups of 64
-    // 5.3 us, 256 of 49 4.05; 256 of 256x14x14 10.9 and 9.6; but 128 of 256x13x13, 338 of 64 4.7, 512 of 43 5.0.
-    if (per_cu <= 8) {
-        const long long even = (pixels + 256 * per_cu - 1) / (256 * per_cu);
-        if (even >= 48 && even < 64) pg.px_tile = (int)even;
+    // Planes of 64 pixels and more: tiles within an image, so that a wave reads one run per channel and no cache line twice.  With the pixels of
+    // the whole batch in a row a tile crosses into the next image's planes: 80 of 512x27x27 from memory 24 us / 30, 200 of 512x13x13 17 / 21, 150 of
+    // 384x15x15 12.7 / 15.2, 256 of 64x56x56 (no tile crosses) 32.7 / 33.2.  Smaller planes (256 of 512x7x7 4.2 / 5.1), and batches that one
+    // workgroup per CU holds only in a row (129 of 512x10x10 9.1 / 11.0, 65 of 64x15x15 3.2 / 3.4), are taken in a row.
+    const long long pixels = (long long)n * hw;
+    const int tiles = (hw + 63) / 64;
+    if (hw >= 64 && ((long long)n * tiles <= 256 || pixels > 256 * 64)) {
+        pg.tiles = tiles;
+        // (a last tile of at most 8 pixels is shared out among the others: 256 of 256x14x14, tiles of 49, 11.3 us, of 64 and 4, 11.7)
+        pg.px_tile = hw - (tiles - 1) * 64 <= 8 ? (hw + tiles - 1) / tiles : 64;
+    } else {
+        // Up to 8 workgroups per CU, the same number on each where that leaves them at least 48 pixels: 256 of 512x7x7, 196 workgroups of 64
+        // 5.3 us, 256 of 49 4.05
+        const long long per_cu = (pixels + 256 * 64 - 1) / (256 * 64);
+        pg.px_tile = 64;
+        if (per_cu <= 8) {
+            const long long even = (pixels + 256 * per_cu - 1) / (256 * per_cu);
+            if (even >= 48 && even < 64) pg.px_tile = (int)even;
+        }
     }
     return launch_binactiv_impl<false>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);
 }
@@ -557,6 +586,8 @@ xnor_status launch_pool_binactiv(const float *x, const float *bn_scale, const fl
     }
     // LDS staging of the input rows a 64-pixel tile touches (compile-time windows only): at most
     // ceil-ish (64 + wo - 2)/wo + 1 pooled rows, hence (rows - 1)*sh + ph input rows of w floats
+    pg.tiles = (ho * wo + 63) / 64;
+    pg.px_tile = 64;
     pg.stage = 0;
     if ((ph == 3 && pw == 3) || (ph == 2 && pw == 2)) {
         const long long prows = std::min<long long>(ho, (64 + wo - 2) / wo + 1);

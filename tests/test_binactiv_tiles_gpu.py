@@ -1,5 +1,5 @@
-"""BinActiv over pixels of the whole batch: tiles that cross images, the last one not full, tiles of fewer than 64 pixels (the same number of
-workgroups on every CU), 4, 8 and 16 waves, channels that fill no group of eight."""
+"""BinActiv: tiles within an image, the last one not full or shared out among the others, and over pixels of the whole batch, where they cross
+images, of fewer than 64 pixels too (the same number of workgroups on every CU); 4, 8 and 16 waves, channels that fill no group of eight."""
 import numpy as np
 import pytest
 import torch
@@ -14,6 +14,8 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("n,c,h,w", [
     (1, 1, 1, 2), (3, 7, 3, 7), (130, 9, 1, 3), (5, 64, 7, 9), (2, 57, 8, 8), (7, 191, 5, 13), (7, 185, 5, 13), (1, 1000, 2, 1),
     (256, 70, 7, 7), (255, 65, 14, 14), (64, 33, 13, 13), (200, 96, 13, 13),
+    (3, 20, 8, 8), (2, 65, 9, 8), (3, 12, 5, 13), (2, 90, 1, 961), (95, 40, 10, 16), (257, 9, 8, 9),     # planes around 64 pixels, batches around 256 tiles
+    (300, 127, 8, 8), (600, 130, 8, 8), (1100, 128, 8, 8), (2100, 64, 8, 8), (520, 320, 8, 8), (515, 318, 1, 64),     # both sides of the wave counts
     (2, 7680, 1, 3), (2, 7690, 1, 3), (1, 7936, 7, 10), (3, 7940, 8, 8), (3, 8064, 1, 3),     # the widest rows of 16, 8 and 4 waves
 ])
 @pytest.mark.parametrize("bn", [False, True])
