@@ -6,6 +6,7 @@
 // kernel run on the transposed, 180-degree-rotated filters (pack_weights.hip, TRANSPOSED).
 #include "xnor_internal.h"
 #include <algorithm>
+#include <cmath>
 
 namespace xnor {
 
@@ -16,7 +17,7 @@ namespace xnor {
 // integer atomic maximum on the float's bit pattern (|gd| >= 0, so the patterns order like the values;
 // the result does not depend on the order of arrival; NaN magnitudes are ignored).
 // What bounds it: memory.  Eight waves from 57 filters on (a group of filters each at least), masks only in a last group that lacks
-// filters, one wave's lane exchanges and one atomic per workgroup, which takes several tiles where there are enough (launch_bingrad_binarize).
+// filters, one wave's lane exchanges and one atomic per workgroup, which takes several tiles where that pays (bingrad_run).
 // Against four waves and an atomic per tile, us in a graph with the launch that clears gmax: 256 of 64x56x56 51.8 -> 33.6, 256 of 128x28x28
 // 22.7 -> 19.9, 128 of 384x13x13 12.9 -> 9.5, 256 of 512x7x7 12.1 -> 7.7, 200 of 17x31x31 12.6 -> 7.8, 9 of 147x29x23 6.85 -> 5.8.
 template <bool HAS_ALPHA, bool HAS_K, int NW>
@@ -108,18 +109,38 @@ __global__ __launch_bounds__(256) void bingrad_plane_kernel(const float *__restr
         plane[(size_t)blockIdx.y * hw + i] = m;
 }
 
+// Tiles of 64 pixels per workgroup of bingrad_binarize_kernel: a run of up to 8 of an image.  A tile of its own costs an atomic maximum each, about 5 ns
+// and 400 ns / n, since all of them meet in the few cache lines of gmax (64 of 64x56x56, 3136 tiles 27.5 us, runs of 8 13.5; 30 of 128x56x56 19.8
+// and 13.4 with runs of 4; 256 of 64x56x56 53.6 and 34.5); long runs leave the CUs of a last or only round with unequal shares of the memory's
+// 5.5 TB/s (146 of 448x27x27, 1752 workgroups of one tile 34.4, 292 of six 48.5; 256 of 256x20x20 from memory 24.9 and 30), and less than two workgroups per CU
+// do not keep it busy.  The run whose slower side is the shortest: 280 layers, 1.02 of the best run's time in the mean (one tile each 1.11, two
+// 1.11, the longest run that leaves every CU a workgroup 1.06).
+static int bingrad_run(int n, int k_out, int hw, size_t words, int waves)
+{
+    const int tiles = (hw + 63) / 64, longest = (int)std::min<long long>({8, tiles, (long long)(32 * 1024 / words)});
+    const double memory = (double)n * k_out * hw * 4 / 5.5e6, atomic = 0.005 + 0.4 / n, round = 256.0 * (32 / waves);      // us; workgroups
+    double best = 0;
+    int best_run = 1;
+    for (int run = 1; run <= longest; ++run) {
+        const double blocks = (double)n * ((tiles + run - 1) / run), share = blocks / 256;
+        const double uneven = (blocks <= round ? std::ceil(share) / share : 1.0) * std::max(2.0 / share, 1.0);
+        const double cost = std::max(memory * uneven, blocks * atomic);
+        if (run == 1 || cost < best) {
+            best = cost;
+            best_run = run;
+        }
+    }
+    return best_run;
+}
+
 xnor_status launch_bingrad_binarize(const float *g, const float *K, const float *alpha, uint32_t *gbits,
                                     float *gmax, int n, int k_out, int hw, hipStream_t stream)
 {
     const int cw = (k_out + 31) / 32;
     const int tiles = (hw + 63) / 64;
     const bool wide = k_out > 56;               // a group of 8 filters for each of eight waves
-    // Runs of up to 8 tiles of 64 pixels of an image per workgroup, while every CU has a workgroup: an atomic maximum per tile costs about 2 ns,
-    // since all of them meet in the few cache lines of gmax (256 of 64x56x56: one tile 51.8 us, seven 33.6; 256 of 128x28x28, one tile 21.5,
-    // three 20.7, seven 19.9; 64 of 256x27x27 13.7 and 12.1 with three)
     const size_t words = (size_t)64 * cw * 4;
-    long long run = std::min<long long>({8, tiles, (long long)n * tiles / 256, (long long)(32 * 1024 / words)});
-    run = std::max<long long>(run, 1);
+    long long run = bingrad_run(n, k_out, hw, words, wide ? 8 : 4);
     const int parts = (int)((tiles + run - 1) / run);
     run = (tiles + parts - 1) / parts;
     const size_t lds = (wide ? 8 : 4) * 64 * sizeof(float) + words * run;

@@ -1,4 +1,5 @@
-"""Gradient binarisation with four and eight waves, filters that fill no group of eight, and the widest word rows that LDS holds."""
+"""Gradient binarisation with four and eight waves, filters that fill no group of eight, runs of several tiles, the last one not
+full, and the widest word rows that LDS holds."""
 import numpy as np
 import pytest
 import torch
@@ -10,7 +11,8 @@ from tests.test_bingrad_gpu import pack_bits
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("n,k,h,w", [(3, 56, 7, 9), (2, 57, 8, 8), (5, 65, 7, 7), (2, 511, 5, 13), (1, 8160, 2, 3), (4, 7, 1, 65), (300, 40, 16, 17), (130, 72, 26, 27)])
+@pytest.mark.parametrize("n,k,h,w", [(3, 56, 7, 9), (2, 57, 8, 8), (5, 65, 7, 7), (2, 511, 5, 13), (1, 8160, 2, 3), (4, 7, 1, 65), (300, 40, 16, 17), (130, 72, 26, 27),
+                                     (64, 72, 30, 30), (200, 17, 31, 31), (30, 100, 40, 41), (70, 64, 57, 56)])
 @pytest.mark.parametrize("with_k,with_alpha", [(True, True), (False, False)])
 def test_signs_and_maxima(n, k, h, w, with_k, with_alpha):
     print("case", n, k, h, w, flush=True)
