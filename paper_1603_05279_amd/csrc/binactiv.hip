@@ -416,13 +416,17 @@ xnor_status launch_binactiv(const float *x, const float *bn_scale, const float *
         // (a last tile of at most 8 pixels is shared out among the others: 256 of 256x14x14, tiles of 49, 11.3 us, of 64 and 4, 11.7)
         pg.px_tile = hw - (tiles - 1) * 64 <= 8 ? (hw + tiles - 1) / tiles : 64;
     } else {
-        // Up to 8 workgroups per CU, the same number on each where that leaves them at least 48 pixels: 256 of 512x7x7, 196 workgroups of 64
-        // 5.3 us, 256 of 49 4.05
-        const long long per_cu = (pixels + 256 * 64 - 1) / (256 * 64);
+        // One workgroup per CU while there are 16 pixels for each: 200 of 512x3x3 from memory, 29 workgroups of 64 pixels 8.8 us, 113 of 16 5.7 (an
+        // image each 5.6); 64 of 512x5x5 6.9 and 5.2.  Whole images where that makes at least half as many: 200 of 512x7x7 from memory, 252
+        // workgroups of 39 6.9, 200 of 49 6.3.  Then up to 8 per CU, the same number on each where that leaves them at least 48 pixels: 256 of 512x7x7,
+        // 196 workgroups of 64 5.3 us, 256 of 49 4.05
+        const long long per_cu = (pixels + 256 * 64 - 1) / (256 * 64), even = (pixels + 256 * per_cu - 1) / (256 * per_cu);
         pg.px_tile = 64;
-        if (per_cu <= 8) {
-            const long long even = (pixels + 256 * per_cu - 1) / (256 * per_cu);
-            if (even >= 48 && even < 64) pg.px_tile = (int)even;
+        if (per_cu == 1) {
+            pg.px_tile = (int)std::max<long long>(even, 16);
+            if (hw > pg.px_tile && hw < 2 * pg.px_tile && hw <= 64) pg.px_tile = hw;
+        } else if (per_cu <= 8 && even >= 48) {
+            pg.px_tile = (int)even;
         }
     }
     return launch_binactiv_impl<false>(x, bn_scale, bn_shift, xbits, A, n, c, hw, pg, stream);

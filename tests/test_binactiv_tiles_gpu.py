@@ -15,6 +15,7 @@ pytestmark = pytest.mark.gpu
     (1, 1, 1, 2), (3, 7, 3, 7), (130, 9, 1, 3), (5, 64, 7, 9), (2, 57, 8, 8), (7, 191, 5, 13), (7, 185, 5, 13), (1, 1000, 2, 1),
     (256, 70, 7, 7), (255, 65, 14, 14), (64, 33, 13, 13), (200, 96, 13, 13),
     (3, 20, 8, 8), (2, 65, 9, 8), (3, 12, 5, 13), (2, 90, 1, 961), (95, 40, 10, 16), (257, 9, 8, 9),     # planes around 64 pixels, batches around 256 tiles
+    (40, 256, 3, 3), (200, 70, 7, 7), (120, 33, 7, 7), (64, 512, 5, 5), (2, 300, 2, 2), (1, 40, 7, 9),     # small planes: 16 pixels, an image
     (300, 127, 8, 8), (600, 130, 8, 8), (1100, 128, 8, 8), (2100, 64, 8, 8), (520, 320, 8, 8), (515, 318, 1, 64),     # both sides of the wave counts
     (2, 7680, 1, 3), (2, 7690, 1, 3), (1, 7936, 7, 10), (3, 7940, 8, 8), (3, 8064, 1, 3),     # the widest rows of 16, 8 and 4 waves
 ])
