@@ -236,10 +236,10 @@ XNOR_API int xnor_conv2d_binactiv_noalloc(const uint32_t *xbits, const uint32_t 
  *   XNOR_POOL_ON_LOAD     (0): xnor_conv2d, then xnor_pool_binactiv on the unpooled tensor
  * Pooling in the epilogue recomputes the convolution rows that neighbouring groups of pooled rows share and
  * sends every result through LDS once more; measured on the AlexNet / ResNet-18 layer shapes it wins where
- * output rows are short (w_out <= 16, 1.1 to 1.25 times the matrix work; 128 images of 384 x 13 x 13 -> 256, 3 x 3 window: 24 us
- * against 35; 256 of 256 x 14 x 14, 2 x 2: 37 against 39) and loses on wide ones (64 of 96 x 27 x 27, 5 x 5 -> 256: 45 against
- * 39; 128 of 128 x 28 x 28: 53 against 39).  From 18 to 24 pixels it is ahead as well (64 of 128 x 20 x 20 -> 256: 23 against
- * 33), which the line does not use.  Also XNOR_POOL_ON_LOAD when xnor_conv2d_pool has no kernel for the geometry.
+ * output rows are short (w_out <= 16, 1.1 to 1.25 times the matrix work; 128 images of 384 x 13 x 13 -> 256, 3 x 3 window: 22 us
+ * against 29; 256 of 256 x 14 x 14, 2 x 2: 34 against 38) and loses on wide ones (64 of 96 x 27 x 27, 5 x 5 -> 256: 42 against
+ * 36; 128 of 128 x 28 x 28: 51 against 33).  Not used by the line: from 18 to 24 pixels it is ahead as well (64 of 128 x 20 x 20 -> 256: 22
+ * against 29), on few images or rows of 7 and 8 behind (16 of 64 x 14 x 14, 2 x 2: 12 against 8; 256 of 512 x 7 x 7: 36 against 34).  Also XNOR_POOL_ON_LOAD when xnor_conv2d_pool has no kernel for the geometry.
  * Returns a negative xnor_status for an invalid descriptor or window.  Host-only, launches nothing.
  */
 #define XNOR_POOL_ON_LOAD 0
